@@ -42,10 +42,11 @@ struct mpm_ctx {
     unsigned* partials = nullptr;
     // hash
     uint64_t *h_keys = nullptr, *h_mask = nullptr;
-    int *h_vals = nullptr, *h_start = nullptr, *h_end = nullptr;
+    int *h_vals = nullptr, *h_start = nullptr, *h_end = nullptr, *h_nslot = nullptr;
+    unsigned* t_cnt = nullptr;
     // blocks
     uint64_t *b_keys = nullptr, *b_mask = nullptr;
-    int *b_nbr = nullptr, *b_start = nullptr, *b_count = nullptr;
+    int *b_nbr = nullptr, *b_start = nullptr, *b_count = nullptr, *b_hs = nullptr;
     unsigned *b_chunks = nullptr, *b_chunk_off = nullptr;
     // work
     int *w_block = nullptr, *w_start = nullptr, *w_end = nullptr;
@@ -66,7 +67,9 @@ struct mpm_ctx {
     bool seg_valid = false;
     int seg_n = -1;
     uint32_t *rs_stay = nullptr, *rs_in = nullptr, *rs_off = nullptr, *rs_oldblk = nullptr;
-    unsigned *rs_cnt = nullptr, *rs_start = nullptr;
+    unsigned *rs_cnt = nullptr, *rs_start = nullptr, *rs_tile = nullptr, *it_mov = nullptr;
+    uint64_t* rs_occ = nullptr;
+    int* rs_nslot = nullptr;
     uint64_t* nh_keys = nullptr;
     uint32_t* nh_cnt = nullptr;
     int* nh_idx = nullptr;
@@ -128,9 +131,12 @@ void free_capacity_buffers(mpm_ctx* c) {
     dfree(c->h_vals);
     dfree(c->h_start);
     dfree(c->h_end);
+    dfree(c->h_nslot);
+    dfree(c->t_cnt);
     dfree(c->b_keys);
     dfree(c->b_mask);
     dfree(c->b_nbr);
+    dfree(c->b_hs);
     dfree(c->b_start);
     dfree(c->b_count);
     dfree(c->b_chunks);
@@ -150,6 +156,10 @@ void free_capacity_buffers(mpm_ctx* c) {
     dfree(c->rs_oldblk);
     dfree(c->rs_cnt);
     dfree(c->rs_start);
+    dfree(c->rs_tile);
+    dfree(c->it_mov);
+    dfree(c->rs_occ);
+    dfree(c->rs_nslot);
     dfree(c->nh_keys);
     dfree(c->nh_cnt);
     dfree(c->nh_idx);
@@ -274,11 +284,14 @@ void fill_params(mpm_ctx* c) {
     P.h_vals = c->h_vals;
     P.h_start = c->h_start;
     P.h_end = c->h_end;
+    P.h_nslot = c->h_nslot;
+    P.t_cnt = c->t_cnt;
     P.h_mask_bits = (unsigned)((1u << c->H_log2) - 1u);
     P.n_probe = 1 << c->H_log2;
     P.b_keys = c->b_keys;
     P.b_mask = c->b_mask;
     P.b_nbr = c->b_nbr;
+    P.b_hs = c->b_hs;
     P.b_start = c->b_start;
     P.b_count = c->b_count;
     P.b_chunks = c->b_chunks;
@@ -305,6 +318,10 @@ void fill_params(mpm_ctx* c) {
     P.rs_off = c->rs_off;
     P.rs_cnt = c->rs_cnt;
     P.rs_start = c->rs_start;
+    P.rs_tile = c->rs_tile;
+    P.it_mov = c->it_mov;
+    P.rs_occ = c->rs_occ;
+    P.rs_nslot = c->rs_nslot;
     P.rs_oldblk = c->rs_oldblk;
     P.nh_keys = c->nh_keys;
     P.nh_cnt = c->nh_cnt;
@@ -325,9 +342,7 @@ int alloc_capacity_buffers(mpm_ctx* c) {
     const size_t cap = (size_t)c->block_cap;
     // room for the smallest work-item size mpm_set_tuning accepts
     c->work_cap = c->block_cap + c->max_particles / MIN_CHUNK + 1;
-    // (the hash compaction keeps two tile sums per tile of the table)
-    int scan_n = std::max({radix_hist_size(c->max_particles), radix_hist_size(c->block_cap), (int)(2 * H),
-                           2 * c->block_cap, 1});
+    int scan_n = std::max({radix_hist_size(c->max_particles), radix_hist_size(c->block_cap), c->block_cap, 1});
     // the incremental re-sort serves hash-built sparse contexts whose particle
     // order may depend on earlier builds
     const bool resort = !c->dense && !c->adjoint && !c->scan_build && !c->det_order;
@@ -339,6 +354,9 @@ int alloc_capacity_buffers(mpm_ctx* c) {
         e = e ? e : dalloc(&c->h_vals, H);
         e = e ? e : dalloc(&c->h_start, H);
         e = e ? e : dalloc(&c->h_end, H);
+        e = e ? e : dalloc(&c->h_nslot, H * NB);
+        e = e ? e : dalloc(&c->t_cnt, LINE * ((H + SCAN_TILE - 1) / SCAN_TILE));
+        e = e ? e : dalloc(&c->b_hs, cap);
     }
     if (!c->dense) {
         e = e ? e : dalloc(&c->b_keys, cap);
@@ -382,6 +400,10 @@ int alloc_capacity_buffers(mpm_ctx* c) {
         e = e ? e : dalloc(&c->rs_oldblk, 2 * cap);
         e = e ? e : dalloc(&c->rs_cnt, 2 * cap);
         e = e ? e : dalloc(&c->rs_start, 2 * cap);
+        e = e ? e : dalloc(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
+        e = e ? e : dalloc(&c->it_mov, (size_t)c->work_cap);
+        e = e ? e : dalloc(&c->rs_occ, 2 * cap);
+        e = e ? e : dalloc(&c->rs_nslot, 2 * cap * NB);
         e = e ? e : dalloc(&c->nh_keys, H);
         e = e ? e : dalloc(&c->nh_cnt, H * NPB);
         e = e ? e : dalloc(&c->nh_idx, H);
@@ -429,6 +451,13 @@ uint32_t* next_bin_buffer(const mpm_ctx* c, bool next_reuse) {
     return c->k1;
 }
 
+// The device parameters of a launch over n particles.
+DevParams params_for(const mpm_ctx* c, int n) {
+    DevParams P = c->P;
+    if (n > FOLD_MAX_N) P.rs_tile = nullptr;
+    return P;
+}
+
 // Whether a build of n particles following the last one re-sorts incrementally.
 bool would_reuse(const mpm_ctx* c, int n) {
     return c->seg_valid && c->seg_n == n &&
@@ -456,8 +485,7 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
         // The sorted keys are not written: P2G reads each block's cell ranges
         // from the re-sort's table, and the next re-sort reads no previous key,
         // so the previous keys' buffer holds the movers' targets instead.
-        e = launch_resort(c->P, fresh, nullptr, vo, c->movers, prev, n, 1u << c->H_log2, c->partials, s,
-                          keys_ready);
+        e = launch_resort(params_for(c, n), fresh, vo, c->movers, prev, n, 1u << c->H_log2, c->partials, s, keys_ready);
         if (e != hipSuccess) return MPM_ERR_HIP;
         ko = prev;
     } else {
@@ -806,7 +834,7 @@ int g2p_impl(mpm_ctx* c, const mpm_particles* in, const mpm_particles* out, hipS
     if (!c->built || in->n != c->built_n) return MPM_ERR_STATE;
     if (in->n == 0) return MPM_OK;
     const int wgs = std::min(c->g2p_wgs, c->work_cap);
-    return hip_status(launch_g2p(c->P, in->x, in->F, in->id, in->inst, out->x, out->v, out->C, out->F, out->tau,
+    return hip_status(launch_g2p(params_for(c, in->n), in->x, in->F, in->id, in->inst, out->x, out->v, out->C, out->F, out->tau,
                                  out->id, out->inst, in->n, c->osrc, c->g2p_block, wgs, s, keys_out, movers_out));
 }
 }  // namespace

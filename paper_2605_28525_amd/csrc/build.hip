@@ -17,22 +17,25 @@
 //                   with a compare-and-swap on EMPTY (Algorithm 6), and ORs the
 //                   node mask into the slot.  The owner run boundaries of the
 //                   sorted order are recorded per slot.
-//   (after an incremental re-sort the insertion runs per re-sort entry
-//   instead, k_hash_insert_entries, from the entry's per-cell table)
-//   compaction      prefix scan over occupied slots -> Phi in slot order; block
-//                   keys, masks and owner segments in Phi order; overflow when
-//                   more than block_capacity slots are occupied (the counter
-//                   check of Algorithm 6); the same scan numbers the work
-//                   items (owner segments in chunks) in Phi order and writes
-//                   them, except for the key-ordered Phi, whose items follow
-//                   from a scan of per-block counts after the reordering.
-//   block setup     upper- and lower-neighbour compact indices (so P2G/G2P
-//                   never probe) and the per-block state the next incremental
-//                   re-sort's counting in G2P needs (the dense baseline also
-//                   clears its grid; the sparse P2G writes every node of every
-//                   active block).
+//   (after an incremental re-sort the blocks are inserted per re-sort entry,
+//   k_rs_finish in resort.hip)
+//   compaction      prefix sums over the occupied slots (counted per tile of the
+//                   table by the insertion) -> Phi in slot order; block keys,
+//                   masks and owner segments in Phi order; overflow when more
+//                   than block_capacity slots are occupied (the counter check
+//                   of Algorithm 6); the same pass numbers the work items
+//                   (owner segments in chunks) in Phi order and writes them,
+//                   except for the key-ordered Phi, whose items follow from a
+//                   scan of per-block counts after the reordering.  It also
+//                   prepares the counting of the next incremental re-sort.
+//   neighbours      the insertion of an owner block records the slots of the
+//                   blocks its stencils reach; P2G, when every Phi is known,
+//                   makes the neighbour tables from them, so nothing probes the
+//                   table a second time.  (The dense baseline also clears its
+//                   grid; the sparse P2G writes every node of every active
+//                   block.)
+#include "hash.h"
 #include "internal.h"
-#include "../../include/mpm.h"
 
 namespace mpmx {
 
@@ -42,6 +45,11 @@ template <int DIM>
 __global__ __launch_bounds__(WG) void k_bin(DevParams P, const float* __restrict__ x,
                                             const uint32_t* __restrict__ inst, int n, uint32_t* __restrict__ keys) {
     const int i0 = blockIdx.x * WG * BIN_PER_THREAD + threadIdx.x;
+    if (P.rs_tile && blockIdx.x == 0) {
+        // a separate binning pass precedes a re-sort's own counting: drop what
+        // a G2P may have counted for a build that did not follow
+        for (int t = threadIdx.x; t < (P.block_cap + RS_TILE - 1) / RS_TILE; t += WG) P.rs_tile[t * LINE] = 0u;
+    }
     float xv[BIN_PER_THREAD][3];
     uint32_t iv[BIN_PER_THREAD];
 #pragma unroll
@@ -71,77 +79,25 @@ __global__ __launch_bounds__(WG) void k_bin(DevParams P, const float* __restrict
     if (bad) raise_flag(P.ctr, bad);
 }
 
-// Claims or finds the slot of key K (Eqs. 23-25): a probed slot is read
-// first and compare-and-swapped from EMPTY only when it is empty (most inserts
-// find their block already claimed by another wave: each block is the owner
-// or an upper neighbour of up to 2^d inserting waves).
-__device__ int hash_insert(const DevParams& P, uint64_t K) {
-    unsigned s = (unsigned)mix64(K) & P.h_mask_bits;
-    for (int r = 0; r < P.n_probe; ++r) {
-        const uint64_t cur = __hip_atomic_load(&P.h_keys[s], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-        if (cur == K) return (int)s;
-        if (cur == EMPTY_KEY) {
-            const uint64_t old = atomicCAS((unsigned long long*)&P.h_keys[s], (unsigned long long)EMPTY_KEY,
-                                           (unsigned long long)K);
-            if (old == EMPTY_KEY || old == K) return (int)s;
-        }
-        s = (s + 1) & P.h_mask_bits;
-    }
-    raise_flag(P.ctr, MPM_FLAG_OVERFLOW);
-    return -1;
-}
-
+template <int DIM>
 __global__ __launch_bounds__(WG) void k_hash_clear(DevParams P, unsigned H) {
+    constexpr int NB = 1 << DIM;
+    const int tiles = ((int)H + SCAN_TILE - 1) / SCAN_TILE;
     for (unsigned s = blockIdx.x * WG + threadIdx.x; s < H; s += gridDim.x * WG) {
         P.h_keys[s] = EMPTY_KEY;
         P.h_mask[s] = 0ull;
         P.h_start[s] = -1;
         P.h_end[s] = -1;
         if (P.h_entry) P.h_entry[s] = -1;
+#pragma unroll
+        for (int d = 0; d < NB; d += 4) *(int4*)&P.h_nslot[(size_t)s * NB + d] = make_int4(-1, -1, -1, -1);
+        if (s < (unsigned)tiles) P.t_cnt[s * LINE] = P.t_cnt[s * LINE + 1] = 0u;
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         P.ctr->nb = 0;
         P.ctr->n_touched = 0;
         P.ctr->n_work = 0;
     }
-}
-
-// Node masks from the occupied base cells of a block.  With bit i + 4 j + 16 k
-// for cell / node (i, j, k), the stencil of a base cell covers nodes +0..+2 on
-// each axis; along one axis that is a dilation inside the block ("own") and a
-// spill of cells 2 and 3 into nodes 0 and 1 of the upper neighbour ("spill").
-// The node mask of neighbour d = (dx, dy, dz) is the composition of the per-axis
-// own/spill maps selected by the bits of d.
-__device__ __forceinline__ uint64_t own_x(uint64_t o) {
-    return o | ((o << 1) & 0xEEEEEEEEEEEEEEEEull) | ((o << 2) & 0xCCCCCCCCCCCCCCCCull);
-}
-__device__ __forceinline__ uint64_t spill_x(uint64_t o) {
-    return ((o >> 2) & 0x1111111111111111ull) | ((o >> 3) & 0x1111111111111111ull) |
-           ((o >> 2) & 0x2222222222222222ull);
-}
-template <int DIM>
-__device__ __forceinline__ uint64_t own_y(uint64_t o) {
-    if (DIM == 2) return (o | (o << 4) | (o << 8)) & 0xFFFFull;
-    return o | ((o << 4) & ~0x000F000F000F000Full) | ((o << 8) & ~0x00FF00FF00FF00FFull);
-}
-template <int DIM>
-__device__ __forceinline__ uint64_t spill_y(uint64_t o) {
-    if (DIM == 2) return ((o >> 8) & 0xFull) | ((o >> 12) & 0xFull) | ((o >> 8) & 0xF0ull);
-    return ((o >> 8) & 0x000F000F000F000Full) | ((o >> 12) & 0x000F000F000F000Full) |
-           ((o >> 8) & 0x00F000F000F000F0ull);
-}
-__device__ __forceinline__ uint64_t own_z(uint64_t o) { return o | (o << 16) | (o << 32); }
-__device__ __forceinline__ uint64_t spill_z(uint64_t o) {
-    return ((o >> 32) & 0xFFFFull) | ((o >> 48) & 0xFFFFull) | ((o >> 32) & 0xFFFF0000ull);
-}
-
-template <int DIM>
-__device__ __forceinline__ uint64_t neighbour_mask(uint64_t occ, int d) {
-    uint64_t o = (d & 1) ? spill_x(occ) : own_x(occ);
-    if (DIM == 2) o &= 0xFFFFull;
-    o = (d & 2) ? spill_y<DIM>(o) : own_y<DIM>(o);
-    if (DIM == 3) o = (d & 4) ? spill_z(o) : own_z(o);
-    return o;
 }
 
 constexpr int HI_ROUNDS = 4;  // sorted particles per lane of k_hash_insert (a wave covers 256)
@@ -175,23 +131,14 @@ __global__ __launch_bounds__(WG) void k_hash_insert(DevParams P, const uint32_t*
     uint64_t p_occ = 0;
     int p_first = 0, p_end = 0;
     auto flush = [&]() {
-        const uint32_t bl = p_seg & ((1u << P.blk_bits) - 1u);
-        const int inst = (int)(p_seg >> P.blk_bits);
-        int bc[3];
-        linear_to_block<DIM>(P, bl, bc);
-        int slot = -1;
-        if (lane < NB) {
-            const uint64_t mymask = neighbour_mask<DIM>(p_occ, lane);
-            if (mymask != 0ull) {
-                const uint64_t Kd =
-                    block_key<DIM>(P, bc[0] + (lane & 1), bc[1] + ((lane >> 1) & 1), bc[2] + ((lane >> 2) & 1), inst);
-                slot = hash_insert(P, Kd);
-                if (slot >= 0) atomicOr((unsigned long long*)&P.h_mask[slot], (unsigned long long)mymask);
-            }
-        }
-        if (lane == 0 && slot >= 0) {  // lane 0 holds the owner block
-            if (p_first > base || seg_before != p_seg) P.h_start[slot] = p_first;
-            if (p_end < stop || seg_after != p_seg) P.h_end[slot] = p_end;
+        const int slot = lane < NB ? insert_block<DIM>(P, p_seg, p_occ, lane) : -1;
+        const int own = readlane32(slot, 0);  // lane 0 holds the owner block
+        // a block that spans waves is inserted by each with a part of its
+        // cells: every part records the slots it reached
+        if (own >= 0 && slot >= 0) P.h_nslot[(size_t)own * NB + lane] = slot;
+        if (lane == 0 && own >= 0) {
+            if (p_first > base || seg_before != p_seg) P.h_start[own] = p_first;
+            if (p_end < stop || seg_after != p_seg) P.h_end[own] = p_end;
         }
     };
 #pragma unroll
@@ -226,174 +173,187 @@ __global__ __launch_bounds__(WG) void k_hash_insert(DevParams P, const uint32_t*
     if (have) flush();
 }
 
-// Insertion after an incremental re-sort: one wave per entry (a previous block
-// or a new one) of the re-sort, whose per-cell first positions and particle
-// count are known, so the base-cell occupancy of the owner block is a ballot
-// over its cells; node masks, inserts and owner segment as in k_hash_insert.
-template <int DIM>
-__global__ __launch_bounds__(WG) void k_hash_insert_entries(DevParams P) {
-    constexpr int NB = 1 << DIM;
-    constexpr int NC = 1 << (2 * DIM);
-    const int lane = __lane_id(), w = threadIdx.x >> 6;
-    const int ne = P.ctr->rs_n_ent;
-    for (int e = blockIdx.x * (WG / 64) + w; e < ne; e += gridDim.x * (WG / 64)) {
-        // every load of the entry issued at once (none waits for the count)
-        const unsigned tot = P.rs_cnt[e];
-        const unsigned first = P.rs_start[e];
-        const unsigned off_raw = lane < NC ? P.rs_off[(size_t)e * NC + lane] : 0u;
-        const uint32_t owner = P.rs_oldblk[e];
-        if (tot == 0u) continue;
-        const unsigned end = first + tot;
-        const unsigned off = lane < NC ? off_raw : end;
-        const unsigned next = __shfl_down(off, 1);
-        const bool occupied = lane < NC && (lane == NC - 1 ? end : next) > off;
-        const uint64_t occ = (uint64_t)__ballot(occupied);
-        const uint32_t bl = owner & ((1u << P.blk_bits) - 1u);
-        const int inst = (int)(owner >> P.blk_bits);
-        int bc[3];
-        linear_to_block<DIM>(P, bl, bc);
-        int slot = -1;
-        if (lane < NB) {
-            const uint64_t mymask = neighbour_mask<DIM>(occ, lane);
-            if (mymask != 0ull) {
-                const uint64_t Kd =
-                    block_key<DIM>(P, bc[0] + (lane & 1), bc[1] + ((lane >> 1) & 1), bc[2] + ((lane >> 2) & 1), inst);
-                slot = hash_insert(P, Kd);
-                if (slot >= 0) atomicOr((unsigned long long*)&P.h_mask[slot], (unsigned long long)mymask);
-            }
-        }
-        if (lane == 0 && slot >= 0) {  // lane 0 holds the owner block
-            P.h_start[slot] = (int)first;
-            P.h_end[slot] = (int)end;
-            if (P.h_entry) P.h_entry[slot] = e;
-        }
-    }
-}
-
-// Work items of a block holding cnt particles (none for a block that only
-// holds stencil nodes).
-__device__ __forceinline__ unsigned block_chunks(const DevParams& P, int cnt) {
-    return cnt > 0 ? (unsigned)((cnt + P.chunk - 1) / P.chunk) : 0u;
-}
-
-// Compaction, first pass: occupied slots per tile of the hash table
-// (partials[tile]) and, with `items`, the work items of their blocks
-// (partials[tiles + tile]).
-__global__ __launch_bounds__(WG) void k_compact_count(DevParams P, int H, unsigned* __restrict__ partials, int tiles,
-                                                      bool items) {
+// Work items per tile of the table (after k_hash_insert, whose waves see only
+// parts of a block; a re-sort's insertion counts them itself).
+__global__ __launch_bounds__(WG) void k_count_items(DevParams P, int H) {
     __shared__ unsigned lds[WG / 64];
-    const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    // all loads in flight at once: clamped index, masked result
-    uint64_t key[SCAN_ITEMS];
-#pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) key[j] = P.h_keys[min(base + j, H - 1)];
-    unsigned s = 0, w = 0;
+    const int base = blockIdx.x * SCAN_TILE + threadIdx.x;
     int st[SCAN_ITEMS], en[SCAN_ITEMS];
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) {
-        const bool occ = base + j < H && key[j] != EMPTY_KEY;
-        s += occ ? 1u : 0u;
-        st[j] = -1;
-        en[j] = -1;
-        if (items && occ) {
-            st[j] = P.h_start[base + j];
-            en[j] = P.h_end[base + j];
-        }
+        const int idx = min(base + j * WG, H - 1);
+        st[j] = P.h_start[idx];
+        en[j] = P.h_end[idx];
     }
+    unsigned w = 0;
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) w += st[j] >= 0 ? block_chunks(P, en[j] - st[j]) : 0u;
+    for (int j = 0; j < SCAN_ITEMS; ++j) w += base + j * WG < H && st[j] >= 0 ? block_chunks(P, en[j] - st[j]) : 0u;
     unsigned tot;
-    wg_excl_scan(s, lds, &tot);
-    if (threadIdx.x == 0) partials[blockIdx.x] = tot;
-    if (items) {
-        wg_excl_scan(w, lds, &tot);
-        if (threadIdx.x == 0) partials[tiles + blockIdx.x] = tot;
-    }
+    wg_excl_scan(w, lds, &tot);
+    if (threadIdx.x == 0) P.t_cnt[blockIdx.x * LINE + 1] = tot;
 }
 
-// Compaction, second pass: Phi in slot order and the block tables; with
-// `items` also the work items of each block, at the exclusive prefix of the
-// item counts in slot order (which is Phi order), so no separate scan of the
-// per-block counts is needed.
-__global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, const unsigned* __restrict__ partials,
-                                                      int tiles, int* __restrict__ slot_of, bool items) {
-    __shared__ unsigned lds[WG / 64];
-    // Loads first: the keys, then the fields of the occupied slots, all in
-    // flight while the tile sums are read and scanned (the barriers of those
-    // scans would otherwise hold them back).
-    const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    uint64_t key[SCAN_ITEMS], mask[SCAN_ITEMS];
-    int st[SCAN_ITEMS], en[SCAN_ITEMS], ent[SCAN_ITEMS];
-    bool occ[SCAN_ITEMS];
-    unsigned s = 0;
+// Compaction: Phi in slot order and the block tables, one workgroup per tile of
+// SCAN_TILE slots, whose occupied slots and work items the insertion counted
+// (t_cnt), so that each tile adds up the counts before it and no pass over the
+// table precedes this one.  A table is a few per cent full: the tile's occupied
+// slots are first listed in LDS (64 contiguous keys per wave and round, a
+// ballot and a popcount each), then every thread takes one slot of the list.
+// The passes are bound by latency, not bandwidth.  (With eight slots per
+// thread carried through, and the counting as a pass of its own, the two took
+// 4.8 + 10.2 us at 32,768 slots and 8.8 + 17.6 us at 2,097,152.)
+// ITEMS: also the work items and the state that the counting of the next
+// incremental re-sort starts from.
+template <int DIM, bool ITEMS>
+__global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int tiles) {
+    constexpr int NB = 1 << DIM, NC = 1 << (2 * DIM);
+    constexpr int NW = WG / 64, ROUNDS = SCAN_TILE / WG;
+    __shared__ unsigned short list[SCAN_TILE];  // occupied slots of the tile, ascending
+    __shared__ unsigned red[NW][4], wcnt[NW * ROUNDS], lds[NW];
+    const int lane = __lane_id(), wv = threadIdx.x >> 6;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int base = blockIdx.x * SCAN_TILE;
+    uint64_t k[ROUNDS];
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
-        const int idx = base + j;
-        key[j] = idx < H ? P.h_keys[idx] : EMPTY_KEY;
+    for (int j = 0; j < ROUNDS; ++j) {
+        const int idx = base + j * WG + (int)threadIdx.x;
+        k[j] = idx < H ? P.h_keys[idx] : EMPTY_KEY;
+    }
+    // sums over the tiles: occupied slots and items before this one, and all
+    unsigned sum[4] = {0u, 0u, 0u, 0u};
+    for (int i = threadIdx.x; i < tiles; i += WG) {
+        const unsigned c = P.t_cnt[i * LINE], it = P.t_cnt[i * LINE + 1];
+        sum[0] += i < (int)blockIdx.x ? c : 0u;
+        sum[1] += i < (int)blockIdx.x ? it : 0u;
+        sum[2] += c;
+        sum[3] += it;
+    }
+    unsigned long long occ[ROUNDS];
+#pragma unroll
+    for (int j = 0; j < ROUNDS; ++j) {
+        occ[j] = __ballot(k[j] != EMPTY_KEY);
+        if (lane == 0) wcnt[j * NW + wv] = (unsigned)__popcll(occ[j]);
     }
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
-        const int idx = base + j;
-        occ[j] = key[j] != EMPTY_KEY;
-        s += occ[j];
-        st[j] = -1;
-        en[j] = -1;
-        if (occ[j]) {
-            mask[j] = P.h_mask[idx];
-            st[j] = P.h_start[idx];
-            en[j] = P.h_end[idx];
-            ent[j] = P.b_entry ? P.h_entry[idx] : -1;
-        }
-    }
-    unsigned wsum = 0;
+    for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) wsum += st[j] >= 0 ? block_chunks(P, en[j] - st[j]) : 0u;
-    unsigned before, total, wbefore = 0, wtotal = 0;
-    tile_offset(partials, blockIdx.x, tiles, lds, &before, &total);
-    if (items) tile_offset(partials + tiles, blockIdx.x, tiles, lds, &wbefore, &wtotal);
-    unsigned tot;
-    unsigned phi = wg_excl_scan(s, lds, &tot) + before;
-    unsigned w = items ? wg_excl_scan(wsum, lds, &tot) + wbefore : 0u;
+        for (int q = 0; q < 4; ++q) sum[q] += __shfl_xor(sum[q], o);
+    if (lane == 0)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) red[wv][q] = sum[q];
+    __syncthreads();
+    // every wave scans the NW * ROUNDS ballot counts for itself
+    const unsigned mine = lane < NW * ROUNDS ? wcnt[lane] : 0u;
+    const unsigned inc = wave_incl_scan(mine);
+    const int n_occ = readlane32((int)inc, 63);
+#pragma unroll
+    for (int j = 0; j < ROUNDS; ++j) {
+        const int q = j * NW + wv;
+        const unsigned first = (unsigned)__shfl((int)(inc - mine), q);
+        if (k[j] != EMPTY_KEY) list[first + (unsigned)__popcll(occ[j] & lt)] = (unsigned short)(j * WG + threadIdx.x);
+    }
+    __syncthreads();
+    unsigned phi0 = 0, it0 = 0, total = 0, wtotal = 0;
+#pragma unroll
+    for (int q = 0; q < NW; ++q) {
+        phi0 += red[q][0];
+        it0 += red[q][1];
+        total += red[q][2];
+        wtotal += red[q][3];
+    }
     bool over = false;
-#pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
-        if (!occ[j]) continue;
-        const int idx = base + j;
-        const int cnt = st[j] >= 0 ? en[j] - st[j] : 0;
+#pragma unroll 1
+    for (int t0 = 0; t0 < n_occ; t0 += WG) {
+        const bool o = t0 + (int)threadIdx.x < n_occ;
+        const int idx = o ? base + list[t0 + threadIdx.x] : 0;
+        const unsigned phi = phi0 + (unsigned)(t0 + (int)threadIdx.x);
+        uint64_t key = 0, mask = 0;
+        int st = -1, en = -1, ent = -1;
+        if (o) {
+            key = P.h_keys[idx];
+            mask = P.h_mask[idx];
+            st = P.h_start[idx];
+            en = P.h_end[idx];
+            if (P.b_entry) ent = P.h_entry[idx];
+        }
+        const int cnt = st >= 0 ? en - st : 0;
         const unsigned chunks = block_chunks(P, cnt);
-        if ((int)phi < P.block_cap) {
-            P.b_keys[phi] = key[j];
-            P.b_mask[phi] = mask[j];
-            P.b_start[phi] = st[j];
+        unsigned w = it0;
+        if (ITEMS) {
+            unsigned tot;
+            w += wg_excl_scan(chunks, lds, &tot);
+            it0 += tot;
+        }
+        const bool fits = o && phi < (unsigned)P.block_cap;
+        if (fits) {
+            P.b_keys[phi] = key;
+            P.b_mask[phi] = mask;
+            P.b_start[phi] = st;
             P.b_count[phi] = cnt;
             P.h_vals[idx] = (int)phi;
-            if (slot_of) slot_of[phi] = idx;
-            if (P.b_entry) P.b_entry[phi] = ent[j];
-            if (items) {
+            P.b_hs[phi] = idx;
+            if (ITEMS) {
+                if (P.b_entry) P.b_entry[phi] = ent;
                 P.b_chunks[phi] = chunks;
-                for (unsigned k = 0; k < chunks; ++k) {
-                    if (w + k >= (unsigned)P.work_cap) {
+                P.b_chunk_off[phi] = w;
+#pragma unroll
+                for (int d = 0; d < NB; d += 4)  // set by the P2G of the blocks that reach this one
+                    *(int4*)&P.b_lo[(size_t)phi * NB + d] = make_int4(-1, -1, -1, -1);
+                for (unsigned q = 0; q < chunks; ++q) {
+                    if (w + q >= (unsigned)P.work_cap) {
                         over = true;
                         break;
                     }
-                    P.w_block[w + k] = (int)phi;
-                    P.w_start[w + k] = st[j] + (int)k * P.chunk;
-                    P.w_end[w + k] = min(st[j] + ((int)k + 1) * P.chunk, en[j]);
+                    P.w_block[w + q] = (int)phi;
+                    P.w_start[w + q] = st + (int)q * P.chunk;
+                    P.w_end[w + q] = min(st + ((int)q + 1) * P.chunk, en);
                 }
             }
-        } else {
+        } else if (o) {
             P.h_vals[idx] = -1;
             over = true;
         }
-        w += chunks;
-        ++phi;
+        if (ITEMS && P.rs_stay) {
+            // for the next incremental re-sort, when a G2P counts for it: the
+            // owner part of the block's sort key, and cleared counts where G2P
+            // will not store them whole (no particle, or several work items
+            // adding theirs; the cell counts of a block without particles are
+            // not read)
+            if (fits) {
+                int bc[3], inst;
+                unblock_key<DIM>(P, key, bc, &inst);
+                bool in_range = inst < max(P.n_inst, 1);
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) in_range = in_range && bc[a] >= 0 && bc[a] < P.nblk[a];
+                const uint32_t bl = DIM == 3 ? ((uint32_t)bc[2] * (uint32_t)P.nblk[1] + (uint32_t)bc[1]) *
+                                                       (uint32_t)P.nblk[0] + (uint32_t)bc[0]
+                                             : (uint32_t)bc[1] * (uint32_t)P.nblk[0] + (uint32_t)bc[0];
+                P.rs_oldblk[phi] = in_range ? ((uint32_t)inst << P.blk_bits) | bl : ~0u;
+                if (chunks != 1u || total > (unsigned)P.block_cap) P.rs_cnt[phi] = 0u;  // past the capacity no G2P counts
+            }
+            unsigned long long multi = __ballot(fits && chunks > 1u);
+            while (multi) {  // a row per step, contiguous
+                const int l = __ffsll((long long)multi) - 1;
+                const unsigned p = (unsigned)readlane32((int)phi, l);
+                if (lane < NC) P.rs_stay[(size_t)p * NC + lane] = 0u;
+                multi &= multi - 1ull;
+            }
+        }
     }
     if (over) raise_flag(P.ctr, MPM_FLAG_OVERFLOW);
-    if (blockIdx.x == 0 && threadIdx.x == 0) {
-        P.ctr->n_touched = total;
-        P.ctr->nb = min((int)total, P.block_cap);
-        // items of blocks past the capacity were not written: no work then
-        if (items) P.ctr->n_work = total <= (unsigned)P.block_cap ? (int)wtotal : 0;
+    if (blockIdx.x == 0) {
+        if (threadIdx.x == 0) {
+            P.ctr->n_touched = total;
+            P.ctr->nb = min((int)total, P.block_cap);
+            if (ITEMS) {
+                // items of blocks past the capacity were not written: no work then
+                P.ctr->n_work = total <= (unsigned)P.block_cap ? (int)wtotal : 0;
+                P.ctr->rs_n_new = 0;    // the new blocks the next re-sort's route claims
+                P.ctr->rs_new_pos = 0;  // and their particles
+            }
+        }
+        if (ITEMS && P.rs_tile)
+            for (int t = threadIdx.x; t < (P.block_cap + RS_TILE - 1) / RS_TILE; t += WG) P.rs_tile[t * LINE] = 0u;
     }
 }
 
@@ -419,79 +379,22 @@ __global__ __launch_bounds__(WG) void k_det_keys(DevParams P, const uint64_t* __
     }
 }
 
+template <int DIM>
 __global__ __launch_bounds__(WG) void k_det_apply(DevParams P, DetTables T, const uint32_t* __restrict__ sorted) {
+    constexpr int NB = 1 << DIM;
     const int nb = P.ctr->nb;
     for (int r = blockIdx.x * WG + threadIdx.x; r < nb; r += gridDim.x * WG) {
         const int b = (int)sorted[r];
         P.b_keys[r] = T.keys[b];
         P.b_mask[r] = T.mask[b];
         P.b_start[r] = T.start[b];
-        P.b_count[r] = T.count[b];
-        P.h_vals[T.slot[b]] = r;
-    }
-}
-
-// Neighbour tables and chunking of the compact blocks, 2^(d+1) lanes per block:
-// lane j < 2^d looks up upper neighbour j, lane 2^d + j lower neighbour j (so
-// the probe chains of a block run side by side, not one after another).
-template <int DIM>
-__global__ __launch_bounds__(WG) void k_block_setup(DevParams P) {
-    constexpr int NB = 1 << DIM;
-    constexpr int LPB = 2 * NB;
-    constexpr int NC = 1 << (2 * DIM);
-    const int nb = P.ctr->nb;
-    const long long total = (long long)nb * LPB;
-    for (long long t = (long long)blockIdx.x * WG + threadIdx.x; t < total; t += (long long)gridDim.x * WG) {
-        const int b = (int)(t / LPB), j = (int)(t % LPB);
-        const int d = j % NB;
-        // the block's count is loaded beside its key, not after the lookups
-        const uint64_t bkey = P.b_keys[b];
-        int bcount = P.b_count[b];
-        asm volatile("" : "+v"(bcount));
-        int bc[3], inst;
-        unblock_key<DIM>(P, bkey, bc, &inst);
-        if (j < NB) {
-            P.b_nbr[b * NB + d] =
-                d == 0 ? b
-                       : hash_lookup(P, block_key<DIM>(P, bc[0] + (d & 1), bc[1] + ((d >> 1) & 1),
-                                                       bc[2] + ((d >> 2) & 1), inst));
-        } else if (P.b_lo) {
-            // lower neighbours that own particles (the blocks whose P2G tiles
-            // reach this block), -1 for the others
-            const int lo = d == 0 ? b
-                                  : hash_lookup(P, block_key<DIM>(P, bc[0] - (d & 1), bc[1] - ((d >> 1) & 1),
-                                                                  bc[2] - ((d >> 2) & 1), inst));
-            P.b_lo[b * NB + d] = (lo >= 0 && P.b_count[lo] > 0) ? lo : -1;
-        }
-        const unsigned chunks = (unsigned)((bcount + P.chunk - 1) / P.chunk);
-        if (j == 0) P.b_chunks[b] = chunks;
-        if (P.rs_stay) {
-            // for the next incremental re-sort, when a G2P bins its output:
-            // the owner part of the block's sort key, and cleared per-cell
-            // stayer counts and entry total where G2P will not store them
-            // whole (no particle, or several work items adding theirs)
-            if (j == 0) {
-                bool in_range = inst < max(P.n_inst, 1);
+        const int cnt = T.count[b], slot = T.slot[b];
+        P.b_count[r] = cnt;
+        P.b_chunks[r] = block_chunks(P, cnt);
+        P.h_vals[slot] = r;
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) in_range = in_range && bc[a] >= 0 && bc[a] < P.nblk[a];
-                uint32_t owner = ~0u;
-                if (in_range) {
-                    const uint32_t bl = DIM == 3 ? ((uint32_t)bc[2] * (uint32_t)P.nblk[1] + (uint32_t)bc[1]) *
-                                                           (uint32_t)P.nblk[0] + (uint32_t)bc[0]
-                                                 : (uint32_t)bc[1] * (uint32_t)P.nblk[0] + (uint32_t)bc[0];
-                    owner = ((uint32_t)inst << P.blk_bits) | bl;
-                }
-                P.rs_oldblk[b] = owner;
-            }
-            if (chunks != 1u) {
-                for (int c = j; c < NC; c += LPB) P.rs_stay[(size_t)b * NC + c] = 0u;
-                if (j == 0) P.rs_cnt[b] = 0u;
-            }
-        }
-    }
-    if (P.rs_stay && blockIdx.x == 0 && threadIdx.x == 0) {
-        P.ctr->rs_n_mov = 0;  // the movers the next G2P lists
-        P.ctr->rs_n_new = 0;  // the new blocks the next re-sort's route claims
+        for (int d = 0; d < NB; ++d) P.b_lo[(size_t)r * NB + d] = -1;
+        P.b_hs[r] = slot;
     }
 }
 
@@ -590,60 +493,53 @@ hipError_t launch_bin(const DevParams& P, const float* x, const uint32_t* inst, 
     return hipGetLastError();
 }
 
-hipError_t launch_build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsigned H, unsigned* partials,
-                               hipStream_t s, bool from_resort, const DetTables* det) {
-    if (!from_resort) k_hash_clear<<<grid_for(H), WG, 0, s>>>(P, H);  // the re-sort's last pass clears it
-    if (n > 0 && from_resort) {
-        const int ge = grid_for(2ll * P.block_cap * 64, 16384);  // one wave per entry
-        if (P.dim == 3)
-            k_hash_insert_entries<3><<<ge, WG, 0, s>>>(P);
-        else
-            k_hash_insert_entries<2><<<ge, WG, 0, s>>>(P);
-    } else if (n > 0) {
-        const int per_wg = WG * HI_ROUNDS;
-        if (P.dim == 3)
-            k_hash_insert<3><<<(n + per_wg - 1) / per_wg, WG, 0, s>>>(P, skeys, n);
-        else
-            k_hash_insert<2><<<(n + per_wg - 1) / per_wg, WG, 0, s>>>(P, skeys, n);
-    }
+namespace {
+template <int DIM>
+hipError_t build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsigned H, unsigned* partials, hipStream_t s,
+                        bool inserted, const DetTables* det) {
     const int tiles = ((int)H + SCAN_TILE - 1) / SCAN_TILE;
-    const int gb = grid_for(P.block_cap, 2048);
-    const int gs = grid_for(2ll * (1 << P.dim) * P.block_cap, 8192);  // k_block_setup: 2^(d+1) lanes per block
+    if (!inserted) {
+        k_hash_clear<DIM><<<grid_for(H), WG, 0, s>>>(P, H);
+        if (n > 0) {
+            const int per_wg = WG * HI_ROUNDS;
+            k_hash_insert<DIM><<<(n + per_wg - 1) / per_wg, WG, 0, s>>>(P, skeys, n);
+            if (!det) k_count_items<<<tiles, WG, 0, s>>>(P, (int)H);
+        }
+    }
     // without the key order, Phi is slot order and the compaction also writes
     // the work items
-    const bool items = det == nullptr;
-    k_compact_count<<<tiles, WG, 0, s>>>(P, (int)H, partials, tiles, items);
-    if (det) {
-        // compaction in slot order into the alternate tables, then the blocks
-        // sorted by key and gathered into the block tables
-        DevParams Pa = P;
-        Pa.b_keys = det->keys;
-        Pa.b_mask = det->mask;
-        Pa.b_start = det->start;
-        Pa.b_count = det->count;
-        k_compact_write<<<tiles, WG, 0, s>>>(Pa, (int)H, partials, tiles, det->slot, false);
-        const int kb = P.blk_bits + (P.n_inst > 1 ? 6 : 0);
-        const uint32_t sentinel = kb >= 32 ? 0xFFFFFFFFu : ((1u << kb) - 1u);
-        if (P.dim == 3)
-            k_det_keys<3><<<gb, WG, 0, s>>>(P, det->keys, det->k[1], sentinel);
-        else
-            k_det_keys<2><<<gb, WG, 0, s>>>(P, det->keys, det->k[1], sentinel);
-        uint32_t *ko = nullptr, *vo = nullptr;
-        hipError_t e = radix_sort(det->k[1], det->k[0], det->k[1], det->v[0], det->v[1], P.block_cap, kb, det->hist,
-                                  partials, &ko, &vo, s);
-        if (e != hipSuccess) return e;
-        k_det_apply<<<gb, WG, 0, s>>>(P, *det, vo);
-    } else {
-        k_compact_write<<<tiles, WG, 0, s>>>(P, (int)H, partials, tiles, nullptr, true);
+    if (!det) {
+        k_compact_write<DIM, true><<<tiles, WG, 0, s>>>(P, (int)H, tiles);
+        // no grid clear: the second P2G pass writes every node of every active block
+        return hipGetLastError();
     }
-    if (P.dim == 3)
-        k_block_setup<3><<<gs, WG, 0, s>>>(P);
-    else
-        k_block_setup<2><<<gs, WG, 0, s>>>(P);
-    hipError_t e = hipGetLastError();
+    // compaction in slot order into the alternate tables, then the blocks
+    // sorted by key and gathered into the block tables
+    const int gb = grid_for(P.block_cap, 2048);
+    DevParams Pa = P;
+    Pa.b_keys = det->keys;
+    Pa.b_mask = det->mask;
+    Pa.b_start = det->start;
+    Pa.b_count = det->count;
+    Pa.b_hs = det->slot;
+    k_compact_write<DIM, false><<<tiles, WG, 0, s>>>(Pa, (int)H, tiles);
+    const int kb = P.blk_bits + (P.n_inst > 1 ? 6 : 0);
+    const uint32_t sentinel = kb >= 32 ? 0xFFFFFFFFu : ((1u << kb) - 1u);
+    k_det_keys<DIM><<<gb, WG, 0, s>>>(P, det->keys, det->k[1], sentinel);
+    uint32_t *ko = nullptr, *vo = nullptr;
+    hipError_t e = radix_sort(det->k[1], det->k[0], det->k[1], det->v[0], det->v[1], P.block_cap, kb, det->hist, partials,
+                              &ko, &vo, s);
     if (e != hipSuccess) return e;
-    // no grid clear: the second P2G pass writes every node of every active block
-    return items ? hipSuccess : launch_work_items(P, partials, s);
+    k_det_apply<DIM><<<gb, WG, 0, s>>>(P, *det, vo);
+    e = hipGetLastError();
+    return e == hipSuccess ? launch_work_items(P, partials, s) : e;
+}
+}  // namespace
+
+hipError_t launch_build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsigned H, unsigned* partials,
+                               hipStream_t s, bool inserted, const DetTables* det) {
+    return P.dim == 3 ? build_sparse<3>(P, skeys, n, H, partials, s, inserted, det)
+                      : build_sparse<2>(P, skeys, n, H, partials, s, inserted, det);
 }
 
 // Work items: exclusive scan of the per-block chunk counts, then the items.

@@ -5,7 +5,8 @@
 //             digit histograms;
 //   hash      H slots: packed block key (u64, EMPTY = ~0), node mask (u64),
 //             compact index (i32), first/one-past-last sorted particle of the
-//             block's owner segment (i32);
+//             block's owner segment (i32), the slots of the 2^d blocks its
+//             stencils reach (i32 each);
 //   blocks    block_capacity entries in compact order Phi: key, node mask,
 //             2^d neighbour compact indices (upper neighbours), owner segment
 //             start and length, P2G/G2P chunk count and offset;
@@ -44,10 +45,23 @@ struct DevCounters {
     int n_work;      // P2G/G2P work items
     unsigned flags;  // sticky MPM_FLAG_* bits
     int rs_n_new;    // incremental re-sort: blocks without a previous slot
-    int rs_n_ent;    //   entries (previous blocks, then new blocks)
-    int rs_n_mov;    //   particles that changed owner block (0 between builds)
-    int pad;
+    int rs_new_pos;  //   particles of the new blocks placed so far
+    int pad[2];
 };
+
+constexpr int RS_TILE = 256;  // entries per partial sum of the re-sort's particle counts
+// Words between counters that many workgroups add to: one cache line each.
+// Adds to one line from several XCDs are served one after another, 15-20 ns
+// each (12,500 adds to a single word took 200 us, a few thousand to counters
+// sharing a line 40 us).
+constexpr int LINE = 32;
+// Particle count up to which the short passes of a build are folded into their
+// neighbours (the re-sort's scan into the placement, the neighbour tables into
+// P2G).  Below it a launch and a pass's latency are what they cost; above it
+// the folded forms' extra loads cost more (2.5 M particles: placement 18.9 us
+// against 14.0 + 9.5 for the scan, P2G +3 us against a 7 us pass; 20 M: 82
+// against 68 + 9, P2G +30 us against 10).
+constexpr int FOLD_MAX_N = 1 << 22;
 
 // Per-instance material and step constants (one entry for a single simulation).
 struct InstMat {
@@ -83,6 +97,9 @@ struct DevParams {
     int* h_vals;
     int* h_start;
     int* h_end;
+    int* h_nslot;           // hash-built tables: per slot of an owner block, the slots of the 2^d
+                            // blocks its stencils reach (d = 0: itself; -1: not reached)
+    unsigned* t_cnt;        // per SCAN_TILE slots, LINE words apart: occupied ones, work items
     unsigned h_mask_bits;   // H - 1
     int n_probe;
     // compact blocks
@@ -93,6 +110,7 @@ struct DevParams {
     int* b_count;
     unsigned* b_chunks;
     unsigned* b_chunk_off;
+    int* b_hs;              // hash slot of each compact block (null: the build makes b_nbr, b_lo itself)
     int block_cap;
     // work items
     int* w_block;
@@ -119,12 +137,17 @@ struct DevParams {
     uint32_t* rs_off;     // first sorted position per entry and cell
     unsigned* rs_cnt;     // particles per entry (stayers from G2P or the count pass, plus movers)
     unsigned* rs_start;   // first sorted position per entry
+    int* rs_nslot;        // h_nslot's row of each entry
+    uint64_t* rs_occ;     // base cells holding particles, per entry
     uint32_t* rs_oldblk;  // owner-block part of the sort key of each entry (~0: empty previous block)
     uint64_t* nh_keys;    // second hash table (same size as the block table): blocks
     uint32_t* nh_cnt;     //   with no previous slot, their movers per cell,
     int* nh_idx;          //   their entry index
     uint32_t* nh_owner;   //   and the owner-block part of their sort key
     uint32_t* rs_new;     // second-table slots in the order of their claims (block_cap entries)
+    unsigned* rs_tile;    // particles per RS_TILE previous blocks (sums of rs_cnt), LINE words apart; null
+                          // above FOLD_MAX_N particles
+    unsigned* it_mov;     // movers of each work item, listed from the item's first position on
     int* h_entry;         // re-sort entry of each hash slot's owner block (-1: none)
     int* b_entry;         // re-sort entry of each compact block (-1: none): its cell
                           // ranges are the entry's row of rs_off
@@ -413,13 +436,13 @@ hipError_t radix_sort(const uint32_t* keys_in, uint32_t* k0, uint32_t* k1, uint3
 int radix_hist_size(int n);
 
 hipError_t launch_bin(const DevParams& P, const float* x, const uint32_t* inst, int n, uint32_t* keys, hipStream_t s);
-// keys_out may be null: the sorted keys are then not written (after an
-// incremental re-sort nothing reads them; P2G takes the cell ranges from the
-// re-sort's per-entry table).  movers and tgt: n entries each (the mover list
-// and each mover's target, which the route records for the placement).
-hipError_t launch_resort(const DevParams& P, const uint32_t* keys_new, uint32_t* keys_out, uint32_t* vals_out,
-                         uint32_t* movers, uint32_t* tgt, int n, unsigned H, unsigned* partials, hipStream_t s,
-                         bool counted = false);
+// The sorted keys are not written (after an incremental re-sort nothing reads
+// them; P2G takes the cell ranges from the re-sort's per-entry table).  movers
+// and tgt: n entries each (the movers of each work item, listed from the item's
+// first position on, and each mover's target, which the route records for the
+// placement).  Fills the block hash as well.
+hipError_t launch_resort(const DevParams& P, const uint32_t* keys_new, uint32_t* vals_out, uint32_t* movers,
+                         uint32_t* tgt, int n, unsigned H, unsigned* partials, hipStream_t s, bool counted = false);
 hipError_t launch_resort_init(const DevParams& P, unsigned H, hipStream_t s);
 // Buffers of the ascending-key Phi order (MPM_FLAG_DETERMINISTIC_ORDER): block
 // tables in slot order, the slot of each, and a radix sort of block_cap
@@ -434,8 +457,9 @@ struct DetTables {
     uint32_t* v[2];
     unsigned* hist;
 };
+// inserted: the re-sort has filled the block hash already.
 hipError_t launch_build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsigned H, unsigned* partials,
-                               hipStream_t s, bool from_resort = false, const DetTables* det = nullptr);
+                               hipStream_t s, bool inserted = false, const DetTables* det = nullptr);
 hipError_t launch_build_dense(const DevParams& P, const uint32_t* skeys, int n, int n_blocks, unsigned* partials,
                               hipStream_t s);
 // update: the grid update (Eqs. 8-12) is applied in P2G's second pass (sparse

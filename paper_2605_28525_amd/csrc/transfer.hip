@@ -39,7 +39,40 @@ namespace mpmx {
 // base node scatters to the same 3^d nodes.  A lane therefore sums its cell's
 // particles into 27 x 4 registers and adds them to the LDS tile once per cell,
 // not once per particle; the tile then goes to HBM as above.
+// Neighbour tables of a hash-built grid, when every Phi is known: lane d of an
+// owner block takes the compact index of the slot that the insertion found for
+// upper neighbour d (-1: not reached) ...
 template <int DIM>
+__device__ __forceinline__ int link_slot(const DevParams& P, int ent, int hs, int d) {
+    // (the re-sort's rows are dense, the full sort's lie by hash slot)
+    return ent >= 0 ? P.rs_nslot[((size_t)ent << DIM) + d] : P.h_nslot[((size_t)hs << DIM) + d];
+}
+// ... and stores it for G2P and, from the other side, for the gather (the
+// block is one of the lower blocks whose tile reaches that neighbour).
+template <int DIM>
+__device__ __forceinline__ void link_store(const DevParams& P, int b, int d, int phi) {
+    P.b_nbr[((size_t)b << DIM) + d] = phi;
+    if (phi >= 0) P.b_lo[((size_t)phi << DIM) + d] = b;
+}
+
+// The tables in a launch of their own, 2^d lanes per block.
+template <int DIM>
+__global__ __launch_bounds__(WG) void k_link(DevParams P) {
+    constexpr int NB = 1 << DIM;
+    const int nb = min(P.ctr->nb, P.block_cap);
+    const int t0 = blockIdx.x * WG + threadIdx.x;
+    for (int b = t0 / NB; b < nb; b += (int)(gridDim.x * WG) / NB) {
+        const int d = t0 % NB;
+        const int cnt = P.b_count[b], hs = P.b_hs[b], ent = P.b_entry ? P.b_entry[b] : -1;
+        if (cnt <= 0) continue;
+        const int slot = link_slot<DIM>(P, ent, hs, d);
+        link_store<DIM>(P, b, d, slot >= 0 ? P.h_vals[slot] : -1);
+    }
+}
+
+// LINK: P2G makes the neighbour tables beside its own work (launch_p2g has the
+// line between the two forms).
+template <int DIM, bool LINK>
 __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __restrict__ x,
                                                  const float* __restrict__ v, const float* __restrict__ C,
                                                  const float* __restrict__ tau, int n,
@@ -59,7 +92,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
     // The count, first sorted position and key of the next block are loaded
     // while the current one is processed (a dense grid has no key table: its
     // key is the linear block index).
-    int cnt_n = 0, st_n = 0, ent_n = -1;
+    int cnt_n = 0, st_n = 0, ent_n = -1, hs_n = 0;
     uint64_t key_n = 0;
     auto fetch_meta = [&](int bb) {
         if (bb < nb) {
@@ -70,16 +103,23 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
             st_n = P.b_start[bb];
             key_n = P.dense ? (uint64_t)bb : P.b_keys[bb];
             ent_n = P.b_entry ? P.b_entry[bb] : -1;
+            if (LINK) hs_n = P.b_hs[bb];
         }
     };
     fetch_meta(blockIdx.x);
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int cnt = cnt_n, st = st_n, ent = ent_n;
+        const int cnt = cnt_n, st = st_n, ent = ent_n, hs = hs_n;
         const uint64_t key = key_n;
         fetch_meta(b + gridDim.x);
         if (cnt <= 0) continue;
         const int en = st + cnt;
-        const int nbv = lane < T::NB ? P.b_nbr[(size_t)b * T::NB + lane] : -1;
+        int nbv = -1;  // compact index of upper neighbour `lane`
+        int slot = -1;  // and its hash slot
+        if (LINK) {
+            if (lane < T::NB) slot = link_slot<DIM>(P, ent, hs, lane);
+        } else if (P.dense) {
+            if (lane < T::NB) nbv = P.b_nbr[(size_t)b * T::NB + lane];
+        }
         for (int t = lane; t < 4 * T::NP; t += 64) (&tile[0][0])[t] = 0.f;
         int bc[3], inst = 0;
         if (P.dense)
@@ -100,7 +140,8 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         // row of first positions; otherwise they are counted from the keys
         interleave_setup<DIM>(il, skeys, st, en, order, ord, P2G_ORDER_STAGE,
                               ent >= 0 ? P.rs_off + (size_t)ent * NC : nullptr);
-        if (lane < T::NB) nbr[lane] = nbv;
+        if (LINK && slot >= 0) nbv = P.h_vals[slot];
+        if (!LINK && lane < T::NB) nbr[lane] = nbv;
         float acc[NK][4];
 #pragma unroll
         for (int k = 0; k < NK; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
@@ -294,6 +335,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                 P.tiles[(size_t)b * T::N + t] =
                     make_float4(tile[0][tp], tile[1][tp], DIM == 3 ? tile[2][tp] : 0.f, tile[3][tp]);
             }
+            if (LINK && lane < T::NB) link_store<DIM>(P, b, lane, nbv);
             __syncthreads();
             continue;
         }
@@ -770,8 +812,8 @@ struct G2POut {
 // keeps the block's owner ("stayers") are counted per base cell in LDS and
 // the counts stored to the block's row of rs_stay and their sum to rs_cnt
 // (added, for blocks split over several items, to what the build cleared);
-// the others ("movers") are appended to out.movers at a position claimed once
-// per wave from the counter rs_n_mov.
+// the others ("movers") are listed in out.movers from the item's first position
+// on, their number in it_mov.
 template <int DIM, int GS>
 __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, int n,
                                             const uint32_t* __restrict__ osrc) {
@@ -785,7 +827,9 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
     __shared__ float fs[DD][MAXI];
     constexpr int NC = 1 << (2 * DIM);
     __shared__ unsigned scnt[NC];  // stayers per base cell of the current item's block
+    __shared__ unsigned mcnt;      // movers of the current item
     if (threadIdx.x < NC) scnt[threadIdx.x] = 0u;
+    if (threadIdx.x == 0) mcnt = 0u;
     const int n_work = min(P.ctr->n_work, P.work_cap);
     const float dx = P.dxf, inv_dx = P.inv_dxf;
     const float cscale = 4.f * inv_dx * inv_dx;  // D_p^{-1} = (4/dx^2) I for quadratic B-splines
@@ -1027,12 +1071,9 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
                         const int leader = __ffsll((long long)mv) - 1;
                         const int lane = __lane_id();
                         unsigned base = 0u;
-                        if (lane == leader) base = atomicAdd((unsigned*)&P.ctr->rs_n_mov, (unsigned)__popcll(mv));
+                        if (lane == leader) base = atomicAdd(&mcnt, (unsigned)__popcll(mv));
                         base = (unsigned)__shfl((int)base, leader);
-                        if (!stay) {
-                            const unsigned slot = base + (unsigned)__popcll(mv & ((1ull << lane) - 1ull));
-                            if (slot < (unsigned)n) out.movers[slot] = (uint32_t)o;
-                        }
+                        if (!stay) out.movers[s + base + (unsigned)__popcll(mv & ((1ull << lane) - 1ull))] = (uint32_t)o;
                     }
                 }
             }
@@ -1095,11 +1136,16 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
                 scnt[threadIdx.x] = 0u;  // ordered before the next item's counting by the barrier of its phase 0
             }
             const unsigned tot = wave_incl_scan(c);
+            if (threadIdx.x == 0) {
+                P.it_mov[w] = mcnt;
+                mcnt = 0u;
+            }
             if (threadIdx.x == 63) {
                 if (chunks == 1u)
                     P.rs_cnt[cur.blk] = tot;
                 else if (tot)
                     atomicAdd(&P.rs_cnt[cur.blk], tot);
+                if (P.rs_tile && tot) atomicAdd(&P.rs_tile[cur.blk / RS_TILE * LINE], tot);
             }
         }
         w += G;
@@ -1112,10 +1158,17 @@ hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const 
                       const uint32_t* order, const uint32_t* skeys, uint32_t* osrc, int grid_blocks, hipStream_t s,
                       bool update) {
     const int g = P.dense ? 65536 : grid_blocks * 4;
-    if (P.dim == 3)
-        k_p2g_cell<3><<<g, 64, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
-    else
-        k_p2g_cell<2><<<g, 64, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
+    const bool link = P.b_hs != nullptr && n <= FOLD_MAX_N;
+    const auto cell =
+        P.dim == 3 ? (link ? k_p2g_cell<3, true> : k_p2g_cell<3, false>) : (link ? k_p2g_cell<2, true> : k_p2g_cell<2, false>);
+    if (P.b_hs && !link) {
+        const int gl = (int)std::min<long long>((((long long)P.block_cap << P.dim) + WG - 1) / WG, 4096);
+        if (P.dim == 3)
+            k_link<3><<<gl, WG, 0, s>>>(P);
+        else
+            k_link<2><<<gl, WG, 0, s>>>(P);
+    }
+    cell<<<g, 64, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
     if (!P.dense) {
         const int gg = (int)std::min<long long>(((long long)P.block_cap + 3) / 4, 16384);  // one wave per block
         if (P.dim == 3) {
