@@ -2,19 +2,29 @@
 // Hencky / Drucker-Prager constitutive map), the grid update and P2G.
 //
 // Per step, with the forward recomputed from the step's input state:
-//   k_g2p_adj      per particle (sorted order): recomputes v_p, B_p, grad v and
+//   k_g2p_adj      per particle (in G2P's output order): recomputes grad v and
 //                  F_trial from the staged grid tile, back-propagates the
 //                  output adjoints through the constitutive map (Daleckii-Krein
 //                  form on the eigen-decomposition of F F^T, with closed-form
 //                  divided differences), and writes x_bar (partial), F_bar, and
-//                  the per-particle (v'_bar, B_bar, W_bar) that the grid needs;
-//                  accumulates dL/dE and dL/dphi.
+//                  the per-particle (x, v'_bar, B_bar, W_bar) that the grid
+//                  needs; accumulates dL/dE and dL/dphi.
 //   k_scatter_adj  v_bar_n = sum_p N v'_bar + N B_bar (x_n - x_p) + W_bar grad N,
-//                  one wave per owner block, one lane per base cell, like P2G.
-//   k_grid_adj     u_bar = (boundary Jacobian) v_bar; p_bar = u_bar / m,
-//                  m_bar = -u_bar . (u - dt g) / m.
+//                  a workgroup per owner block, a lane per base cell and rank
+//                  group, like P2G; the tiles go to the tile store.
+//   k_gather_adj   sums the tiles that cover a node (as P2G's second pass does)
+//                  and applies the adjoint of the grid update: u_bar = (boundary
+//                  Jacobian) v_bar; p_bar = u_bar / m, m_bar = -u_bar . (u - dt g) / m.
+//                  (On a dense grid the scatter adds to a cleared grid instead,
+//                  and k_grid_adj follows.)
 //   k_p2g_adj      per particle gather of (p_bar, m_bar): v_bar, C_bar, tau_bar
 //                  and the position terms (shape-function gradient and Hessian).
+//
+// The gathers need sums over the stencil of the node vectors against N, its
+// gradient and its Hessian.  All are products of one-dimensional factors, so
+// they are formed an axis at a time (gather_moments), about 1000 fused
+// multiply-adds per particle instead of 3500 with the factors of each node
+// formed in full.
 #include <math.h>
 
 #include <algorithm>
@@ -24,126 +34,109 @@
 
 namespace mpmx {
 
-// x / sinh(x), smooth through 0
-__device__ __forceinline__ float x_over_sinh(float x) {
-    if (fabsf(x) < 1e-2f) return 1.f - x * x * (1.f / 6.f);
-    return x / sinhf(x);
+// 1 / x to about half an ulp: hardware reciprocal and one Newton step.
+__device__ __forceinline__ float rcp_nr(float x) {
+    const float r = __builtin_amdgcn_rcpf(x);
+    return fmaf(fmaf(-x, r, 1.f), r, r);
 }
-// sinh(beta x / 2) / sinh(x), smooth through 0
-__device__ __forceinline__ float sinh_ratio(float beta, float x) {
-    const float hb = 0.5f * beta;
-    if (fabsf(x) < 1e-2f) return hb * (1.f + (hb * hb - 1.f) * x * x * (1.f / 6.f));
-    return sinhf(hb * x) / sinhf(x);
+// sinh(y) / y from y^2 <= 1 (the next term is below 2e-10)
+__device__ __forceinline__ float shc(float y2) {
+    return 1.f + y2 * (1.f / 6.f) * (1.f + y2 * (1.f / 20.f) * (1.f + y2 * (1.f / 42.f) * (1.f + y2 * (1.f / 72.f) *
+           (1.f + y2 * (1.f / 110.f)))));
+}
+// x / sinh(x), and sinh(hb x) / sinh(x) for |hb| <= 1/2, smooth through 0
+__device__ __forceinline__ void sinh_ratios(float hb, float x, float* x_over_sinh, float* ratio) {
+    if (fabsf(x) <= 1.f) {
+        *x_over_sinh = rcp_nr(shc(x * x));
+        *ratio = hb * shc(hb * x * hb * x) * *x_over_sinh;
+    } else {
+        const float sh = sinhf(x);
+        *x_over_sinh = x / sh;
+        *ratio = sinhf(hb * x) / sh;
+    }
+}
+// ln(1 + m): 2 atanh(m / (2 + m)) by its series near 0, where 1 + m would round
+__device__ __forceinline__ float log1p_small(float m) {
+    if (fabsf(m) > 0.3f) return logf(fmaxf(1.f + m, 1e-6f));
+    const float z = m * rcp_nr(2.f + m), z2 = z * z;
+    return 2.f * z * (1.f + z2 * (1.f / 3.f + z2 * (0.2f + z2 * (1.f / 7.f + z2 * (1.f / 9.f + z2 * (1.f / 11.f))))));
 }
 
 // Adjoint of (F^E, tau) = Z(F_trial).  Inputs: Ft (F_trial), Fe_bar (full),
 // tau_bar as stored components; outputs: Ft_bar, dL/dE, dL/dalpha.
+//
+// In principal values the return map gives eps'_i = kappa eps_i + c0 for all i
+// (elastic: kappa = 1, c0 = 0; apex: both 0; cone: the closed forms below), so
+//   exp(eps'_i - eps_i) = h_i, exp(-eps_i) = q_i
+// give every divided difference: for i != j, with x = eps_i - eps_j,
+//   (tau_i - tau_j) / (lam_i - lam_j) = mu kappa q_i q_j x / sinh x,
+//   (h_i - h_j) / (lam_i - lam_j) = sqrt(h_i h_j) q_i q_j sinh(beta x / 2) / sinh x
+// (lam = exp(2 eps), beta = kappa - 1), and the Jacobian of the cone map is
+// applied to a vector without being formed.
 template <int DIM>
 __device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const float (*Fe_bar)[3],
                                  const float* tau_bar_c, float (*Ft_bar)[3], float* E_bar, float* a_bar) {
-    float Hm[3][3], M[3][3], U[3][3];
+    float M[3][3], U[3][3];
+    {
+        float Hm[3][3];
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) Hm[a][b] = (a < DIM && b < DIM) ? Ft[a][b] - (a == b ? 1.f : 0.f) : 0.f;
+            for (int b = 0; b < 3; ++b) Hm[a][b] = (a < DIM && b < DIM) ? Ft[a][b] - (a == b ? 1.f : 0.f) : 0.f;
 #pragma unroll
-    for (int a = 0; a < 3; ++a)
+        for (int a = 0; a < 3; ++a)
 #pragma unroll
-        for (int b = 0; b < 3; ++b) {
-            float s = Hm[a][b] + Hm[b][a];
+            for (int b = a; b < 3; ++b) {
+                float s = Hm[a][b] + Hm[b][a];
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) s += Hm[a][c] * Hm[b][c];
-            M[a][b] = s;
-        }
+                for (int c = 0; c < DIM; ++c) s += Hm[a][c] * Hm[b][c];
+                M[a][b] = M[b][a] = s;
+            }
+    }
     jacobi_sym<DIM>(M, U);
-    float lam[3] = {1.f, 1.f, 1.f}, eps[3] = {0.f, 0.f, 0.f};
-    float tr = 0.f;
+    float q[3] = {1.f, 1.f, 1.f}, eps[3] = {0.f, 0.f, 0.f}, tr = 0.f;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
-        lam[a] = fmaxf(1.f + M[a][a], 1e-6f);
-        eps[a] = 0.5f * logf(lam[a]);
+        const float lam = fmaxf(1.f + M[a][a], 1e-6f);
+        eps[a] = 0.5f * log1p_small(M[a][a]);
+        const float r = __builtin_amdgcn_rsqf(lam);
+        q[a] = fmaf(0.5f * r, fmaf(-lam * r, r, 1.f), r);  // 1 / sqrt(lam), one Newton step
         tr += eps[a];
     }
-    // return map, its Jacobian J = d eps'/d eps, d eps'/d alpha, and kappa with
-    // eps'_i - eps'_j = kappa (eps_i - eps_j)
-    float e2[3], J[3][3], da[3] = {0.f, 0.f, 0.f}, kappa = 1.f;
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-        e2[a] = eps[a];
-#pragma unroll
-        for (int b = 0; b < 3; ++b) J[a][b] = a == b ? 1.f : 0.f;
-    }
+    float e2[3] = {eps[0], eps[1], eps[2]}, nh[3] = {0.f, 0.f, 0.f}, kappa = 1.f, ca = 0.f, rnd = 0.f;
+    int branch = 0;  // 0 elastic, 1 apex, 2 cone
     if (P.model == MPM_MODEL_DP) {
-        float dev[3], nd2 = 0.f;
+        float dev[3] = {0.f, 0.f, 0.f}, nd2 = 0.f;
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
             dev[a] = eps[a] - tr / (float)DIM;
             nd2 += dev[a] * dev[a];
         }
         const float nd = sqrtf(nd2);
-        const float dg = nd + P.dp_coef * tr * P.alpha;
+        ca = P.dp_coef * P.alpha;
         if (tr > 0.f) {
+            branch = 1;
             kappa = 0.f;
-#pragma unroll
-            for (int a = 0; a < 3; ++a) {
-                e2[a] = 0.f;
-#pragma unroll
-                for (int b = 0; b < 3; ++b) J[a][b] = 0.f;
-            }
-        } else if (dg > 0.f) {
-            const float ca = P.dp_coef * P.alpha;
-            kappa = -ca * tr / nd;
-            float nh[3];
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) nh[a] = dev[a] / nd;
+            e2[0] = e2[1] = e2[2] = 0.f;
+        } else if (nd + ca * tr > 0.f) {
+            branch = 2;
+            rnd = rcp_nr(nd);
+            kappa = -ca * tr * rnd;
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
+                nh[a] = dev[a] * rnd;
                 e2[a] = tr / (float)DIM - ca * tr * nh[a];
-                da[a] = -P.dp_coef * tr * nh[a];
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) {
-                    const float pdev = (a == b ? 1.f : 0.f) - 1.f / (float)DIM;
-                    J[a][b] = 1.f / (float)DIM - ca * (nh[a] + tr * (pdev - nh[a] * nh[b]) / nd);
-                }
             }
         }
     }
-    float tr2 = 0.f;
+    float tr2 = 0.f, h[3] = {1.f, 1.f, 1.f};
 #pragma unroll
     for (int a = 0; a < DIM; ++a) tr2 += e2[a];
-    const float c0 = e2[0] - kappa * eps[0];
-    const float beta = kappa - 1.f;
-    float t[3], h[3], Jt[3][3], Jh[3][3];
+    if (branch != 0)
 #pragma unroll
-    for (int i = 0; i < DIM; ++i) {
-        t[i] = 2.f * P.mu * e2[i] + P.lam * tr2;
-        h[i] = expf(e2[i] - eps[i]);
-    }
-#pragma unroll
-    for (int i = 0; i < DIM; ++i)
-#pragma unroll
-        for (int j = 0; j < DIM; ++j) {
-            float cj = 0.f;
-#pragma unroll
-            for (int k = 0; k < DIM; ++k) cj += ((i == k ? 2.f * P.mu : 0.f) + P.lam) * J[k][j];
-            Jt[i][j] = cj / (2.f * lam[j]);
-            Jh[i][j] = h[i] * (J[i][j] - (i == j ? 1.f : 0.f)) / (2.f * lam[j]);
-        }
-    // symmetric adjoint of tau from stored components
-    float Yt_s[3][3], Hb[3][3];
-    if (DIM == 3) {
-        Yt_s[0][0] = tau_bar_c[0];
-        Yt_s[1][1] = tau_bar_c[1];
-        Yt_s[2][2] = tau_bar_c[2];
-        Yt_s[0][1] = Yt_s[1][0] = 0.5f * tau_bar_c[3];
-        Yt_s[1][2] = Yt_s[2][1] = 0.5f * tau_bar_c[4];
-        Yt_s[0][2] = Yt_s[2][0] = 0.5f * tau_bar_c[5];
-    } else {
-        Yt_s[0][0] = tau_bar_c[0];
-        Yt_s[1][1] = tau_bar_c[1];
-        Yt_s[0][1] = Yt_s[1][0] = 0.5f * tau_bar_c[2];
-    }
-    // H_bar = Fe_bar Ft^T (symmetrised); Ft_bar = H Fe_bar with H = U diag(h) U^T
+        for (int a = 0; a < DIM; ++a) h[a] = __builtin_amdgcn_exp2f((e2[a] - eps[a]) * 1.44269504f);
+    // H = U diag(h) U^T: Ft_bar = H Fe_bar for now; H_bar = Fe_bar Ft^T
+    float Hb[3][3];
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -153,77 +146,102 @@ __device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const
             for (int c = 0; c < DIM; ++c) s += Fe_bar[a][c] * Ft[b][c];
             Hb[a][b] = s;
         }
+    {
+        float Hmat[3][3];
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
+        for (int a = 0; a < DIM; ++a)
 #pragma unroll
-        for (int b = a + 1; b < DIM; ++b) Hb[a][b] = Hb[b][a] = 0.5f * (Hb[a][b] + Hb[b][a]);
-    float Hmat[3][3];
+            for (int b = a; b < DIM; ++b) {
+                float s = 0.f;
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            float s = 0.f;
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) s += U[a][c] * h[c] * U[b][c];
-            Hmat[a][b] = s;
-        }
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            float s = 0.f;
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) s += Hmat[a][c] * Fe_bar[c][b];
-            Ft_bar[a][b] = s;
-        }
-    // rotate into the eigenbasis: Y = U^T Ybar U
-    float Yt[3][3], Yh[3][3], tmp1[3][3], tmp2[3][3];
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            float s1 = 0.f, s2 = 0.f;
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                s1 += Yt_s[a][c] * U[c][b];
-                s2 += Hb[a][c] * U[c][b];
+                for (int c = 0; c < DIM; ++c) s += U[a][c] * h[c] * U[b][c];
+                Hmat[a][b] = Hmat[b][a] = s;
             }
-            tmp1[a][b] = s1;
-            tmp2[a][b] = s2;
-        }
 #pragma unroll
-    for (int a = 0; a < DIM; ++a)
+        for (int a = 0; a < DIM; ++a)
 #pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            float s1 = 0.f, s2 = 0.f;
+            for (int b = 0; b < DIM; ++b) {
+                float s = 0.f;
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                s1 += U[c][a] * tmp1[c][b];
-                s2 += U[c][a] * tmp2[c][b];
+                for (int c = 0; c < DIM; ++c) s += Hmat[a][c] * Fe_bar[c][b];
+                Ft_bar[a][b] = s;
             }
-            Yt[a][b] = s1;
-            Yh[a][b] = s2;
+    }
+    // symmetric parts in the eigenbasis: Y = U^T sym(.) U (upper triangles)
+    float Yt[3][3], Yh[3][3];
+    {
+        float ts[3][3], t1[3][3], t2[3][3];
+        if (DIM == 3) {
+            ts[0][0] = tau_bar_c[0];
+            ts[1][1] = tau_bar_c[1];
+            ts[2][2] = tau_bar_c[2];
+            ts[0][1] = ts[1][0] = 0.5f * tau_bar_c[3];
+            ts[1][2] = ts[2][1] = 0.5f * tau_bar_c[4];
+            ts[0][2] = ts[2][0] = 0.5f * tau_bar_c[5];
+        } else {
+            ts[0][0] = tau_bar_c[0];
+            ts[1][1] = tau_bar_c[1];
+            ts[0][1] = ts[1][0] = 0.5f * tau_bar_c[2];
         }
+#pragma unroll
+        for (int a = 0; a < DIM; ++a)
+#pragma unroll
+            for (int b = 0; b < DIM; ++b) {
+                float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) {
+                    s1 += ts[a][c] * U[c][b];
+                    s2 += 0.5f * (Hb[a][c] + Hb[c][a]) * U[c][b];
+                }
+                t1[a][b] = s1;
+                t2[a][b] = s2;
+            }
+#pragma unroll
+        for (int a = 0; a < DIM; ++a)
+#pragma unroll
+            for (int b = a; b < DIM; ++b) {
+                float s1 = 0.f, s2 = 0.f;
+#pragma unroll
+                for (int c = 0; c < DIM; ++c) {
+                    s1 += U[c][a] * t1[c][b];
+                    s2 += U[c][a] * t2[c][b];
+                }
+                Yt[a][b] = s1;
+                Yh[a][b] = s2;
+            }
+    }
+    // diagonal: S_jj = (sum_i J_ij z_i - h_j Yh_jj) / (2 lam_j) with J = d eps'/d eps
+    // and z_i = 2 mu Yt_ii + lambda tr(Yt) + h_i Yh_ii
+    float trY = 0.f, z[3] = {0.f, 0.f, 0.f}, Z = 0.f, nz = 0.f, eb = 0.f;
+#pragma unroll
+    for (int i = 0; i < DIM; ++i) trY += Yt[i][i];
+#pragma unroll
+    for (int i = 0; i < DIM; ++i) {
+        z[i] = 2.f * P.mu * Yt[i][i] + P.lam * trY + h[i] * Yh[i][i];
+        Z += z[i];
+        nz += nh[i] * z[i];
+        eb += Yt[i][i] * (2.f * P.mu * e2[i] + P.lam * tr2);
+    }
     float S[3][3];
 #pragma unroll
     for (int j = 0; j < DIM; ++j) {
-        float s = 0.f;
-#pragma unroll
-        for (int i = 0; i < DIM; ++i) s += Jt[i][j] * Yt[i][i] + Jh[i][j] * Yh[i][i];
-        S[j][j] = s;
+        float Jz = branch == 0 ? z[j] : 0.f;
+        if (branch == 2)
+            Jz = Z / (float)DIM - ca * (nz + tr * rnd * (z[j] - Z / (float)DIM - nz * nh[j]));
+        S[j][j] = 0.5f * q[j] * q[j] * (Jz - h[j] * Yh[j][j]);
     }
+    const float hb = 0.5f * (kappa - 1.f);
 #pragma unroll
     for (int i = 0; i < DIM; ++i)
 #pragma unroll
-        for (int j = 0; j < DIM; ++j) {
-            if (i == j) continue;
-            const float x = eps[i] - eps[j], mid = 0.5f * (eps[i] + eps[j]);
-            const float Kt = P.mu * kappa * expf(-2.f * mid) * x_over_sinh(x);
-            const float Kh = expf(c0 + (beta - 2.f) * mid) * sinh_ratio(beta, x);
-            S[i][j] = Kt * Yt[i][j] + Kh * Yh[i][j];
+        for (int j = i + 1; j < DIM; ++j) {
+            float xs, sr;
+            sinh_ratios(hb, eps[i] - eps[j], &xs, &sr);
+            const float qq = q[i] * q[j];
+            S[i][j] = S[j][i] = qq * (P.mu * kappa * xs * Yt[i][j] + sqrtf(h[i] * h[j]) * sr * Yh[i][j]);
         }
     // b_bar = U S U^T; Ft_bar += 2 b_bar Ft
-    float bb[3][3];
+    float t1[3][3], bb[3][3];
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -231,21 +249,17 @@ __device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const
             float s = 0.f;
 #pragma unroll
             for (int c = 0; c < DIM; ++c) s += S[a][c] * U[b][c];
-            tmp1[a][b] = s;
+            t1[a][b] = s;
         }
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
-        for (int b = 0; b < DIM; ++b) {
+        for (int b = a; b < DIM; ++b) {
             float s = 0.f;
 #pragma unroll
-            for (int c = 0; c < DIM; ++c) s += U[a][c] * tmp1[c][b];
-            bb[a][b] = s;
+            for (int c = 0; c < DIM; ++c) s += U[a][c] * t1[c][b];
+            bb[a][b] = bb[b][a] = s;
         }
-#pragma unroll
-    for (int a = 0; a < DIM; ++a)
-#pragma unroll
-        for (int b = a + 1; b < DIM; ++b) bb[a][b] = bb[b][a] = 0.5f * (bb[a][b] + bb[b][a]);
 #pragma unroll
     for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -255,18 +269,162 @@ __device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const
             for (int c = 0; c < DIM; ++c) s += bb[a][c] * Ft[c][b];
             Ft_bar[a][b] += 2.f * s;
         }
-    // parameters: tau is proportional to E; alpha enters eps' (plastic branch)
-    float eb = 0.f, ab = 0.f;
+    // parameters: tau is proportional to E; alpha enters eps' on the cone,
+    // d eps'/d alpha = -dp_coef tr nh
+    *E_bar = eb * rcp_nr(P.E);
+    *a_bar = -P.dp_coef * tr * nz;
+}
+
+// Sums over a particle's stencil, of the tile's node vectors v and (MASS) their
+// fourth component m, with d = x_n - x_p:
+//   V_a = sum N v_a, W_ab = sum v_a dN/dx_b, S_c = sum dN/dx_c (v . U d),
+//   FULL_Y:  Y_a(bc) = sum v_a d2N/dx_b dx_c, (bc) = xx, yy, zz, xy, yz, xz
+//            (2D: xx, yy, xy);
+//   !FULL_Y: T_c = sum_b d2N/dx_b dx_c (Q v)_b for a symmetric Q known beforehand;
+//   ND:      D_ab = sum N v_a d_b;   MASS: G_c = sum m dN/dx_c.
+template <int DIM, bool FULL_Y, bool ND, bool MASS>
+struct Moments {
+    float V[3] = {0, 0, 0}, W[3][3] = {{0}}, S[3] = {0, 0, 0};
+    float Y[FULL_Y ? 3 : 1][6] = {{0}}, T[3] = {0, 0, 0};
+    float D[ND ? 3 : 1][3] = {{0}}, G[3] = {0, 0, 0};
+};
+
+// padded float4 tile in LDS: row and plane strides (as k_g2p's)
+constexpr int ADJ_SY = 20;
+template <int DIM>
+constexpr int adj_sz() { return DIM == 3 ? 120 : 0; }
+template <int DIM>
+constexpr int adj_tile() { return DIM == 3 ? 6 * 120 : 6 * ADJ_SY; }
+
+template <int DIM, bool FULL_Y, bool ND, bool MASS>
+__device__ __forceinline__ void gather_moments(const float4* vt, const int* lb, const float* t, const float* u,
+                                               float dx, float inv_dx, const float (*U)[3], const float (*Q)[3],
+                                               Moments<DIM, FULL_Y, ND, MASS>& O) {
+    float w[3][3], dw[3][3];
+    bspline<DIM>(t, u, inv_dx, w, dw);
+    const float i2 = inv_dx * inv_dx;
+    auto off = [&](int a, int k) { return ((float)k - 0.5f - t[a]) * dx; };
+    const float4* base = vt + lb[0] + ADJ_SY * lb[1] + (DIM == 3 ? adj_sz<DIM>() * lb[2] : 0);
+    // column a of a matrix with the plane sums of one kind
+    auto dot = [](const float (*m)[3], int col, const float* v) {
+        float r = m[0][col] * v[0];
 #pragma unroll
-    for (int i = 0; i < DIM; ++i) {
-        eb += Yt[i][i] * t[i];
-        float cda = 0.f;
+        for (int a = 1; a < DIM; ++a) r = fmaf(m[a][col], v[a], r);
+        return r;
+    };
+#pragma unroll 1
+    for (int kz = 0; kz < (DIM == 3 ? 3 : 1); ++kz) {
+        // sums over the plane, factors along x and y: N N, N' N, N N', N'' N,
+        // N' N', N N'', (N d) N, N (N d), (N' d) N, N' (N d), (N d) N', N (N' d)
+        float A0[3] = {0, 0, 0}, A1[3] = {0, 0, 0}, A2[3] = {0, 0, 0}, A3[3] = {0, 0, 0}, A4[3] = {0, 0, 0},
+              A5[3] = {0, 0, 0}, A6[3] = {0, 0, 0}, A7[3] = {0, 0, 0}, A8[3] = {0, 0, 0}, A9[3] = {0, 0, 0},
+              Aa[3] = {0, 0, 0}, Ab[3] = {0, 0, 0};
+        float B0 = 0, B1 = 0, B2 = 0;
 #pragma unroll
-        for (int k = 0; k < DIM; ++k) cda += ((i == k ? 2.f * P.mu : 0.f) + P.lam) * da[k];
-        ab += Yt[i][i] * cda + Yh[i][i] * h[i] * da[i];
+        for (int ky = 0; ky < 3; ++ky) {
+            float r0[3] = {0, 0, 0}, r1[3] = {0, 0, 0}, r2[3] = {0, 0, 0}, r3[3] = {0, 0, 0}, r4[3] = {0, 0, 0};
+            float m0 = 0, m1 = 0;
+#pragma unroll
+            for (int kx = 0; kx < 3; ++kx) {
+                const float4 g = base[kx + ADJ_SY * ky];
+                const float v[3] = {g.x, g.y, g.z};
+                const float wx = w[0][kx], dwx = dw[0][kx], ox = off(0, kx), ddx = kx == 1 ? -2.f * i2 : i2;
+                const float wdx = wx * ox, dwdx = dwx * ox;
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) {
+                    r0[a] = fmaf(wx, v[a], r0[a]);
+                    r1[a] = fmaf(dwx, v[a], r1[a]);
+                    r2[a] = fmaf(ddx, v[a], r2[a]);
+                    r3[a] = fmaf(wdx, v[a], r3[a]);
+                    r4[a] = fmaf(dwdx, v[a], r4[a]);
+                }
+                if (MASS) {
+                    m0 = fmaf(wx, g.w, m0);
+                    m1 = fmaf(dwx, g.w, m1);
+                }
+            }
+            const float wy = w[1][ky], dwy = dw[1][ky], oy = off(1, ky), ddy = ky == 1 ? -2.f * i2 : i2;
+            const float wyd = wy * oy, dwyd = dwy * oy;
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                A0[a] = fmaf(wy, r0[a], A0[a]);
+                A1[a] = fmaf(wy, r1[a], A1[a]);
+                A2[a] = fmaf(dwy, r0[a], A2[a]);
+                A3[a] = fmaf(wy, r2[a], A3[a]);
+                A4[a] = fmaf(dwy, r1[a], A4[a]);
+                A5[a] = fmaf(ddy, r0[a], A5[a]);
+                A6[a] = fmaf(wy, r3[a], A6[a]);
+                A7[a] = fmaf(wyd, r0[a], A7[a]);
+                A8[a] = fmaf(wy, r4[a], A8[a]);
+                A9[a] = fmaf(wyd, r1[a], A9[a]);
+                Aa[a] = fmaf(dwy, r3[a], Aa[a]);
+                Ab[a] = fmaf(dwyd, r0[a], Ab[a]);
+            }
+            if (MASS) {
+                B0 = fmaf(wy, m0, B0);
+                B1 = fmaf(wy, m1, B1);
+                B2 = fmaf(dwy, m0, B2);
+            }
+            // one row of LDS reads in flight at a time, and the row's sums
+            // finished here: left to itself the compiler sinks sums below
+            // their last use and keeps all 27 node vectors live
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) {
+                asm volatile("" : "+v"(A0[a]), "+v"(A1[a]), "+v"(A2[a]), "+v"(A3[a]), "+v"(A4[a]), "+v"(A5[a]));
+                asm volatile("" : "+v"(A6[a]), "+v"(A7[a]), "+v"(A8[a]), "+v"(A9[a]), "+v"(Aa[a]), "+v"(Ab[a]));
+            }
+            if (MASS) asm volatile("" : "+v"(B0), "+v"(B1), "+v"(B2));
+        }
+        base += adj_sz<DIM>();
+        auto pick = [&](const float* f) { return kz == 0 ? f[0] : kz == 1 ? f[1] : f[2]; };
+        const float wz = DIM == 3 ? pick(w[2]) : 1.f, dwz = DIM == 3 ? pick(dw[2]) : 0.f;
+        const float oz = DIM == 3 ? off(2, kz) : 0.f, ddz = kz == 1 ? -2.f * i2 : i2;
+        const float wzd = wz * oz, dwzd = dwz * oz;
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            O.V[a] = fmaf(wz, A0[a], O.V[a]);
+            O.W[a][0] = fmaf(wz, A1[a], O.W[a][0]);
+            O.W[a][1] = fmaf(wz, A2[a], O.W[a][1]);
+            if (DIM == 3) O.W[a][2] = fmaf(dwz, A0[a], O.W[a][2]);
+            if (FULL_Y) {
+                O.Y[a][0] = fmaf(wz, A3[a], O.Y[a][0]);
+                O.Y[a][1] = fmaf(wz, A5[a], O.Y[a][1]);
+                O.Y[a][DIM == 3 ? 3 : 2] = fmaf(wz, A4[a], O.Y[a][DIM == 3 ? 3 : 2]);
+                if (DIM == 3) {
+                    O.Y[a][2] = fmaf(ddz, A0[a], O.Y[a][2]);
+                    O.Y[a][4] = fmaf(dwz, A2[a], O.Y[a][4]);
+                    O.Y[a][5] = fmaf(dwz, A1[a], O.Y[a][5]);
+                }
+            }
+            if (ND) {
+                O.D[a][0] = fmaf(wz, A6[a], O.D[a][0]);
+                O.D[a][1] = fmaf(wz, A7[a], O.D[a][1]);
+                if (DIM == 3) O.D[a][2] = fmaf(wzd, A0[a], O.D[a][2]);
+            }
+        }
+        O.S[0] = fmaf(wz, dot(U, 0, A8) + dot(U, 1, A9), O.S[0]);
+        O.S[1] = fmaf(wz, dot(U, 0, Aa) + dot(U, 1, Ab), O.S[1]);
+        if (DIM == 3) {
+            O.S[0] = fmaf(wzd, dot(U, 2, A1), O.S[0]);
+            O.S[1] = fmaf(wzd, dot(U, 2, A2), O.S[1]);
+            O.S[2] = fmaf(dwz, dot(U, 0, A6) + dot(U, 1, A7), fmaf(dwzd, dot(U, 2, A0), O.S[2]));
+        }
+        if (!FULL_Y) {
+            O.T[0] = fmaf(wz, dot(Q, 0, A3) + dot(Q, 1, A4), O.T[0]);
+            O.T[1] = fmaf(wz, dot(Q, 0, A4) + dot(Q, 1, A5), O.T[1]);
+            if (DIM == 3) {
+                O.T[0] = fmaf(dwz, dot(Q, 2, A1), O.T[0]);
+                O.T[1] = fmaf(dwz, dot(Q, 2, A2), O.T[1]);
+                O.T[2] = fmaf(dwz, dot(Q, 0, A1) + dot(Q, 1, A2), fmaf(ddz, dot(Q, 2, A0), O.T[2]));
+            }
+        }
+        if (MASS) {
+            O.G[0] = fmaf(wz, B1, O.G[0]);
+            O.G[1] = fmaf(wz, B2, O.G[1]);
+            if (DIM == 3) O.G[2] = fmaf(dwz, B0, O.G[2]);
+        }
     }
-    *E_bar = eb / P.E;
-    *a_bar = ab;
 }
 
 struct OutBar {
@@ -277,142 +435,108 @@ struct OutBar {
     const float* tau;
 };
 
-// shape-function value, gradient and Hessian at stencil offset (kx, ky, kz)
+// Work of one workgroup of the per-particle reverse kernels: ADJ_WG positions of
+// a work item (an item of up to `chunk` particles is shared by `parts`
+// workgroups; small items in flight at once matter more here than the tile
+// that each of them stages).
+constexpr int ADJ_WG = 128;
+
+// Stages the tile of work item `blk` from a node array into LDS; the origin of
+// the block goes to org (every thread).  Ends with a barrier.
 template <int DIM>
-__device__ __forceinline__ void shape_k(const float (*wt)[3], const float (*dw)[3], const float* ddw, int kx, int ky,
-                                        int kz, float* N, float* G, float (*Hs)[3]) {
-    const int k[3] = {kx, ky, kz};
-    float w[3] = {1.f, 1.f, 1.f}, d[3] = {0.f, 0.f, 0.f}, dd[3] = {0.f, 0.f, 0.f};
+__device__ __forceinline__ void stage_tile(const DevParams& P, const float4* __restrict__ grid, int blk, float4* vt,
+                                           int* org) {
+    using T = Tile<DIM>;
+    block_coords<DIM>(P, blk, org);
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        w[a] = wt[a][k[a]];
-        d[a] = dw[a][k[a]];
-        dd[a] = ddw[k[a]];
-    }
-    *N = w[0] * w[1] * w[2];
+    for (int a = 0; a < 3; ++a) org[a] *= BLK;
 #pragma unroll
-    for (int a = 0; a < DIM; ++a) {
-        float g = d[a];
-#pragma unroll
-        for (int e = 0; e < DIM; ++e)
-            if (e != a) g *= w[e];
-        G[a] = g;
-#pragma unroll
-        for (int b = 0; b < DIM; ++b) {
-            float hh;
-            if (a == b) {
-                hh = dd[a];
-#pragma unroll
-                for (int e = 0; e < DIM; ++e)
-                    if (e != a) hh *= w[e];
-            } else {
-                hh = d[a] * d[b];
-#pragma unroll
-                for (int e = 0; e < DIM; ++e)
-                    if (e != a && e != b) hh *= w[e];
-            }
-            Hs[a][b] = hh;
+    for (int r = 0; r < (T::N + ADJ_WG - 1) / ADJ_WG; ++r) {
+        const int t = (int)threadIdx.x + r * ADJ_WG;
+        if (t < T::N) {
+            const int I = t % T::E, J = (t / T::E) % T::E, K = DIM == 3 ? t / (T::E * T::E) : 0;
+            const int d = (I >> 2) | ((J >> 2) << 1) | ((K >> 2) << 2);
+            const int phi = P.b_nbr[(size_t)blk * T::NB + d];
+            const int l = (I & 3) + BLK * ((J & 3) + BLK * (K & 3));
+            vt[I + ADJ_SY * J + adj_sz<DIM>() * K] =
+                phi >= 0 ? grid[(size_t)phi * T::NPB + l] : make_float4(0.f, 0.f, 0.f, 0.f);
         }
     }
+    __syncthreads();
 }
 
+// osrc[o]: the input particle that G2P stores at position o.  A work item's
+// range of positions holds particles of its block whichever way the block's
+// particles are listed, so the item's part is walked in output order: the
+// output adjoints and the scratch are read and written contiguously.
 template <int DIM>
-__global__ __launch_bounds__(WG) void k_g2p_adj(DevParams P, const float* __restrict__ x, const float* __restrict__ F,
-                                                OutBar ob, float* __restrict__ x_bar, float* __restrict__ F_bar, int n,
-                                                const uint32_t* __restrict__ order,
-                                                const uint32_t* __restrict__ skeys) {
-    using T = Tile<DIM>;
+__global__ __launch_bounds__(ADJ_WG, 3) void k_g2p_adj(DevParams P, const float* __restrict__ x,
+                                                    const float* __restrict__ F, OutBar ob, float* __restrict__ x_bar,
+                                                    float* __restrict__ F_bar, int n, const uint32_t* __restrict__ osrc,
+                                                    int parts) {
     constexpr int NS = DIM == 3 ? 6 : 3;
     constexpr int DD = DIM * DIM;
-    __shared__ float4 vt[T::N];
-    __shared__ int nbr[T::NB];
-    __shared__ int org[3];
-    __shared__ float red[2][WG / 64];
-    __shared__ Interleave<DIM> il;
-    const int n_work = min(P.ctr->n_work, P.work_cap);
+    __shared__ float4 vt[adj_tile<DIM>()];
+    __shared__ float red[2][ADJ_WG / 64];
+    const int n_work = min(P.ctr->n_work, P.work_cap) * parts;
     const float dt = P.dt, dx = P.dxf, inv_dx = P.inv_dxf;
     const float bscale = 4.f * inv_dx * inv_dx;
     float accE = 0.f, accA = 0.f;
     for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
-        const int blk = P.w_block[w], s = P.w_start[w], e = P.w_end[w];
-        if (threadIdx.x < T::NB) nbr[threadIdx.x] = P.b_nbr[blk * T::NB + threadIdx.x];
-        if (threadIdx.x == 0) {
-            int bc[3];
-            block_coords<DIM>(P, blk, bc);
-            org[0] = bc[0] * BLK;
-            org[1] = bc[1] * BLK;
-            org[2] = bc[2] * BLK;
-        }
-        interleave_setup<DIM>(il, skeys, P.b_start[blk], P.b_start[blk] + P.b_count[blk]);
-        for (int t = threadIdx.x; t < T::N; t += WG) {
-            const int I = t % T::E, J = (t / T::E) % T::E, K = DIM == 3 ? t / (T::E * T::E) : 0;
-            const int d = (I >> 2) | ((J >> 2) << 1) | ((K >> 2) << 2);
-            const int phi = nbr[d];
-            const int l = (I & 3) + BLK * ((J & 3) + BLK * (K & 3));
-            vt[t] = phi >= 0 ? P.grid[(size_t)phi * T::NPB + l] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int i = s + (int)threadIdx.x; i < e; i += WG) {
-            const size_t q = order[i];
-            const size_t o = (size_t)interleave_pos<DIM>(il, i, skeys[i]);  // where G2P stored it
-            float xp[3] = {0, 0, 0}, Fp[3][3];
+        const int it = w / parts;
+        const int s = P.w_start[it] + (w % parts) * ADJ_WG, e = min(P.w_end[it], s + ADJ_WG);
+        if (s >= e) continue;
+        const int o = s + (int)threadIdx.x;
+        // what the gather needs is loaded before the tile's barrier, the rest
+        // after it (registers: three waves per SIMD)
+        const int oc = min(o, e - 1);
+        const size_t q = osrc[oc];
+        float xp[3] = {0, 0, 0}, Bb[3][3] = {{0}};
 #pragma unroll
-            for (int a = 0; a < DIM; ++a) xp[a] = x[(size_t)a * n + q];
+        for (int a = 0; a < DIM; ++a) xp[a] = x[(size_t)a * n + q];
 #pragma unroll
-            for (int a = 0; a < DIM; ++a)
+        for (int k = 0; k < DD; ++k) Bb[k / DIM][k % DIM] = ob.C[(size_t)k * n + oc];
+        int org[3];
+        stage_tile<DIM>(P, P.grid, P.w_block[it], vt, org);
+        if (o < e) {
 #pragma unroll
-                for (int b = 0; b < DIM; ++b) Fp[a][b] = F[(size_t)(a * DIM + b) * n + q];
+            for (int k = 0; k < DD; ++k) Bb[k / DIM][k % DIM] *= bscale;
             int lb[3] = {0, 0, 0};
             float tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1};
             particle_frame<DIM>(P, xp, org, lb, tt, uu);
-            float wt[3][3], dw[3][3], ddw[3], dxn[3][3];
-            bspline<DIM>(tt, uu, inv_dx, wt, dw);
-            bspline_dd(inv_dx * inv_dx, ddw);
+            Moments<DIM, true, false, false> Mo;
+            gather_moments<DIM, true, false, false>(vt, lb, tt, uu, dx, inv_dx, Bb, Bb, Mo);
+            __builtin_amdgcn_sched_barrier(0);
+            float Fp[3][3], xbo[3] = {0, 0, 0}, vpb[3] = {0, 0, 0};
 #pragma unroll
-            for (int a = 0; a < DIM; ++a)
+            for (int a = 0; a < DIM; ++a) {
+                xbo[a] = ob.x[(size_t)a * n + o];
+                vpb[a] = ob.v[(size_t)a * n + o] + dt * xbo[a];
+            }
 #pragma unroll
-                for (int k = 0; k < 3; ++k) dxn[a][k] = ((float)k - 0.5f - tt[a]) * dx;
-            // forward recompute: grad v
-            float W[3][3] = {{0}};
+            for (int k = 0; k < DD; ++k) Fp[k / DIM][k % DIM] = F[(size_t)k * n + q];
+            float* sc = P.adj_scratch;
+            float xb[3];
 #pragma unroll
-            for (int kz = 0; kz < (DIM == 3 ? 3 : 1); ++kz)
+            for (int c = 0; c < DIM; ++c) {
+                // position adjoint through the weights of v_p and B_p
+                xb[c] = xbo[c] + Mo.S[c];
 #pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
+                for (int a = 0; a < DIM; ++a) xb[c] += Mo.W[a][c] * vpb[a] - Bb[a][c] * Mo.V[a];
+                sc[(size_t)c * n + o] = vpb[c];
+                sc[(size_t)(DIM + 2 * DD + c) * n + o] = xp[c];
+            }
 #pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) {
-                        const int idx = (lb[0] + kx) + T::E * ((lb[1] + ky) + (DIM == 3 ? T::E * (lb[2] + kz) : 0));
-                        const float4 g4 = vt[idx];
-                        const float vn[3] = {g4.x, g4.y, g4.z};
-                        float N, G[3], Hs[3][3];
-                        shape_k<DIM>(wt, dw, ddw, kx, ky, kz, &N, G, Hs);
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) W[a][b] += vn[a] * G[b];
-                    }
-            float Ft[3][3];
+            for (int k = 0; k < DD; ++k) sc[(size_t)(DIM + k) * n + o] = Bb[k / DIM][k % DIM];
+            float Ft[3][3], Fbo[3][3] = {{0}}, tbo[6] = {0};
 #pragma unroll
             for (int a = 0; a < DIM; ++a)
 #pragma unroll
                 for (int b = 0; b < DIM; ++b) {
                     float s2 = 0.f;
 #pragma unroll
-                    for (int c = 0; c < DIM; ++c) s2 += W[a][c] * Fp[c][b];
+                    for (int c = 0; c < DIM; ++c) s2 += Mo.W[a][c] * Fp[c][b];
                     Ft[a][b] = Fp[a][b] + dt * s2;
-                }
-            // output adjoints at the particle's G2P output position o
-            float xbo[3] = {0, 0, 0}, vbo[3] = {0, 0, 0}, Cbo[3][3] = {{0}}, Fbo[3][3] = {{0}}, tbo[6] = {0};
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) {
-                xbo[a] = ob.x[(size_t)a * n + o];
-                vbo[a] = ob.v[(size_t)a * n + o];
-            }
-#pragma unroll
-            for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) {
-                    Cbo[a][b] = ob.C[(size_t)(a * DIM + b) * n + o];
                     Fbo[a][b] = ob.F[(size_t)(a * DIM + b) * n + o];
                 }
 #pragma unroll
@@ -422,7 +546,7 @@ __global__ __launch_bounds__(WG) void k_g2p_adj(DevParams P, const float* __rest
             accE += eb;
             accA += ab;
             // F_trial = (I + dt W) F
-            float Fb[3][3], Wb[3][3];
+            float Wb[3][3];
 #pragma unroll
             for (int a = 0; a < DIM; ++a)
 #pragma unroll
@@ -430,72 +554,33 @@ __global__ __launch_bounds__(WG) void k_g2p_adj(DevParams P, const float* __rest
                     float s1 = Ftb[a][b], s2 = 0.f;
 #pragma unroll
                     for (int c = 0; c < DIM; ++c) {
-                        s1 += dt * W[c][a] * Ftb[c][b];
+                        s1 += dt * Mo.W[c][a] * Ftb[c][b];
                         s2 += Ftb[a][c] * Fp[b][c];
                     }
-                    Fb[a][b] = s1;
+                    F_bar[(size_t)(a * DIM + b) * n + q] = s1;
                     Wb[a][b] = dt * s2;
+                    sc[(size_t)(DIM + DD + a * DIM + b) * n + o] = Wb[a][b];
                 }
-            float vpb[3], Bb[3][3], xb[3];
+            // and through the weights of grad v
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
-                vpb[a] = vbo[a] + dt * xbo[a];
-                xb[a] = xbo[a];
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) Bb[a][b] = bscale * Cbo[a][b];
+                if (DIM == 3) {
+                    xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][3] + Wb[a][2] * Mo.Y[a][5];
+                    xb[1] += Wb[a][0] * Mo.Y[a][3] + Wb[a][1] * Mo.Y[a][1] + Wb[a][2] * Mo.Y[a][4];
+                    xb[2] += Wb[a][0] * Mo.Y[a][5] + Wb[a][1] * Mo.Y[a][4] + Wb[a][2] * Mo.Y[a][2];
+                } else {
+                    xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][2];
+                    xb[1] += Wb[a][0] * Mo.Y[a][2] + Wb[a][1] * Mo.Y[a][1];
+                }
             }
-            // position adjoint through the weights of the gather
 #pragma unroll
-            for (int kz = 0; kz < (DIM == 3 ? 3 : 1); ++kz)
-#pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) {
-                        const int idx = (lb[0] + kx) + T::E * ((lb[1] + ky) + (DIM == 3 ? T::E * (lb[2] + kz) : 0));
-                        const float4 g4 = vt[idx];
-                        const float vn[3] = {g4.x, g4.y, g4.z};
-                        float N, G[3], Hs[3][3];
-                        shape_k<DIM>(wt, dw, ddw, kx, ky, kz, &N, G, Hs);
-                        const float dd[3] = {dxn[0][kx], dxn[1][ky], DIM == 3 ? dxn[2][kz] : 0.f};
-                        float s1 = 0.f, s2 = 0.f, BtV[3] = {0, 0, 0}, WtV[3] = {0, 0, 0};
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a) {
-                            s1 += vn[a] * vpb[a];
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) {
-                                s2 += vn[a] * Bb[a][b] * dd[b];
-                                BtV[b] += Bb[a][b] * vn[a];
-                                WtV[b] += Wb[a][b] * vn[a];
-                            }
-                        }
-#pragma unroll
-                        for (int c = 0; c < DIM; ++c) {
-                            float hv = 0.f;
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) hv += Hs[b][c] * WtV[b];
-                            xb[c] += G[c] * (s1 + s2) - N * BtV[c] + hv;
-                        }
-                    }
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) x_bar[(size_t)a * n + q] = xb[a];
-#pragma unroll
-            for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) F_bar[(size_t)(a * DIM + b) * n + q] = Fb[a][b];
-            float* sc = P.adj_scratch;
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) sc[(size_t)a * n + i] = vpb[a];
-#pragma unroll
-            for (int k = 0; k < DD; ++k) {
-                sc[(size_t)(DIM + k) * n + i] = Bb[k / DIM][k % DIM];
-                sc[(size_t)(DIM + DD + k) * n + i] = Wb[k / DIM][k % DIM];
-            }
+            for (int c = 0; c < DIM; ++c) x_bar[(size_t)c * n + q] = xb[c];
         }
         __syncthreads();
     }
-    // parameter gradients: wave reduction, then one atomic per workgroup that
-    // had an item (same-address float atomics serialise in L2: thousands of
-    // empty workgroups adding zeros made the reverse sweep 1.8x slower)
+    // parameter gradients: one partial sum per workgroup, added up by the
+    // scatter that follows (adds to one address from many workgroups are
+    // served one after another, 15 ns each)
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1) {
         accE += __shfl_xor(accE, o);
@@ -506,130 +591,196 @@ __global__ __launch_bounds__(WG) void k_g2p_adj(DevParams P, const float* __rest
         red[1][threadIdx.x >> 6] = accA;
     }
     __syncthreads();
-    if (threadIdx.x == 0 && (int)blockIdx.x < n_work) {
+    if (threadIdx.x == 0) {
         float se = 0.f, sa = 0.f;
 #pragma unroll
-        for (int k = 0; k < WG / 64; ++k) {
+        for (int k = 0; k < ADJ_WG / 64; ++k) {
             se += red[0][k];
             sa += red[1][k];
         }
-        atomicAdd(&P.param_bar[0], se);
-        atomicAdd(&P.param_bar[1], sa * P.dalpha_dphi);
+        P.adj_part[2 * blockIdx.x] = se;
+        P.adj_part[2 * blockIdx.x + 1] = sa;
     }
 }
 
-// v_bar_n = sum_p N v'_bar + N B_bar (x_n - x_p) + W_bar grad N; same block /
-// cell organisation as the forward P2G (one wave per owner block, one lane per
-// base cell, register sums merged into an LDS tile offset by offset).
-template <int DIM>
-__global__ __launch_bounds__(64) void k_scatter_adj(DevParams P, const float* __restrict__ x, int n,
-                                                    const uint32_t* __restrict__ order,
-                                                    const uint32_t* __restrict__ skeys) {
+// v_bar_n = sum_p N v'_bar + N B_bar (x_n - x_p) + W_bar grad N, organised like
+// the forward P2G: a workgroup per owner block, a lane per base cell, register
+// sums merged into an LDS tile offset by offset.  The workgroup's 64 NW / 4^d
+// groups of 4^d lanes take the particles of a cell in turns, each group with a
+// tile of its own, summed when the tiles are stored.  A block's walk is a
+// serial chain of as many rounds as its fullest cell has particles for each
+// group; several waves per block shorten it where the blocks leave SIMDs idle
+// (launch_scatter_adj has the line).  Cells are read in G2P's output order, in
+// which consecutive lanes hold consecutive addresses.
+// The first workgroup also adds up the parameter gradients' partial sums.
+template <int DIM, int NW>
+__global__ __launch_bounds__(64 * NW) void k_scatter_adj(DevParams P, int n, const uint32_t* __restrict__ skeys,
+                                                         int n_part, int parts) {
     using T = Tile<DIM>;
     constexpr int NC = T::NPB;
     constexpr int NK = DIM == 3 ? 27 : 9;
     constexpr int DD = DIM * DIM;
-    __shared__ float tile[3][T::NP];
-    __shared__ int cs[NC], ce[NC];
-    const int lane = threadIdx.x;
+    constexpr int TH = 64 * NW, SPL = TH / NC;
+    __shared__ float tile[SPL][3][T::NP];
+    __shared__ Interleave<DIM> il;
+    const int lane = threadIdx.x, cell = lane % NC, grp = lane / NC;
     const int nb = min(P.ctr->nb, P.block_cap);
     const float dx = P.dxf, inv_dx = P.inv_dxf;
     const float* sc = P.adj_scratch;
+    if (blockIdx.x == 0 && threadIdx.x < 64) {
+        n_part = min(n_part, min(P.ctr->n_work, P.work_cap) * parts);  // the rest had no item
+        double se = 0.0, sa = 0.0;
+        for (int i = threadIdx.x; i < n_part; i += 64) {
+            se += (double)P.adj_part[2 * i];
+            sa += (double)P.adj_part[2 * i + 1];
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) {
+            se += __shfl_xor(se, o);
+            sa += __shfl_xor(sa, o);
+        }
+        if (threadIdx.x == 0) {
+            P.param_bar[0] += (float)se;
+            P.param_bar[1] += (float)(sa * (double)P.dalpha_dphi);
+        }
+    }
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
-        const int cnt = P.b_count[b];
+        const int cnt = P.b_count[b], st = P.b_start[b];
         if (cnt <= 0) continue;
-        const int st = P.b_start[b], en = st + cnt;
-        for (int t = lane; t < 3 * T::NP; t += 64) (&tile[0][0])[t] = 0.f;
-        for (int c = lane; c < NC; c += 64) cs[c] = ce[c] = 0;
+        for (int t = lane; t < SPL * 3 * T::NP; t += TH) (&tile[0][0][0])[t] = 0.f;
         int bc[3];
         block_coords<DIM>(P, b, bc);
-        const int org[3] = {bc[0] * BLK, bc[1] * BLK, bc[2] * BLK};
-        __syncthreads();
-        for (int i = st + lane; i < en; i += 64) {
-            const uint32_t c = skeys[i] & (NC - 1);
-            if (i == st || (skeys[i - 1] & (NC - 1)) != c) cs[c] = i;
-            if (i == en - 1 || (skeys[i + 1] & (NC - 1)) != c) ce[c] = i + 1;
-        }
-        __syncthreads();
+        const int lb[3] = {cell & 3, (cell >> 2) & 3, DIM == 3 ? (cell >> 4) & 3 : 0};
+        const double base[3] = {(double)(bc[0] * BLK + lb[0]), (double)(bc[1] * BLK + lb[1]),
+                                (double)(bc[2] * BLK + lb[2])};
+        interleave_setup<DIM>(il, skeys, st, st + cnt);
         float acc[NK][3];
 #pragma unroll
         for (int k = 0; k < NK; ++k) acc[k][0] = acc[k][1] = acc[k][2] = 0.f;
-        int lb[3] = {lane & 3, (lane >> 2) & 3, DIM == 3 ? (lane >> 4) & 3 : 0};
-        bool has = false;
-        if (lane < NC) {
-            const int c0 = cs[lane], c1 = ce[lane];
-            has = c1 > c0;
-            for (int i = c0; i < c1; ++i) {
-                const size_t q = order[i];
-                float xp[3] = {0, 0, 0};
+        const int nj = il.ce[cell] - il.cs[cell];
+        const bool has = nj > grp;
+        struct Part {
+            float x[3], v[3], A[9], W[9];
+        };
+        auto load_into = [&](Part& p, int j) {
+            const size_t o = (size_t)interleave_pos_cj<DIM>(il, cell, j);
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) xp[a] = x[(size_t)a * n + q];
-                float vb[3] = {0, 0, 0}, A[3][3] = {{0}}, G[3][3] = {{0}};
+            for (int a = 0; a < DIM; ++a) {
+                p.v[a] = sc[(size_t)a * n + o];
+                p.x[a] = sc[(size_t)(DIM + 2 * DD + a) * n + o];
+            }
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) vb[a] = sc[(size_t)a * n + i];
+            for (int k = 0; k < DD; ++k) {
+                p.A[k] = sc[(size_t)(DIM + k) * n + o];
+                p.W[k] = sc[(size_t)(DIM + DD + k) * n + o];
+            }
+        };
+        auto process = [&](const Part& p) {
+            float t[3] = {0, 0, 0}, u[3] = {1, 1, 1};
+            particle_frame_at<DIM>(P, p.x, base, t, u);
+            float wt[3][3], dw[3][3], dxn[3][3];
+            bspline<DIM>(t, u, inv_dx, wt, dw);
 #pragma unroll
-                for (int k = 0; k < DD; ++k) {
-                    A[k / DIM][k % DIM] = sc[(size_t)(DIM + k) * n + i];
-                    G[k / DIM][k % DIM] = -sc[(size_t)(DIM + DD + k) * n + i];
-                }
-                float tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1};
-                particle_frame<DIM>(P, xp, org, lb, tt, uu);
-                float wt[3][3], dw[3][3], dxn[3][3];
-                bspline<DIM>(tt, uu, inv_dx, wt, dw);
+            for (int a = 0; a < DIM; ++a)
 #pragma unroll
-                for (int a = 0; a < DIM; ++a)
+                for (int k = 0; k < 3; ++k) dxn[a][k] = ((float)k - 0.5f - t[a]) * dx;
+            // the P2G's factorisation: w_x b(ky, kz) + (w_z w_y) h(kx)
+            float h[3][3];
 #pragma unroll
-                    for (int k = 0; k < 3; ++k) dxn[a][k] = ((float)k - 0.5f - tt[a]) * dx;
+            for (int kx = 0; kx < 3; ++kx)
 #pragma unroll
-                for (int kz = 0; kz < (DIM == 3 ? 3 : 1); ++kz)
+                for (int q = 0; q < DIM; ++q)
+                    h[kx][q] = wt[0][kx] * dxn[0][kx] * p.A[q * DIM] + dw[0][kx] * p.W[q * DIM];
+            if (DIM == 3) {
+                float Z[3][3];
 #pragma unroll
-                    for (int ky = 0; ky < 3; ++ky) {
-                        const float wz = DIM == 3 ? wt[2][kz] : 1.f;
-                        const float al = wt[1][ky] * wz;
-                        const float gy = dw[1][ky] * wz;
-                        const float gz = DIM == 3 ? wt[1][ky] * dw[2][kz] : 0.f;
-                        const float dy = dxn[1][ky], dz = DIM == 3 ? dxn[2][kz] : 0.f;
+                for (int kz = 0; kz < 3; ++kz)
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        Z[kz][q] = wt[2][kz] * dxn[2][kz] * p.A[q * DIM + 2] + dw[2][kz] * p.W[q * DIM + 2];
+#pragma unroll
+                for (int ky = 0; ky < 3; ++ky) {
+                    const float wy = wt[1][ky];
+                    float Y[3];
+#pragma unroll
+                    for (int q = 0; q < 3; ++q)
+                        Y[q] = wy * (p.v[q] + p.A[q * DIM + 1] * dxn[1][ky]) + p.W[q * DIM + 1] * dw[1][ky];
+#pragma unroll
+                    for (int kz = 0; kz < 3; ++kz) {
+                        const float wz = wt[2][kz], wzy = wz * wy;
                         float be[3];
 #pragma unroll
-                        for (int a = 0; a < DIM; ++a)
-                            be[a] = al * (vb[a] + A[a][1] * dy + (DIM == 3 ? A[a][2] * dz : 0.f)) - G[a][1] * gy -
-                                    (DIM == 3 ? G[a][2] * gz : 0.f);
+                        for (int q = 0; q < 3; ++q) be[q] = wz * Y[q] + wy * Z[kz][q];
+#pragma unroll
+                        for (int kx = 0; kx < 3; ++kx)
+#pragma unroll
+                            for (int q = 0; q < 3; ++q) {
+                                float& a = acc[kx + 3 * (ky + 3 * kz)][q];
+                                a = fmaf(wt[0][kx], be[q], fmaf(wzy, h[kx][q], a));
+                            }
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int ky = 0; ky < 3; ++ky) {
+                    const float wy = wt[1][ky];
+#pragma unroll
+                    for (int q = 0; q < 2; ++q) {
+                        const float Y = wy * (p.v[q] + p.A[q * DIM + 1] * dxn[1][ky]) + p.W[q * DIM + 1] * dw[1][ky];
 #pragma unroll
                         for (int kx = 0; kx < 3; ++kx) {
-                            const int k = kx + 3 * (ky + 3 * kz);
-                            const float wx = wt[0][kx];
-                            const float ca = al * wx * dxn[0][kx], cg = al * dw[0][kx];
-#pragma unroll
-                            for (int a = 0; a < DIM; ++a) acc[k][a] += wx * be[a] + A[a][0] * ca - G[a][0] * cg;
+                            float& a = acc[kx + 3 * ky][q];
+                            a = fmaf(wt[0][kx], Y, fmaf(wy, h[kx][q], a));
                         }
                     }
+                }
             }
+        };
+        // two register sets take turns: the loads of the next particle are in
+        // flight while the current one is accumulated (as in P2G)
+        Part pa, pb;
+        if (has) load_into(pa, grp);
+        for (int j = grp; j < nj; j += 2 * SPL) {
+            load_into(pb, min(j + SPL, nj - 1));
+            process(pa);
+            load_into(pa, min(j + 2 * SPL, nj - 1));
+            if (j + SPL < nj) process(pb);
         }
+        // merge into the group's tile: for a fixed offset distinct cells
+        // address distinct nodes; a group's cells are all in one wave, whose
+        // LDS accesses are served in the order they are issued
 #pragma unroll
         for (int k = 0; k < NK; ++k) {
             const int kx = k % 3, ky = (k / 3) % 3, kz = DIM == 3 ? k / 9 : 0;
             const int idx = T::pad(lb[0] + kx, lb[1] + ky, DIM == 3 ? lb[2] + kz : 0);
             if (has) {
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) tile[a][idx] += acc[k][a];
+                for (int a = 0; a < DIM; ++a) tile[grp][a][idx] += acc[k][a];
             }
-            __syncthreads();
+            __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+            __builtin_amdgcn_wave_barrier();
         }
-        for (int t = lane; t < T::N; t += 64) {
-            const int I = t % T::E;
-            const int J = (t / T::E) % T::E;
-            const int K = DIM == 3 ? t / (T::E * T::E) : 0;
+        __syncthreads();
+        for (int t = lane; t < T::N; t += TH) {
+            int I, J, K;
+            T::store_node(t, &I, &J, &K);
             const int tp = T::pad(I, J, K);
-            const float p0 = tile[0][tp], p1 = tile[1][tp], p2 = DIM == 3 ? tile[2][tp] : 0.f;
-            if (p0 != 0.f || p1 != 0.f || p2 != 0.f) {
+            float g[3] = {0, 0, 0};
+#pragma unroll
+            for (int r = 0; r < SPL; ++r)
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) g[a] += tile[r][a][tp];
+            if (!P.dense) {
+                P.tiles[(size_t)b * T::N + t] = make_float4(g[0], g[1], g[2], 0.f);
+            } else if (g[0] != 0.f || g[1] != 0.f || g[2] != 0.f) {
                 const int d = (I >> 2) | ((J >> 2) << 1) | ((K >> 2) << 2);
                 const int phi = P.b_nbr[(size_t)b * T::NB + d];
                 if (phi >= 0) {
                     const int l = (I & 3) + BLK * ((J & 3) + BLK * (K & 3));
-                    float* g = reinterpret_cast<float*>(&P.grid_bar[(size_t)phi * T::NPB + l]);
-                    atomicAdd(g + 0, p0);
-                    atomicAdd(g + 1, p1);
-                    if (DIM == 3) atomicAdd(g + 2, p2);
+                    float* o = reinterpret_cast<float*>(&P.grid_bar[(size_t)phi * T::NPB + l]);
+                    atomicAdd(o + 0, g[0]);
+                    atomicAdd(o + 1, g[1]);
+                    if (DIM == 3) atomicAdd(o + 2, g[2]);
                 }
             }
         }
@@ -637,47 +788,82 @@ __global__ __launch_bounds__(64) void k_scatter_adj(DevParams P, const float* __
     }
 }
 
+// Adjoint of one node's update: gb = v_bar, gu = (u, m) from the forward pass;
+// returns (p_bar, m_bar).
 template <int DIM>
-__global__ __launch_bounds__(WG) void k_grid_adj(DevParams P, long long n_nodes_host) {
-    constexpr int NPB = Tile<DIM>::NPB;
-    const long long n_nodes = n_nodes_host >= 0 ? n_nodes_host : (long long)P.ctr->nb * NPB;
-    for (long long s = (long long)blockIdx.x * WG + threadIdx.x; s < n_nodes; s += (long long)gridDim.x * WG) {
-        const float4 gb = P.grid_bar[s];
-        const float4 gu = P.grid_u[s];
-        const float m = gu.w;
-        float4 out = make_float4(0.f, 0.f, 0.f, 0.f);
-        if (m > 0.f) {
-            float ub[3] = {gb.x, gb.y, gb.z};
-            const float u[3] = {gu.x, gu.y, gu.z};
-            const int b = (int)(s / NPB), l = (int)(s % NPB);
-            int bc[3];
-            block_coords<DIM>(P, b, bc);
-            const int node[3] = {bc[0] * BLK + (l & 3), bc[1] * BLK + ((l >> 2) & 3),
-                                 DIM == 3 ? bc[2] * BLK + (l >> 4) : 0};
-            // Jacobian of the wall projections (diagonal 0/1), applied to the adjoint
+__device__ __forceinline__ float4 node_adj(const DevParams& P, const int* node, float4 gb, float4 gu) {
+    const float m = gu.w;
+    if (!(m > 0.f)) return make_float4(0.f, 0.f, 0.f, 0.f);
+    float ub[3] = {gb.x, gb.y, gb.z};
+    const float u[3] = {gu.x, gu.y, gu.z};
+    // Jacobian of the wall projections (diagonal 0/1), applied to the adjoint
 #pragma unroll
-            for (int a = 0; a < DIM; ++a) {
+    for (int a = 0; a < DIM; ++a) {
 #pragma unroll
-                for (int side = 0; side < 2; ++side) {
-                    const bool on = side == 0 ? node[a] < P.bound : node[a] > P.cells[a] - P.bound;
-                    if (!on) continue;
-                    const int kind = P.bc[a][side];
-                    if (kind == MPM_BC_STICKY) {
-                        ub[0] = ub[1] = ub[2] = 0.f;
-                    } else if (kind == MPM_BC_SLIP) {
-                        ub[a] = 0.f;
-                    } else if (kind == MPM_BC_SEPARATE) {
-                        if (side == 0 ? u[a] < 0.f : u[a] > 0.f) ub[a] = 0.f;
-                    }
-                }
+        for (int side = 0; side < 2; ++side) {
+            const bool on = side == 0 ? node[a] < P.bound : node[a] > P.cells[a] - P.bound;
+            if (!on) continue;
+            const int kind = P.bc[a][side];
+            if (kind == MPM_BC_STICKY) {
+                ub[0] = ub[1] = ub[2] = 0.f;
+            } else if (kind == MPM_BC_SLIP) {
+                ub[a] = 0.f;
+            } else if (kind == MPM_BC_SEPARATE) {
+                if (side == 0 ? u[a] < 0.f : u[a] > 0.f) ub[a] = 0.f;
             }
-            const float inv = 1.f / m;
-            float mb = 0.f;
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) mb -= ub[a] * (u[a] - P.dt * P.g[a]);
-            out = make_float4(ub[0] * inv, ub[1] * inv, DIM == 3 ? ub[2] * inv : 0.f, mb * inv);
         }
-        P.grid_bar[s] = out;
+    }
+    const float inv = 1.f / m;
+    float mb = 0.f;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) mb -= ub[a] * (u[a] - P.dt * P.g[a]);
+    return make_float4(ub[0] * inv, ub[1] * inv, DIM == 3 ? ub[2] * inv : 0.f, mb * inv);
+}
+
+// Sparse grids: the sum of the tiles that cover each node (k_p2g_gather's
+// pattern, one wave per block), then the node's adjoint.
+template <int DIM>
+__global__ __launch_bounds__(WG) void k_gather_adj(DevParams P) {
+    using T = Tile<DIM>;
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    const int nb = min(P.ctr->nb, P.block_cap);
+    const int I = lane & 3, J = (lane >> 2) & 3, K = DIM == 3 ? (lane >> 4) & 3 : 0;
+    for (int b = blockIdx.x * (WG / 64) + w; b < nb; b += gridDim.x * (WG / 64)) {
+        int src[T::NB];
+#pragma unroll
+        for (int d = 0; d < T::NB; ++d) src[d] = P.b_lo[(size_t)b * T::NB + d];
+        int bc[3];
+        block_coords<DIM>(P, b, bc);
+        const size_t s = (size_t)b * T::NPB + lane;
+        const float4 gu = lane < T::NPB ? P.grid_u[s] : make_float4(0.f, 0.f, 0.f, 0.f);
+        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+        for (int d = 0; d < T::NB; ++d) {
+            const int ex = d & 1, ey = (d >> 1) & 1, ez = (d >> 2) & 1;
+            const bool reach = (!ex || I < 2) && (!ey || J < 2) && (DIM == 2 || !ez || K < 2);
+            if (src[d] >= 0 && reach && lane < T::NPB) {
+                const float4 g = P.tiles[(size_t)src[d] * T::N + T::store_index(I + 4 * ex, J + 4 * ey, K + 4 * ez)];
+                sum.x += g.x;
+                sum.y += g.y;
+                sum.z += g.z;
+            }
+        }
+        const int node[3] = {bc[0] * BLK + I, bc[1] * BLK + J, DIM == 3 ? bc[2] * BLK + K : 0};
+        if (lane < T::NPB) P.grid_bar[s] = node_adj<DIM>(P, node, sum, gu);
+    }
+}
+
+// Dense grids: the node's adjoint in place, after the scatter's atomics.
+template <int DIM>
+__global__ __launch_bounds__(WG) void k_grid_adj(DevParams P, long long n_nodes) {
+    constexpr int NPB = Tile<DIM>::NPB;
+    for (long long s = (long long)blockIdx.x * WG + threadIdx.x; s < n_nodes; s += (long long)gridDim.x * WG) {
+        const int b = (int)(s / NPB), l = (int)(s % NPB);
+        int bc[3];
+        block_coords<DIM>(P, b, bc);
+        const int node[3] = {bc[0] * BLK + (l & 3), bc[1] * BLK + ((l >> 2) & 3),
+                             DIM == 3 ? bc[2] * BLK + (l >> 4) : 0};
+        P.grid_bar[s] = node_adj<DIM>(P, node, P.grid_bar[s], P.grid_u[s]);
     }
 }
 
@@ -695,189 +881,139 @@ struct PBar {
 };
 
 template <int DIM>
-__global__ __launch_bounds__(WG) void k_p2g_adj(DevParams P, PIn in, PBar bar, int n,
-                                                const uint32_t* __restrict__ order) {
-    using T = Tile<DIM>;
+__global__ __launch_bounds__(ADJ_WG, 3) void k_p2g_adj(DevParams P, PIn in, PBar bar, int n,
+                                                    const uint32_t* __restrict__ osrc, int parts) {
+    constexpr int DD = DIM * DIM;
     constexpr int NS = DIM == 3 ? 6 : 3;
-    __shared__ float4 gt[T::N];
-    __shared__ int nbr[T::NB];
-    __shared__ int org[3];
-    const int n_work = min(P.ctr->n_work, P.work_cap);
+    __shared__ float4 vt[adj_tile<DIM>()];
+    const int n_work = min(P.ctr->n_work, P.work_cap) * parts;
     const float mp = P.p_mass, dtv = P.dt * P.p_vol0;
-    const float dx = P.dxf, inv_dx = P.inv_dxf;
     for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
-        const int blk = P.w_block[w], s = P.w_start[w], e = P.w_end[w];
-        if (threadIdx.x < T::NB) nbr[threadIdx.x] = P.b_nbr[blk * T::NB + threadIdx.x];
-        if (threadIdx.x == 0) {
-            int bc[3];
-            block_coords<DIM>(P, blk, bc);
-            org[0] = bc[0] * BLK;
-            org[1] = bc[1] * BLK;
-            org[2] = bc[2] * BLK;
-        }
-        __syncthreads();
-        for (int t = threadIdx.x; t < T::N; t += WG) {
-            const int I = t % T::E, J = (t / T::E) % T::E, K = DIM == 3 ? t / (T::E * T::E) : 0;
-            const int d = (I >> 2) | ((J >> 2) << 1) | ((K >> 2) << 2);
-            const int phi = nbr[d];
-            const int l = (I & 3) + BLK * ((J & 3) + BLK * (K & 3));
-            gt[t] = phi >= 0 ? P.grid_bar[(size_t)phi * T::NPB + l] : make_float4(0.f, 0.f, 0.f, 0.f);
-        }
-        __syncthreads();
-#pragma unroll 1
-        for (int i = s + (int)threadIdx.x; i < e; i += WG) {
-            const size_t q = order[i];
-            float xp[3] = {0, 0, 0}, vp[3] = {0, 0, 0}, Cp[3][3] = {{0}}, tau[3][3] = {{0}};
+        const int it = w / parts;
+        const int s = P.w_start[it] + (w % parts) * ADJ_WG, e = min(P.w_end[it], s + ADJ_WG);
+        if (s >= e) continue;
+        const int o = s + (int)threadIdx.x;
+        // what the gather needs is loaded before the tile's barrier, the rest
+        // after it (registers: three waves per SIMD)
+        const size_t q = osrc[min(o, e - 1)];
+        float xp[3] = {0, 0, 0}, C[3][3] = {{0}}, tc[NS];
 #pragma unroll
-            for (int a = 0; a < DIM; ++a) {
-                xp[a] = in.x[(size_t)a * n + q];
-                vp[a] = in.v[(size_t)a * n + q];
-            }
+        for (int a = 0; a < DIM; ++a) xp[a] = in.x[(size_t)a * n + q];
 #pragma unroll
-            for (int a = 0; a < DIM; ++a)
+        for (int k = 0; k < DD; ++k) C[k / DIM][k % DIM] = in.C[(size_t)k * n + q];
 #pragma unroll
-                for (int b = 0; b < DIM; ++b) Cp[a][b] = in.C[(size_t)(a * DIM + b) * n + q];
+        for (int k = 0; k < NS; ++k) tc[k] = in.tau[(size_t)k * n + q];
+        int org[3];
+        stage_tile<DIM>(P, P.grid_bar, P.w_block[it], vt, org);
+        if (o < e) {
+            float tau[3][3] = {{0}};
             if (DIM == 3) {
-                tau[0][0] = in.tau[q];
-                tau[1][1] = in.tau[(size_t)n + q];
-                tau[2][2] = in.tau[2 * (size_t)n + q];
-                tau[0][1] = tau[1][0] = in.tau[3 * (size_t)n + q];
-                tau[1][2] = tau[2][1] = in.tau[4 * (size_t)n + q];
-                tau[0][2] = tau[2][0] = in.tau[5 * (size_t)n + q];
+                tau[0][0] = tc[0];
+                tau[1][1] = tc[1];
+                tau[2][2] = tc[2];
+                tau[0][1] = tau[1][0] = tc[3];
+                tau[1][2] = tau[2][1] = tc[4];
+                tau[0][2] = tau[2][0] = tc[5];
             } else {
-                tau[0][0] = in.tau[q];
-                tau[1][1] = in.tau[(size_t)n + q];
-                tau[0][1] = tau[1][0] = in.tau[2 * (size_t)n + q];
+                tau[0][0] = tc[0];
+                tau[1][1] = tc[1];
+                tau[0][1] = tau[1][0] = tc[2];
             }
             int lb[3] = {0, 0, 0};
             float tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1};
             particle_frame<DIM>(P, xp, org, lb, tt, uu);
-            float wt[3][3], dw[3][3], ddw[3], dxn[3][3];
-            bspline<DIM>(tt, uu, inv_dx, wt, dw);
-            bspline_dd(inv_dx * inv_dx, ddw);
-#pragma unroll
-            for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                for (int k = 0; k < 3; ++k) dxn[a][k] = ((float)k - 0.5f - tt[a]) * dx;
-            float vb[3] = {0, 0, 0}, Cb[3][3] = {{0}}, tb[3][3] = {{0}}, xb[3] = {0, 0, 0};
-#pragma unroll
-            for (int kz = 0; kz < (DIM == 3 ? 3 : 1); ++kz)
-#pragma unroll
-                for (int ky = 0; ky < 3; ++ky)
-#pragma unroll
-                    for (int kx = 0; kx < 3; ++kx) {
-                        const int idx = (lb[0] + kx) + T::E * ((lb[1] + ky) + (DIM == 3 ? T::E * (lb[2] + kz) : 0));
-                        const float4 g4 = gt[idx];
-                        const float pb[3] = {g4.x, g4.y, g4.z};
-                        const float mb = g4.w;
-                        float N, G[3], Hs[3][3];
-                        shape_k<DIM>(wt, dw, ddw, kx, ky, kz, &N, G, Hs);
-                        const float dd[3] = {dxn[0][kx], dxn[1][ky], DIM == 3 ? dxn[2][kz] : 0.f};
-                        // mom = v + C dxn ; tau p_bar
-                        float pm = 0.f, CtP[3] = {0, 0, 0}, tP[3] = {0, 0, 0};
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a) {
-                            float ma = vp[a];
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) {
-                                ma += Cp[a][b] * dd[b];
-                                CtP[b] += Cp[a][b] * pb[a];
-                                tP[b] += tau[a][b] * pb[a];
-                            }
-                            pm += pb[a] * ma;
-                        }
-#pragma unroll
-                        for (int a = 0; a < DIM; ++a) {
-                            vb[a] += mp * N * pb[a];
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) {
-                                Cb[a][b] += mp * N * pb[a] * dd[b];
-                                tb[a][b] -= dtv * pb[a] * G[b];
-                            }
-                        }
-#pragma unroll
-                        for (int c = 0; c < DIM; ++c) {
-                            float ht = 0.f;
-#pragma unroll
-                            for (int b = 0; b < DIM; ++b) ht += Hs[b][c] * tP[b];
-                            xb[c] += mb * mp * G[c] + mp * G[c] * pm - N * mp * CtP[c] - dtv * ht;
-                        }
-                    }
+            Moments<DIM, false, true, true> Mo;
+            gather_moments<DIM, false, true, true>(vt, lb, tt, uu, P.dxf, P.inv_dxf, C, tau, Mo);
+            __builtin_amdgcn_sched_barrier(0);
+            float vp[3] = {0, 0, 0}, xb[3] = {0, 0, 0};
 #pragma unroll
             for (int a = 0; a < DIM; ++a) {
-                bar.v[(size_t)a * n + q] = vb[a];
-                bar.x[(size_t)a * n + q] += xb[a];
+                vp[a] = in.v[(size_t)a * n + q];
+                xb[a] = bar.x[(size_t)a * n + q];
             }
 #pragma unroll
-            for (int a = 0; a < DIM; ++a)
+            for (int c = 0; c < DIM; ++c) {
+                float g = Mo.G[c] + Mo.S[c];
 #pragma unroll
-                for (int b = 0; b < DIM; ++b) bar.C[(size_t)(a * DIM + b) * n + q] = Cb[a][b];
+                for (int a = 0; a < DIM; ++a) g += Mo.W[a][c] * vp[a] - C[a][c] * Mo.V[a];
+                bar.x[(size_t)c * n + q] = xb[c] + (mp * g - dtv * Mo.T[c]);
+                bar.v[(size_t)c * n + q] = mp * Mo.V[c];
+            }
+#pragma unroll
+            for (int k = 0; k < DD; ++k) bar.C[(size_t)k * n + q] = mp * Mo.D[k / DIM][k % DIM];
             if (DIM == 3) {
-                bar.tau[q] = tb[0][0];
-                bar.tau[(size_t)n + q] = tb[1][1];
-                bar.tau[2 * (size_t)n + q] = tb[2][2];
-                bar.tau[3 * (size_t)n + q] = tb[0][1] + tb[1][0];
-                bar.tau[4 * (size_t)n + q] = tb[1][2] + tb[2][1];
-                bar.tau[5 * (size_t)n + q] = tb[0][2] + tb[2][0];
+                bar.tau[q] = -dtv * Mo.W[0][0];
+                bar.tau[(size_t)n + q] = -dtv * Mo.W[1][1];
+                bar.tau[2 * (size_t)n + q] = -dtv * Mo.W[2][2];
+                bar.tau[3 * (size_t)n + q] = -dtv * (Mo.W[0][1] + Mo.W[1][0]);
+                bar.tau[4 * (size_t)n + q] = -dtv * (Mo.W[1][2] + Mo.W[2][1]);
+                bar.tau[5 * (size_t)n + q] = -dtv * (Mo.W[0][2] + Mo.W[2][0]);
             } else {
-                bar.tau[q] = tb[0][0];
-                bar.tau[(size_t)n + q] = tb[1][1];
-                bar.tau[2 * (size_t)n + q] = tb[0][1] + tb[1][0];
+                bar.tau[q] = -dtv * Mo.W[0][0];
+                bar.tau[(size_t)n + q] = -dtv * Mo.W[1][1];
+                bar.tau[2 * (size_t)n + q] = -dtv * (Mo.W[0][1] + Mo.W[1][0]);
             }
         }
         __syncthreads();
     }
 }
 
-template <int DIM>
-__global__ __launch_bounds__(WG) void k_grid_bar_clear(DevParams P, long long n_nodes_host) {
-    constexpr int NPB = Tile<DIM>::NPB;
-    const long long n_nodes = n_nodes_host >= 0 ? n_nodes_host : (long long)P.ctr->nb * NPB;
+__global__ __launch_bounds__(WG) void k_grid_bar_clear(DevParams P, long long n_nodes) {
     for (long long s = (long long)blockIdx.x * WG + threadIdx.x; s < n_nodes; s += (long long)gridDim.x * WG)
         P.grid_bar[s] = make_float4(0.f, 0.f, 0.f, 0.f);
 }
 
+namespace {
+// Workgroups of the per-particle kernels and parts per work item.
+int adj_parts(const DevParams& P) { return (P.chunk + ADJ_WG - 1) / ADJ_WG; }
+int adj_grid(const DevParams& P) { return (int)std::min<long long>((long long)P.work_cap * adj_parts(P), ADJ_MAX_WGS); }
+}  // namespace
+
 hipError_t launch_g2p_adj(const DevParams& P, const float* x, const float* F, const float* const* out_bar, float* x_bar,
-                          float* F_bar, int n, const uint32_t* order, const uint32_t* skeys, int grid_blocks,
-                          hipStream_t s) {
+                          float* F_bar, int n, const uint32_t* osrc, hipStream_t s) {
     OutBar ob{out_bar[0], out_bar[1], out_bar[2], out_bar[3], out_bar[4]};
-    if (P.dim == 3)
-        k_g2p_adj<3><<<grid_blocks, WG, 0, s>>>(P, x, F, ob, x_bar, F_bar, n, order, skeys);
-    else
-        k_g2p_adj<2><<<grid_blocks, WG, 0, s>>>(P, x, F, ob, x_bar, F_bar, n, order, skeys);
+    const auto k = P.dim == 3 ? k_g2p_adj<3> : k_g2p_adj<2>;
+    k<<<adj_grid(P), ADJ_WG, 0, s>>>(P, x, F, ob, x_bar, F_bar, n, osrc, adj_parts(P));
     return hipGetLastError();
 }
 
-hipError_t launch_scatter_adj(const DevParams& P, const float* x, int n, const uint32_t* order, const uint32_t* skeys,
-                              int grid_blocks, hipStream_t s) {
-    const long long nodes = (long long)P.block_cap * (P.dim == 3 ? 64 : 16);
-    const int gc = (int)std::min<long long>((nodes + WG - 1) / WG, P.dense ? 65536 : 8192);
-    if (P.dim == 3) {
-        k_grid_bar_clear<3><<<gc, WG, 0, s>>>(P, P.dense ? nodes : -1);
-        k_scatter_adj<3><<<P.dense ? 65536 : grid_blocks * 4, 64, 0, s>>>(P, x, n, order, skeys);
+hipError_t launch_scatter_adj(const DevParams& P, int n, const uint32_t* skeys, int grid_blocks, hipStream_t s) {
+    if (P.dense) {
+        const long long nodes = (long long)P.block_cap * (P.dim == 3 ? 64 : 16);
+        k_grid_bar_clear<<<(int)std::min<long long>((nodes + WG - 1) / WG, 65536), WG, 0, s>>>(P, nodes);
+    }
+    const int g = P.dense ? 65536 : grid_blocks * 4, np = adj_grid(P);
+    // as many waves per block as keep every block's waves resident at once (two
+    // per SIMD; 262,144 particles fill about 730 blocks)
+    if (P.dim == 2)
+        k_scatter_adj<2, 1><<<g, 64, 0, s>>>(P, n, skeys, np, adj_parts(P));
+    else if (n <= (1 << 16))
+        k_scatter_adj<3, 4><<<g, 256, 0, s>>>(P, n, skeys, np, adj_parts(P));
+    else if (n <= (1 << 18))
+        k_scatter_adj<3, 2><<<g, 128, 0, s>>>(P, n, skeys, np, adj_parts(P));
+    else
+        k_scatter_adj<3, 1><<<g, 64, 0, s>>>(P, n, skeys, np, adj_parts(P));
+    return hipGetLastError();
+}
+
+hipError_t launch_grid_adj(const DevParams& P, hipStream_t s) {
+    if (P.dense) {
+        const long long nodes = (long long)P.block_cap * (P.dim == 3 ? 64 : 16);
+        const auto k = P.dim == 3 ? k_grid_adj<3> : k_grid_adj<2>;
+        k<<<(int)std::min<long long>((nodes + WG - 1) / WG, 65536), WG, 0, s>>>(P, nodes);
     } else {
-        k_grid_bar_clear<2><<<gc, WG, 0, s>>>(P, P.dense ? nodes : -1);
-        k_scatter_adj<2><<<P.dense ? 65536 : grid_blocks * 4, 64, 0, s>>>(P, x, n, order, skeys);
+        const auto k = P.dim == 3 ? k_gather_adj<3> : k_gather_adj<2>;
+        k<<<(int)std::min<long long>(((long long)P.block_cap + 3) / 4, 16384), WG, 0, s>>>(P);
     }
     return hipGetLastError();
 }
 
-hipError_t launch_grid_adj(const DevParams& P, long long n_nodes_host, int grid_blocks, hipStream_t s) {
-    if (P.dim == 3)
-        k_grid_adj<3><<<grid_blocks, WG, 0, s>>>(P, n_nodes_host);
-    else
-        k_grid_adj<2><<<grid_blocks, WG, 0, s>>>(P, n_nodes_host);
-    return hipGetLastError();
-}
-
 hipError_t launch_p2g_adj(const DevParams& P, const float* const* in, float* const* in_bar, int n,
-                          const uint32_t* order, int grid_blocks, hipStream_t s) {
+                          const uint32_t* osrc, hipStream_t s) {
     PIn pin{in[0], in[1], in[2], in[3]};
     PBar pb{in_bar[0], in_bar[1], in_bar[2], in_bar[3]};
-    if (P.dim == 3)
-        k_p2g_adj<3><<<grid_blocks, WG, 0, s>>>(P, pin, pb, n, order);
-    else
-        k_p2g_adj<2><<<grid_blocks, WG, 0, s>>>(P, pin, pb, n, order);
+    const auto k = P.dim == 3 ? k_p2g_adj<3> : k_p2g_adj<2>;
+    k<<<adj_grid(P), ADJ_WG, 0, s>>>(P, pin, pb, n, osrc, adj_parts(P));
     return hipGetLastError();
 }
 

@@ -55,7 +55,7 @@ struct mpm_ctx {
     int* b_lo = nullptr;
     float4* grid_u = nullptr;
     float4* grid_bar = nullptr;
-    float* adj_scratch = nullptr;
+    float *adj_scratch = nullptr, *adj_part = nullptr;
     bool adjoint = false;
     float* heightmap = nullptr;
     DevCounters* ctr = nullptr;
@@ -79,6 +79,7 @@ struct mpm_ctx {
     int* b_entry = nullptr;
     uint32_t* order = nullptr;
     uint32_t* skeys = nullptr;
+    uint32_t* keys_dst = nullptr;  // where a full sort leaves the sorted keys (null: its own buffers)
     uint32_t* osrc = nullptr;  // G2P output position -> input index (the spare sort value buffer)
     uint32_t* movers = nullptr;  // incremental re-sort: particles that changed owner block
     // scan-based construction (MPM_FLAG_SCAN_BUILD): mask-domain scratch for
@@ -92,13 +93,14 @@ struct mpm_ctx {
     DetTables det{};
     // Reverse-mode tape: for each step of a recorded segment, what its adjoint
     // reads from the step's build and transfers (block and work tables, both
-    // grids, counters, sorted keys and order).
+    // grids, counters, sorted keys and G2P's output layout).
     struct TapeSlot {
         uint64_t* b_keys = nullptr;
         int *b_nbr = nullptr, *b_start = nullptr, *b_count = nullptr;
         int *w_block = nullptr, *w_start = nullptr, *w_end = nullptr;
         float4 *grid = nullptr, *grid_u = nullptr;
-        uint32_t *order = nullptr, *skeys = nullptr;
+        int* b_lo = nullptr;
+        uint32_t *osrc = nullptr, *skeys = nullptr;
     };
     std::vector<TapeSlot> tape;
     DevCounters* tape_ctr = nullptr;  // one per slot
@@ -191,7 +193,8 @@ void free_tape(mpm_ctx* c) {
         dfree(t.w_end);
         dfree(t.grid);
         dfree(t.grid_u);
-        dfree(t.order);
+        dfree(t.b_lo);
+        dfree(t.osrc);
         dfree(t.skeys);
     }
     c->tape.clear();
@@ -208,6 +211,7 @@ void free_all(mpm_ctx* c) {
     dfree(c->hist);
     dfree(c->heightmap);
     dfree(c->adj_scratch);
+    dfree(c->adj_part);
     dfree(c->inst);
     dfree(c->ctr);
     dfree(c->movers);
@@ -309,6 +313,7 @@ void fill_params(mpm_ctx* c) {
     P.grid_u = c->grid_u;
     P.grid_bar = c->grid_bar;
     P.adj_scratch = c->adj_scratch;
+    P.adj_part = c->adj_part;
     P.param_bar = nullptr;
     P.n_inst = c->n_inst;
     P.blk_bits = c->blk_bits;
@@ -494,7 +499,9 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
             if (e != hipSuccess) return MPM_ERR_HIP;
         }
         if (n > 0) {
-            e = radix_sort(c->k1, c->k0, c->k1, c->v0, c->v1, n, c->key_bits, c->hist, c->partials, &ko, &vo, s);
+            uint32_t *k0 = c->k0, *k1 = c->k1;
+            if (c->keys_dst) (radix_passes(c->key_bits) & 1 ? k0 : k1) = c->keys_dst;
+            e = radix_sort(c->k1, k0, k1, c->v0, c->v1, n, c->key_bits, c->hist, c->partials, &ko, &vo, s);
             if (e != hipSuccess) return MPM_ERR_HIP;
         }
     }
@@ -530,6 +537,7 @@ void bind_slot(mpm_ctx* c, int j) {
     const mpm_ctx::TapeSlot& t = c->tape[(size_t)j];
     c->P.b_keys = t.b_keys;
     c->P.b_nbr = t.b_nbr;
+    c->P.b_lo = t.b_lo;
     c->P.b_start = t.b_start;
     c->P.b_count = t.b_count;
     c->P.w_block = t.w_block;
@@ -722,7 +730,8 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     e = e ? e : dalloc(&c->hist, (size_t)radix_hist_size(q->max_particles));
     if (!c->dense && !c->adjoint && !c->scan_build && !c->det_order) e = e ? e : dalloc(&c->movers, np);
     e = e ? e : dalloc(&c->ctr, 1);
-    if (c->adjoint) e = e ? e : dalloc(&c->adj_scratch, np * (size_t)(c->dim + 2 * c->dim * c->dim));
+    if (c->adjoint) e = e ? e : dalloc(&c->adj_scratch, np * (size_t)(2 * c->dim + 2 * c->dim * c->dim));
+    if (c->adjoint) e = e ? e : dalloc(&c->adj_part, 2 * (size_t)ADJ_MAX_WGS);
     if (e == hipSuccess && q->heightmap) {
         const size_t hn = (size_t)(q->cells[0] + 1) * (size_t)(q->cells[1] + 1);
         e = dalloc(&c->heightmap, hn);
@@ -887,18 +896,16 @@ int mpm_g2p_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ob, co
     const float* obp[5] = {ob->x, ob->v, ob->C, ob->F, ob->tau};
     const int wgs = std::min(c->g2p_wgs, c->work_cap);
     hipStream_t s = (hipStream_t)stream;
-    hipError_t e = launch_g2p_adj(P, in->x, in->F, obp, ib->x, ib->F, in->n, c->order, c->skeys, wgs, s);
-    if (e == hipSuccess) e = launch_scatter_adj(P, in->x, in->n, c->order, c->skeys, wgs, s);
+    hipError_t e = launch_g2p_adj(P, in->x, in->F, obp, ib->x, ib->F, in->n, c->osrc, s);
+    if (e == hipSuccess) e = launch_scatter_adj(P, in->n, c->skeys, wgs, s);
     return hip_status(e);
 }
 
 int mpm_grid_update_adj(mpm_ctx* c, void* stream) {
     if (!c) return MPM_ERR_ARG;
     if (!c->adjoint || !c->built) return MPM_ERR_STATE;
-    const long long NPB = 1ll << (2 * c->dim);
-    const long long nodes = (long long)c->block_cap * NPB;
-    long long wgs = std::min<long long>((nodes + WG - 1) / WG, c->dense ? 65536 : 8192);
-    return hip_status(launch_grid_adj(c->P, c->dense ? nodes : -1, (int)std::max(1ll, wgs), (hipStream_t)stream));
+    if (c->built_n == 0) return MPM_OK;  // no particle, no adjoint
+    return hip_status(launch_grid_adj(c->P, (hipStream_t)stream));
 }
 
 int mpm_p2g_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ib, void* stream) {
@@ -908,8 +915,7 @@ int mpm_p2g_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ib, vo
     if (in->n == 0) return MPM_OK;
     const float* inp[4] = {in->x, in->v, in->C, in->tau};
     float* ibp[4] = {ib->x, ib->v, ib->C, ib->tau};
-    const int wgs = std::min(c->g2p_wgs, c->work_cap);
-    return hip_status(launch_p2g_adj(c->P, inp, ibp, in->n, c->order, wgs, (hipStream_t)stream));
+    return hip_status(launch_p2g_adj(c->P, inp, ibp, in->n, c->osrc, (hipStream_t)stream));
 }
 
 int mpm_step_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ob, const mpm_particles* ib,
@@ -946,7 +952,8 @@ int mpm_tape_reserve(mpm_ctx* c, int n_slots) {
         e = e ? e : dalloc(&t.w_end, wc);
         e = e ? e : dalloc(&t.grid, cap * NPB);
         e = e ? e : dalloc(&t.grid_u, cap * NPB);
-        e = e ? e : dalloc(&t.order, np);
+        e = e ? e : dalloc(&t.b_lo, cap * NB);
+        e = e ? e : dalloc(&t.osrc, np);
         e = e ? e : dalloc(&t.skeys, np);
     }
     if (e != hipSuccess) {
@@ -962,20 +969,19 @@ int mpm_tape_forward(mpm_ctx* c, const mpm_particles* states, int n_steps, void*
     if (st != MPM_OK) return st;
     hipStream_t s = (hipStream_t)stream;
     const DevParams saved = c->P;
-    const size_t bytes = (size_t)states[0].n * sizeof(uint32_t);
     for (int j = 0; j < n_steps && st == MPM_OK; ++j) {
         bind_slot(c, j);
+        // the sort and P2G write the slot's arrays
+        c->keys_dst = c->tape[(size_t)j].skeys;
         st = mpm_sparse_build(c, &states[j], stream);
-        if (st == MPM_OK && bytes &&
-            (hipMemcpyAsync(c->tape[(size_t)j].order, c->order, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess ||
-             hipMemcpyAsync(c->tape[(size_t)j].skeys, c->skeys, bytes, hipMemcpyDeviceToDevice, s) != hipSuccess))
-            st = MPM_ERR_HIP;
+        c->osrc = c->tape[(size_t)j].osrc;
         if (st == MPM_OK) st = mpm_p2g(c, &states[j], stream);
         if (st == MPM_OK) st = mpm_grid_update(c, stream);
         if (st == MPM_OK) st = mpm_g2p(c, &states[j], &states[j + 1], stream);
     }
     // the context's own tables were not written: no build is current
     c->P = saved;
+    c->keys_dst = nullptr;
     c->built = false;
     c->seg_valid = false;
     if (n_steps > 0) {
@@ -998,13 +1004,13 @@ int mpm_tape_adjoint(mpm_ctx* c, const mpm_particles* states, int n_steps, const
     }
     hipStream_t s = (hipStream_t)stream;
     const DevParams saved = c->P;
-    uint32_t* const saved_order = c->order;
+    uint32_t* const saved_osrc = c->osrc;
     uint32_t* const saved_skeys = c->skeys;
     const mpm_particles* ob = bar;
     const mpm_particles* ib = spare;
     for (int j = n_steps - 1; j >= 0 && st == MPM_OK; --j) {
         bind_slot(c, j);
-        c->order = c->tape[(size_t)j].order;
+        c->osrc = c->tape[(size_t)j].osrc;
         c->skeys = c->tape[(size_t)j].skeys;
         c->built = true;
         c->built_n = states[j].n;
@@ -1014,7 +1020,7 @@ int mpm_tape_adjoint(mpm_ctx* c, const mpm_particles* states, int n_steps, const
         std::swap(ob, ib);
     }
     c->P = saved;
-    c->order = saved_order;
+    c->osrc = saved_osrc;
     c->skeys = saved_skeys;
     c->built = false;
     c->seg_valid = false;

@@ -126,7 +126,8 @@ struct DevParams {
     // reverse mode (allocated with MPM_FLAG_ADJOINT)
     float4* grid_u;      // pre-boundary nodal velocity u = p/m + dt g, and m
     float4* grid_bar;    // adjoint of the nodal velocity, then (p_bar, m_bar)
-    float* adj_scratch;  // per sorted particle: v'_bar (d), B_bar (d*d), W_bar (d*d); plane stride n
+    float* adj_scratch;  // per G2P output position: v'_bar (d), B_bar (d*d), W_bar (d*d), x (d); plane stride n
+    float* adj_part;     // per workgroup of the reverse G2P: dL/dE, dL/dalpha
     float* param_bar;    // accumulated dL/dE, dL/dphi (per degree)
     float E;
     float dalpha_dphi;   // d alpha / d phi, per degree
@@ -434,6 +435,8 @@ hipError_t radix_sort(const uint32_t* keys_in, uint32_t* k0, uint32_t* k1, uint3
                       int key_bits, unsigned* hist, unsigned* partials, uint32_t** keys_out, uint32_t** vals_out,
                       hipStream_t s);
 int radix_hist_size(int n);
+// Passes of the sort; the sorted keys end in k0 when the count is odd, else in k1.
+constexpr int radix_passes(int key_bits) { return key_bits <= 8 ? 1 : (key_bits + 7) / 8; }
 
 hipError_t launch_bin(const DevParams& P, const float* x, const uint32_t* inst, int n, uint32_t* keys, hipStream_t s);
 // The sorted keys are not written (after an incremental re-sort nothing reads
@@ -474,14 +477,14 @@ hipError_t launch_g2p(const DevParams& P, const float* x_in, const float* F_in, 
                       int grid_blocks, hipStream_t s, uint32_t* keys_out = nullptr,
                       uint32_t* movers_out = nullptr);
 hipError_t launch_clear_flags(DevCounters* c, hipStream_t s);
+// Reverse kernels; osrc[o]: input index of the particle at G2P output position o.
+constexpr int ADJ_MAX_WGS = 8192;  // workgroups of the per-particle kernels at most
 hipError_t launch_g2p_adj(const DevParams& P, const float* x, const float* F, const float* const* out_bar, float* x_bar,
-                          float* F_bar, int n, const uint32_t* order, const uint32_t* skeys, int grid_blocks,
-                          hipStream_t s);
-hipError_t launch_scatter_adj(const DevParams& P, const float* x, int n, const uint32_t* order, const uint32_t* skeys,
-                              int grid_blocks, hipStream_t s);
-hipError_t launch_grid_adj(const DevParams& P, long long n_nodes_host, int grid_blocks, hipStream_t s);
+                          float* F_bar, int n, const uint32_t* osrc, hipStream_t s);
+hipError_t launch_scatter_adj(const DevParams& P, int n, const uint32_t* skeys, int grid_blocks, hipStream_t s);
+hipError_t launch_grid_adj(const DevParams& P, hipStream_t s);
 hipError_t launch_p2g_adj(const DevParams& P, const float* const* in, float* const* in_bar, int n,
-                          const uint32_t* order, int grid_blocks, hipStream_t s);
+                          const uint32_t* osrc, hipStream_t s);
 hipError_t launch_copy_active(const DevParams& P, uint64_t* keys, uint64_t* masks, int cap, hipStream_t s);
 
 }  // namespace mpmx

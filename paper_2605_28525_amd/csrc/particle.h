@@ -97,15 +97,6 @@ __device__ __forceinline__ void bspline(const float* t, const float* u, float in
     }
 }
 
-
-// second derivative (in xi) of the 1D quadratic B-spline at the three stencil
-// nodes: +1, -2, +1 (times inv_dx^2)
-__device__ __forceinline__ void bspline_dd(float inv_dx2, float* ddw) {
-    ddw[0] = inv_dx2;
-    ddw[1] = -2.f * inv_dx2;
-    ddw[2] = inv_dx2;
-}
-
 // ---------------------------------------------------------------------------
 // constitutive update: Hencky strain from the eigen-decomposition of
 // F F^T - I (cyclic Jacobi), Drucker-Prager return map, Kirchhoff stress.

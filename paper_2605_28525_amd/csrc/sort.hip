@@ -148,7 +148,7 @@ hipError_t radix_sort(const uint32_t* keys_in, uint32_t* k0, uint32_t* k1, uint3
                       int key_bits, unsigned* hist, unsigned* partials, uint32_t** keys_out, uint32_t** vals_out,
                       hipStream_t s) {
     const int n_tiles = (n + SORT_TILE - 1) / SORT_TILE;
-    const int passes = key_bits <= 8 ? 1 : (key_bits + 7) / 8;
+    const int passes = radix_passes(key_bits);
     const uint32_t* kin = keys_in;
     const uint32_t* vin = nullptr;
     for (int p = 0; p < passes; ++p) {
