@@ -73,10 +73,28 @@ __device__ __forceinline__ float log1p_small(float m) {
 //   (h_i - h_j) / (lam_i - lam_j) = sqrt(h_i h_j) q_i q_j sinh(beta x / 2) / sinh x
 // (lam = exp(2 eps), beta = kappa - 1), and the Jacobian of the cone map is
 // applied to a vector without being formed.
-template <int DIM>
-__device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const float (*Fe_bar)[3],
-                                 const float* tau_bar_c, float (*Ft_bar)[3], float* E_bar, float* a_bar) {
-    float M[3][3], U[3][3];
+//
+// Which branch of the return map a particle within rounding of a kink takes
+// is settled by one fixed evaluation of F_trial (trial_by_nodes) and of the
+// strains (NODES), not by the faster ones used elsewhere: the gradients jump
+// there, so a particle that fell on the other side would move dL/dphi by its
+// whole share (3e-4 of it, in one of 262,144 particles over 20 steps).
+// The two evaluations of tr differ by 3e-8 rms (1 + M rounds in each strain).
+// Deciding takes 7 us of 50 at 262,144 particles: 4 us for the registers of
+// the second copy of the code, 3 us to run it.
+constexpr float KINK_TOL = 2.5e-7f;
+struct Principal {
+    float U[3][3];                 // eigenvectors of F_trial F_trial^T
+    float q[3] = {1.f, 1.f, 1.f};  // exp(-eps)
+    float eps[3] = {0.f, 0.f, 0.f}, dev[3] = {0.f, 0.f, 0.f};
+    float tr = 0.f, nd = 0.f;  // trace of eps, norm of dev
+    int branch = 0;            // 0 elastic, 1 apex, 2 cone
+};
+// Whether the branch is in doubt (never with NODES).
+template <int DIM, bool NODES>
+__device__ __forceinline__ bool principal_strains(const DevParams& P, const float (*Ft)[3], Principal& S) {
+    float M[3][3];
+    const float ca = P.dp_coef * P.alpha;
     {
         float Hm[3][3];
 #pragma unroll
@@ -93,40 +111,56 @@ __device__ void constitutive_adj(const DevParams& P, const float (*Ft)[3], const
                 M[a][b] = M[b][a] = s;
             }
     }
-    jacobi_sym<DIM>(M, U);
-    float q[3] = {1.f, 1.f, 1.f}, eps[3] = {0.f, 0.f, 0.f}, tr = 0.f;
+    jacobi_sym<DIM>(M, S.U);
+    float wide = 1.f;
+    S.tr = 0.f;
 #pragma unroll
     for (int a = 0; a < DIM; ++a) {
         const float lam = fmaxf(1.f + M[a][a], 1e-6f);
-        eps[a] = 0.5f * log1p_small(M[a][a]);
+        S.eps[a] = 0.5f * (NODES ? logf(lam) : log1p_small(M[a][a]));
         const float r = __builtin_amdgcn_rsqf(lam);
-        q[a] = fmaf(0.5f * r, fmaf(-lam * r, r, 1.f), r);  // 1 / sqrt(lam), one Newton step
-        tr += eps[a];
+        S.q[a] = fmaf(0.5f * r, fmaf(-lam * r, r, 1.f), r);  // 1 / sqrt(lam), one Newton step
+        wide = fmaxf(wide, S.q[a] * S.q[a]);
+        S.tr += S.eps[a];
     }
-    float e2[3] = {eps[0], eps[1], eps[2]}, nh[3] = {0.f, 0.f, 0.f}, kappa = 1.f, ca = 0.f, rnd = 0.f;
-    int branch = 0;  // 0 elastic, 1 apex, 2 cone
-    if (P.model == MPM_MODEL_DP) {
-        float dev[3] = {0.f, 0.f, 0.f}, nd2 = 0.f;
+    if (P.model != MPM_MODEL_DP) return false;
+    float nd2 = 0.f;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        S.dev[a] = S.eps[a] - S.tr / (float)DIM;
+        nd2 += S.dev[a] * S.dev[a];
+    }
+    S.nd = sqrtf(nd2);
+    const float dg = S.nd + P.dp_coef * S.tr * P.alpha, tol = KINK_TOL * wide;
+    S.branch = S.tr > 0.f ? 1 : dg > 0.f ? 2 : 0;
+    if (NODES) {
+        if (S.branch != 2)  // not needed any more in the form that decided
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) S.eps[a] = 0.5f * log1p_small(M[a][a]);
+        return false;
+    }
+    return !(fabsf(S.tr) > tol && (S.branch == 1 || fabsf(dg) > tol * (1.f + ca)));
+}
+
+// Adjoint of (F^E, tau) = Z(F_trial) from the strains of F_trial.
+template <int DIM>
+__device__ __forceinline__ void constitutive_adj(const DevParams& P, const Principal& pr, const float (*Ft)[3],
+                                                 const float (*Fe_bar)[3], const float* tau_bar_c, float (*Ft_bar)[3],
+                                                 float* E_bar, float* a_bar) {
+    const float (*U)[3] = pr.U;
+    const float *q = pr.q, *eps = pr.eps, *dev = pr.dev, tr = pr.tr, nd = pr.nd, ca = P.dp_coef * P.alpha;
+    const int branch = pr.branch;
+    float e2[3] = {eps[0], eps[1], eps[2]}, nh[3] = {0.f, 0.f, 0.f}, kappa = 1.f, rnd = 0.f;
+    if (branch == 1) {
+        kappa = 0.f;
+        e2[0] = e2[1] = e2[2] = 0.f;
+    } else if (branch == 2) {
+        rnd = rcp_nr(nd);
+        kappa = -ca * tr * rnd;
 #pragma unroll
         for (int a = 0; a < DIM; ++a) {
-            dev[a] = eps[a] - tr / (float)DIM;
-            nd2 += dev[a] * dev[a];
-        }
-        const float nd = sqrtf(nd2);
-        ca = P.dp_coef * P.alpha;
-        if (tr > 0.f) {
-            branch = 1;
-            kappa = 0.f;
-            e2[0] = e2[1] = e2[2] = 0.f;
-        } else if (nd + ca * tr > 0.f) {
-            branch = 2;
-            rnd = rcp_nr(nd);
-            kappa = -ca * tr * rnd;
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) {
-                nh[a] = dev[a] * rnd;
-                e2[a] = tr / (float)DIM - ca * tr * nh[a];
-            }
+            nh[a] = dev[a] * rnd;
+            e2[a] = tr / (float)DIM - ca * tr * nh[a];
         }
     }
     float tr2 = 0.f, h[3] = {1.f, 1.f, 1.f};
@@ -465,22 +499,164 @@ __device__ __forceinline__ void stage_tile(const DevParams& P, const float4* __r
     __syncthreads();
 }
 
+// F_trial of input particle q with grad v summed node by node (rarely called:
+// rolled, and everything is read again).
+template <int DIM>
+__device__ __forceinline__ void trial_by_nodes(const DevParams& P, const float4* vt, const int* org,
+                                               const float* __restrict__ x, const float* __restrict__ F, size_t q,
+                                               int n, float (*Ft)[3]) {
+    float xp[3] = {0, 0, 0}, tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1}, wt[3][3], dw[3][3], W[3][3] = {{0}};
+    int lb[3] = {0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) xp[a] = x[(size_t)a * n + q];
+    particle_frame<DIM>(P, xp, org, lb, tt, uu);
+    bspline<DIM>(tt, uu, P.inv_dxf, wt, dw);
+    const float4* base = vt + lb[0] + ADJ_SY * lb[1] + (DIM == 3 ? adj_sz<DIM>() * lb[2] : 0);
+    auto pick = [](const float* f, int k) { return k == 0 ? f[0] : k == 1 ? f[1] : f[2]; };
+#pragma unroll 1
+    for (int k = 0; k < (DIM == 3 ? 27 : 9); ++k) {  // x fastest
+        const int kk[3] = {k % 3, k / 3 % 3, k / 9};
+        const float4 g4 = base[kk[0] + ADJ_SY * kk[1] + adj_sz<DIM>() * kk[2]];
+        const float v[3] = {g4.x, g4.y, g4.z};
+        float w[3] = {1.f, 1.f, 1.f}, d[3] = {0.f, 0.f, 0.f};
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) {
+            w[a] = pick(wt[a], kk[a]);
+            d[a] = pick(dw[a], kk[a]);
+        }
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+            float g = d[b];
+#pragma unroll
+            for (int e = 0; e < DIM; ++e)
+                if (e != b) g *= w[e];
+#pragma unroll
+            for (int a = 0; a < DIM; ++a) W[a][b] += v[a] * g;
+        }
+    }
+    float Fp[3][3];
+#pragma unroll
+    for (int k = 0; k < DIM * DIM; ++k) Fp[k / DIM][k % DIM] = F[(size_t)k * n + q];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a)
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+            float s = 0.f;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) s += W[a][c] * Fp[c][b];
+            Ft[a][b] = Fp[a][b] + P.dt * s;
+        }
+}
+
+// One particle of k_g2p_adj; false where its branch has to be settled by NODES
+// (what was written up to there is written again).
+template <int DIM, bool NODES>
+__device__ __forceinline__ bool g2p_adj_particle(const DevParams& P, const float4* vt, const int* org,
+                                                 const float* __restrict__ x, const float* __restrict__ F,
+                                                 const OutBar& ob, float* __restrict__ x_bar,
+                                                 float* __restrict__ F_bar, int n, int o, size_t q, const float* xp,
+                                                 const float (*Bb)[3], float* accE, float* accA) {
+    constexpr int NS = DIM == 3 ? 6 : 3;
+    constexpr int DD = DIM * DIM;
+    const float dt = P.dt, dx = P.dxf, inv_dx = P.inv_dxf;
+    int lb[3] = {0, 0, 0};
+    float tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1};
+    particle_frame<DIM>(P, xp, org, lb, tt, uu);
+    Moments<DIM, true, false, false> Mo;
+    gather_moments<DIM, true, false, false>(vt, lb, tt, uu, dx, inv_dx, Bb, Bb, Mo);
+    __builtin_amdgcn_sched_barrier(0);
+    float Fp[3][3], xbo[3] = {0, 0, 0}, vpb[3] = {0, 0, 0};
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        xbo[a] = ob.x[(size_t)a * n + o];
+        vpb[a] = ob.v[(size_t)a * n + o] + dt * xbo[a];
+    }
+#pragma unroll
+    for (int k = 0; k < DD; ++k) Fp[k / DIM][k % DIM] = F[(size_t)k * n + q];
+    float* sc = P.adj_scratch;
+    float xb[3];
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) {
+        // position adjoint through the weights of v_p and B_p
+        xb[c] = xbo[c] + Mo.S[c];
+#pragma unroll
+        for (int a = 0; a < DIM; ++a) xb[c] += Mo.W[a][c] * vpb[a] - Bb[a][c] * Mo.V[a];
+        sc[(size_t)c * n + o] = vpb[c];
+        sc[(size_t)(DIM + 2 * DD + c) * n + o] = xp[c];
+    }
+#pragma unroll
+    for (int k = 0; k < DD; ++k) sc[(size_t)(DIM + k) * n + o] = Bb[k / DIM][k % DIM];
+    float Ft[3][3], Fbo[3][3] = {{0}}, tbo[6] = {0};
+    Principal pr;
+#pragma unroll
+    for (int a = 0; a < DIM; ++a)
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+            float s2 = 0.f;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) s2 += Mo.W[a][c] * Fp[c][b];
+            Ft[a][b] = Fp[a][b] + dt * s2;
+        }
+#pragma unroll
+    for (int k = 0; k < DD; ++k) Fbo[k / DIM][k % DIM] = ob.F[(size_t)k * n + o];
+#pragma unroll
+    for (int k = 0; k < NS; ++k) tbo[k] = ob.tau[(size_t)k * n + o];
+    if (NODES) trial_by_nodes<DIM>(P, vt, org, x, F, q, n, Ft);
+    if (principal_strains<DIM, NODES>(P, Ft, pr)) return false;
+    float Ftb[3][3], eb, ab;
+    constitutive_adj<DIM>(P, pr, Ft, Fbo, tbo, Ftb, &eb, &ab);
+    *accE += eb;
+    *accA += ab;
+    // F_trial = (I + dt W) F
+    float Wb[3][3];
+#pragma unroll
+    for (int a = 0; a < DIM; ++a)
+#pragma unroll
+        for (int b = 0; b < DIM; ++b) {
+            float s1 = Ftb[a][b], s2 = 0.f;
+#pragma unroll
+            for (int c = 0; c < DIM; ++c) {
+                s1 += dt * Mo.W[c][a] * Ftb[c][b];
+                s2 += Ftb[a][c] * Fp[b][c];
+            }
+            F_bar[(size_t)(a * DIM + b) * n + q] = s1;
+            Wb[a][b] = dt * s2;
+            sc[(size_t)(DIM + DD + a * DIM + b) * n + o] = Wb[a][b];
+        }
+    // and through the weights of grad v
+#pragma unroll
+    for (int a = 0; a < DIM; ++a) {
+        if (DIM == 3) {
+            xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][3] + Wb[a][2] * Mo.Y[a][5];
+            xb[1] += Wb[a][0] * Mo.Y[a][3] + Wb[a][1] * Mo.Y[a][1] + Wb[a][2] * Mo.Y[a][4];
+            xb[2] += Wb[a][0] * Mo.Y[a][5] + Wb[a][1] * Mo.Y[a][4] + Wb[a][2] * Mo.Y[a][2];
+        } else {
+            xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][2];
+            xb[1] += Wb[a][0] * Mo.Y[a][2] + Wb[a][1] * Mo.Y[a][1];
+        }
+    }
+#pragma unroll
+    for (int c = 0; c < DIM; ++c) x_bar[(size_t)c * n + q] = xb[c];
+    return true;
+}
+
 // osrc[o]: the input particle that G2P stores at position o.  A work item's
 // range of positions holds particles of its block whichever way the block's
 // particles are listed, so the item's part is walked in output order: the
 // output adjoints and the scratch are read and written contiguously.
+// Bound by its arithmetic and registers (about 3000 instructions a particle at
+// three waves per SIMD; its bytes take 16 us): 262,144 particles in 50 us, 109
+// before (27 nodes times all Hessian factors, 283 registers, one wave per SIMD).
 template <int DIM>
 __global__ __launch_bounds__(ADJ_WG, 3) void k_g2p_adj(DevParams P, const float* __restrict__ x,
                                                     const float* __restrict__ F, OutBar ob, float* __restrict__ x_bar,
                                                     float* __restrict__ F_bar, int n, const uint32_t* __restrict__ osrc,
                                                     int parts) {
-    constexpr int NS = DIM == 3 ? 6 : 3;
     constexpr int DD = DIM * DIM;
     __shared__ float4 vt[adj_tile<DIM>()];
     __shared__ float red[2][ADJ_WG / 64];
     const int n_work = min(P.ctr->n_work, P.work_cap) * parts;
-    const float dt = P.dt, dx = P.dxf, inv_dx = P.inv_dxf;
-    const float bscale = 4.f * inv_dx * inv_dx;
+    const float bscale = 4.f * P.inv_dxf * P.inv_dxf;
     float accE = 0.f, accA = 0.f;
     for (int w = blockIdx.x; w < n_work; w += gridDim.x) {
         const int it = w / parts;
@@ -501,80 +677,17 @@ __global__ __launch_bounds__(ADJ_WG, 3) void k_g2p_adj(DevParams P, const float*
         if (o < e) {
 #pragma unroll
             for (int k = 0; k < DD; ++k) Bb[k / DIM][k % DIM] *= bscale;
-            int lb[3] = {0, 0, 0};
-            float tt[3] = {0, 0, 0}, uu[3] = {1, 1, 1};
-            particle_frame<DIM>(P, xp, org, lb, tt, uu);
-            Moments<DIM, true, false, false> Mo;
-            gather_moments<DIM, true, false, false>(vt, lb, tt, uu, dx, inv_dx, Bb, Bb, Mo);
-            __builtin_amdgcn_sched_barrier(0);
-            float Fp[3][3], xbo[3] = {0, 0, 0}, vpb[3] = {0, 0, 0};
+            bool sure = g2p_adj_particle<DIM, false>(P, vt, org, x, F, ob, x_bar, F_bar, n, o, q, xp, Bb, &accE, &accA);
+            if (!sure) {
+                int o2 = o;
+                asm volatile("" : "+v"(o2));  // nothing of the first attempt is kept for the second
+                const size_t q2 = osrc[o2];
 #pragma unroll
-            for (int a = 0; a < DIM; ++a) {
-                xbo[a] = ob.x[(size_t)a * n + o];
-                vpb[a] = ob.v[(size_t)a * n + o] + dt * xbo[a];
+                for (int a = 0; a < DIM; ++a) xp[a] = x[(size_t)a * n + q2];
+#pragma unroll
+                for (int k = 0; k < DD; ++k) Bb[k / DIM][k % DIM] = bscale * ob.C[(size_t)k * n + o2];
+                g2p_adj_particle<DIM, true>(P, vt, org, x, F, ob, x_bar, F_bar, n, o2, q2, xp, Bb, &accE, &accA);
             }
-#pragma unroll
-            for (int k = 0; k < DD; ++k) Fp[k / DIM][k % DIM] = F[(size_t)k * n + q];
-            float* sc = P.adj_scratch;
-            float xb[3];
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) {
-                // position adjoint through the weights of v_p and B_p
-                xb[c] = xbo[c] + Mo.S[c];
-#pragma unroll
-                for (int a = 0; a < DIM; ++a) xb[c] += Mo.W[a][c] * vpb[a] - Bb[a][c] * Mo.V[a];
-                sc[(size_t)c * n + o] = vpb[c];
-                sc[(size_t)(DIM + 2 * DD + c) * n + o] = xp[c];
-            }
-#pragma unroll
-            for (int k = 0; k < DD; ++k) sc[(size_t)(DIM + k) * n + o] = Bb[k / DIM][k % DIM];
-            float Ft[3][3], Fbo[3][3] = {{0}}, tbo[6] = {0};
-#pragma unroll
-            for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) {
-                    float s2 = 0.f;
-#pragma unroll
-                    for (int c = 0; c < DIM; ++c) s2 += Mo.W[a][c] * Fp[c][b];
-                    Ft[a][b] = Fp[a][b] + dt * s2;
-                    Fbo[a][b] = ob.F[(size_t)(a * DIM + b) * n + o];
-                }
-#pragma unroll
-            for (int k = 0; k < NS; ++k) tbo[k] = ob.tau[(size_t)k * n + o];
-            float Ftb[3][3], eb, ab;
-            constitutive_adj<DIM>(P, Ft, Fbo, tbo, Ftb, &eb, &ab);
-            accE += eb;
-            accA += ab;
-            // F_trial = (I + dt W) F
-            float Wb[3][3];
-#pragma unroll
-            for (int a = 0; a < DIM; ++a)
-#pragma unroll
-                for (int b = 0; b < DIM; ++b) {
-                    float s1 = Ftb[a][b], s2 = 0.f;
-#pragma unroll
-                    for (int c = 0; c < DIM; ++c) {
-                        s1 += dt * Mo.W[c][a] * Ftb[c][b];
-                        s2 += Ftb[a][c] * Fp[b][c];
-                    }
-                    F_bar[(size_t)(a * DIM + b) * n + q] = s1;
-                    Wb[a][b] = dt * s2;
-                    sc[(size_t)(DIM + DD + a * DIM + b) * n + o] = Wb[a][b];
-                }
-            // and through the weights of grad v
-#pragma unroll
-            for (int a = 0; a < DIM; ++a) {
-                if (DIM == 3) {
-                    xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][3] + Wb[a][2] * Mo.Y[a][5];
-                    xb[1] += Wb[a][0] * Mo.Y[a][3] + Wb[a][1] * Mo.Y[a][1] + Wb[a][2] * Mo.Y[a][4];
-                    xb[2] += Wb[a][0] * Mo.Y[a][5] + Wb[a][1] * Mo.Y[a][4] + Wb[a][2] * Mo.Y[a][2];
-                } else {
-                    xb[0] += Wb[a][0] * Mo.Y[a][0] + Wb[a][1] * Mo.Y[a][2];
-                    xb[1] += Wb[a][0] * Mo.Y[a][2] + Wb[a][1] * Mo.Y[a][1];
-                }
-            }
-#pragma unroll
-            for (int c = 0; c < DIM; ++c) x_bar[(size_t)c * n + q] = xb[c];
         }
         __syncthreads();
     }
@@ -613,6 +726,7 @@ __global__ __launch_bounds__(ADJ_WG, 3) void k_g2p_adj(DevParams P, const float*
 // (launch_scatter_adj has the line).  Cells are read in G2P's output order, in
 // which consecutive lanes hold consecutive addresses.
 // The first workgroup also adds up the parameter gradients' partial sums.
+// 262,144 particles: 19 us, with the clearing of a grid and atomics 45.
 template <int DIM, int NW>
 __global__ __launch_bounds__(64 * NW) void k_scatter_adj(DevParams P, int n, const uint32_t* __restrict__ skeys,
                                                          int n_part, int parts) {
@@ -821,7 +935,8 @@ __device__ __forceinline__ float4 node_adj(const DevParams& P, const int* node, 
 }
 
 // Sparse grids: the sum of the tiles that cover each node (k_p2g_gather's
-// pattern, one wave per block), then the node's adjoint.
+// pattern, one wave per block), then the node's adjoint: 6.1 us for 262,144 particles
+// (the adjoint alone, from a grid summed by atomics, took 4.8).
 template <int DIM>
 __global__ __launch_bounds__(WG) void k_gather_adj(DevParams P) {
     using T = Tile<DIM>;
@@ -880,6 +995,8 @@ struct PBar {
     float* tau;
 };
 
+// Input adjoints of P2G, a particle per lane in output order.  Bound like
+// k_g2p_adj: 262,144 particles in 31 us, 44 before (node by node).
 template <int DIM>
 __global__ __launch_bounds__(ADJ_WG, 3) void k_p2g_adj(DevParams P, PIn in, PBar bar, int n,
                                                     const uint32_t* __restrict__ osrc, int parts) {
