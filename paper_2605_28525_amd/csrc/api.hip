@@ -88,6 +88,8 @@ struct mpm_ctx {
     void* sb_mem = nullptr;
     int* sb_seg = nullptr;
     SbScratch sb{};
+    // full sort by counting, where the potential domain fits a table
+    TabSort tab{};
     // ascending-key Phi order (MPM_FLAG_DETERMINISTIC_ORDER, hash builds)
     bool det_order = false;
     DetTables det{};
@@ -215,6 +217,11 @@ void free_all(mpm_ctx* c) {
     dfree(c->inst);
     dfree(c->ctr);
     dfree(c->movers);
+    dfree(c->tab.cnt);
+    dfree(c->tab.start);
+    dfree(c->tab.ent);
+    dfree(c->tab.part);
+    dfree(c->tab.n_ent);
     if (c->sb_mem) (void)hipFree(c->sb_mem);
     c->sb_mem = nullptr;
     dfree(c->sb_seg);
@@ -478,6 +485,7 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
     const int n = p->n;
     hipError_t e;
     uint32_t *ko = c->k1, *vo = c->v0;
+    bool inserted = false;  // the sort has filled the block hash
     if (reuse && n > 0) {
         uint32_t* prev = c->skeys;
         uint32_t* fresh = prev == c->k0 ? c->k1 : c->k0;
@@ -493,12 +501,21 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
         e = launch_resort(params_for(c, n), fresh, vo, c->movers, prev, n, 1u << c->H_log2, c->partials, s, keys_ready);
         if (e != hipSuccess) return MPM_ERR_HIP;
         ko = prev;
+        inserted = true;
     } else {
         if (!keys_ready) {
             e = launch_bin(c->P, p->x, p->inst, n, c->k1, s);
             if (e != hipSuccess) return MPM_ERR_HIP;
         }
-        if (n > 0) {
+        if (n > 0 && c->tab.cnt) {
+            // sorted keys over the block-grouped indices, which each wave has read
+            uint32_t* tmp = c->k0;
+            ko = c->keys_dst ? c->keys_dst : tmp;
+            vo = c->v0;
+            inserted = !c->dense && !c->scan_build;
+            e = launch_tab_sort(c->P, c->tab, c->k1, c->v1, tmp, vo, ko, n, 1u << c->H_log2, inserted, s);
+            if (e != hipSuccess) return MPM_ERR_HIP;
+        } else if (n > 0) {
             uint32_t *k0 = c->k0, *k1 = c->k1;
             if (c->keys_dst) (radix_passes(c->key_bits) & 1 ? k0 : k1) = c->keys_dst;
             e = radix_sort(c->k1, k0, k1, c->v0, c->v1, n, c->key_bits, c->hist, c->partials, &ko, &vo, s);
@@ -513,7 +530,7 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
     else if (c->scan_build)
         e = launch_build_scan(c->P, ko, n, c->sb, c->partials, s);
     else
-        e = launch_build_sparse(c->P, ko, n, 1u << c->H_log2, c->partials, s, reuse && n > 0,
+        e = launch_build_sparse(c->P, ko, n, 1u << c->H_log2, c->partials, s, inserted,
                                 c->det_order ? &c->det : nullptr);
     return hip_status(e);
 }
@@ -738,6 +755,22 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
         if (e == hipSuccess) e = hipMemcpy(c->heightmap, q->heightmap, hn * sizeof(float), hipMemcpyHostToDevice);
     }
     if (e == hipSuccess) e = hipMemset(c->ctr, 0, sizeof(DevCounters));
+    {
+        const long long ids = n_inst > 1 ? (long long)n_inst << c->blk_bits : c->n_blocks_total;
+        const bool each_step = c->dense || c->adjoint || c->scan_build || c->det_order ||
+                               (q->flags & MPM_FLAG_FULL_SORT);
+        if (e == hipSuccess && ids <= TAB_MAX_IDS && (each_step || q->max_particles <= TAB_MAX_ONCE)) {
+            TabSort& t = c->tab;
+            t.ids = (int)ids;
+            t.ent_cap = (int)std::min<long long>(ids, q->max_particles);
+            e = dalloc(&t.cnt, (size_t)ids);
+            e = e ? e : dalloc(&t.start, (size_t)ids);
+            e = e ? e : dalloc(&t.ent, (size_t)t.ent_cap);
+            e = e ? e : dalloc(&t.part, 2 * (((size_t)ids + SCAN_TILE - 1) / SCAN_TILE));
+            e = e ? e : dalloc(&t.n_ent, 1);
+            e = e ? e : launch_tab_init(t, nullptr);
+        }
+    }
     if (e == hipSuccess && c->scan_build) {
         const long long mm = c->n_blocks_total;
         e = hipMalloc(&c->sb_mem, sb_scratch_bytes(mm));

@@ -3,9 +3,10 @@
 //   k_bin           base node per particle (float64 index arithmetic), owner
 //                   block and a u32 sort key = linear block id << 2d | local
 //                   cell of the base node;
-//   sort            groups particles by owner block: the radix sort of
-//                   sort.hip, or after a build of as many particles the
-//                   incremental re-sort of resort.hip;
+//   sort            groups particles by owner block: the counting sort of
+//                   tabsort.hip (in large domains the radix sort of sort.hip),
+//                   or after a build of as many particles the incremental
+//                   re-sort of resort.hip;
 //   k_hash_clear    keys <- EMPTY, masks <- 0 (Algorithm 5, initialisation);
 //   k_hash_insert   per sorted particle: the stencil touches its owner block and
 //                   only the upper neighbours it spills into (base local index
@@ -17,8 +18,8 @@
 //                   with a compare-and-swap on EMPTY (Algorithm 6), and ORs the
 //                   node mask into the slot.  The owner run boundaries of the
 //                   sorted order are recorded per slot.
-//   (after an incremental re-sort the blocks are inserted per re-sort entry,
-//   k_rs_finish in resort.hip)
+//   (the counting sort clears and fills the hash table itself, an occupied
+//   block at a time; so does the incremental re-sort, per entry)
 //   compaction      prefix sums over the occupied slots (counted per tile of the
 //                   table by the insertion) -> Phi in slot order; block keys,
 //                   masks and owner segments in Phi order; overflow when more
@@ -81,18 +82,7 @@ __global__ __launch_bounds__(WG) void k_bin(DevParams P, const float* __restrict
 
 template <int DIM>
 __global__ __launch_bounds__(WG) void k_hash_clear(DevParams P, unsigned H) {
-    constexpr int NB = 1 << DIM;
-    const int tiles = ((int)H + SCAN_TILE - 1) / SCAN_TILE;
-    for (unsigned s = blockIdx.x * WG + threadIdx.x; s < H; s += gridDim.x * WG) {
-        P.h_keys[s] = EMPTY_KEY;
-        P.h_mask[s] = 0ull;
-        P.h_start[s] = -1;
-        P.h_end[s] = -1;
-        if (P.h_entry) P.h_entry[s] = -1;
-#pragma unroll
-        for (int d = 0; d < NB; d += 4) *(int4*)&P.h_nslot[(size_t)s * NB + d] = make_int4(-1, -1, -1, -1);
-        if (s < (unsigned)tiles) P.t_cnt[s * LINE] = P.t_cnt[s * LINE + 1] = 0u;
-    }
+    clear_hash<1 << DIM>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         P.ctr->nb = 0;
         P.ctr->n_touched = 0;

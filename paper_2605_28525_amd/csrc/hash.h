@@ -67,6 +67,22 @@ __device__ __forceinline__ uint64_t neighbour_mask(uint64_t occ, int d) {
     return o;
 }
 
+// Empties the block hash: thread t of nt (Algorithm 5, initialisation).
+template <int NB>
+__device__ __forceinline__ void clear_hash(const DevParams& P, unsigned H, unsigned t, unsigned nt) {
+    const unsigned tiles = (H + SCAN_TILE - 1) / SCAN_TILE;
+    for (unsigned s = t; s < H; s += nt) {
+        P.h_keys[s] = EMPTY_KEY;
+        P.h_mask[s] = 0ull;
+        P.h_start[s] = -1;
+        P.h_end[s] = -1;
+        if (P.h_entry) P.h_entry[s] = -1;
+#pragma unroll
+        for (int d = 0; d < NB; d += 4) *(int4*)&P.h_nslot[(size_t)s * NB + d] = make_int4(-1, -1, -1, -1);
+        if (s < tiles) P.t_cnt[s * LINE] = P.t_cnt[s * LINE + 1] = 0u;
+    }
+}
+
 // Work items of a block holding cnt particles (none for a block that only
 // holds stencil nodes).
 __device__ __forceinline__ unsigned block_chunks(const DevParams& P, int cnt) {

@@ -438,6 +438,30 @@ int radix_hist_size(int n);
 // Passes of the sort; the sorted keys end in k0 when the count is odd, else in k1.
 constexpr int radix_passes(int key_bits) { return key_bits <= 8 ? 1 : (key_bits + 7) / 8; }
 
+// Full sort by counting in a table of owner blocks (tabsort.hip).  Builds of
+// 4,096 / 262,144 / 2,097,152 / 4,194,304 particles (439,000 owner blocks in the
+// domain) that were in order, as every step after the first finds them: 29 / 32 /
+// 68 / 109 us, by radix passes 96 / 122 / 165 / 221; in random order 30 / 71 /
+// 228 / 397, by radix passes 96 / 123 / 165 / 222 (the two lines cross at 1.2
+// million).  So a context that sorts in every step takes the table, one that
+// sorts only for its first build takes it up to TAB_MAX_ONCE particles.
+// Largest domain: 32 MB of counts and positions; 4.1 million blocks add 10 us.
+constexpr int TAB_MAX_IDS = 1 << 22;
+constexpr int TAB_MAX_ONCE = 1 << 20;
+struct TabSort {
+    unsigned* cnt;    // particles per owner block (instance and linear block); zero between sorts
+    unsigned* start;  // first position of each occupied block
+    uint4* ent;       // occupied blocks in ascending order: block, first position, particles
+    unsigned* part;   // tile sums of the scan
+    int* n_ent;
+    int ids, ent_cap;
+};
+hipError_t launch_tab_init(const TabSort& T, hipStream_t s);
+// keys: unsorted; rank, tmp: scratch; order, skeys: the result (skeys may be
+// tmp).  hash: also clears the block hash and inserts every block.
+hipError_t launch_tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
+                           uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s);
+
 hipError_t launch_bin(const DevParams& P, const float* x, const uint32_t* inst, int n, uint32_t* keys, hipStream_t s);
 // The sorted keys are not written (after an incremental re-sort nothing reads
 // them; P2G takes the cell ranges from the re-sort's per-entry table).  movers

@@ -1,0 +1,319 @@
+// Full sort of the particles by (owner block, base cell), stable, by counting in
+// a table of every owner block of the potential domain.  Gives exactly the order
+// of the radix sort (sort.hip), which serves domains too large for a table
+// (TAB_MAX_IDS).
+//
+//   count    one thread per particle: lanes of a wave that share a block are
+//            merged, one add per block and wave claims their places in the
+//            block (the order of claims is arbitrary); the hash table is
+//            cleared behind it;
+//   scan     two launches over the table: first position and entry number of
+//            each occupied block, entries in ascending block order;
+//   place    one thread per particle: its index goes to its place;
+//   order    one workgroup per entry: the block's indices are counted into its
+//            cells and each cell's few indices put in ascending order, which
+//            makes the sort stable whatever the claims' order was; permutation
+//            and keys are written.  One wave meanwhile inserts the block into
+//            the hash table (hash-built grids): its occupied cells are known.
+//
+// The radix sort needs three to four passes of four launches each for these
+// keys, all bound by latency at moderate sizes; with the hash clearing, the
+// insertion (which served a wave's blocks one after another) and the item
+// count a full build took 16-21 launches before the compaction.  Here each of
+// the five is a short chain of dependent accesses: at 262,144 particles in order
+// 4.8 us for the count, 3.9 and 4.5 for the scan, 2.8 for the places, 9.4 for the
+// order with the insertion, where three radix passes took 69, the insertion 20
+// and clearing and item count 9.  (A wave per block that ordered each cell by
+// insertion and only then inserted its block took 16.)
+#include <algorithm>
+
+#include "hash.h"
+
+namespace mpmx {
+
+namespace {
+
+// Occupied blocks and particles per tile of SCAN_TILE table entries.
+__global__ __launch_bounds__(WG) void k_tab_reduce(TabSort T) {
+    __shared__ unsigned lds[WG / 64];
+    const int base = blockIdx.x * SCAN_TILE + threadIdx.x;
+    unsigned c = 0, z = 0, v[SCAN_ITEMS];
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j * WG < T.ids ? T.cnt[base + j * WG] : 0u;
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) {
+        c += v[j];
+        z += v[j] != 0u ? 1u : 0u;
+    }
+    unsigned tc, tz;
+    wg_excl_scan(c, lds, &tc);
+    wg_excl_scan(z, lds, &tz);
+    if (threadIdx.x == 0) {
+        T.part[2 * blockIdx.x] = tc;
+        T.part[2 * blockIdx.x + 1] = tz;
+    }
+}
+
+__global__ __launch_bounds__(WG) void k_tab_down(TabSort T, int tiles) {
+    __shared__ unsigned lds[WG / 64], red[WG / 64][4];
+    const int lane = __lane_id(), w = threadIdx.x >> 6;
+    const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
+    unsigned v[SCAN_ITEMS], s[4] = {0u, 0u, 0u, 0u}, c = 0u, z = 0u;
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j < T.ids ? T.cnt[base + j] : 0u;
+    // sums of the tiles before this one, and the occupied blocks of all
+    for (int i = threadIdx.x; i < tiles; i += WG) {
+        const unsigned pc = T.part[2 * i], pz = T.part[2 * i + 1];
+        s[0] += i < (int)blockIdx.x ? pc : 0u;
+        s[1] += i < (int)blockIdx.x ? pz : 0u;
+        s[2] += pz;
+    }
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], o);
+    if (lane == 0)
+#pragma unroll
+        for (int q = 0; q < 3; ++q) red[w][q] = s[q];
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) {
+        c += v[j];
+        z += v[j] != 0u ? 1u : 0u;
+    }
+    unsigned tot;
+    unsigned pos = wg_excl_scan(c, lds, &tot);
+    unsigned ent = wg_excl_scan(z, lds, &tot);  // its barriers also publish red
+    unsigned all = 0u;
+#pragma unroll
+    for (int q = 0; q < WG / 64; ++q) {
+        pos += red[q][0];
+        ent += red[q][1];
+        all += red[q][2];
+    }
+    if (blockIdx.x == 0 && threadIdx.x == 0) *T.n_ent = (int)all;
+#pragma unroll
+    for (int j = 0; j < SCAN_ITEMS; ++j) {
+        if (v[j] == 0u) continue;
+        T.start[base + j] = pos;
+        if ((int)ent < T.ent_cap) T.ent[ent] = make_uint4((unsigned)(base + j), pos, v[j], 0u);
+        pos += v[j];
+        ++ent;
+    }
+}
+
+}  // namespace
+
+template <int DIM, bool HASH>
+__global__ __launch_bounds__(WG) void k_tab_count(DevParams P, TabSort T, const uint32_t* __restrict__ keys,
+                                                  uint32_t* __restrict__ rank, int n, unsigned H) {
+    constexpr int CB = 2 * DIM, NB = 1 << DIM;
+    const int i = blockIdx.x * WG + threadIdx.x, lane = __lane_id();
+    const bool valid = i < n;
+    const uint32_t id = valid ? min(keys[i] >> CB, (uint32_t)T.ids - 1u) : ~0u;
+    // lanes of the same block: the first of them claims places for all
+    unsigned long long todo = __ballot(valid), grp = 0ull;
+    while (todo) {
+        const int leader = __ffsll((long long)todo) - 1;
+        const unsigned long long same = __ballot(valid && id == (uint32_t)readlane32((int)id, leader));
+        if ((same >> lane) & 1ull) grp = same;
+        todo &= ~same;
+    }
+    const int leader = grp ? __ffsll((long long)grp) - 1 : lane;
+    unsigned first = 0u;
+    if (valid && lane == leader) first = atomicAdd(&T.cnt[id], (unsigned)__popcll(grp));
+    first = (unsigned)__shfl((int)first, leader);
+    if (valid) rank[i] = first + (unsigned)__popcll(grp & ((1ull << lane) - 1ull));
+    if (HASH) clear_hash<NB>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
+}
+
+template <int CB>
+__global__ __launch_bounds__(WG) void k_tab_place(TabSort T, const uint32_t* __restrict__ keys,
+                                                  const uint32_t* __restrict__ rank, uint32_t* __restrict__ tmp, int n) {
+    const int i = blockIdx.x * WG + threadIdx.x;
+    if (i >= n) return;
+    const unsigned pos = T.start[min(keys[i] >> CB, (uint32_t)T.ids - 1u)] + rank[i];
+    if (pos < (unsigned)n) tmp[pos] = (uint32_t)i;
+}
+
+namespace {
+
+constexpr int TAB_STAGE = 1024;  // particles of a block that a workgroup orders in LDS
+
+// A block too full for LDS: LSD radix passes by the wave over its c indices
+// (8-bit digits of the index, then the cell), a -> b -> a ..., ending in b.
+// cnt64: particles per cell on return (lane = cell).
+template <int CB>
+__device__ void wave_radix(uint32_t* a, uint32_t* b, int c, int idx_bits, const uint32_t* __restrict__ keys,
+                           unsigned* hist, int lane, unsigned* cnt64) {
+    constexpr int NC = 1 << CB;
+    const unsigned long long lt = (1ull << lane) - 1ull;
+    const int passes = (idx_bits + 7) / 8 + 1;
+    auto ld = [](uint32_t* p) { return __hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT); };
+    uint32_t* const out = b;
+    for (int p = 0; p < passes; ++p) {
+        const bool cells = p == passes - 1;
+        auto digit = [&](uint32_t v) { return cells ? keys[v] & (NC - 1) : (v >> (8 * p)) & 255u; };
+        for (int q = lane; q < 256; q += 64) hist[q] = 0u;
+        for (int i = lane; i < c; i += 64) atomicAdd(&hist[digit(ld(a + i))], 1u);
+        if (cells) *cnt64 = lane < NC ? hist[lane] : 0u;
+        unsigned h[4], s = 0u;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            h[q] = hist[4 * lane + q];
+            s += h[q];
+        }
+        unsigned e = wave_incl_scan(s) - s;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+            hist[4 * lane + q] = e;
+            e += h[q];
+        }
+        for (int i0 = 0; i0 < c; i0 += 64) {
+            const bool valid = i0 + lane < c;
+            const uint32_t v = valid ? ld(a + i0 + lane) : 0u;
+            const unsigned d = valid ? digit(v) : 0u;
+            unsigned long long m = __ballot(valid);
+#pragma unroll
+            for (int q = 0; q < 8; ++q) {
+                const bool bit = (d >> q) & 1u;
+                const unsigned long long bb = __ballot(bit);
+                m &= bit ? bb : ~bb;
+            }
+            const unsigned at = hist[d];
+            if (valid) {
+                b[at + (unsigned)__popcll(m & lt)] = v;
+                if ((m & lt) == 0ull) hist[d] = at + (unsigned)__popcll(m);
+            }
+        }
+        __threadfence();
+        uint32_t* t = a;
+        a = b;
+        b = t;
+    }
+    if (a != out) {  // an even number of passes ended in the source
+        for (int i = lane; i < c; i += 64) out[i] = ld(a + i);
+        __threadfence();
+    }
+}
+
+}  // namespace
+
+// tmp and skeys may be one buffer: a block's range is read before it is written.
+// One workgroup per occupied block.  Its particles are listed cell by cell in
+// LDS, then each counts the smaller indices of its cell: no step depends on the
+// one before it, where ordering a cell by insertion is a chain of LDS accesses.
+template <int DIM, bool HASH>
+__global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const uint32_t* __restrict__ keys,
+                                                  uint32_t* tmp, uint32_t* order, uint32_t* skeys, int n, int idx_bits) {
+    constexpr int CB = 2 * DIM, NC = 1 << CB, NB = 1 << DIM, R = TAB_STAGE / WG;
+    __shared__ uint32_t sidx[TAB_STAGE];
+    __shared__ unsigned char scell[TAB_STAGE];
+    __shared__ unsigned cnt[NC], first[NC], hist[256];
+    const int lane = __lane_id(), t = threadIdx.x;
+    const int ne = min(*T.n_ent, T.ent_cap);
+    for (int e = blockIdx.x; e < ne; e += gridDim.x) {
+        const uint4 en = T.ent[e];
+        const uint32_t id = en.x;
+        const int st = (int)en.y, c = min((int)en.z, n - st);
+        const bool staged = c <= TAB_STAGE;
+        if (t < NC) cnt[t] = 0u;
+        __syncthreads();
+        if (staged) {
+            uint32_t ix[R];
+            unsigned cl[R], at[R];
+#pragma unroll
+            for (int r = 0; r < R; ++r) ix[r] = r * WG + t < c ? tmp[st + r * WG + t] : 0u;
+#pragma unroll
+            for (int r = 0; r < R; ++r) cl[r] = r * WG + t < c ? keys[ix[r]] & (NC - 1) : 0u;
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r * WG + t < c) at[r] = atomicAdd(&cnt[cl[r]], 1u);
+            __syncthreads();
+            if (t < 64) {
+                const unsigned m = t < NC ? cnt[t] : 0u, f = wave_incl_scan(m) - m;
+                if (t < NC) first[t] = f;
+            }
+            __syncthreads();
+#pragma unroll
+            for (int r = 0; r < R; ++r)
+                if (r * WG + t < c) {
+                    const unsigned p = first[cl[r]] + at[r];
+                    sidx[p] = ix[r];
+                    scell[p] = (unsigned char)cl[r];
+                }
+        } else if (t < 64) {
+            unsigned m = 0u;
+            wave_radix<CB>(tmp + st, order + st, c, idx_bits, keys, hist, lane, &m);
+            if (t < NC) cnt[t] = m;
+        }
+        __syncthreads();
+        if (t == 0) T.cnt[id] = 0u;  // the table is left empty
+        if (HASH && t >= WG - 64) {
+            const uint64_t occ = (uint64_t)__ballot(lane < NC && cnt[lane & (NC - 1)] != 0u);
+            const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
+            const int own = readlane32(slot, 0);
+            if (own >= 0 && lane < NB) P.h_nslot[(size_t)own * NB + lane] = slot;
+            if (own >= 0 && lane == 0) {
+                P.h_start[own] = st;
+                P.h_end[own] = st + c;
+                atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
+            }
+        }
+        if (staged) {
+            for (int j = t; j < c; j += WG) {
+                const uint32_t v = sidx[j];
+                const unsigned cl = scell[j], f = first[cl], m = cnt[cl];
+                unsigned at = f;
+                for (unsigned q = 0; q < m; ++q) at += sidx[f + q] < v ? 1u : 0u;
+                order[st + at] = v;
+                skeys[st + at] = (id << CB) | cl;
+            }
+        } else {
+            for (int j = t; j < c; j += WG)
+                skeys[st + j] = (id << CB) |
+                                (keys[__hip_atomic_load(order + st + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)] &
+                                 (NC - 1));
+        }
+        __syncthreads();
+    }
+}
+
+__global__ __launch_bounds__(WG) void k_tab_init(TabSort T) {
+    for (int t = blockIdx.x * WG + threadIdx.x; t < T.ids; t += gridDim.x * WG) T.cnt[t] = 0u;
+}
+
+hipError_t launch_tab_init(const TabSort& T, hipStream_t s) {
+    k_tab_init<<<std::max(1, std::min((T.ids + WG - 1) / WG, 2048)), WG, 0, s>>>(T);
+    return hipGetLastError();
+}
+
+namespace {
+template <int DIM>
+hipError_t tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
+                    uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s) {
+    const int g = (n + WG - 1) / WG, tiles = (T.ids + SCAN_TILE - 1) / SCAN_TILE;
+    const int go = std::max(1, std::min(T.ent_cap, 2048));  // what the chip holds
+    int bits = 1;
+    while (bits < 30 && (1 << bits) < n) ++bits;
+    if (hash)  // at least 64 workgroups for the clearing
+        k_tab_count<DIM, true><<<std::max(g, 64), WG, 0, s>>>(P, T, keys, rank, n, H);
+    else
+        k_tab_count<DIM, false><<<g, WG, 0, s>>>(P, T, keys, rank, n, 0u);
+    k_tab_reduce<<<tiles, WG, 0, s>>>(T);
+    k_tab_down<<<tiles, WG, 0, s>>>(T, tiles);
+    k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
+    if (hash)
+        k_tab_order<DIM, true><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+    else
+        k_tab_order<DIM, false><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+    return hipGetLastError();
+}
+}  // namespace
+
+hipError_t launch_tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
+                           uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s) {
+    return P.dim == 3 ? tab_sort<3>(P, T, keys, rank, tmp, order, skeys, n, H, hash, s)
+                      : tab_sort<2>(P, T, keys, rank, tmp, order, skeys, n, H, hash, s);
+}
+
+}  // namespace mpmx
