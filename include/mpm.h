@@ -352,8 +352,12 @@ int mpm_step_adj(mpm_ctx* ctx, const mpm_particles* in, const mpm_particles* out
  *   (in that set's order), on return dL/d(states[0]) (in states[0]'s order);
  *   `spare` is scratch of the same layout; param_bar accumulates as for
  *   mpm_step_adj.  Status flags raised in the slots are merged into the
- *   context's own (mpm_get_status). */
+ *   context's own (mpm_get_status).
+ * mpm_tape_serial: a number that changes whenever the slots' contents do
+ *   (mpm_tape_reserve, mpm_tape_forward), so that a caller who keeps a
+ *   recorded segment for later can tell whether it is still there. */
 int mpm_tape_reserve(mpm_ctx* ctx, int n_slots);
+int mpm_tape_serial(mpm_ctx* ctx, long long* serial);
 int mpm_tape_forward(mpm_ctx* ctx, const mpm_particles* states, int n_steps, void* stream);
 int mpm_tape_adjoint(mpm_ctx* ctx, const mpm_particles* states, int n_steps, const mpm_particles* bar,
                      const mpm_particles* spare, float* param_bar, void* stream);

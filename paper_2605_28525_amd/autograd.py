@@ -6,6 +6,9 @@ every `checkpoint` steps.  Backward: for each checkpoint segment, last first,
 the segment is recomputed from its checkpoint on the library's tape (every
 step's input state, and its build and grids in one tape slot per step), then
 the hand-written adjoint transfers run step by step in reverse over the tape.
+Where gradients will be asked for, the forward pass runs the last segment on
+the tape already, and its backward finds it there unless another pass has used
+the tape in between.
 Gradients: dL/dE, dL/dphi (per degree) and dL/dv0 (in the initial particle
 order).
 
@@ -42,6 +45,7 @@ class Rollout:
         self.param_bar = torch.zeros(2, dtype=torch.float32, device=device)
         self._arange = torch.arange(self.n, dtype=torch.long, device=device)
         self.checkpoints = []
+        self.recorded = None   # the tape's serial after the last forward pass that recorded
 
     def close(self):
         if self.ctx:
@@ -51,29 +55,48 @@ class Rollout:
     def set_material(self, E: float, phi: float):
         M.mpm_set_material(self.ctx, float(E), self.nu, float(phi), self.dt)
 
-    def run_forward(self, v0: torch.Tensor, E: float, phi: float, keep_checkpoints=True):
-        """Returns the final ParticleSet (positions in a permuted order, ids carried)."""
+    def _segment(self, k: int, first):
+        """Sets of a segment of k steps that starts from `first`."""
+        while len(self._pool) < self.K + 1:
+            self._pool.append(M.ParticleSet(self.dim, self.n, self.device, zero=False))
+        return [first] + self._pool[1:k + 1]
+
+    def run_forward(self, v0: torch.Tensor, E: float, phi: float, keep_checkpoints=True, record=False):
+        """Returns the final ParticleSet (positions in a permuted order, ids carried).
+        With `record` (and checkpoints) the last segment runs on the tape, and
+        `recorded` names that recording for `backward`."""
         self.set_material(E, phi)
         a, b = self._bufs
         a.copy_(self.init)
         a.v.copy_(v0)
         a.id.copy_(torch.arange(self.n, dtype=torch.int32, device=self.device))
         self.checkpoints = []
+        self.recorded = None
         for s0 in range(0, self.steps, self.K):
-            if keep_checkpoints:
-                self.checkpoints.append(M.ParticleSet(self.dim, self.n, self.device).copy_(a))
             k = min(self.K, self.steps - s0)
+            if record and keep_checkpoints and s0 + k == self.steps:
+                # the state itself is the checkpoint: no step overwrites it
+                self.checkpoints.append(a)
+                self._bufs = [M.ParticleSet(self.dim, self.n, self.device, zero=False), b]
+                states = self._segment(k, a)
+                M.mpm_tape_forward(self.ctx, [st.view() for st in states])
+                self.recorded = M.mpm_tape_serial(self.ctx)
+                return states[-1]
+            if keep_checkpoints:
+                self.checkpoints.append(M.ParticleSet(self.dim, self.n, self.device, zero=False).copy_(a))
             M.mpm_step(self.ctx, a.view(), b.view(), k)
             if k % 2 == 1:
                 a, b = b, a
         self._bufs = [a, b]
         return a
 
-    def backward(self, checkpoints, final_ids: torch.Tensor, x_bar: torch.Tensor, E: float, phi: float):
+    def backward(self, checkpoints, final_ids: torch.Tensor, x_bar: torch.Tensor, E: float, phi: float, recorded=None):
         """x_bar: dL/dx of the final state of the forward pass that kept
         `checkpoints` (same order as `final_ids`).  The material of that pass is
         set again, so other forward passes on this Rollout in between do not
-        change the result.  Returns (dL/dE, dL/dphi, dL/dv0)."""
+        change the result.  `recorded`: that pass's recording of the last
+        segment, used if it is still on the tape.  Returns (dL/dE, dL/dphi,
+        dL/dv0)."""
         if len(checkpoints) != (self.steps + self.K - 1) // self.K:
             raise ValueError("checkpoint list does not cover the rollout")
         self.set_material(E, phi)
@@ -83,23 +106,22 @@ class Rollout:
         for key in ("v", "C", "F", "tau"):
             getattr(bar, key).zero_()
         bar.x.copy_(x_bar)
-        while len(self._pool) < self.K + 1:
-            self._pool.append(M.ParticleSet(self.dim, self.n, self.device, zero=False))
         nseg = len(checkpoints)
         for si in range(nseg - 1, -1, -1):
             s0 = si * self.K
             k = min(self.K, self.steps - s0)
-            states = self._pool[:k + 1]
-            states[0].copy_(checkpoints[si])
+            states = self._segment(k, checkpoints[si])
             views = [st.view() for st in states]
-            M.mpm_tape_forward(self.ctx, views)
-            # align the incoming adjoint with the recomputed end state by id
-            # (always applied, so that no host sync decides whether to)
-            inv = torch.empty_like(bar_ids, dtype=torch.long)
-            inv[bar_ids.long()] = self._arange
-            perm = inv[states[-1].id.long()]
-            for key in ("x", "v", "C", "F", "tau"):
-                getattr(bar, key).copy_(getattr(bar, key)[:, perm])
+            if si < nseg - 1 or recorded is None or recorded != M.mpm_tape_serial(self.ctx):
+                M.mpm_tape_forward(self.ctx, views)
+                # align the incoming adjoint with the recomputed end state by id
+                # (always applied, so that no host sync decides whether to)
+                inv = torch.empty_like(bar_ids, dtype=torch.long)
+                inv[bar_ids.long()] = self._arange
+                perm = inv[states[-1].id.long()]
+                for key in ("x", "v", "C", "F", "tau"):
+                    torch.index_select(getattr(bar, key), 1, perm, out=getattr(spare, key))
+                bar, spare = spare, bar
             # every field of the input adjoint is overwritten; the result is in bar
             M.mpm_tape_adjoint(self.ctx, views, bar.view(), spare.view(), self.param_bar)
             bar_ids = states[0].id.clone()
@@ -114,9 +136,10 @@ class Rollout:
 
 class _RolloutFn(torch.autograd.Function):
     @staticmethod
-    def forward(ctx, E, phi, v0, roll: Rollout):
-        final = roll.run_forward(v0.detach(), float(E), float(phi))
+    def forward(ctx, E, phi, v0, roll: Rollout, record=False):
+        final = roll.run_forward(v0.detach(), float(E), float(phi), record=record)
         ctx.roll = roll
+        ctx.recorded = roll.recorded
         # run_forward allocates a fresh checkpoint list every call and the final
         # state lives in buffers the next forward pass overwrites: keep the list,
         # the ids and the material of this pass, not the buffers
@@ -134,13 +157,14 @@ class _RolloutFn(torch.autograd.Function):
         roll = ctx.roll
         # grad_x is in caller order; bring it to the final state's order
         x_bar = grad_x[:, ctx.ids.long()].contiguous()
-        gE, gphi, gv0 = roll.backward(ctx.checkpoints, ctx.ids, x_bar, *ctx.material)
+        gE, gphi, gv0 = roll.backward(ctx.checkpoints, ctx.ids, x_bar, *ctx.material, ctx.recorded)
         dev = grad_x.device
         return (torch.tensor(gE, dtype=torch.float64, device=dev), torch.tensor(gphi, dtype=torch.float64, device=dev),
-                gv0, None)
+                gv0, None, None)
 
 
 def rollout(E: torch.Tensor, phi: torch.Tensor, v0: torch.Tensor, roll: Rollout) -> torch.Tensor:
     """Final positions (d, n) in the caller's particle order, differentiable with
     respect to E, phi (degrees) and v0 (d, n)."""
-    return _RolloutFn.apply(E, phi, v0, roll)
+    record = torch.is_grad_enabled() and any(torch.is_tensor(t) and t.requires_grad for t in (E, phi, v0))
+    return _RolloutFn.apply(E, phi, v0, roll, record)

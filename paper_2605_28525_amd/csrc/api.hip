@@ -105,6 +105,7 @@ struct mpm_ctx {
         uint32_t *osrc = nullptr, *skeys = nullptr;
     };
     std::vector<TapeSlot> tape;
+    long long tape_serial = 0;  // changes with the slots' contents, or with what reads them (the chunk size)
     DevCounters* tape_ctr = nullptr;  // one per slot
 };
 
@@ -185,6 +186,7 @@ void free_capacity_buffers(mpm_ctx* c) {
 }
 
 void free_tape(mpm_ctx* c) {
+    ++c->tape_serial;
     for (auto& t : c->tape) {
         dfree(t.b_keys);
         dfree(t.b_nbr);
@@ -997,9 +999,16 @@ int mpm_tape_reserve(mpm_ctx* c, int n_slots) {
     return MPM_OK;
 }
 
+int mpm_tape_serial(mpm_ctx* c, long long* serial) {
+    if (!c || !serial) return MPM_ERR_ARG;
+    *serial = c->tape_serial;
+    return MPM_OK;
+}
+
 int mpm_tape_forward(mpm_ctx* c, const mpm_particles* states, int n_steps, void* stream) {
     int st = tape_args_ok(c, states, n_steps);
     if (st != MPM_OK) return st;
+    ++c->tape_serial;
     hipStream_t s = (hipStream_t)stream;
     const DevParams saved = c->P;
     for (int j = 0; j < n_steps && st == MPM_OK; ++j) {
@@ -1207,6 +1216,7 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
     if (new_chunk > g2p_max_items(new_block)) return MPM_ERR_ARG;
     if (new_chunk != c->chunk) {
         c->chunk = c->P.chunk = new_chunk;
+        ++c->tape_serial;
         c->built = false;  // work items of the last build used the old size
     }
     c->g2p_block = new_block;
@@ -1218,6 +1228,7 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
 int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int* chosen, void* stream) {
     if (!c || !particles_ok(c, a, true) || !b || b->n != a->n) return MPM_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
+    ++c->tape_serial;
     // (G2P workgroup size, particles per work item) pairs, persistent workgroup counts
     static const int shapes[][2] = {{64, 64},   {64, 128},  {128, 128}, {128, 256},
                                     {256, 256}, {256, 512}, {256, 768}};

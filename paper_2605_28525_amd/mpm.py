@@ -110,6 +110,7 @@ _SIGS = {
     "mpm_step_adj": (c_int, [_PCTX, POINTER(mpm_particles), POINTER(mpm_particles), POINTER(mpm_particles),
                              c_void_p, c_void_p]),
     "mpm_tape_reserve": (c_int, [_PCTX, c_int]),
+    "mpm_tape_serial": (c_int, [_PCTX, POINTER(ctypes.c_longlong)]),
     "mpm_tape_forward": (c_int, [_PCTX, POINTER(mpm_particles), c_int, c_void_p]),
     "mpm_tape_adjoint": (c_int, [_PCTX, POINTER(mpm_particles), c_int, POINTER(mpm_particles),
                                  POINTER(mpm_particles), c_void_p, c_void_p]),
@@ -270,6 +271,13 @@ def _particle_array(states):
     for i, st in enumerate(states):
         arr[i] = st
     return arr
+
+
+def mpm_tape_serial(ctx) -> int:
+    """Changes whenever the contents of the tape's slots do."""
+    out = ctypes.c_longlong(0)
+    _check(lib.mpm_tape_serial(ctx, ctypes.byref(out)), "mpm_tape_serial")
+    return out.value
 
 
 def mpm_tape_forward(ctx, states, stream=None):
