@@ -897,16 +897,15 @@ int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_s
     for (int k = 0; k < n_steps; ++k) {
         int st = sparse_build(c, cur, s, keys_ready);
         // on a sparse grid the grid update runs inside P2G's second pass (the
-        // grid between the two is not visible to the caller here; reverse-mode
-        // contexts keep the separate calls their tape repeats); with zero
-        // particles the grid update still runs on its own
-        const bool fuse_update = !c->dense && !c->adjoint && cur->n > 0;
+        // grid between the two is not visible to the caller here; the reverse
+        // mode's copy of it is written either way); with zero particles the
+        // grid update still runs on its own
+        const bool fuse_update = !c->dense && cur->n > 0;
         if (st == MPM_OK) st = p2g_impl(c, cur, s, fuse_update);
         if (st == MPM_OK && !fuse_update) st = mpm_grid_update(c, stream);
         // Between two steps of this call nothing else touches the positions,
-        // so G2P bins them as it writes them.  Not in reverse-mode contexts,
-        // whose tape records each build as mpm_sparse_build makes it.
-        keys_ready = k + 1 < n_steps && !c->adjoint && cur->n > 0;
+        // so G2P bins them as it writes them.
+        keys_ready = k + 1 < n_steps && cur->n > 0;
         const bool next_reuse = would_reuse(c, nxt->n);
         uint32_t* keys_out = keys_ready ? next_bin_buffer(c, next_reuse) : nullptr;
         // with an incremental re-sort next, G2P also does its counting
@@ -958,8 +957,9 @@ int mpm_step_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ob, c
     if (!c) return MPM_ERR_ARG;
     if (!c->adjoint) return MPM_ERR_STATE;
     int st = mpm_sparse_build(c, in, stream);
-    if (st == MPM_OK) st = mpm_p2g(c, in, stream);
-    if (st == MPM_OK) st = mpm_grid_update(c, stream);
+    const bool fuse_update = st == MPM_OK && !c->dense && in->n > 0;
+    if (st == MPM_OK) st = p2g_impl(c, in, (hipStream_t)stream, fuse_update);
+    if (st == MPM_OK && !fuse_update) st = mpm_grid_update(c, stream);
     if (st == MPM_OK) st = mpm_g2p_adj(c, in, ob, ib, param_bar, stream);
     if (st == MPM_OK) st = mpm_grid_update_adj(c, stream);
     if (st == MPM_OK) st = mpm_p2g_adj(c, in, ib, stream);
@@ -1011,15 +1011,18 @@ int mpm_tape_forward(mpm_ctx* c, const mpm_particles* states, int n_steps, void*
     ++c->tape_serial;
     hipStream_t s = (hipStream_t)stream;
     const DevParams saved = c->P;
+    const bool any = states[0].n > 0;
     for (int j = 0; j < n_steps && st == MPM_OK; ++j) {
         bind_slot(c, j);
-        // the sort and P2G write the slot's arrays
+        // the sort and P2G write the slot's arrays; the grid update and the
+        // next step's binning run where mpm_step runs them
         c->keys_dst = c->tape[(size_t)j].skeys;
-        st = mpm_sparse_build(c, &states[j], stream);
+        st = sparse_build(c, &states[j], s, any && j > 0);
         c->osrc = c->tape[(size_t)j].osrc;
-        if (st == MPM_OK) st = mpm_p2g(c, &states[j], stream);
-        if (st == MPM_OK) st = mpm_grid_update(c, stream);
-        if (st == MPM_OK) st = mpm_g2p(c, &states[j], &states[j + 1], stream);
+        if (st == MPM_OK) st = p2g_impl(c, &states[j], s, any);
+        if (st == MPM_OK && !any) st = mpm_grid_update(c, stream);
+        uint32_t* keys_out = any && j + 1 < n_steps ? next_bin_buffer(c, false) : nullptr;
+        if (st == MPM_OK) st = g2p_impl(c, &states[j], &states[j + 1], s, keys_out, nullptr);
     }
     // the context's own tables were not written: no build is current
     c->P = saved;
@@ -1258,7 +1261,7 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
                     // G2P as inside mpm_step: it also bins and counts for the
                     // next build (which the next trial's build ignores)
                     const bool next_reuse = would_reuse(c, b->n);
-                    uint32_t* keys_out = !c->adjoint && a->n > 0 ? next_bin_buffer(c, next_reuse) : nullptr;
+                    uint32_t* keys_out = a->n > 0 ? next_bin_buffer(c, next_reuse) : nullptr;
                     uint32_t* movers_out = keys_out && next_reuse ? c->movers : nullptr;
                     st = g2p_impl(c, a, b, s, keys_out, movers_out);
                 }
