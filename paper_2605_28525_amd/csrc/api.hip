@@ -76,6 +76,7 @@ struct mpm_ctx {
     uint32_t* nh_owner = nullptr;
     uint32_t* rs_new = nullptr;
     int* h_entry = nullptr;
+    int row_cap = 0;
     int* b_entry = nullptr;
     uint32_t* order = nullptr;
     uint32_t* skeys = nullptr;
@@ -342,6 +343,7 @@ void fill_params(mpm_ctx* c) {
     P.nh_idx = c->nh_idx;
     P.nh_owner = c->nh_owner;
     P.rs_new = c->rs_new;
+    P.row_cap = c->row_cap;
     P.h_entry = c->h_entry;
     P.b_entry = c->b_entry;
     fill_material(c);
@@ -410,19 +412,24 @@ int alloc_capacity_buffers(mpm_ctx* c) {
     if (resort) {
         e = e ? e : dalloc(&c->rs_stay, cap * NPB);
         e = e ? e : dalloc(&c->rs_in, 2 * cap * NPB);
-        e = e ? e : dalloc(&c->rs_off, 2 * cap * NPB);
         e = e ? e : dalloc(&c->rs_oldblk, 2 * cap);
         e = e ? e : dalloc(&c->rs_cnt, 2 * cap);
         e = e ? e : dalloc(&c->rs_start, 2 * cap);
         e = e ? e : dalloc(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
         e = e ? e : dalloc(&c->it_mov, (size_t)c->work_cap);
         e = e ? e : dalloc(&c->rs_occ, 2 * cap);
-        e = e ? e : dalloc(&c->rs_nslot, 2 * cap * NB);
         e = e ? e : dalloc(&c->nh_keys, H);
         e = e ? e : dalloc(&c->nh_cnt, H * NPB);
         e = e ? e : dalloc(&c->nh_idx, H);
         e = e ? e : dalloc(&c->nh_owner, H);
         e = e ? e : dalloc(&c->rs_new, cap);
+    }
+    // rows of cell ranges and neighbour slots, one per entry of a sort that
+    // inserts its blocks itself
+    c->row_cap = resort ? 2 * c->block_cap : hashed && !c->det_order && c->tab.cnt ? c->block_cap : 0;
+    if (c->row_cap > 0) {
+        e = e ? e : dalloc(&c->rs_off, (size_t)c->row_cap * NPB);
+        e = e ? e : dalloc(&c->rs_nslot, (size_t)c->row_cap * NB);
         e = e ? e : dalloc(&c->h_entry, H);
         e = e ? e : dalloc(&c->b_entry, cap);
     }

@@ -82,7 +82,7 @@ __global__ __launch_bounds__(WG) void k_bin(DevParams P, const float* __restrict
 
 template <int DIM>
 __global__ __launch_bounds__(WG) void k_hash_clear(DevParams P, unsigned H) {
-    clear_hash<1 << DIM>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
+    clear_hash<1 << DIM, true>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
     if (blockIdx.x == 0 && threadIdx.x == 0) {
         P.ctr->nb = 0;
         P.ctr->n_touched = 0;

@@ -67,8 +67,9 @@ __device__ __forceinline__ uint64_t neighbour_mask(uint64_t occ, int d) {
     return o;
 }
 
-// Empties the block hash: thread t of nt (Algorithm 5, initialisation).
-template <int NB>
+// Empties the block hash: thread t of nt (Algorithm 5, initialisation).  LINKS:
+// also the neighbours' slots, for insertions that store only the reached ones.
+template <int NB, bool LINKS>
 __device__ __forceinline__ void clear_hash(const DevParams& P, unsigned H, unsigned t, unsigned nt) {
     const unsigned tiles = (H + SCAN_TILE - 1) / SCAN_TILE;
     for (unsigned s = t; s < H; s += nt) {
@@ -77,8 +78,9 @@ __device__ __forceinline__ void clear_hash(const DevParams& P, unsigned H, unsig
         P.h_start[s] = -1;
         P.h_end[s] = -1;
         if (P.h_entry) P.h_entry[s] = -1;
+        if (LINKS)
 #pragma unroll
-        for (int d = 0; d < NB; d += 4) *(int4*)&P.h_nslot[(size_t)s * NB + d] = make_int4(-1, -1, -1, -1);
+            for (int d = 0; d < NB; d += 4) *(int4*)&P.h_nslot[(size_t)s * NB + d] = make_int4(-1, -1, -1, -1);
         if (s < tiles) P.t_cnt[s * LINE] = P.t_cnt[s * LINE + 1] = 0u;
     }
 }

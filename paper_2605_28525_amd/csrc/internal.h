@@ -149,9 +149,10 @@ struct DevParams {
     unsigned* rs_tile;    // particles per RS_TILE previous blocks (sums of rs_cnt), LINE words apart; null
                           // above FOLD_MAX_N particles
     unsigned* it_mov;     // movers of each work item, listed from the item's first position on
-    int* h_entry;         // re-sort entry of each hash slot's owner block (-1: none)
-    int* b_entry;         // re-sort entry of each compact block (-1: none): its cell
+    int* h_entry;         // the sort's entry of each hash slot's owner block (-1: none)
+    int* b_entry;         // the sort's entry of each compact block (-1: none): its cell
                           // ranges are the entry's row of rs_off
+    int row_cap;          // rows of rs_off and rs_nslot (0: none)
     // ensembles
     int n_inst;          // 1 = single simulation
     int blk_bits;        // bits of the linear block id inside the sort key

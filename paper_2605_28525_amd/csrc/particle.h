@@ -190,59 +190,21 @@ __device__ __forceinline__ unsigned long long lanes_matching(unsigned v, bool va
 // the segment are sorted by base cell, so a cell's range starts after the
 // particles of all lower cells: the cells are counted (keys loaded in batches,
 // one wave-wide match per 64 keys, one LDS add per distinct cell) and the
-// ranges follow from an exclusive scan of the counts.  Optionally the first
-// `stage_max` entries of another per-particle array (`stage_src[st ..]`) are
-// copied to LDS (`stage_dst`) by the same batched loads.  With `cell_first`
-// (the first sorted position of each base cell, which an incremental re-sort
-// leaves per block) the counts are taken from it and no key is read.
+// ranges follow from an exclusive scan of the counts.
 template <int DIM>
-__device__ void interleave_setup(Interleave<DIM>& L, const uint32_t* __restrict__ skeys, int st, int en,
-                                 const uint32_t* __restrict__ stage_src = nullptr, uint32_t* stage_dst = nullptr,
-                                 int stage_max = 0, const uint32_t* __restrict__ cell_first = nullptr) {
+__device__ void interleave_setup(Interleave<DIM>& L, const uint32_t* __restrict__ skeys, int st, int en) {
     constexpr int NC = Interleave<DIM>::NC;
-    const int stage_end = stage_dst ? min(en, st + stage_max) : st;
     const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n_waves = blockDim.x >> 6;
     const unsigned long long lt = (1ull << lane) - 1ull;
-    if (cell_first) {
-        // the cell table and the first batch of the staged array are loaded
-        // together, then further batches (IL_BATCH loads in flight per lane)
-        int first = 0, next = 0;
-        if (threadIdx.x < NC) {
-            first = (int)cell_first[threadIdx.x];
-            next = threadIdx.x + 1 < NC ? (int)cell_first[threadIdx.x + 1] : en;
-        }
-        for (int i0 = st + wave * 64 * IL_BATCH; i0 < stage_end; i0 += n_waves * 64 * IL_BATCH) {
-            uint32_t v[IL_BATCH];
-#pragma unroll
-            for (int r = 0; r < IL_BATCH; ++r) {
-                const int i = i0 + r * 64 + lane;
-                v[r] = i < stage_end ? stage_src[i] : 0u;
-            }
-#pragma unroll
-            for (int r = 0; r < IL_BATCH; ++r) {
-                const int i = i0 + r * 64 + lane;
-                if (i < stage_end) stage_dst[i - st] = v[r];
-            }
-        }
-        if (threadIdx.x < NC) L.ce[threadIdx.x] = next - first;
-        if (threadIdx.x == 0) L.st = st;
-    } else {
-        for (int c = threadIdx.x; c < NC; c += blockDim.x) L.ce[c] = 0;  // per-cell counts first
-        if (threadIdx.x == 0) L.st = st;
-    }
+    for (int c = threadIdx.x; c < NC; c += blockDim.x) L.ce[c] = 0;  // per-cell counts first
+    if (threadIdx.x == 0) L.st = st;
     __syncthreads();
-    for (int i0 = st + wave * 64 * IL_BATCH; !cell_first && i0 < en; i0 += n_waves * 64 * IL_BATCH) {
-        uint32_t k[IL_BATCH], v[IL_BATCH];
+    for (int i0 = st + wave * 64 * IL_BATCH; i0 < en; i0 += n_waves * 64 * IL_BATCH) {
+        uint32_t k[IL_BATCH];
 #pragma unroll
         for (int r = 0; r < IL_BATCH; ++r) {
             const int i = i0 + r * 64 + lane;
             k[r] = i < en ? skeys[i] : 0u;
-            v[r] = i < stage_end ? stage_src[i] : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < IL_BATCH; ++r) {
-            const int i = i0 + r * 64 + lane;
-            if (i < stage_end) stage_dst[i - st] = v[r];
         }
 #pragma unroll
         for (int r = 0; r < IL_BATCH; ++r) {

@@ -123,7 +123,7 @@ __global__ __launch_bounds__(WG) void k_tab_count(DevParams P, TabSort T, const 
     if (valid && lane == leader) first = atomicAdd(&T.cnt[id], (unsigned)__popcll(grp));
     first = (unsigned)__shfl((int)first, leader);
     if (valid) rank[i] = first + (unsigned)__popcll(grp & ((1ull << lane) - 1ull));
-    if (HASH) clear_hash<NB>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
+    if (HASH) clear_hash<NB, false>(P, H, blockIdx.x * WG + threadIdx.x, gridDim.x * WG);
 }
 
 template <int CB>
@@ -247,15 +247,27 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
             if (t < NC) cnt[t] = m;
         }
         __syncthreads();
+        if (!staged && t < 64) {
+            const unsigned m = t < NC ? cnt[t] : 0u, f = wave_incl_scan(m) - m;
+            if (t < NC) first[t] = f;
+        }
+        if (HASH && e < P.row_cap && t < NC) P.rs_off[(size_t)e * NC + t] = (unsigned)st + first[t];
         if (t == 0) T.cnt[id] = 0u;  // the table is left empty
         if (HASH && t >= WG - 64) {
             const uint64_t occ = (uint64_t)__ballot(lane < NC && cnt[lane & (NC - 1)] != 0u);
             const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
             const int own = readlane32(slot, 0);
-            if (own >= 0 && lane < NB) P.h_nslot[(size_t)own * NB + lane] = slot;
+            const bool row = e < P.row_cap;  // with the cell ranges below, for P2G
+            if (own >= 0 && lane < NB) {
+                if (row)
+                    P.rs_nslot[(size_t)e * NB + lane] = slot;
+                else
+                    P.h_nslot[(size_t)own * NB + lane] = slot;
+            }
             if (own >= 0 && lane == 0) {
                 P.h_start[own] = st;
                 P.h_end[own] = st + c;
+                if (row) P.h_entry[own] = e;
                 atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
             }
         }

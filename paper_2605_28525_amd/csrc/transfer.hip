@@ -83,7 +83,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
     constexpr int NC = T::NPB;  // base cells per block
     constexpr int NK = DIM == 3 ? 27 : 9;
     __shared__ float tile[4][T::NP];
-    __shared__ Interleave<DIM> il;  // cell ranges and the G2P output layout of the block
+    __shared__ unsigned ccnt[NC];   // particles per base cell (blocks without a row of cell ranges)
     __shared__ uint32_t ord[P2G_ORDER_STAGE];
     __shared__ int nbr[T::NB];  // compact indices of the blocks the tile covers
     const int lane = threadIdx.x;
@@ -94,8 +94,10 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
     // key is the linear block index).
     int cnt_n = 0, st_n = 0, ent_n = -1, hs_n = 0;
     uint64_t key_n = 0;
+    // (Beyond the last block, within the capacity, it is loaded and not used:
+    // the first loads do not wait for the block count.)
     auto fetch_meta = [&](int bb) {
-        if (bb < nb) {
+        if (bb < P.block_cap) {
             // the same in every lane; hidden so that the values stay in vector
             // registers and nothing waits for them before they are used
             asm volatile("" : "+v"(bb));
@@ -132,14 +134,48 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         const float mp = mat.p_mass;
         const float dtv = mat.dt * mat.p_vol0 / mp;
         const int org[3] = {bc[0] * BLK, bc[1] * BLK, bc[2] * BLK};
-        // cell ranges of the block and its G2P output layout (rank-major over
-        // the base cells), with the block's permutation staged in LDS by the
-        // same loads; each lane records where G2P will store its cell's
-        // particles as it visits them (osrc)
-        // after an incremental re-sort the block's cell ranges are its entry's
-        // row of first positions; otherwise they are counted from the keys
-        interleave_setup<DIM>(il, skeys, st, en, order, ord, P2G_ORDER_STAGE,
-                              ent >= 0 ? P.rs_off + (size_t)ent * NC : nullptr);
+        // cell ranges: the row of first positions that the sort left for the
+        // block, or counted from the keys; the block's permutation is staged
+        // in LDS by the same loads
+        const bool rows = ent >= 0;
+        unsigned row = 0u;
+        if (rows) {
+            if (lane < NC) row = P.rs_off[(size_t)ent * NC + lane];
+        } else if (lane < NC) {
+            ccnt[lane] = 0u;
+        }
+        const int stage_end = min(en, st + P2G_ORDER_STAGE);
+        for (int i0 = st; i0 < (rows ? stage_end : en); i0 += 64 * IL_BATCH) {
+            uint32_t vq[IL_BATCH], kq[IL_BATCH];
+#pragma unroll
+            for (int r = 0; r < IL_BATCH; ++r) {
+                const int i = i0 + r * 64 + lane;
+                vq[r] = i < stage_end ? order[i] : 0u;
+                kq[r] = !rows && i < en ? skeys[i] : 0u;
+            }
+#pragma unroll
+            for (int r = 0; r < IL_BATCH; ++r) {
+                const int i = i0 + r * 64 + lane;
+                if (i < stage_end) ord[i - st] = vq[r];
+                if (!rows && i < en) atomicAdd(&ccnt[kq[r] & (NC - 1)], 1u);
+            }
+        }
+        __syncthreads();
+        int c0, c1;
+        if (rows) {
+            const int up = __shfl_down((int)row, 1);
+            c0 = (int)row;
+            c1 = lane + 1 < NC ? up : en;
+        } else {
+            const unsigned m = lane < NC ? ccnt[lane] : 0u;
+            c1 = st + (int)wave_incl_scan(m);
+            c0 = c1 - (int)m;
+        }
+        if (lane >= NC) c0 = c1 = 0;
+        // particles beyond the interleaved ranks, of the cells before this one
+        const int late = max(c1 - c0 - IL_ROUNDS, 0);
+        int late0 = 0;
+        if (__ballot(late > 0)) late0 = (int)wave_incl_scan((unsigned)late) - late;
         if (LINK && slot >= 0) nbv = P.h_vals[slot];
         if (!LINK && lane < T::NB) nbr[lane] = nbv;
         float acc[NK][4];
@@ -147,8 +183,12 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         for (int k = 0; k < NK; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
         int lb[3] = {lane & 3, (lane >> 2) & 3, DIM == 3 ? (lane >> 4) & 3 : 0};
         const double base[3] = {(double)(org[0] + lb[0]), (double)(org[1] + lb[1]), (double)(org[2] + lb[2])};
-        const int c0 = lane < NC ? il.cs[lane] : 0, c1 = lane < NC ? il.ce[lane] : 0;
         const bool has = c1 > c0;
+        // G2P stores a block's particles rank-major over its cells; the lanes
+        // walk their cells rank by rank, so the lanes still walking at rank j
+        // are the cells that hold more than j particles
+        int out0 = st;  // output position of the first particle of the current rank
+        const unsigned long long lt = (1ull << lane) - 1ull;
         // The walk over the lane's particles, with the source index read from
         // the LDS copy of the permutation when the block fits it (the usual
         // case) and from HBM otherwise: one uniform choice per block, so each
@@ -281,7 +321,13 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                     }
                 }
                 // the G2P output position of this particle records its source
-                osrc[interleave_pos_cj<DIM>(il, lane, i - c0)] = qp;
+                if (i - c0 < IL_ROUNDS) {
+                    const unsigned long long m = __ballot(true);
+                    osrc[out0 + __popcll(m & lt)] = qp;
+                    out0 += __popcll(m);
+                } else {
+                    osrc[out0 + late0 + (i - c0 - IL_ROUNDS)] = qp;
+                }
             };
             uint32_t qa = 0, qb = 0;
             if (has) {
