@@ -225,6 +225,9 @@ void free_all(mpm_ctx* c) {
     dfree(c->tab.ent);
     dfree(c->tab.part);
     dfree(c->tab.n_ent);
+    dfree(c->tab.occ);
+    dfree(c->tab.eidx);
+    dfree(c->tab.box);
     if (c->sb_mem) (void)hipFree(c->sb_mem);
     c->sb_mem = nullptr;
     dfree(c->sb_seg);
@@ -344,6 +347,8 @@ void fill_params(mpm_ctx* c) {
     P.nh_owner = c->nh_owner;
     P.rs_new = c->rs_new;
     P.row_cap = c->row_cap;
+    P.d_ent = c->dense ? c->tab.ent : nullptr;
+    P.d_n = c->tab.n_ent;
     P.h_entry = c->h_entry;
     P.b_entry = c->b_entry;
     fill_material(c);
@@ -426,12 +431,17 @@ int alloc_capacity_buffers(mpm_ctx* c) {
     }
     // rows of cell ranges and neighbour slots, one per entry of a sort that
     // inserts its blocks itself
-    c->row_cap = resort ? 2 * c->block_cap : hashed && !c->det_order && c->tab.cnt ? c->block_cap : 0;
+    // (a dense grid's blocks beyond DENSE_ROWS, most of them empty, go without)
+    constexpr int DENSE_ROWS = 1 << 16;
+    c->row_cap = resort                            ? 2 * c->block_cap
+                 : !c->tab.cnt || c->det_order     ? 0
+                 : c->dense                        ? std::min(c->tab.ent_cap, DENSE_ROWS)
+                                                   : c->block_cap;
     if (c->row_cap > 0) {
         e = e ? e : dalloc(&c->rs_off, (size_t)c->row_cap * NPB);
-        e = e ? e : dalloc(&c->rs_nslot, (size_t)c->row_cap * NB);
-        e = e ? e : dalloc(&c->h_entry, H);
-        e = e ? e : dalloc(&c->b_entry, cap);
+        if (hashed) e = e ? e : dalloc(&c->rs_nslot, (size_t)c->row_cap * NB);
+        if (hashed) e = e ? e : dalloc(&c->h_entry, H);
+        if (!c->dense) e = e ? e : dalloc(&c->b_entry, cap);
     }
     if (e != hipSuccess) {
         (void)hipGetLastError();
@@ -439,6 +449,15 @@ int alloc_capacity_buffers(mpm_ctx* c) {
         return MPM_ERR_NOMEM;
     }
     fill_params(c);
+    if (c->dense) {
+        e = launch_dense_neighbours(c->P, c->block_cap, nullptr);
+        if (e == hipSuccess) e = hipDeviceSynchronize();
+        if (e != hipSuccess) {
+            (void)hipGetLastError();
+            free_capacity_buffers(c);
+            return MPM_ERR_HIP;
+        }
+    }
     if (resort) {
         // zeroed mover counters and an empty second table, as every re-sort leaves them
         e = launch_resort_init(c->P, (unsigned)H, nullptr);
@@ -494,7 +513,7 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
     const int n = p->n;
     hipError_t e;
     uint32_t *ko = c->k1, *vo = c->v0;
-    bool inserted = false;  // the sort has filled the block hash
+    bool inserted = false;  // the sort has filled the block hash (or what replaces it)
     if (reuse && n > 0) {
         uint32_t* prev = c->skeys;
         uint32_t* fresh = prev == c->k0 ? c->k1 : c->k0;
@@ -516,13 +535,14 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
             e = launch_bin(c->P, p->x, p->inst, n, c->k1, s);
             if (e != hipSuccess) return MPM_ERR_HIP;
         }
-        if (n > 0 && c->tab.cnt) {
+        if (c->tab.cnt && (n > 0 || c->dense)) {
             // sorted keys over the block-grouped indices, which each wave has read
             uint32_t* tmp = c->k0;
             ko = c->keys_dst ? c->keys_dst : tmp;
             vo = c->v0;
-            inserted = !c->dense && !c->scan_build;
-            e = launch_tab_sort(c->P, c->tab, c->k1, c->v1, tmp, vo, ko, n, 1u << c->H_log2, inserted, s);
+            const TabMode mode = c->dense ? TAB_DENSE : c->scan_build ? TAB_SCAN : TAB_HASH;
+            inserted = true;
+            e = launch_tab_sort(c->P, c->tab, c->k1, c->v1, tmp, vo, ko, n, 1u << c->H_log2, mode, s);
             if (e != hipSuccess) return MPM_ERR_HIP;
         } else if (n > 0) {
             uint32_t *k0 = c->k0, *k1 = c->k1;
@@ -535,9 +555,11 @@ int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bo
     c->order = vo;
     c->osrc = vo == c->v0 ? c->v1 : c->v0;
     if (c->dense)
-        e = launch_build_dense(c->P, ko, n, (int)c->n_blocks_total, c->partials, s);
+        e = inserted ? launch_grid_clear(c->P, (int)c->n_blocks_total, s)
+                     : launch_build_dense(c->P, ko, n, (int)c->n_blocks_total, c->partials, s);
     else if (c->scan_build)
-        e = launch_build_scan(c->P, ko, n, c->sb, c->partials, s);
+        e = inserted ? launch_build_scan_tab(c->P, c->tab, c->sb, s)
+                     : launch_build_scan(c->P, ko, n, c->sb, c->partials, s);
     else
         e = launch_build_sparse(c->P, ko, n, 1u << c->H_log2, c->partials, s, inserted,
                                 c->det_order ? &c->det : nullptr);
@@ -775,8 +797,14 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
             e = dalloc(&t.cnt, (size_t)ids);
             e = e ? e : dalloc(&t.start, (size_t)ids);
             e = e ? e : dalloc(&t.ent, (size_t)t.ent_cap);
-            e = e ? e : dalloc(&t.part, 2 * (((size_t)ids + SCAN_TILE - 1) / SCAN_TILE));
+            const size_t tiles = ((size_t)ids + SCAN_TILE - 1) / SCAN_TILE;
+            e = e ? e : dalloc(&t.part, (c->scan_build ? 8 : 4) * tiles);
             e = e ? e : dalloc(&t.n_ent, 1);
+            if (c->scan_build) {
+                e = e ? e : dalloc(&t.occ, (size_t)ids);
+                e = e ? e : dalloc(&t.eidx, (size_t)ids);
+                e = e ? e : dalloc(&t.box, 8 * tiles);
+            }
             e = e ? e : launch_tab_init(t, nullptr);
         }
     }

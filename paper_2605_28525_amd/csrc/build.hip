@@ -439,21 +439,27 @@ __global__ __launch_bounds__(WG) void k_dense_segments(DevParams P, const uint32
     if (i == n - 1 || (skeys[i + 1] >> CB) != bl) P.b_count[bl] = i + 1;  // end, converted below
 }
 
-template <int DIM>
-__global__ __launch_bounds__(WG) void k_dense_setup(DevParams P, int n_blocks) {
-    constexpr int NB = 1 << DIM;
+__global__ __launch_bounds__(WG) void k_dense_counts(DevParams P, int n_blocks) {
     for (int b = blockIdx.x * WG + threadIdx.x; b < n_blocks; b += gridDim.x * WG) {
         const int st = P.b_start[b];
         const int cnt = st >= 0 ? P.b_count[b] - st : 0;
         P.b_count[b] = cnt;
-        P.b_chunks[b] = (unsigned)((cnt + P.chunk - 1) / P.chunk);
+        P.b_chunks[b] = block_chunks(P, cnt);
+    }
+}
+
+// Upper neighbours on a dense grid: the same for every build, written once.
+template <int DIM>
+__global__ __launch_bounds__(WG) void k_dense_neighbours(DevParams P, int n_blocks) {
+    constexpr int NB = 1 << DIM;
+    for (int b = blockIdx.x * WG + threadIdx.x; b < n_blocks; b += gridDim.x * WG) {
         int bc[3];
         linear_to_block<DIM>(P, (uint32_t)b, bc);
 #pragma unroll
         for (int d = 0; d < NB; ++d) {
             const int x = bc[0] + (d & 1), y = bc[1] + ((d >> 1) & 1), z = bc[2] + ((d >> 2) & 1);
             const bool in = x < P.nblk[0] && y < P.nblk[1] && (DIM == 2 || z < P.nblk[2]);
-            P.b_nbr[b * NB + d] = in ? (DIM == 3 ? (z * P.nblk[1] + y) * P.nblk[0] + x : y * P.nblk[0] + x) : -1;
+            P.b_nbr[(size_t)b * NB + d] = in ? (DIM == 3 ? (z * P.nblk[1] + y) * P.nblk[0] + x : y * P.nblk[0] + x) : -1;
         }
     }
 }
@@ -541,6 +547,16 @@ hipError_t launch_work_items(const DevParams& P, unsigned* partials, hipStream_t
     return hipGetLastError();
 }
 
+hipError_t launch_dense_neighbours(const DevParams& P, int n_blocks, hipStream_t s) {
+    if (P.dim == 3)
+        k_dense_neighbours<3><<<grid_for(n_blocks), WG, 0, s>>>(P, n_blocks);
+    else
+        k_dense_neighbours<2><<<grid_for(n_blocks), WG, 0, s>>>(P, n_blocks);
+    return hipGetLastError();
+}
+
+// The dense tables from sorted keys (after a radix sort; the counting sort fills
+// them itself).
 hipError_t launch_build_dense(const DevParams& P, const uint32_t* skeys, int n, int n_blocks, unsigned* partials,
                               hipStream_t s) {
     const int gb = grid_for(n_blocks);
@@ -551,14 +567,15 @@ hipError_t launch_build_dense(const DevParams& P, const uint32_t* skeys, int n, 
         else
             k_dense_segments<2><<<(n + WG - 1) / WG, WG, 0, s>>>(P, skeys, n);
     }
-    if (P.dim == 3)
-        k_dense_setup<3><<<gb, WG, 0, s>>>(P, n_blocks);
-    else
-        k_dense_setup<2><<<gb, WG, 0, s>>>(P, n_blocks);
+    k_dense_counts<<<gb, WG, 0, s>>>(P, n_blocks);
     hipError_t e = scan_exclusive(P.b_chunks, P.b_chunk_off, n_blocks, nullptr, partials,
                                   (unsigned*)&P.ctr->n_work, s);
     if (e != hipSuccess) return e;
     k_work_write<<<gb, WG, 0, s>>>(P);
+    return launch_grid_clear(P, n_blocks, s);
+}
+
+hipError_t launch_grid_clear(const DevParams& P, int n_blocks, hipStream_t s) {
     const long long NPB = P.dim == 3 ? 64 : 16;
     if (P.dim == 3)
         k_grid_clear<3><<<grid_for((long long)n_blocks * NPB, 65536), WG, 0, s>>>(P, (long long)n_blocks * NPB);

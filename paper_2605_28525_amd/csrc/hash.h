@@ -85,12 +85,6 @@ __device__ __forceinline__ void clear_hash(const DevParams& P, unsigned H, unsig
     }
 }
 
-// Work items of a block holding cnt particles (none for a block that only
-// holds stencil nodes).
-__device__ __forceinline__ unsigned block_chunks(const DevParams& P, int cnt) {
-    return cnt > 0 ? (unsigned)((cnt + P.chunk - 1) / P.chunk) : 0u;
-}
-
 // Inserts block d of the 2^d blocks that the stencils of owner block `seg`
 // (instance and linear block) with base cells `occ` can reach.  Returns its
 // slot, -1 where it is not reached (or, with the overflow flag, where no slot

@@ -153,6 +153,8 @@ struct DevParams {
     int* b_entry;         // the sort's entry of each compact block (-1: none): its cell
                           // ranges are the entry's row of rs_off
     int row_cap;          // rows of rs_off and rs_nslot (0: none)
+    const uint4* d_ent;   // dense grids, after a counting sort: the occupied blocks (TabSort::ent) and their
+    const int* d_n;       // number; null after a radix sort
     // ensembles
     int n_inst;          // 1 = single simulation
     int blk_bits;        // bits of the linear block id inside the sort key
@@ -416,6 +418,36 @@ struct SbScratch {
     long long max_m;
 };
 
+// Work items of a block holding cnt particles (none for a block that only
+// holds stencil nodes).
+__device__ __forceinline__ unsigned block_chunks(const DevParams& P, int cnt) {
+    return cnt > 0 ? (unsigned)((cnt + P.chunk - 1) / P.chunk) : 0u;
+}
+
+// Box [lo, hi] over the workgroup's threads, left in every thread.
+__device__ __forceinline__ void box_reduce(int* lo, int* hi, int (*red)[6]) {
+    const int w = threadIdx.x >> 6;
+#pragma unroll
+    for (int a = 0; a < 3; ++a) {
+        for (int m = 32; m >= 1; m >>= 1) {
+            lo[a] = min(lo[a], __shfl_xor(lo[a], m));
+            hi[a] = max(hi[a], __shfl_xor(hi[a], m));
+        }
+        if (__lane_id() == 0) {
+            red[w][a] = lo[a];
+            red[w][3 + a] = hi[a];
+        }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int a = 0; a < 3; ++a)
+#pragma unroll
+        for (int q = 0; q < WG / 64; ++q) {
+            lo[a] = min(lo[a], red[q][a]);
+            hi[a] = max(hi[a], red[q][3 + a]);
+        }
+}
+
 // ---------------------------------------------------------------------------
 // host-side launchers (each returns hipError_t of the launch)
 hipError_t scan_exclusive(const unsigned* in, unsigned* out, int n, const int* n_dev, unsigned* partials,
@@ -453,15 +485,26 @@ struct TabSort {
     unsigned* cnt;    // particles per owner block (instance and linear block); zero between sorts
     unsigned* start;  // first position of each occupied block
     uint4* ent;       // occupied blocks in ascending order: block, first position, particles
-    unsigned* part;   // tile sums of the scan
+    unsigned* part;   // tile sums of the scan: particles, occupied blocks, work items (4 words per tile;
+                      // 8 for a scan-built context, whose build keeps its own there afterwards)
     int* n_ent;
     int ids, ent_cap;
+    // scan-built contexts: occupied base cells and entry of each block (occ zero
+    // between builds), bounding box of each tile's occupied blocks
+    uint64_t* occ;
+    int* eidx;
+    int* box;  // 8 words per tile: lo[3], -, hi[3], -
+};
+enum TabMode {
+    TAB_HASH,   // the sort clears the block hash and inserts every block
+    TAB_DENSE,  // the sort fills a dense grid's block tables and work items
+    TAB_SCAN    // the sort leaves counts and occupied cells for launch_build_scan_tab
 };
 hipError_t launch_tab_init(const TabSort& T, hipStream_t s);
-// keys: unsorted; rank, tmp: scratch; order, skeys: the result (skeys may be
-// tmp).  hash: also clears the block hash and inserts every block.
+// keys: unsorted; rank, tmp: scratch; order, skeys: the result (skeys may be tmp).
 hipError_t launch_tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
-                           uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s);
+                           uint32_t* order, uint32_t* skeys, int n, unsigned H, TabMode mode, hipStream_t s);
+hipError_t launch_build_scan_tab(const DevParams& P, const TabSort& T, const SbScratch& S, hipStream_t s);
 
 hipError_t launch_bin(const DevParams& P, const float* x, const uint32_t* inst, int n, uint32_t* keys, hipStream_t s);
 // The sorted keys are not written (after an incremental re-sort nothing reads
@@ -490,6 +533,8 @@ hipError_t launch_build_sparse(const DevParams& P, const uint32_t* skeys, int n,
                                hipStream_t s, bool inserted = false, const DetTables* det = nullptr);
 hipError_t launch_build_dense(const DevParams& P, const uint32_t* skeys, int n, int n_blocks, unsigned* partials,
                               hipStream_t s);
+hipError_t launch_dense_neighbours(const DevParams& P, int n_blocks, hipStream_t s);
+hipError_t launch_grid_clear(const DevParams& P, int n_blocks, hipStream_t s);
 // update: the grid update (Eqs. 8-12) is applied in P2G's second pass (sparse
 // grids), which then leaves velocities instead of momenta in the grid.
 hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const float* C, const float* tau, int n,

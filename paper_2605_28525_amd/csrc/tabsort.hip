@@ -16,6 +16,12 @@
 //            and keys are written.  One wave meanwhile inserts the block into
 //            the hash table (hash-built grids): its occupied cells are known.
 //
+// On a dense grid the scan also writes the block tables and work items, as the
+// block index is Phi there (six launches, 22 us of a step of 262,144 particles
+// in 23,465 blocks, less), and P2G walks the entries instead of the domain (30
+// us against 40).  For a scan-built context the order leaves each block's
+// occupied cells and the counts stay for the build (scanbuild.hip).
+//
 // The radix sort needs three to four passes of four launches each for these
 // keys, all bound by latency at moderate sizes; with the hash clearing, the
 // insertion (which served a wave's blocks one after another) and the item
@@ -26,6 +32,7 @@
 // and clearing and item count 9.  (A wave per block that ordered each cell by
 // insertion and only then inserted its block took 16.)
 #include <algorithm>
+#include <climits>
 
 #include "hash.h"
 
@@ -33,72 +40,142 @@ namespace mpmx {
 
 namespace {
 
-// Occupied blocks and particles per tile of SCAN_TILE table entries.
-__global__ __launch_bounds__(WG) void k_tab_reduce(TabSort T) {
+// Per tile of SCAN_TILE table entries: particles and occupied blocks; DENSE: work
+// items; SCAN: bounding box of the occupied blocks.
+template <int DIM, TabMode MODE>
+__global__ __launch_bounds__(WG) void k_tab_reduce(DevParams P, TabSort T) {
     __shared__ unsigned lds[WG / 64];
+    __shared__ int red[WG / 64][6];
     const int base = blockIdx.x * SCAN_TILE + threadIdx.x;
-    unsigned c = 0, z = 0, v[SCAN_ITEMS];
+    unsigned c = 0, z = 0, w = 0, v[SCAN_ITEMS];
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j * WG < T.ids ? T.cnt[base + j * WG] : 0u;
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) {
         c += v[j];
         z += v[j] != 0u ? 1u : 0u;
+        if (MODE == TAB_DENSE) w += block_chunks(P, (int)v[j]);
     }
-    unsigned tc, tz;
+    unsigned tc, tz, tw = 0u;
     wg_excl_scan(c, lds, &tc);
     wg_excl_scan(z, lds, &tz);
+    if (MODE == TAB_DENSE) wg_excl_scan(w, lds, &tw);
     if (threadIdx.x == 0) {
-        T.part[2 * blockIdx.x] = tc;
-        T.part[2 * blockIdx.x + 1] = tz;
+        T.part[4 * blockIdx.x] = tc;
+        T.part[4 * blockIdx.x + 1] = tz;
+        T.part[4 * blockIdx.x + 2] = tw;
+    }
+    if (MODE == TAB_SCAN) {
+        int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {-1, -1, -1};
+        if (tz != 0u) {
+#pragma unroll 1
+            for (int j = 0; j < SCAN_ITEMS; ++j) {
+                if (base + j * WG >= T.ids || T.cnt[base + j * WG] == 0u) continue;
+                int bc[3];
+                linear_to_block<DIM>(P, (uint32_t)(base + j * WG), bc);
+#pragma unroll
+                for (int a = 0; a < DIM; ++a) {
+                    lo[a] = min(lo[a], bc[a]);
+                    hi[a] = max(hi[a], bc[a]);
+                }
+            }
+        }
+        box_reduce(lo, hi, red);
+        if (threadIdx.x == 0)
+#pragma unroll
+            for (int a = 0; a < 3; ++a) {
+                T.box[8 * blockIdx.x + a] = lo[a];
+                T.box[8 * blockIdx.x + 4 + a] = hi[a];
+            }
     }
 }
 
-__global__ __launch_bounds__(WG) void k_tab_down(TabSort T, int tiles) {
-    __shared__ unsigned lds[WG / 64], red[WG / 64][4];
+template <TabMode MODE>
+__global__ __launch_bounds__(WG) void k_tab_down(DevParams P, TabSort T, int tiles) {
+    __shared__ unsigned lds[WG / 64], red[WG / 64][5];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
     const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    unsigned v[SCAN_ITEMS], s[4] = {0u, 0u, 0u, 0u}, c = 0u, z = 0u;
+    unsigned v[SCAN_ITEMS], s[5] = {0u, 0u, 0u, 0u, 0u}, c = 0u, z = 0u, it = 0u;
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j < T.ids ? T.cnt[base + j] : 0u;
-    // sums of the tiles before this one, and the occupied blocks of all
+    // sums of the tiles before this one, and the occupied blocks (DENSE: and
+    // the work items) of all
     for (int i = threadIdx.x; i < tiles; i += WG) {
-        const unsigned pc = T.part[2 * i], pz = T.part[2 * i + 1];
-        s[0] += i < (int)blockIdx.x ? pc : 0u;
-        s[1] += i < (int)blockIdx.x ? pz : 0u;
-        s[2] += pz;
+        const uint4 p = *(const uint4*)&T.part[4 * i];
+        const bool before = i < (int)blockIdx.x;
+        s[0] += before ? p.x : 0u;
+        s[1] += before ? p.y : 0u;
+        s[2] += p.y;
+        if (MODE == TAB_DENSE) {
+            s[3] += before ? p.z : 0u;
+            s[4] += p.z;
+        }
     }
+    constexpr int NS = MODE == TAB_DENSE ? 5 : 3;
 #pragma unroll
     for (int o = 32; o > 0; o >>= 1)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) s[q] += __shfl_xor(s[q], o);
+        for (int q = 0; q < NS; ++q) s[q] += __shfl_xor(s[q], o);
     if (lane == 0)
 #pragma unroll
-        for (int q = 0; q < 3; ++q) red[w][q] = s[q];
+        for (int q = 0; q < NS; ++q) red[w][q] = s[q];
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) {
         c += v[j];
         z += v[j] != 0u ? 1u : 0u;
+        if (MODE == TAB_DENSE) it += block_chunks(P, (int)v[j]);
     }
     unsigned tot;
     unsigned pos = wg_excl_scan(c, lds, &tot);
     unsigned ent = wg_excl_scan(z, lds, &tot);  // its barriers also publish red
-    unsigned all = 0u;
+    unsigned item = MODE == TAB_DENSE ? wg_excl_scan(it, lds, &tot) : 0u;
+    unsigned all = 0u, items = 0u;
 #pragma unroll
     for (int q = 0; q < WG / 64; ++q) {
         pos += red[q][0];
         ent += red[q][1];
         all += red[q][2];
+        if (MODE == TAB_DENSE) {
+            item += red[q][3];
+            items += red[q][4];
+        }
     }
-    if (blockIdx.x == 0 && threadIdx.x == 0) *T.n_ent = (int)all;
+    if (blockIdx.x == 0 && threadIdx.x == 0) {
+        *T.n_ent = (int)all;
+        if (MODE == TAB_DENSE) {
+            P.ctr->nb = T.ids;
+            P.ctr->n_touched = T.ids;
+            P.ctr->n_work = (int)items;
+        }
+    }
+    bool over = false;
 #pragma unroll
     for (int j = 0; j < SCAN_ITEMS; ++j) {
+        const int b = base + j;
+        if (MODE == TAB_DENSE && b < T.ids) {
+            const unsigned k = block_chunks(P, (int)v[j]);
+            P.b_start[b] = v[j] != 0u ? (int)pos : -1;
+            P.b_count[b] = (int)v[j];
+            P.b_chunks[b] = k;
+            for (unsigned q = 0; q < k; ++q) {
+                if (item + q >= (unsigned)P.work_cap) {
+                    over = true;
+                    break;
+                }
+                P.w_block[item + q] = b;
+                P.w_start[item + q] = (int)pos + (int)q * P.chunk;
+                P.w_end[item + q] = (int)(pos + min((q + 1u) * (unsigned)P.chunk, v[j]));
+            }
+            item += k;
+        }
         if (v[j] == 0u) continue;
-        T.start[base + j] = pos;
-        if ((int)ent < T.ent_cap) T.ent[ent] = make_uint4((unsigned)(base + j), pos, v[j], 0u);
+        T.start[b] = pos;
+        if (MODE == TAB_SCAN) T.eidx[b] = (int)ent;
+        if ((int)ent < T.ent_cap) T.ent[ent] = make_uint4((unsigned)b, pos, v[j], 0u);
         pos += v[j];
         ++ent;
     }
+    if (over) raise_flag(P.ctr, MPM_FLAG_OVERFLOW);
 }
 
 }  // namespace
@@ -202,7 +279,7 @@ __device__ void wave_radix(uint32_t* a, uint32_t* b, int c, int idx_bits, const 
 // One workgroup per occupied block.  Its particles are listed cell by cell in
 // LDS, then each counts the smaller indices of its cell: no step depends on the
 // one before it, where ordering a cell by insertion is a chain of LDS accesses.
-template <int DIM, bool HASH>
+template <int DIM, TabMode MODE>
 __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const uint32_t* __restrict__ keys,
                                                   uint32_t* tmp, uint32_t* order, uint32_t* skeys, int n, int idx_bits) {
     constexpr int CB = 2 * DIM, NC = 1 << CB, NB = 1 << DIM, R = TAB_STAGE / WG;
@@ -251,24 +328,27 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
             const unsigned m = t < NC ? cnt[t] : 0u, f = wave_incl_scan(m) - m;
             if (t < NC) first[t] = f;
         }
-        if (HASH && e < P.row_cap && t < NC) P.rs_off[(size_t)e * NC + t] = (unsigned)st + first[t];
-        if (t == 0) T.cnt[id] = 0u;  // the table is left empty
-        if (HASH && t >= WG - 64) {
+        if (e < P.row_cap && t < NC) P.rs_off[(size_t)e * NC + t] = (unsigned)st + first[t];
+        if (MODE != TAB_SCAN && t == 0) T.cnt[id] = 0u;  // the table is left empty (a scan build empties it itself)
+        if (MODE != TAB_DENSE && t >= WG - 64) {
             const uint64_t occ = (uint64_t)__ballot(lane < NC && cnt[lane & (NC - 1)] != 0u);
-            const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
-            const int own = readlane32(slot, 0);
-            const bool row = e < P.row_cap;  // with the cell ranges below, for P2G
-            if (own >= 0 && lane < NB) {
-                if (row)
-                    P.rs_nslot[(size_t)e * NB + lane] = slot;
-                else
-                    P.h_nslot[(size_t)own * NB + lane] = slot;
-            }
-            if (own >= 0 && lane == 0) {
-                P.h_start[own] = st;
-                P.h_end[own] = st + c;
-                if (row) P.h_entry[own] = e;
-                atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
+            if (MODE == TAB_SCAN && lane == 0) T.occ[id] = occ;
+            if (MODE == TAB_HASH) {
+                const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
+                const int own = readlane32(slot, 0);
+                const bool row = e < P.row_cap;  // with the cell ranges below, for P2G
+                if (own >= 0 && lane < NB) {
+                    if (row)
+                        P.rs_nslot[(size_t)e * NB + lane] = slot;
+                    else
+                        P.h_nslot[(size_t)own * NB + lane] = slot;
+                }
+                if (own >= 0 && lane == 0) {
+                    P.h_start[own] = st;
+                    P.h_end[own] = st + c;
+                    if (row) P.h_entry[own] = e;
+                    atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
+                }
             }
         }
         if (staged) {
@@ -291,7 +371,10 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
 }
 
 __global__ __launch_bounds__(WG) void k_tab_init(TabSort T) {
-    for (int t = blockIdx.x * WG + threadIdx.x; t < T.ids; t += gridDim.x * WG) T.cnt[t] = 0u;
+    for (int t = blockIdx.x * WG + threadIdx.x; t < T.ids; t += gridDim.x * WG) {
+        T.cnt[t] = 0u;
+        if (T.occ) T.occ[t] = 0ull;
+    }
 }
 
 hipError_t launch_tab_init(const TabSort& T, hipStream_t s) {
@@ -300,32 +383,33 @@ hipError_t launch_tab_init(const TabSort& T, hipStream_t s) {
 }
 
 namespace {
-template <int DIM>
+template <int DIM, TabMode MODE>
 hipError_t tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
-                    uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s) {
+                    uint32_t* order, uint32_t* skeys, int n, unsigned H, hipStream_t s) {
+    constexpr bool HASH = MODE == TAB_HASH;
     const int g = (n + WG - 1) / WG, tiles = (T.ids + SCAN_TILE - 1) / SCAN_TILE;
     const int go = std::max(1, std::min(T.ent_cap, 2048));  // what the chip holds
     int bits = 1;
     while (bits < 30 && (1 << bits) < n) ++bits;
-    if (hash)  // at least 64 workgroups for the clearing
-        k_tab_count<DIM, true><<<std::max(g, 64), WG, 0, s>>>(P, T, keys, rank, n, H);
-    else
-        k_tab_count<DIM, false><<<g, WG, 0, s>>>(P, T, keys, rank, n, 0u);
-    k_tab_reduce<<<tiles, WG, 0, s>>>(T);
-    k_tab_down<<<tiles, WG, 0, s>>>(T, tiles);
-    k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
-    if (hash)
-        k_tab_order<DIM, true><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
-    else
-        k_tab_order<DIM, false><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+    // (hash: at least 64 workgroups for the clearing)
+    if (n > 0) k_tab_count<DIM, HASH><<<HASH ? std::max(g, 64) : g, WG, 0, s>>>(P, T, keys, rank, n, H);
+    k_tab_reduce<DIM, MODE><<<tiles, WG, 0, s>>>(P, T);
+    k_tab_down<MODE><<<tiles, WG, 0, s>>>(P, T, tiles);
+    if (n > 0) {
+        k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
+        k_tab_order<DIM, MODE><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+    }
     return hipGetLastError();
 }
 }  // namespace
 
 hipError_t launch_tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
-                           uint32_t* order, uint32_t* skeys, int n, unsigned H, bool hash, hipStream_t s) {
-    return P.dim == 3 ? tab_sort<3>(P, T, keys, rank, tmp, order, skeys, n, H, hash, s)
-                      : tab_sort<2>(P, T, keys, rank, tmp, order, skeys, n, H, hash, s);
+                           uint32_t* order, uint32_t* skeys, int n, unsigned H, TabMode mode, hipStream_t s) {
+    const bool d3 = P.dim == 3;
+    const auto f = mode == TAB_HASH    ? (d3 ? tab_sort<3, TAB_HASH> : tab_sort<2, TAB_HASH>)
+                   : mode == TAB_DENSE ? (d3 ? tab_sort<3, TAB_DENSE> : tab_sort<2, TAB_DENSE>)
+                                       : (d3 ? tab_sort<3, TAB_SCAN> : tab_sort<2, TAB_SCAN>);
+    return f(P, T, keys, rank, tmp, order, skeys, n, H, s);
 }
 
 }  // namespace mpmx

@@ -87,7 +87,10 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
     __shared__ uint32_t ord[P2G_ORDER_STAGE];
     __shared__ int nbr[T::NB];  // compact indices of the blocks the tile covers
     const int lane = threadIdx.x;
-    const int nb = min(P.ctr->nb, P.block_cap);
+    // a dense grid's occupied blocks are listed where its sort counted them;
+    // P2G then walks the list, not the domain
+    const bool listed = !LINK && P.d_ent != nullptr;
+    const int nb = listed ? *P.d_n : min(P.ctr->nb, P.block_cap);
     const float dx = P.dxf, inv_dx = P.inv_dxf;
     // The count, first sorted position and key of the next block are loaded
     // while the current one is processed (a dense grid has no key table: its
@@ -101,6 +104,15 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
             // the same in every lane; hidden so that the values stay in vector
             // registers and nothing waits for them before they are used
             asm volatile("" : "+v"(bb));
+            if (listed) {
+                if (bb >= nb) return;  // (the list is shorter than the capacity)
+                const uint4 en = P.d_ent[bb];
+                key_n = en.x;
+                st_n = (int)en.y;
+                cnt_n = (int)en.z;
+                ent_n = bb < P.row_cap ? bb : -1;
+                return;
+            }
             cnt_n = P.b_count[bb];
             st_n = P.b_start[bb];
             key_n = P.dense ? (uint64_t)bb : P.b_keys[bb];
@@ -120,7 +132,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         if (LINK) {
             if (lane < T::NB) slot = link_slot<DIM>(P, ent, hs, lane);
         } else if (P.dense) {
-            if (lane < T::NB) nbv = P.b_nbr[(size_t)b * T::NB + lane];
+            if (lane < T::NB) nbv = P.b_nbr[(size_t)key * T::NB + lane];
         }
         for (int t = lane; t < 4 * T::NP; t += 64) (&tile[0][0])[t] = 0.f;
         int bc[3], inst = 0;
@@ -1203,7 +1215,7 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
 hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const float* C, const float* tau, int n,
                       const uint32_t* order, const uint32_t* skeys, uint32_t* osrc, int grid_blocks, hipStream_t s,
                       bool update) {
-    const int g = P.dense ? 65536 : grid_blocks * 4;
+    const int g = P.dense && !P.d_ent ? 65536 : grid_blocks * 4;
     const bool link = P.b_hs != nullptr && n <= FOLD_MAX_N;
     const auto cell =
         P.dim == 3 ? (link ? k_p2g_cell<3, true> : k_p2g_cell<3, false>) : (link ? k_p2g_cell<2, true> : k_p2g_cell<2, false>);

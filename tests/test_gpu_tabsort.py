@@ -152,3 +152,90 @@ def test_order_of_an_ensemble():
         assert np.array_equal(order.cpu().numpy(), expected_order(ens.x, m.dx, m.cells, 3, ens.inst))
     finally:
         sim.close()
+
+
+def _far_cloud(dim, n, seed):
+    """n particles around the middle of a 40-cell box, some blocks full, some with one."""
+    rng = np.random.default_rng(seed)
+    c = np.concatenate([rng.normal(16, 2.5, (dim, n - n // 8)), rng.uniform(7, 30, (dim, n // 8))], axis=1)
+    return (np.clip(c, 6.1, 33.9)[:, rng.permutation(n)] * 0.25).astype(np.float32)
+
+
+@pytest.mark.parametrize("flags", ["full", "scan", "dense", "adjoint"])
+@pytest.mark.parametrize("dim", [2, 3])
+@pytest.mark.parametrize("n", [1, 700, 6000])
+def test_steps_equal_those_of_a_larger_domain(n, dim, flags):
+    """The same particles in a domain within the table and in one of more than
+    4.2 million blocks, which keeps the radix sort and the builds from sorted
+    keys: the same active blocks in the same order, particles bit for bit (on a
+    dense grid, whose P2G adds with atomics, to the parity tolerance)."""
+    from paper_2605_28525_amd import mpm as M
+    from parity_util import RTOL, assert_field, tau_floor
+    fl = {"full": M.MPM_FLAG_FULL_SORT, "scan": M.MPM_FLAG_SCAN_BUILD, "dense": 0, "adjoint": M.MPM_FLAG_ADJOINT}[flags]
+    _announce("table against radix", n, dim, flags)
+    x = _far_cloud(dim, n, 11)
+    got = []
+    for cells in [(40, 48, 44)[:dim], (660, 656, 652)[:dim] if dim == 3 else (8300, 8260)]:
+        w = wl.tiny_3d(n=48, ties=False) if dim == 3 else wl.collapse_2d()
+        w.dim, w.dx, w.cells, w.dt = dim, 0.25, cells, 1e-3
+        for k, a in _state(x, 6).items():
+            setattr(w, k, a)
+        sim = M.Simulation(w, flags=fl, block_capacity=4096,
+                           grid_mode=M.MPM_GRID_DENSE if flags == "dense" else M.MPM_GRID_SPARSE)
+        try:
+            sim.step(3)
+            rc, f = sim.status()
+            assert rc == 0, f
+            act = None
+            if flags != "dense":
+                import torch
+                M.mpm_sparse_build(sim.ctx, sim.a.view())
+                nb, _ = M.mpm_active_count(sim.ctx)
+                kh = torch.empty(nb, dtype=torch.int64, device="cuda")
+                mh = torch.empty_like(kh)
+                M.mpm_get_active(sim.ctx, kh, mh, nb)
+                act = np.stack([kh.cpu().numpy(), mh.cpu().numpy()])
+                if flags != "scan":  # (slot order)
+                    act = act[:, np.argsort(act[0])]
+            got.append((sim.a.to_arrays(), sim.a.ids(), act))
+        finally:
+            sim.close()
+    (sa, ia, aa), (sb, ib, ab) = got
+    assert np.array_equal(ia, ib)
+    if aa is not None:
+        assert np.array_equal(aa, ab)
+    for k in sa:
+        if flags == "dense":
+            assert_field(k, sa[k], sb[k], RTOL, atol=tau_floor(w) if k == "tau" else 0.0)
+        else:
+            assert np.array_equal(sa[k], sb[k]), k
+
+
+def test_scan_build_past_its_capacity():
+    """More active blocks than the capacity: the overflow is raised, the count
+    is the whole one, and the context works again with fewer particles."""
+    from paper_2605_28525_amd import mpm as M
+    x = _far_cloud(3, 3000, 5)
+    w = wl.tiny_3d(n=48, ties=False)
+    w.dx, w.cells, w.dt = 0.25, (40, 48, 44), 1e-3
+    for k, a in _state(x, 6).items():
+        setattr(w, k, a)
+    _announce("scan build past its capacity")
+    big = M.Simulation(w, flags=M.MPM_FLAG_SCAN_BUILD, block_capacity=4096)
+    small = M.Simulation(w, flags=M.MPM_FLAG_SCAN_BUILD, block_capacity=40)
+    try:
+        M.mpm_sparse_build(big.ctx, big.a.view())
+        nb, touched = M.mpm_active_count(big.ctx)
+        assert nb == touched > 40
+        M.mpm_sparse_build(small.ctx, small.a.view())
+        assert M.mpm_active_count(small.ctx) == (40, touched)
+        assert small.status()[0] != 0
+        M.mpm_clear_status(small.ctx)
+        few = M.ParticleSet(3, 4)
+        few.x[:] = small.a.x[:, :1]
+        M.mpm_sparse_build(small.ctx, few.view())
+        nb, touched = M.mpm_active_count(small.ctx)
+        assert 0 < nb == touched <= 8 and small.status()[0] == 0
+    finally:
+        big.close()
+        small.close()
