@@ -32,7 +32,7 @@
 namespace mpmx {
 
 // ---------------------------------------------------------------------------
-// P2G, one wave64 per owner block and one lane per base cell.
+// P2G, one wave64 (or two) per owner block and one lane per base cell.
 //
 // Inside a block the sorted order groups particles by the local index of their
 // base node (the low 2d bits of the sort key), and every particle with the same
@@ -70,10 +70,27 @@ __global__ __launch_bounds__(WG) void k_link(DevParams P) {
     }
 }
 
+// A stress component (stored order) that the rows Q0 .. Q1 - 1 of tau hold.
+template <int DIM>
+constexpr bool stress_of_rows(int k, int q0, int q1) {
+    // row and column of component k: diagonal, then xy, yz, xz (2D: xy)
+    const int r = k < DIM ? k : k == 4 ? 1 : 0;
+    const int c = k < DIM ? k : k == DIM ? 1 : 2;
+    return (r >= q0 && r < q1) || (c >= q0 && c < q1);
+}
+template <int V>
+using int_c = std::integral_constant<int, V>;
+
+// Bound by vector issue: about 430 instructions per rank of a block's cells,
+// one rank after another, so that a block takes 12 us however few there are.
+// NW = 2: two waves walk the same cells, one for two momentum components, one
+// for the third and the mass, every sum in the order of the single wave's
+// (launch_p2g has the line).  In a step of 25,600 particles 15.6 us against 19.8,
+// of 262,144 19.9 against 22.3.
 // LINK: P2G makes the neighbour tables beside its own work (launch_p2g has the
 // line between the two forms).
-template <int DIM, bool LINK>
-__global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __restrict__ x,
+template <int DIM, bool LINK, int NW>
+__global__ __launch_bounds__(64 * NW) void k_p2g_cell(DevParams P, const float* __restrict__ x,
                                                  const float* __restrict__ v, const float* __restrict__ C,
                                                  const float* __restrict__ tau, int n,
                                                  const uint32_t* __restrict__ order,
@@ -82,11 +99,12 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
     constexpr int NS = DIM == 3 ? 6 : 3;
     constexpr int NC = T::NPB;  // base cells per block
     constexpr int NK = DIM == 3 ? 27 : 9;
+    constexpr int TH = 64 * NW;
     __shared__ float tile[4][T::NP];
     __shared__ unsigned ccnt[NC];   // particles per base cell (blocks without a row of cell ranges)
     __shared__ uint32_t ord[P2G_ORDER_STAGE];
     __shared__ int nbr[T::NB];  // compact indices of the blocks the tile covers
-    const int lane = threadIdx.x;
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     // a dense grid's occupied blocks are listed where its sort counted them;
     // P2G then walks the list, not the domain
     const bool listed = !LINK && P.d_ent != nullptr;
@@ -130,11 +148,11 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         int nbv = -1;  // compact index of upper neighbour `lane`
         int slot = -1;  // and its hash slot
         if (LINK) {
-            if (lane < T::NB) slot = link_slot<DIM>(P, ent, hs, lane);
+            if (tid < T::NB) slot = link_slot<DIM>(P, ent, hs, lane);
         } else if (P.dense) {
-            if (lane < T::NB) nbv = P.b_nbr[(size_t)key * T::NB + lane];
+            if (tid < T::NB) nbv = P.b_nbr[(size_t)key * T::NB + lane];
         }
-        for (int t = lane; t < 4 * T::NP; t += 64) (&tile[0][0])[t] = 0.f;
+        for (int t = tid; t < 4 * T::NP; t += TH) (&tile[0][0])[t] = 0.f;
         int bc[3], inst = 0;
         if (P.dense)
             linear_to_block<DIM>(P, (uint32_t)key, bc);
@@ -153,21 +171,23 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         unsigned row = 0u;
         if (rows) {
             if (lane < NC) row = P.rs_off[(size_t)ent * NC + lane];
-        } else if (lane < NC) {
-            ccnt[lane] = 0u;
+        } else {
+            if (tid < NC) ccnt[tid] = 0u;
+            if (NW > 1) __syncthreads();
         }
         const int stage_end = min(en, st + P2G_ORDER_STAGE);
-        for (int i0 = st; i0 < (rows ? stage_end : en); i0 += 64 * IL_BATCH) {
-            uint32_t vq[IL_BATCH], kq[IL_BATCH];
+        constexpr int BATCH = IL_BATCH / NW;
+        for (int i0 = st; i0 < (rows ? stage_end : en); i0 += TH * BATCH) {
+            uint32_t vq[BATCH], kq[BATCH];
 #pragma unroll
-            for (int r = 0; r < IL_BATCH; ++r) {
-                const int i = i0 + r * 64 + lane;
+            for (int r = 0; r < BATCH; ++r) {
+                const int i = i0 + r * TH + tid;
                 vq[r] = i < stage_end ? order[i] : 0u;
                 kq[r] = !rows && i < en ? skeys[i] : 0u;
             }
 #pragma unroll
-            for (int r = 0; r < IL_BATCH; ++r) {
-                const int i = i0 + r * 64 + lane;
+            for (int r = 0; r < BATCH; ++r) {
+                const int i = i0 + r * TH + tid;
                 if (i < stage_end) ord[i - st] = vq[r];
                 if (!rows && i < en) atomicAdd(&ccnt[kq[r] & (NC - 1)], 1u);
             }
@@ -189,7 +209,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         int late0 = 0;
         if (__ballot(late > 0)) late0 = (int)wave_incl_scan((unsigned)late) - late;
         if (LINK && slot >= 0) nbv = P.h_vals[slot];
-        if (!LINK && lane < T::NB) nbr[lane] = nbv;
+        if (!LINK && tid < T::NB) nbr[tid] = nbv;
         float acc[NK][4];
 #pragma unroll
         for (int k = 0; k < NK; ++k) acc[k][0] = acc[k][1] = acc[k][2] = acc[k][3] = 0.f;
@@ -206,8 +226,10 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
         // case) and from HBM otherwise: one uniform choice per block, so each
         // variant uses one kind of load and the loads of the next particle stay
         // in flight across the accumulation of the current one.
-        auto walk = [&](auto staged) {
-            constexpr bool STAGED = decltype(staged)::value;
+        // The wave's components: momentum Q0 .. Q1 - 1, and the mass.
+        auto walk = [&](auto staged, auto first_q, auto last_q, auto mass) {
+            constexpr bool STAGED = decltype(staged)::value, MASS = decltype(mass)::value;
+            constexpr int Q0 = decltype(first_q)::value, Q1 = decltype(last_q)::value;
             auto src = [&](int i) -> uint32_t {
                 if constexpr (STAGED)
                     return ord[i - st];
@@ -228,15 +250,17 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
 #pragma unroll
                 for (int a = 0; a < DIM; ++a) {
                     xs[a] = x[(size_t)a * n + q];
-                    vs[a] = v[(size_t)a * n + q];
+                    if (a >= Q0 && a < Q1) vs[a] = v[(size_t)a * n + q];
                 }
 #pragma unroll
-                for (int k = 0; k < DIM * DIM; ++k) Cs[k] = C[(size_t)k * n + q];
+                for (int k = Q0 * DIM; k < Q1 * DIM; ++k) Cs[k] = C[(size_t)k * n + q];
 #pragma unroll
-                for (int k = 0; k < NS; ++k) ts[k] = tau[(size_t)k * n + q];
+                for (int k = 0; k < NS; ++k)
+                    if (stress_of_rows<DIM>(k, Q0, Q1)) ts[k] = tau[(size_t)k * n + q];
             };
             auto process = [&](const float* xp, const float* vp, const float* Cp, const float* tp, uint32_t qp,
-                               int i) {
+                               int i, auto even) {
+                constexpr bool EVEN = decltype(even)::value;
                 float t[3] = {0, 0, 0}, u[3] = {1, 1, 1};
                 particle_frame_at<DIM>(P, xp, base, t, u);
                 float wt[3][3], dw[3][3];
@@ -244,7 +268,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                 // per unit mass: m v -> v, A = m C -> C, G = dt V0 tau / m
                 float mv[3], A[3][3], G[3][3];
 #pragma unroll
-                for (int a = 0; a < DIM; ++a) {
+                for (int a = Q0; a < Q1; ++a) {
                     mv[a] = vp[a];
 #pragma unroll
                     for (int bb = 0; bb < DIM; ++bb) A[a][bb] = Cp[a * DIM + bb];
@@ -274,13 +298,16 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                 //   Y(ky) = w_y (m v + A_1 dx_y) - G_1 dw_y,  Z(kz) = w_z dx_z A_2 - G_2 dw_z,
                 //   h(kx) = (w_x dx_x) A_0 - dw_x G_0
                 // (columns A_j, G_j): two fused multiply-adds per node and momentum
-                // component, one for the mass w_x (w_z w_y).
+                // component, one for the mass w_x (w_z w_y).  The contractions are
+                // written out, so that every form of this code rounds alike (left
+                // to the compiler, they depend on what is compiled around them):
+                // as it chose them for one wave, b's in turns with the rank.
                 float h[3][3], wd[3];
 #pragma unroll
                 for (int kx = 0; kx < 3; ++kx) {
                     wd[kx] = wt[0][kx] * dxn[0][kx];
 #pragma unroll
-                    for (int q = 0; q < DIM; ++q) h[kx][q] = wd[kx] * A[q][0] - dw[0][kx] * G[q][0];
+                    for (int q = Q0; q < Q1; ++q) h[kx][q] = fmaf(wd[kx], A[q][0], -(dw[0][kx] * G[q][0]));
                 }
                 if (DIM == 3) {
                     float Z[3][3];
@@ -288,29 +315,32 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                     for (int kz = 0; kz < 3; ++kz) {
                         const float wzd = wt[2][kz] * dxn[2][kz];
 #pragma unroll
-                        for (int q = 0; q < 3; ++q) Z[kz][q] = wzd * A[q][2] - G[q][2] * dw[2][kz];
+                        for (int q = Q0; q < Q1; ++q) Z[kz][q] = fmaf(wzd, A[q][2], -(G[q][2] * dw[2][kz]));
                     }
 #pragma unroll
                     for (int ky = 0; ky < 3; ++ky) {
                         const float wy = wt[1][ky];
                         float Y[3];
 #pragma unroll
-                        for (int q = 0; q < 3; ++q) Y[q] = wy * (mv[q] + A[q][1] * dxn[1][ky]) - G[q][1] * dw[1][ky];
+                        for (int q = Q0; q < Q1; ++q)
+                            Y[q] = fmaf(wy, fmaf(A[q][1], dxn[1][ky], mv[q]), -(G[q][1] * dw[1][ky]));
 #pragma unroll
                         for (int kz = 0; kz < 3; ++kz) {
                             const float wz = wt[2][kz];
                             const float wzy = wz * wy;
                             float be[3];
 #pragma unroll
-                            for (int q = 0; q < 3; ++q) be[q] = wz * Y[q] + wy * Z[kz][q];
+                            for (int q = Q0; q < Q1; ++q)
+                                be[q] = (q < 2) == EVEN ? fmaf(wy, Z[kz][q], wz * Y[q]) : fmaf(wz, Y[q], wy * Z[kz][q]);
 
 #pragma unroll
                             for (int kx = 0; kx < 3; ++kx) {
                                 const int k = kx + 3 * (ky + 3 * kz);
                                 const float wx = wt[0][kx];
 #pragma unroll
-                                for (int q = 0; q < 3; ++q) acc[k][q] = fmaf(wx, be[q], fmaf(wzy, h[kx][q], acc[k][q]));
-                                acc[k][3] = fmaf(wx, wzy, acc[k][3]);
+                                for (int q = Q0; q < Q1; ++q)
+                                    acc[k][q] = fmaf(wx, be[q], fmaf(wzy, h[kx][q], acc[k][q]));
+                                if (MASS) acc[k][3] = fmaf(wx, wzy, acc[k][3]);
                             }
                         }
                     }
@@ -333,6 +363,7 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
                     }
                 }
                 // the G2P output position of this particle records its source
+                if (!MASS) return;  // (one wave of the block does)
                 if (i - c0 < IL_ROUNDS) {
                     const unsigned long long m = __ballot(true);
                     osrc[out0 + __popcll(m & lt)] = qp;
@@ -349,32 +380,46 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
             for (int i = c0; i < c1; i += 2) {
                 qb = src(min(i + 1, c1 - 1));
                 load_into(xb, vb, Cb, tb, qb);
-                process(xa, va, Ca, ta, qa, i);
+                process(xa, va, Ca, ta, qa, i, std::true_type{});
                 qa = src(min(i + 2, c1 - 1));
                 load_into(xa, va, Ca, ta, qa);
-                if (i + 1 < c1) process(xb, vb, Cb, tb, qb, i + 1);
+                if (i + 1 < c1) process(xb, vb, Cb, tb, qb, i + 1, std::false_type{});
             }
         };
-        if (cnt <= P2G_ORDER_STAGE)
-            walk(std::true_type{});
-        else
-            walk(std::false_type{});
         // Merge the cell sums (per unit mass, scaled by m_p here) into the
-        // tile.  For a fixed offset k, distinct
-        // cells address distinct nodes, so each offset is a conflict-free
-        // read-add-write; the barrier orders successive offsets, which may hit
-        // the same node from neighbouring cells.
+        // tile.  For a fixed offset k, distinct cells address distinct nodes,
+        // so each offset is a conflict-free read-add-write; successive offsets
+        // may hit the same node from neighbouring cells, and a wave's LDS
+        // accesses are served in order.
+        auto merge = [&](auto first_q, auto last_q, auto mass) {
+            constexpr int Q0 = decltype(first_q)::value, Q1 = decltype(last_q)::value;
+            constexpr bool MASS = decltype(mass)::value;
 #pragma unroll
-        for (int k = 0; k < NK; ++k) {
-            const int kx = k % 3, ky = (k / 3) % 3, kz = DIM == 3 ? k / 9 : 0;
-            const int idx = T::pad(lb[0] + kx, lb[1] + ky, DIM == 3 ? lb[2] + kz : 0);
-            if (has) {
-                tile[0][idx] = fmaf(mp, acc[k][0], tile[0][idx]);
-                tile[1][idx] = fmaf(mp, acc[k][1], tile[1][idx]);
-                if (DIM == 3) tile[2][idx] = fmaf(mp, acc[k][2], tile[2][idx]);
-                tile[3][idx] = fmaf(mp, acc[k][3], tile[3][idx]);
+            for (int k = 0; k < NK; ++k) {
+                const int kx = k % 3, ky = (k / 3) % 3, kz = DIM == 3 ? k / 9 : 0;
+                const int idx = T::pad(lb[0] + kx, lb[1] + ky, DIM == 3 ? lb[2] + kz : 0);
+                if (has) {
+#pragma unroll
+                    for (int q = Q0; q < Q1; ++q) tile[q][idx] = fmaf(mp, acc[k][q], tile[q][idx]);
+                    if (MASS) tile[3][idx] = fmaf(mp, acc[k][3], tile[3][idx]);
+                }
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
-            __syncthreads();
+        };
+        auto walk_part = [&](auto first_q, auto last_q, auto mass) {
+            if (cnt <= P2G_ORDER_STAGE)
+                walk(std::true_type{}, first_q, last_q, mass);
+            else
+                walk(std::false_type{}, first_q, last_q, mass);
+            merge(first_q, last_q, mass);
+        };
+        if constexpr (NW == 1) {
+            walk_part(int_c<0>{}, int_c<DIM>{}, std::true_type{});
+        } else if (wave == 0) {
+            walk_part(int_c<0>{}, int_c<2>{}, std::false_type{});
+        } else {
+            walk_part(int_c<2>{}, int_c<3>{}, std::true_type{});
         }
         __syncthreads();
         if (!P.dense) {
@@ -385,19 +430,19 @@ __global__ __launch_bounds__(64) void k_p2g_cell(DevParams P, const float* __res
             // memory operations in flight static, so the wait for the next
             // block's metadata does not also wait for these stores.
 #pragma unroll
-            for (int r = 0; r < (T::N + 63) / 64; ++r) {
-                const int t = min(lane + 64 * r, T::N - 1);
+            for (int r = 0; r < (T::N + TH - 1) / TH; ++r) {
+                const int t = min(tid + TH * r, T::N - 1);
                 int I, J, K;
                 T::store_node(t, &I, &J, &K);
                 const int tp = T::pad(I, J, K);
                 P.tiles[(size_t)b * T::N + t] =
                     make_float4(tile[0][tp], tile[1][tp], DIM == 3 ? tile[2][tp] : 0.f, tile[3][tp]);
             }
-            if (LINK && lane < T::NB) link_store<DIM>(P, b, lane, nbv);
+            if (LINK && tid < T::NB) link_store<DIM>(P, b, lane, nbv);
             __syncthreads();
             continue;
         }
-        for (int t = lane; t < T::N; t += 64) {
+        for (int t = tid; t < T::N; t += TH) {
             const int I = t % T::E;
             const int J = (t / T::E) % T::E;
             const int K = DIM == 3 ? t / (T::E * T::E) : 0;
@@ -1212,13 +1257,23 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
     }
 }
 
+// Two waves per block share its components where one per block leaves SIMDs
+// idle: P2G (with the gather, 8 particles per cell) of 4,096 / 65,536 /
+// 262,144 / 393,216 / 524,288 / 2,097,152 particles in 26 / 25 / 29 / 35 / 39 / 85
+// us, with one wave 31 / 32 / 34 / 38 / 39 / 82.  (A wave per component: 26 / 29 /
+// 45 / 53 / 58 / 122; loads two particles ahead instead of one: 24 / 25 / 35 / 43 /
+// 48 / 105, and no gain inside a step.)
+constexpr int P2G_SPLIT_MAX_N = 3 << 17;
+
 hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const float* C, const float* tau, int n,
                       const uint32_t* order, const uint32_t* skeys, uint32_t* osrc, int grid_blocks, hipStream_t s,
                       bool update) {
     const int g = P.dense && !P.d_ent ? 65536 : grid_blocks * 4;
     const bool link = P.b_hs != nullptr && n <= FOLD_MAX_N;
-    const auto cell =
-        P.dim == 3 ? (link ? k_p2g_cell<3, true> : k_p2g_cell<3, false>) : (link ? k_p2g_cell<2, true> : k_p2g_cell<2, false>);
+    const int waves = P.dim == 3 && n <= P2G_SPLIT_MAX_N ? 2 : 1;
+    const auto cell = P.dim == 2   ? (link ? k_p2g_cell<2, true, 1> : k_p2g_cell<2, false, 1>)
+                      : waves == 2 ? (link ? k_p2g_cell<3, true, 2> : k_p2g_cell<3, false, 2>)
+                                   : (link ? k_p2g_cell<3, true, 1> : k_p2g_cell<3, false, 1>);
     if (P.b_hs && !link) {
         const int gl = (int)std::min<long long>((((long long)P.block_cap << P.dim) + WG - 1) / WG, 4096);
         if (P.dim == 3)
@@ -1226,7 +1281,7 @@ hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const 
         else
             k_link<2><<<gl, WG, 0, s>>>(P);
     }
-    cell<<<g, 64, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
+    cell<<<g, 64 * waves, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
     if (!P.dense) {
         const int gg = (int)std::min<long long>(((long long)P.block_cap + 3) / 4, 16384);  // one wave per block
         if (P.dim == 3) {
