@@ -907,7 +907,10 @@ struct G2POut {
     uint32_t* movers;  // optional (with keys): the next incremental re-sort's counting, see k_g2p
 };
 
-// GS threads per workgroup, work items of at most g2p_max_items(GS) particles.
+// GS threads per workgroup, work items of at most PER particles per thread: every
+// thread loads PER particles ahead whatever its item holds, so a PER larger than
+// the chunk size asks for is loads and staging for nothing (3 for items of 512:
+// 2,097,152 particles in 136 us, 2: 131).
 //
 // With out.keys the kernel also bins each new position (the next build's
 // sort key).  With out.movers as well it does the counting of the next
@@ -917,7 +920,7 @@ struct G2POut {
 // (added, for blocks split over several items, to what the build cleared);
 // the others ("movers") are listed in out.movers from the item's first position
 // on, their number in it_mov.
-template <int DIM, int GS>
+template <int DIM, int GS, int PER>
 __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, int n,
                                             const uint32_t* __restrict__ osrc) {
     using T = Tile<DIM>;
@@ -925,7 +928,7 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
     constexpr int DD = DIM * DIM;
     constexpr int VSY = 20, VSZ = DIM == 3 ? 120 : 0;  // padded float4 tile: row / plane strides
     __shared__ float4 vt[DIM == 3 ? 6 * VSZ : 6 * VSY];
-    constexpr int MAXI = g2p_max_items(GS);
+    constexpr int MAXI = PER * GS;
     __shared__ float xs[DIM][MAXI];
     __shared__ float fs[DD][MAXI];
     constexpr int NC = 1 << (2 * DIM);
@@ -946,7 +949,6 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
     // Every lane issues every load (indices past an item or the tile are
     // clamped into range and the values are discarded), so the number of
     // loads in flight does not depend on the lane's position in the item.
-    constexpr int PER = MAXI / GS;                 // particles per thread
     constexpr int TPER = (T::N + GS - 1) / GS;     // tile nodes per thread
     const int tid = threadIdx.x;
     const int G = gridDim.x;
@@ -1314,15 +1316,19 @@ hipError_t launch_g2p(const DevParams& P, const float* x_in, const float* F_in, 
     G2PIn in{x_in, F_in, id_in, inst_in};
     G2POut out{x_out, v_out, C_out, F_out, tau_out, id_out, inst_out, keys_out, keys_out ? movers_out : nullptr};
     if (g2p_max_items(block_size) < P.chunk) return hipErrorInvalidValue;  // work items must fit the LDS staging
-    switch (block_size * 4 + P.dim) {
-        case 64 * 4 + 3: k_g2p<3, 64><<<grid_blocks, 64, 0, s>>>(P, in, out, n, osrc); break;
-        case 128 * 4 + 3: k_g2p<3, 128><<<grid_blocks, 128, 0, s>>>(P, in, out, n, osrc); break;
-        case 256 * 4 + 3: k_g2p<3, 256><<<grid_blocks, 256, 0, s>>>(P, in, out, n, osrc); break;
-        case 64 * 4 + 2: k_g2p<2, 64><<<grid_blocks, 64, 0, s>>>(P, in, out, n, osrc); break;
-        case 128 * 4 + 2: k_g2p<2, 128><<<grid_blocks, 128, 0, s>>>(P, in, out, n, osrc); break;
-        case 256 * 4 + 2: k_g2p<2, 256><<<grid_blocks, 256, 0, s>>>(P, in, out, n, osrc); break;
-        default: return hipErrorInvalidValue;
+    const int per = (P.chunk + block_size - 1) / block_size;
+    using Kernel = void (*)(DevParams, G2PIn, G2POut, int, const uint32_t*);
+    Kernel k = nullptr;
+    if (block_size == 256) {
+        k = P.dim == 3 ? (per == 1 ? k_g2p<3, 256, 1> : per == 2 ? k_g2p<3, 256, 2> : k_g2p<3, 256, 3>)
+                       : (per == 1 ? k_g2p<2, 256, 1> : per == 2 ? k_g2p<2, 256, 2> : k_g2p<2, 256, 3>);
+    } else if (block_size == 128) {
+        k = P.dim == 3 ? k_g2p<3, 128, 2> : k_g2p<2, 128, 2>;
+    } else if (block_size == 64) {
+        k = P.dim == 3 ? k_g2p<3, 64, 2> : k_g2p<2, 64, 2>;
     }
+    if (!k) return hipErrorInvalidValue;
+    k<<<grid_blocks, block_size, 0, s>>>(P, in, out, n, osrc);
     return hipGetLastError();
 }
 
