@@ -878,20 +878,19 @@ int mpm_sparse_build(mpm_ctx* c, const mpm_particles* p, void* stream) {
 }
 
 namespace {
-// mpm_p2g; with `update` (sparse grids) P2G's second pass also applies the grid
-// update, so the grid holds velocities afterwards.
-int p2g_impl(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool update) {
+// mpm_p2g, its second pass as `second` says.
+int p2g_impl(mpm_ctx* c, const mpm_particles* p, hipStream_t s, P2GSecond second) {
     if (!c || !particles_ok(c, p, true)) return MPM_ERR_ARG;
     if (!c->built || p->n != c->built_n) return MPM_ERR_STATE;
     if (p->n == 0) return MPM_OK;
     const int wgs = std::min(c->p2g_wgs, c->work_cap);
     return hip_status(
-        launch_p2g(c->P, p->x, p->v, p->C, p->tau, p->n, c->order, c->skeys, c->osrc, wgs, s, update));
+        launch_p2g(c->P, p->x, p->v, p->C, p->tau, p->n, c->order, c->skeys, c->osrc, wgs, s, second));
 }
 }  // namespace
 
 int mpm_p2g(mpm_ctx* c, const mpm_particles* p, void* stream) {
-    return p2g_impl(c, p, (hipStream_t)stream, false);
+    return p2g_impl(c, p, (hipStream_t)stream, P2G_SUM);
 }
 
 int mpm_grid_update(mpm_ctx* c, void* stream) {
@@ -908,7 +907,7 @@ namespace {
 // mpm_g2p; with keys_out, the kernel also bins the positions it writes (the
 // next build then skips its binning pass).
 int g2p_impl(mpm_ctx* c, const mpm_particles* in, const mpm_particles* out, hipStream_t s, uint32_t* keys_out,
-             uint32_t* movers_out) {
+             uint32_t* movers_out, bool gather = false) {
     if (!c || !particles_ok(c, in, false) || !out || out->n != in->n) return MPM_ERR_ARG;
     if (in->n > 0) {
         if (!out->x || !out->v || !out->C || !out->F || !out->tau || !in->F) return MPM_ERR_ARG;
@@ -919,7 +918,8 @@ int g2p_impl(mpm_ctx* c, const mpm_particles* in, const mpm_particles* out, hipS
     if (in->n == 0) return MPM_OK;
     const int wgs = std::min(c->g2p_wgs, c->work_cap);
     return hip_status(launch_g2p(params_for(c, in->n), in->x, in->F, in->id, in->inst, out->x, out->v, out->C, out->F, out->tau,
-                                 out->id, out->inst, in->n, c->osrc, c->g2p_block, wgs, s, keys_out, movers_out));
+                                 out->id, out->inst, in->n, c->osrc, c->g2p_block, wgs, s, keys_out, movers_out,
+                                 gather));
 }
 }  // namespace
 
@@ -941,7 +941,10 @@ int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_s
         // mode's copy of it is written either way); with zero particles the
         // grid update still runs on its own
         const bool fuse_update = !c->dense && cur->n > 0;
-        if (st == MPM_OK) st = p2g_impl(c, cur, s, fuse_update);
+        // between two steps nothing else reads the grid either
+        const bool gather = fuse_update && k + 1 < n_steps && !c->adjoint && cur->n <= G2P_GATHER_MAX_N &&
+                            c->g2p_block == 256 && c->chunk <= 512;
+        if (st == MPM_OK) st = p2g_impl(c, cur, s, gather ? P2G_LEFT_TO_G2P : fuse_update ? P2G_UPDATE : P2G_SUM);
         if (st == MPM_OK && !fuse_update) st = mpm_grid_update(c, stream);
         // Between two steps of this call nothing else touches the positions,
         // so G2P bins them as it writes them.
@@ -950,7 +953,7 @@ int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_s
         uint32_t* keys_out = keys_ready ? next_bin_buffer(c, next_reuse) : nullptr;
         // with an incremental re-sort next, G2P also does its counting
         uint32_t* movers_out = keys_ready && next_reuse ? c->movers : nullptr;
-        if (st == MPM_OK) st = g2p_impl(c, cur, nxt, s, keys_out, movers_out);
+        if (st == MPM_OK) st = g2p_impl(c, cur, nxt, s, keys_out, movers_out, gather);
         if (st != MPM_OK) return st;
         std::swap(cur, nxt);
     }
@@ -998,7 +1001,7 @@ int mpm_step_adj(mpm_ctx* c, const mpm_particles* in, const mpm_particles* ob, c
     if (!c->adjoint) return MPM_ERR_STATE;
     int st = mpm_sparse_build(c, in, stream);
     const bool fuse_update = st == MPM_OK && !c->dense && in->n > 0;
-    if (st == MPM_OK) st = p2g_impl(c, in, (hipStream_t)stream, fuse_update);
+    if (st == MPM_OK) st = p2g_impl(c, in, (hipStream_t)stream, fuse_update ? P2G_UPDATE : P2G_SUM);
     if (st == MPM_OK && !fuse_update) st = mpm_grid_update(c, stream);
     if (st == MPM_OK) st = mpm_g2p_adj(c, in, ob, ib, param_bar, stream);
     if (st == MPM_OK) st = mpm_grid_update_adj(c, stream);
@@ -1059,7 +1062,7 @@ int mpm_tape_forward(mpm_ctx* c, const mpm_particles* states, int n_steps, void*
         c->keys_dst = c->tape[(size_t)j].skeys;
         st = sparse_build(c, &states[j], s, any && j > 0);
         c->osrc = c->tape[(size_t)j].osrc;
-        if (st == MPM_OK) st = p2g_impl(c, &states[j], s, any);
+        if (st == MPM_OK) st = p2g_impl(c, &states[j], s, any ? P2G_UPDATE : P2G_SUM);
         if (st == MPM_OK && !any) st = mpm_grid_update(c, stream);
         uint32_t* keys_out = any && j + 1 < n_steps ? next_bin_buffer(c, false) : nullptr;
         if (st == MPM_OK) st = g2p_impl(c, &states[j], &states[j + 1], s, keys_out, nullptr);

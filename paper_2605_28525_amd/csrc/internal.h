@@ -63,6 +63,14 @@ constexpr int LINE = 32;
 // against 68 + 9, P2G +30 us against 10).
 constexpr int FOLD_MAX_N = 1 << 22;
 
+// Up to this many particles mpm_step leaves P2G's second pass to G2P, except in
+// its last step, whose grid stays readable: a launch less, against nodes formed
+// by each block that reads them.  Whole steps of 4,096 / 32,768 / 65,536 / 131,072 /
+// 262,144 / 2,097,152 particles in 56 / 59 / 61 / 74 / 80 / 290 us, with the pass 57 /
+// 61 / 62 / 73 / 79 / 267; in a graph of 25,600 53 against 56, of 4,096 in 2D
+// 38 against 40.
+constexpr int G2P_GATHER_MAX_N = 1 << 16;
+
 // Per-instance material and step constants (one entry for a single simulation).
 struct InstMat {
     float mu, lam, alpha, dp_coef;
@@ -535,17 +543,20 @@ hipError_t launch_build_dense(const DevParams& P, const uint32_t* skeys, int n, 
                               hipStream_t s);
 hipError_t launch_dense_neighbours(const DevParams& P, int n_blocks, hipStream_t s);
 hipError_t launch_grid_clear(const DevParams& P, int n_blocks, hipStream_t s);
-// update: the grid update (Eqs. 8-12) is applied in P2G's second pass (sparse
-// grids), which then leaves velocities instead of momenta in the grid.
+// P2G's second pass (sparse grids): the sums of the tiles; with the grid update
+// (Eqs. 8-12), which leaves velocities instead of momenta in the grid; or none,
+// where G2P forms the nodes it reads (launch_g2p with gather) and nothing else
+// reads the grid.
+enum P2GSecond { P2G_SUM, P2G_UPDATE, P2G_LEFT_TO_G2P };
 hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const float* C, const float* tau, int n,
                       const uint32_t* order, const uint32_t* skeys, uint32_t* osrc, int grid_blocks, hipStream_t s,
-                      bool update = false);
+                      P2GSecond second = P2G_SUM);
 hipError_t launch_grid_update(const DevParams& P, long long n_nodes_host, int grid_blocks, hipStream_t s);
 hipError_t launch_g2p(const DevParams& P, const float* x_in, const float* F_in, const uint32_t* id_in,
                       const uint32_t* inst_in, float* x_out, float* v_out, float* C_out, float* F_out, float* tau_out,
                       uint32_t* id_out, uint32_t* inst_out, int n, const uint32_t* osrc, int block_size,
                       int grid_blocks, hipStream_t s, uint32_t* keys_out = nullptr,
-                      uint32_t* movers_out = nullptr);
+                      uint32_t* movers_out = nullptr, bool gather = false);
 hipError_t launch_clear_flags(DevCounters* c, hipStream_t s);
 // Reverse kernels; osrc[o]: input index of the particle at G2P output position o.
 constexpr int ADJ_MAX_WGS = 8192;  // workgroups of the per-particle kernels at most

@@ -562,6 +562,28 @@ __device__ __forceinline__ void node_update_inputs(const DevParams& P, int b, in
     if (DIM == 3 && P.has_terrain) terrain_heights(P, node[0], node[1], h);
 }
 
+// Sum of the tile entries that cover node (I, J, K) of a block, src: the block
+// and its lower neighbours that own particles, else -1.
+template <int DIM>
+__device__ __forceinline__ float4 tile_sum(const DevParams& P, const int* src, int I, int J, int K, bool on) {
+    using T = Tile<DIM>;
+    float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
+#pragma unroll
+    for (int d = 0; d < T::NB; ++d) {
+        const int dx = d & 1, dy = (d >> 1) & 1, dz = (d >> 2) & 1;
+        const bool reach = (!dx || I < 2) && (!dy || J < 2) && (DIM == 2 || !dz || K < 2);
+        if (src[d] >= 0 && reach && on) {
+            const int t = T::store_index(I + 4 * dx, J + 4 * dy, K + 4 * dz);
+            const float4 g = P.tiles[(size_t)src[d] * T::N + t];
+            sum.x += g.x;
+            sum.y += g.y;
+            sum.z += g.z;
+            sum.w += g.w;
+        }
+    }
+    return sum;
+}
+
 // P2G, second pass on a sparse grid: node n of block b receives the tile
 // entries that cover it, from b's own tile and from the tiles of the lower
 // neighbours b - d (d in {0,1}^d) whose 6-node tiles reach n (local index < 2
@@ -584,20 +606,7 @@ __global__ __launch_bounds__(WG) void k_p2g_gather(DevParams P) {
         int node[3] = {0, 0, 0};
         float dtn = P.dt, h[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
         if (UPDATE) node_update_inputs<DIM>(P, b, lane, node, &dtn, h);
-        float4 sum = make_float4(0.f, 0.f, 0.f, 0.f);
-#pragma unroll
-        for (int d = 0; d < T::NB; ++d) {
-            const int dx = d & 1, dy = (d >> 1) & 1, dz = (d >> 2) & 1;
-            const bool reach = (!dx || I < 2) && (!dy || J < 2) && (DIM == 2 || !dz || K < 2);
-            if (src[d] >= 0 && reach && lane < T::NPB) {
-                const int t = T::store_index(I + 4 * dx, J + 4 * dy, K + 4 * dz);
-                const float4 g = P.tiles[(size_t)src[d] * T::N + t];
-                sum.x += g.x;
-                sum.y += g.y;
-                sum.z += g.z;
-                sum.w += g.w;
-            }
-        }
+        const float4 sum = tile_sum<DIM>(P, src, I, J, K, lane < T::NPB);
         if (lane < T::NPB) {
             const size_t s = (size_t)b * T::NPB + lane;
             P.grid[s] = UPDATE ? node_update<DIM>(P, s, node, dtn, sum, h) : sum;
@@ -920,7 +929,11 @@ struct G2POut {
 // (added, for blocks split over several items, to what the build cleared);
 // the others ("movers") are listed in out.movers from the item's first position
 // on, their number in it_mov.
-template <int DIM, int GS, int PER>
+//
+// GATHER: P2G's second pass with the grid update happens here, each workgroup
+// forming the nodes of its own tile (a node is formed by each of the up to 2^d
+// blocks that read it, and the grid is not written): launch_g2p has the line.
+template <int DIM, int GS, int PER, bool GATHER>
 __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, int n,
                                             const uint32_t* __restrict__ osrc) {
     using T = Tile<DIM>;
@@ -1006,7 +1019,7 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
             pin[k] = in.inst ? in.inst[q] : 0u;
         }
 #pragma unroll
-        for (int k = 0; k < TPER; ++k) {
+        for (int k = 0; k < TPER && !GATHER; ++k) {
             const int t = min(tid + k * GS, T::N - 1);
             const int I = t % T::E, J = (t / T::E) % T::E, K = DIM == 3 ? t / (T::E * T::E) : 0;
             const int l = (I & 3) + BLK * ((J & 3) + BLK * (K & 3));
@@ -1048,7 +1061,21 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
             const int t = tid + k * GS;
             if (t < T::N) {
                 const int I = t % T::E, J = (t / T::E) % T::E, K = DIM == 3 ? t / (T::E * T::E) : 0;
-                vt[I + VSY * J + VSZ * K] = pphi[k] >= 0 ? pt[k] : make_float4(0.f, 0.f, 0.f, 0.f);
+                float4 g = make_float4(0.f, 0.f, 0.f, 0.f);
+                if (!GATHER) {
+                    if (pphi[k] >= 0) g = pt[k];
+                } else if (pphi[k] >= 0) {
+                    int src[T::NB], bc[3], inst = 0;
+#pragma unroll
+                    for (int d = 0; d < T::NB; ++d) src[d] = P.b_lo[(size_t)pphi[k] * T::NB + d];
+                    unblock_key<DIM>(P, key, bc, &inst);
+                    const int node[3] = {bc[0] * BLK + I, bc[1] * BLK + J, DIM == 3 ? bc[2] * BLK + K : 0};
+                    float h[5] = {0.f, 0.f, 0.f, 0.f, 0.f};
+                    if (DIM == 3 && P.has_terrain) terrain_heights(P, node[0], node[1], h);
+                    const float4 sum = tile_sum<DIM>(P, src, I & 3, J & 3, K & 3, true);
+                    g = node_update<DIM>(P, 0, node, P.n_inst > 1 ? P.inst[inst].dt : P.dt, sum, h);
+                }
+                vt[I + VSY * J + VSZ * K] = g;
             }
         }
         __syncthreads();
@@ -1269,7 +1296,7 @@ constexpr int P2G_SPLIT_MAX_N = 3 << 17;
 
 hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const float* C, const float* tau, int n,
                       const uint32_t* order, const uint32_t* skeys, uint32_t* osrc, int grid_blocks, hipStream_t s,
-                      bool update) {
+                      P2GSecond second) {
     const int g = P.dense && !P.d_ent ? 65536 : grid_blocks * 4;
     const bool link = P.b_hs != nullptr && n <= FOLD_MAX_N;
     const int waves = P.dim == 3 && n <= P2G_SPLIT_MAX_N ? 2 : 1;
@@ -1284,7 +1311,8 @@ hipError_t launch_p2g(const DevParams& P, const float* x, const float* v, const 
             k_link<2><<<gl, WG, 0, s>>>(P);
     }
     cell<<<g, 64 * waves, 0, s>>>(P, x, v, C, tau, n, order, skeys, osrc);
-    if (!P.dense) {
+    if (!P.dense && second != P2G_LEFT_TO_G2P) {
+        const bool update = second == P2G_UPDATE;
         const int gg = (int)std::min<long long>(((long long)P.block_cap + 3) / 4, 16384);  // one wave per block
         if (P.dim == 3) {
             if (update)
@@ -1312,20 +1340,26 @@ hipError_t launch_grid_update(const DevParams& P, long long n_nodes_host, int gr
 hipError_t launch_g2p(const DevParams& P, const float* x_in, const float* F_in, const uint32_t* id_in,
                       const uint32_t* inst_in, float* x_out, float* v_out, float* C_out, float* F_out, float* tau_out,
                       uint32_t* id_out, uint32_t* inst_out, int n, const uint32_t* osrc, int block_size,
-                      int grid_blocks, hipStream_t s, uint32_t* keys_out, uint32_t* movers_out) {
+                      int grid_blocks, hipStream_t s, uint32_t* keys_out, uint32_t* movers_out, bool gather) {
     G2PIn in{x_in, F_in, id_in, inst_in};
     G2POut out{x_out, v_out, C_out, F_out, tau_out, id_out, inst_out, keys_out, keys_out ? movers_out : nullptr};
     if (g2p_max_items(block_size) < P.chunk) return hipErrorInvalidValue;  // work items must fit the LDS staging
     const int per = (P.chunk + block_size - 1) / block_size;
     using Kernel = void (*)(DevParams, G2PIn, G2POut, int, const uint32_t*);
     Kernel k = nullptr;
-    if (block_size == 256) {
-        k = P.dim == 3 ? (per == 1 ? k_g2p<3, 256, 1> : per == 2 ? k_g2p<3, 256, 2> : k_g2p<3, 256, 3>)
-                       : (per == 1 ? k_g2p<2, 256, 1> : per == 2 ? k_g2p<2, 256, 2> : k_g2p<2, 256, 3>);
+    const bool d3 = P.dim == 3;
+    if (gather) {
+        if (block_size != 256 || per > 2 || P.dense || P.grid_u) return hipErrorInvalidValue;
+        k = per == 1 ? (d3 ? k_g2p<3, 256, 1, true> : k_g2p<2, 256, 1, true>)
+                     : (d3 ? k_g2p<3, 256, 2, true> : k_g2p<2, 256, 2, true>);
+    } else if (block_size == 256) {
+        k = per == 1   ? (d3 ? k_g2p<3, 256, 1, false> : k_g2p<2, 256, 1, false>)
+            : per == 2 ? (d3 ? k_g2p<3, 256, 2, false> : k_g2p<2, 256, 2, false>)
+                       : (d3 ? k_g2p<3, 256, 3, false> : k_g2p<2, 256, 3, false>);
     } else if (block_size == 128) {
-        k = P.dim == 3 ? k_g2p<3, 128, 2> : k_g2p<2, 128, 2>;
+        k = d3 ? k_g2p<3, 128, 2, false> : k_g2p<2, 128, 2, false>;
     } else if (block_size == 64) {
-        k = P.dim == 3 ? k_g2p<3, 64, 2> : k_g2p<2, 64, 2>;
+        k = d3 ? k_g2p<3, 64, 2, false> : k_g2p<2, 64, 2, false>;
     }
     if (!k) return hipErrorInvalidValue;
     k<<<grid_blocks, block_size, 0, s>>>(P, in, out, n, osrc);
