@@ -15,6 +15,43 @@
 
 using namespace mpmx;
 
+// Device buffers that live and die together, in one allocation (each hipMalloc and
+// hipFree costs a context 5 to 100 us).
+struct Arena {
+    struct Want {
+        void** p;
+        size_t bytes;
+    };
+    std::vector<Want> wants;
+    void* mem = nullptr;
+    template <typename T>
+    void need(T** p, size_t count) {
+        *p = nullptr;
+        wants.push_back({(void**)p, (std::max<size_t>(count, 1) * sizeof(T) + 255) & ~(size_t)255});
+    }
+    hipError_t commit() {
+        size_t total = 0;
+        for (const Want& w : wants) total += w.bytes;
+        hipError_t e = hipMalloc(&mem, std::max<size_t>(total, 256));
+        if (e != hipSuccess) {
+            mem = nullptr;
+            return e;
+        }
+        char* at = (char*)mem;
+        for (const Want& w : wants) {
+            *w.p = at;
+            at += w.bytes;
+        }
+        return hipSuccess;
+    }
+    void release() {
+        for (const Want& w : wants) *w.p = nullptr;
+        wants.clear();
+        if (mem) (void)hipFree(mem);
+        mem = nullptr;
+    }
+};
+
 struct mpm_ctx {
     mpm_params prm;
     int dim = 3;
@@ -105,25 +142,13 @@ struct mpm_ctx {
         int* b_lo = nullptr;
         uint32_t *osrc = nullptr, *skeys = nullptr;
     };
+    Arena own, sized, taped;  // per context; by the capacities; the tape's slots
     std::vector<TapeSlot> tape;
     long long tape_serial = 0;  // changes with the slots' contents, or with what reads them (the chunk size)
     DevCounters* tape_ctr = nullptr;  // one per slot
 };
 
 namespace {
-
-template <typename T>
-hipError_t dalloc(T** p, size_t count) {
-    *p = nullptr;
-    if (count == 0) count = 1;
-    return hipMalloc((void**)p, count * sizeof(T));
-}
-
-template <typename T>
-void dfree(T*& p) {
-    if (p) (void)hipFree((void*)p);
-    p = nullptr;
-}
 
 int bits_for(long long v) {
     int b = 0;
@@ -132,105 +157,20 @@ int bits_for(long long v) {
 }
 
 void free_capacity_buffers(mpm_ctx* c) {
-    dfree(c->h_keys);
-    dfree(c->h_mask);
-    dfree(c->h_vals);
-    dfree(c->h_start);
-    dfree(c->h_end);
-    dfree(c->h_nslot);
-    dfree(c->t_cnt);
-    dfree(c->b_keys);
-    dfree(c->b_mask);
-    dfree(c->b_nbr);
-    dfree(c->b_hs);
-    dfree(c->b_start);
-    dfree(c->b_count);
-    dfree(c->b_chunks);
-    dfree(c->b_chunk_off);
-    dfree(c->w_block);
-    dfree(c->w_start);
-    dfree(c->w_end);
-    dfree(c->grid);
-    dfree(c->tiles);
-    dfree(c->b_lo);
-    dfree(c->grid_u);
-    dfree(c->grid_bar);
-    dfree(c->partials);
-    dfree(c->rs_stay);
-    dfree(c->rs_in);
-    dfree(c->rs_off);
-    dfree(c->rs_oldblk);
-    dfree(c->rs_cnt);
-    dfree(c->rs_start);
-    dfree(c->rs_tile);
-    dfree(c->it_mov);
-    dfree(c->rs_occ);
-    dfree(c->rs_nslot);
-    dfree(c->nh_keys);
-    dfree(c->nh_cnt);
-    dfree(c->nh_idx);
-    dfree(c->nh_owner);
-    dfree(c->rs_new);
-    dfree(c->h_entry);
-    dfree(c->b_entry);
-    dfree(c->det.keys);
-    dfree(c->det.mask);
-    dfree(c->det.start);
-    dfree(c->det.count);
-    dfree(c->det.slot);
-    for (int j = 0; j < 2; ++j) {
-        dfree(c->det.k[j]);
-        dfree(c->det.v[j]);
-    }
-    dfree(c->det.hist);
+    c->sized.release();
     c->seg_valid = false;
 }
 
 void free_tape(mpm_ctx* c) {
     ++c->tape_serial;
-    for (auto& t : c->tape) {
-        dfree(t.b_keys);
-        dfree(t.b_nbr);
-        dfree(t.b_start);
-        dfree(t.b_count);
-        dfree(t.w_block);
-        dfree(t.w_start);
-        dfree(t.w_end);
-        dfree(t.grid);
-        dfree(t.grid_u);
-        dfree(t.b_lo);
-        dfree(t.osrc);
-        dfree(t.skeys);
-    }
+    c->taped.release();
     c->tape.clear();
-    dfree(c->tape_ctr);
 }
 
 void free_all(mpm_ctx* c) {
     free_tape(c);
     free_capacity_buffers(c);
-    dfree(c->k0);
-    dfree(c->k1);
-    dfree(c->v0);
-    dfree(c->v1);
-    dfree(c->hist);
-    dfree(c->heightmap);
-    dfree(c->adj_scratch);
-    dfree(c->adj_part);
-    dfree(c->inst);
-    dfree(c->ctr);
-    dfree(c->movers);
-    dfree(c->tab.cnt);
-    dfree(c->tab.start);
-    dfree(c->tab.ent);
-    dfree(c->tab.part);
-    dfree(c->tab.n_ent);
-    dfree(c->tab.occ);
-    dfree(c->tab.eidx);
-    dfree(c->tab.box);
-    if (c->sb_mem) (void)hipFree(c->sb_mem);
-    c->sb_mem = nullptr;
-    dfree(c->sb_seg);
+    c->own.release();
 }
 
 void release_graph(mpm_ctx* c) {
@@ -368,66 +308,66 @@ int alloc_capacity_buffers(mpm_ctx* c) {
     // order may depend on earlier builds
     const bool resort = !c->dense && !c->adjoint && !c->scan_build && !c->det_order;
     const bool hashed = !c->dense && !c->scan_build;
-    hipError_t e = hipSuccess;
+    Arena& A = c->sized;
     if (hashed) {
-        e = e ? e : dalloc(&c->h_keys, H);
-        e = e ? e : dalloc(&c->h_mask, H);
-        e = e ? e : dalloc(&c->h_vals, H);
-        e = e ? e : dalloc(&c->h_start, H);
-        e = e ? e : dalloc(&c->h_end, H);
-        e = e ? e : dalloc(&c->h_nslot, H * NB);
-        e = e ? e : dalloc(&c->t_cnt, LINE * ((H + SCAN_TILE - 1) / SCAN_TILE));
-        e = e ? e : dalloc(&c->b_hs, cap);
+        A.need(&c->h_keys, H);
+        A.need(&c->h_mask, H);
+        A.need(&c->h_vals, H);
+        A.need(&c->h_start, H);
+        A.need(&c->h_end, H);
+        A.need(&c->h_nslot, H * NB);
+        A.need(&c->t_cnt, LINE * ((H + SCAN_TILE - 1) / SCAN_TILE));
+        A.need(&c->b_hs, cap);
     }
     if (!c->dense) {
-        e = e ? e : dalloc(&c->b_keys, cap);
-        e = e ? e : dalloc(&c->b_mask, cap);
+        A.need(&c->b_keys, cap);
+        A.need(&c->b_mask, cap);
     }
     if (hashed && c->det_order) {
-        e = e ? e : dalloc(&c->det.keys, cap);
-        e = e ? e : dalloc(&c->det.mask, cap);
-        e = e ? e : dalloc(&c->det.start, cap);
-        e = e ? e : dalloc(&c->det.count, cap);
-        e = e ? e : dalloc(&c->det.slot, cap);
+        A.need(&c->det.keys, cap);
+        A.need(&c->det.mask, cap);
+        A.need(&c->det.start, cap);
+        A.need(&c->det.count, cap);
+        A.need(&c->det.slot, cap);
         for (int j = 0; j < 2; ++j) {
-            e = e ? e : dalloc(&c->det.k[j], cap);
-            e = e ? e : dalloc(&c->det.v[j], cap);
+            A.need(&c->det.k[j], cap);
+            A.need(&c->det.v[j], cap);
         }
-        e = e ? e : dalloc(&c->det.hist, (size_t)radix_hist_size(c->block_cap));
+        A.need(&c->det.hist, (size_t)radix_hist_size(c->block_cap));
     }
-    e = e ? e : dalloc(&c->b_nbr, cap * NB);
-    e = e ? e : dalloc(&c->b_start, cap);
-    e = e ? e : dalloc(&c->b_count, cap);
-    e = e ? e : dalloc(&c->b_chunks, cap);
-    e = e ? e : dalloc(&c->b_chunk_off, cap);
-    e = e ? e : dalloc(&c->w_block, (size_t)c->work_cap);
-    e = e ? e : dalloc(&c->w_start, (size_t)c->work_cap);
-    e = e ? e : dalloc(&c->w_end, (size_t)c->work_cap);
-    e = e ? e : dalloc(&c->grid, cap * NPB);
+    A.need(&c->b_nbr, cap * NB);
+    A.need(&c->b_start, cap);
+    A.need(&c->b_count, cap);
+    A.need(&c->b_chunks, cap);
+    A.need(&c->b_chunk_off, cap);
+    A.need(&c->w_block, (size_t)c->work_cap);
+    A.need(&c->w_start, (size_t)c->work_cap);
+    A.need(&c->w_end, (size_t)c->work_cap);
+    A.need(&c->grid, cap * NPB);
     if (!c->dense) {
         const size_t tile_nodes = c->dim == 3 ? 216 : 36;
-        e = e ? e : dalloc(&c->tiles, cap * tile_nodes);
-        e = e ? e : dalloc(&c->b_lo, cap * NB);
+        A.need(&c->tiles, cap * tile_nodes);
+        A.need(&c->b_lo, cap * NB);
     }
     if (c->adjoint) {
-        e = e ? e : dalloc(&c->grid_u, cap * NPB);
-        e = e ? e : dalloc(&c->grid_bar, cap * NPB);
+        A.need(&c->grid_u, cap * NPB);
+        A.need(&c->grid_bar, cap * NPB);
     }
-    e = e ? e : dalloc(&c->partials, (size_t)scan_partials_size(scan_n));
+    A.need(&c->partials, (size_t)scan_partials_size(scan_n));
     if (resort) {
-        e = e ? e : dalloc(&c->rs_stay, cap * NPB);
-        e = e ? e : dalloc(&c->rs_in, 2 * cap * NPB);
-        e = e ? e : dalloc(&c->rs_oldblk, 2 * cap);
-        e = e ? e : dalloc(&c->rs_cnt, 2 * cap);
-        e = e ? e : dalloc(&c->rs_start, 2 * cap);
-        e = e ? e : dalloc(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
-        e = e ? e : dalloc(&c->it_mov, (size_t)c->work_cap);
-        e = e ? e : dalloc(&c->rs_occ, 2 * cap);
-        e = e ? e : dalloc(&c->nh_keys, H);
-        e = e ? e : dalloc(&c->nh_cnt, H * NPB);
-        e = e ? e : dalloc(&c->nh_idx, H);
-        e = e ? e : dalloc(&c->nh_owner, H);
-        e = e ? e : dalloc(&c->rs_new, cap);
+        A.need(&c->rs_stay, cap * NPB);
+        A.need(&c->rs_in, 2 * cap * NPB);
+        A.need(&c->rs_oldblk, 2 * cap);
+        A.need(&c->rs_cnt, 2 * cap);
+        A.need(&c->rs_start, 2 * cap);
+        A.need(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
+        A.need(&c->it_mov, (size_t)c->work_cap);
+        A.need(&c->rs_occ, 2 * cap);
+        A.need(&c->nh_keys, H);
+        A.need(&c->nh_cnt, H * NPB);
+        A.need(&c->nh_idx, H);
+        A.need(&c->nh_owner, H);
+        A.need(&c->rs_new, cap);
     }
     // rows of cell ranges and neighbour slots, one per entry of a sort that
     // inserts its blocks itself
@@ -438,11 +378,12 @@ int alloc_capacity_buffers(mpm_ctx* c) {
                  : c->dense                        ? std::min(c->tab.ent_cap, DENSE_ROWS)
                                                    : c->block_cap;
     if (c->row_cap > 0) {
-        e = e ? e : dalloc(&c->rs_off, (size_t)c->row_cap * NPB);
-        if (hashed) e = e ? e : dalloc(&c->rs_nslot, (size_t)c->row_cap * NB);
-        if (hashed) e = e ? e : dalloc(&c->h_entry, H);
-        if (!c->dense) e = e ? e : dalloc(&c->b_entry, cap);
+        A.need(&c->rs_off, (size_t)c->row_cap * NPB);
+        if (hashed) A.need(&c->rs_nslot, (size_t)c->row_cap * NB);
+        if (hashed) A.need(&c->h_entry, H);
+        if (!c->dense) A.need(&c->b_entry, cap);
     }
+    hipError_t e = A.commit();
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_capacity_buffers(c);
@@ -774,59 +715,57 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
         int v = atoi(pw);
         if (v >= 1 && v <= 1 << 20) c->p2g_wgs = c->g2p_wgs = v;
     }
-    hipError_t e = hipSuccess;
     const size_t np = (size_t)q->max_particles;
-    e = e ? e : dalloc(&c->k0, np);
-    e = e ? e : dalloc(&c->k1, np);
-    e = e ? e : dalloc(&c->v0, np);
-    e = e ? e : dalloc(&c->v1, np);
-    e = e ? e : dalloc(&c->hist, (size_t)radix_hist_size(q->max_particles));
-    if (!c->dense && !c->adjoint && !c->scan_build && !c->det_order) e = e ? e : dalloc(&c->movers, np);
-    e = e ? e : dalloc(&c->ctr, 1);
-    if (c->adjoint) e = e ? e : dalloc(&c->adj_scratch, np * (size_t)(2 * c->dim + 2 * c->dim * c->dim));
-    if (c->adjoint) e = e ? e : dalloc(&c->adj_part, 2 * (size_t)ADJ_MAX_WGS);
-    if (e == hipSuccess && q->heightmap) {
-        const size_t hn = (size_t)(q->cells[0] + 1) * (size_t)(q->cells[1] + 1);
-        e = dalloc(&c->heightmap, hn);
-        if (e == hipSuccess) e = hipMemcpy(c->heightmap, q->heightmap, hn * sizeof(float), hipMemcpyHostToDevice);
-    }
-    if (e == hipSuccess) e = hipMemset(c->ctr, 0, sizeof(DevCounters));
-    {
-        const long long ids = n_inst > 1 ? (long long)n_inst << c->blk_bits : c->n_blocks_total;
-        const bool each_step = c->dense || c->adjoint || c->scan_build || c->det_order ||
-                               (q->flags & MPM_FLAG_FULL_SORT);
-        if (e == hipSuccess && ids <= TAB_MAX_IDS && (each_step || q->max_particles <= TAB_MAX_ONCE)) {
-            TabSort& t = c->tab;
-            t.ids = (int)ids;
-            t.ent_cap = (int)std::min<long long>(ids, q->max_particles);
-            e = dalloc(&t.cnt, (size_t)ids);
-            e = e ? e : dalloc(&t.start, (size_t)ids);
-            e = e ? e : dalloc(&t.ent, (size_t)t.ent_cap);
-            const size_t tiles = ((size_t)ids + SCAN_TILE - 1) / SCAN_TILE;
-            e = e ? e : dalloc(&t.part, (c->scan_build ? 8 : 4) * tiles);
-            e = e ? e : dalloc(&t.n_ent, 1);
-            if (c->scan_build) {
-                e = e ? e : dalloc(&t.occ, (size_t)ids);
-                e = e ? e : dalloc(&t.eidx, (size_t)ids);
-                e = e ? e : dalloc(&t.box, 8 * tiles);
-            }
-            e = e ? e : launch_tab_init(t, nullptr);
+    const size_t hn = q->heightmap ? (size_t)(q->cells[0] + 1) * (size_t)(q->cells[1] + 1) : 0;
+    Arena& A = c->own;
+    A.need(&c->k0, np);
+    A.need(&c->k1, np);
+    A.need(&c->v0, np);
+    A.need(&c->v1, np);
+    A.need(&c->hist, (size_t)radix_hist_size(q->max_particles));
+    if (!c->dense && !c->adjoint && !c->scan_build && !c->det_order) A.need(&c->movers, np);
+    A.need(&c->ctr, 1);
+    if (c->adjoint) A.need(&c->adj_scratch, np * (size_t)(2 * c->dim + 2 * c->dim * c->dim));
+    if (c->adjoint) A.need(&c->adj_part, 2 * (size_t)ADJ_MAX_WGS);
+    if (hn) A.need(&c->heightmap, hn);
+    const long long ids = n_inst > 1 ? (long long)n_inst << c->blk_bits : c->n_blocks_total;
+    const bool each_step = c->dense || c->adjoint || c->scan_build || c->det_order || (q->flags & MPM_FLAG_FULL_SORT);
+    const bool table = ids <= TAB_MAX_IDS && (each_step || q->max_particles <= TAB_MAX_ONCE);
+    if (table) {
+        TabSort& t = c->tab;
+        const size_t tiles = ((size_t)ids + SCAN_TILE - 1) / SCAN_TILE;
+        t.ids = (int)ids;
+        t.ent_cap = (int)std::min<long long>(ids, q->max_particles);
+        A.need(&t.cnt, (size_t)ids);
+        A.need(&t.start, (size_t)ids);
+        A.need(&t.ent, (size_t)t.ent_cap);
+        A.need(&t.part, (c->scan_build ? 8 : 4) * tiles);
+        A.need(&t.n_ent, 1);
+        if (c->scan_build) {
+            A.need(&t.occ, (size_t)ids);
+            A.need(&t.eidx, (size_t)ids);
+            A.need(&t.box, 8 * tiles);
         }
     }
-    if (e == hipSuccess && c->scan_build) {
-        const long long mm = c->n_blocks_total;
-        e = hipMalloc(&c->sb_mem, sb_scratch_bytes(mm));
-        if (e == hipSuccess) e = dalloc(&c->sb_seg, (size_t)(2 * mm));
-        if (e == hipSuccess) c->sb = sb_carve(c->sb_mem, mm, c->sb_seg, c->sb_seg + mm);
+    if (c->scan_build) {
+        A.need((char**)&c->sb_mem, sb_scratch_bytes(c->n_blocks_total));
+        A.need(&c->sb_seg, (size_t)(2 * c->n_blocks_total));
     }
+    if (n_inst > 1) A.need(&c->inst, (size_t)n_inst);
+    hipError_t e = A.commit();
+    if (e == hipSuccess && hn)
+        e = hipMemcpy(c->heightmap, q->heightmap, hn * sizeof(float), hipMemcpyHostToDevice);
+    if (e == hipSuccess) e = hipMemset(c->ctr, 0, sizeof(DevCounters));
+    if (e == hipSuccess && table) e = launch_tab_init(c->tab, nullptr);
+    if (e == hipSuccess && c->scan_build)
+        c->sb = sb_carve(c->sb_mem, c->n_blocks_total, c->sb_seg, c->sb_seg + c->n_blocks_total);
     if (e == hipSuccess && n_inst > 1) {
         InstMat host[MAX_INSTANCES];
         for (int i = 0; i < n_inst; ++i) {
             const mpm_instance& m = q->instances[i];
             host[i] = make_instmat(c->dim, m.E, m.nu, m.friction_deg, m.dt, m.p_mass, m.p_vol0);
         }
-        e = dalloc(&c->inst, (size_t)n_inst);
-        if (e == hipSuccess) e = hipMemcpy(c->inst, host, n_inst * sizeof(InstMat), hipMemcpyHostToDevice);
+        e = hipMemcpy(c->inst, host, n_inst * sizeof(InstMat), hipMemcpyHostToDevice);
     }
     c->prm.instances = nullptr;
     if (e != hipSuccess) {
@@ -1017,23 +956,25 @@ int mpm_tape_reserve(mpm_ctx* c, int n_slots) {
     if (n_slots == 0) return MPM_OK;
     const size_t NB = (size_t)1 << c->dim, NPB = (size_t)1 << (2 * c->dim);
     const size_t cap = (size_t)c->block_cap, wc = (size_t)c->work_cap, np = (size_t)c->max_particles;
-    hipError_t e = dalloc(&c->tape_ctr, (size_t)n_slots);
-    if (e == hipSuccess) e = hipMemset(c->tape_ctr, 0, (size_t)n_slots * sizeof(DevCounters));
+    Arena& A = c->taped;
+    A.need(&c->tape_ctr, (size_t)n_slots);
     c->tape.resize((size_t)n_slots);
     for (auto& t : c->tape) {
-        e = e ? e : dalloc(&t.b_keys, cap);
-        e = e ? e : dalloc(&t.b_nbr, cap * NB);
-        e = e ? e : dalloc(&t.b_start, cap);
-        e = e ? e : dalloc(&t.b_count, cap);
-        e = e ? e : dalloc(&t.w_block, wc);
-        e = e ? e : dalloc(&t.w_start, wc);
-        e = e ? e : dalloc(&t.w_end, wc);
-        e = e ? e : dalloc(&t.grid, cap * NPB);
-        e = e ? e : dalloc(&t.grid_u, cap * NPB);
-        e = e ? e : dalloc(&t.b_lo, cap * NB);
-        e = e ? e : dalloc(&t.osrc, np);
-        e = e ? e : dalloc(&t.skeys, np);
+        A.need(&t.b_keys, cap);
+        A.need(&t.b_nbr, cap * NB);
+        A.need(&t.b_start, cap);
+        A.need(&t.b_count, cap);
+        A.need(&t.w_block, wc);
+        A.need(&t.w_start, wc);
+        A.need(&t.w_end, wc);
+        A.need(&t.grid, cap * NPB);
+        A.need(&t.grid_u, cap * NPB);
+        A.need(&t.b_lo, cap * NB);
+        A.need(&t.osrc, np);
+        A.need(&t.skeys, np);
     }
+    hipError_t e = A.commit();
+    if (e == hipSuccess) e = hipMemset(c->tape_ctr, 0, (size_t)n_slots * sizeof(DevCounters));
     if (e != hipSuccess) {
         (void)hipGetLastError();
         free_tape(c);
