@@ -59,7 +59,7 @@ class Rollout:
         """Sets of a segment of k steps that starts from `first`."""
         while len(self._pool) < self.K + 1:
             self._pool.append(M.ParticleSet(self.dim, self.n, self.device, zero=False))
-        return [first] + self._pool[1:k + 1]
+        return [first] + self._pool[:k]
 
     def run_forward(self, v0: torch.Tensor, E: float, phi: float, keep_checkpoints=True, record=False):
         """Returns the final ParticleSet (positions in a permuted order, ids carried).
