@@ -447,7 +447,7 @@ bool would_reuse(const mpm_ctx* c, int n) {
 
 // One build.  `reuse`: the previous build's segments, hash table and sorted
 // keys (same particle count) seed an incremental re-sort instead of the full
-// radix sort; the new sorted keys then take the previous ones' buffer.
+// sort; the new sorted keys then take the previous ones' buffer.
 // `keys_ready`: the binning was already done (by the G2P that wrote these
 // positions) into next_bin_buffer(c, reuse).
 int build_once(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool reuse, bool keys_ready = false) {

@@ -1,5 +1,5 @@
 // Incremental re-sort of the particles by owner block: the alternative to the
-// full radix sort (sort.hip) for a build that follows a build of the same
+// full sorts (tabsort.hip, sort.hip) for a build that follows a build of the same
 // number of particles on the same context.
 //
 // The particle at position i of a step's G2P output belongs to the owner

@@ -312,7 +312,7 @@ __device__ __forceinline__ int sb_phi_at(const DevParams& P, const SbBox& B, con
     return p < (unsigned)P.block_cap ? (int)p : -1;
 }
 
-// Upper and lower neighbours (as k_block_setup, looked up in the domain) and
+// Upper and lower neighbours (looked up in the domain) and
 // the chunk count of each block.
 template <int DIM>
 __global__ __launch_bounds__(WG) void k_sb_block_setup(DevParams P, const SbBox* __restrict__ box,

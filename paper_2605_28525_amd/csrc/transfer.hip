@@ -6,7 +6,7 @@
 // Their 3^d stencils cover a (4+2)^d node tile anchored at that block's origin,
 // which spans the block and its upper neighbours (2^d blocks).
 //
-//   P2G: one wave per owner block accumulates the mass and momentum of the
+//   P2G: a workgroup of one or two waves per owner block accumulates the mass and momentum of the
 //        block's particles into an LDS tile and stores the tile to its own slot
 //        in HBM; a second pass gives each node the sum of the (at most 2^d)
 //        tiles that cover it (inside mpm_step it also applies the grid
