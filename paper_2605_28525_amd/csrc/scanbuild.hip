@@ -418,7 +418,7 @@ hipError_t launch_scan_active(const DevParams& P, const float* x, int n, const S
 // its table a bounding box: nothing is read per particle, no mask is gathered
 // twice, and the compaction writes the block tables and the work items, as the
 // hash build's does.  Three launches, each a chain of two or three accesses:
-// 8.6, 5.4 and 3.8 us of a step of 312,500 particles; from the sorted keys it
+// 8.0, 5.5 and 3.8 us of a step of 312,500 particles; from the sorted keys it
 // took twelve, 54 us.
 //
 //   k_sbt_flag   box from the tiles' boxes; node masks of the domain's blocks
@@ -473,31 +473,37 @@ __global__ __launch_bounds__(WG) void k_sbt_flag(DevParams P, TabSort T, SbScrat
     }
     if (blockIdx.x == 0 && threadIdx.x == 0) *S.box = B;
     for (int tile = blockIdx.x; tile * SBT_TILE < B.m; tile += gridDim.x) {
+        // (every load at a clamped index and masked afterwards: behind the bounds'
+        // branches they went out one by one, 8.6 us; an empty block's masks, most of
+        // the box, are still skipped)
+        uint64_t o[SBT_ITEMS][NB];
+        unsigned own[SBT_ITEMS], in[SBT_ITEMS];
+#pragma unroll
+        for (int j = 0; j < SBT_ITEMS; ++j) {
+            int c[3];
+            sb_coords(B, min(tile * SBT_TILE + j * WG + (int)threadIdx.x, (int)B.m - 1), c);
+            in[j] = 0u;
+#pragma unroll
+            for (int d = 0; d < NB; ++d) {
+                const int a0 = c[0] - (d & 1), a1 = c[1] - ((d >> 1) & 1), a2 = c[2] - ((d >> 2) & 1);
+                const int id = sb_linear<DIM>(P, B, max(a0, 0), max(a1, 0), max(a2, 0));
+                o[j][d] = T.occ[id];
+                if (d == 0) own[j] = T.cnt[id];
+                in[j] |= (a0 | a1 | a2) >= 0 ? 1u << d : 0u;
+            }
+        }
         unsigned act = 0u, items = 0u;
 #pragma unroll
         for (int j = 0; j < SBT_ITEMS; ++j) {
             const int t = tile * SBT_TILE + j * WG + (int)threadIdx.x;
-            if (t >= B.m) continue;
-            int c[3];
-            sb_coords(B, t, c);
-            uint64_t o[NB];
-            unsigned own = 0u;
-#pragma unroll
-            for (int d = 0; d < NB; ++d) {
-                const int a0 = c[0] - (d & 1), a1 = c[1] - ((d >> 1) & 1), a2 = c[2] - ((d >> 2) & 1);
-                o[d] = 0ull;
-                if (a0 < 0 || a1 < 0 || a2 < 0) continue;
-                const int id = sb_linear<DIM>(P, B, a0, a1, a2);
-                o[d] = T.occ[id];
-                if (d == 0) own = T.cnt[id];
-            }
             uint64_t mask = 0ull;
 #pragma unroll
             for (int d = 0; d < NB; ++d)
-                if (o[d]) mask |= neighbour_mask<DIM>(o[d], d);
+                if ((in[j] >> d & 1u) && o[j][d]) mask |= neighbour_mask<DIM>(o[j][d], d);
+            if (t >= B.m) continue;
             S.occ[t] = mask;
             act += mask != 0ull ? 1u : 0u;
-            items += block_chunks(P, (int)own);
+            items += block_chunks(P, (int)own[j]);
         }
         unsigned ta, ti;
         wg_excl_scan(act, lds, &ta);
