@@ -62,6 +62,7 @@ struct mpm_ctx {
     int H_log2 = 0;
     int work_cap = 0;
     int chunk = 512;
+    int asked_chunk = 512;  // by a tuning call, or the general default: what mpm_set_tuning checks a block against
     int max_particles = 0;
     bool dense = false;
     int p2g_wgs = 8192;     // persistent workgroups of the P2G launch
@@ -709,7 +710,7 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     if (q->max_particles <= 1 << 18) c->chunk = 256;
     if (const char* ch = getenv("MPMX_CHUNK")) {
         int v = atoi(ch);
-        if (v >= MIN_CHUNK && v <= MAX_CHUNK) c->chunk = v;
+        if (v >= MIN_CHUNK && v <= MAX_CHUNK) c->chunk = c->asked_chunk = v;
     }
     if (const char* pw = getenv("MPMX_WGS")) {
         int v = atoi(pw);
@@ -1200,7 +1201,8 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
         return MPM_ERR_ARG;
     const int new_chunk = chunk ? chunk : c->chunk;
     const int new_block = g2p_block ? g2p_block : c->g2p_block;
-    if (new_chunk > g2p_max_items(new_block)) return MPM_ERR_ARG;
+    if (std::max(new_chunk, chunk ? 0 : c->asked_chunk) > g2p_max_items(new_block)) return MPM_ERR_ARG;
+    if (chunk) c->asked_chunk = chunk;
     if (new_chunk != c->chunk) {
         c->chunk = c->P.chunk = new_chunk;
         ++c->tape_serial;
@@ -1271,7 +1273,7 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
         for (int wi = 0; wi < NW; ++wi)
             if (g2p_ms[si][wi] < g2p_ms[best_s][best_w]) best_s = si, best_w = wi;
     c->g2p_block = shapes[best_s][0];
-    c->chunk = c->P.chunk = shapes[best_s][1];
+    c->chunk = c->asked_chunk = c->P.chunk = shapes[best_s][1];
     c->p2g_wgs = wgs[best_p2g];
     c->g2p_wgs = wgs[best_w];
     c->built = false;

@@ -37,3 +37,21 @@ def test_item_size_does_not_change_a_step(name, dim):
         ref = ref or got
         for k in ref:
             assert np.array_equal(ref[k], got[k]), (chunk, k)
+
+
+def test_kept_item_size_is_the_general_default():
+    """A workgroup size set alone is checked against work items of 512, also in
+    a small context, whose items are of 256."""
+    from paper_2605_28525_amd import mpm as M
+    sim = M.Simulation(wl.collapse_2d())
+    try:
+        for blk in (64, 128):
+            with pytest.raises(M.MPMError):
+                M.mpm_set_tuning(sim.ctx, g2p_block=blk)
+        M.mpm_set_tuning(sim.ctx, g2p_block=256)
+        M.mpm_set_tuning(sim.ctx, chunk=128, g2p_block=64)
+        M.mpm_set_tuning(sim.ctx, g2p_block=128)
+        sim.step(2)
+        assert sim.status()[0] == 0
+    finally:
+        sim.close()
