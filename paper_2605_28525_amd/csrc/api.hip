@@ -734,7 +734,7 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     const bool table = ids <= TAB_MAX_IDS && (each_step || q->max_particles <= TAB_MAX_ONCE);
     if (table) {
         TabSort& t = c->tab;
-        const size_t tiles = ((size_t)ids + SCAN_TILE - 1) / SCAN_TILE;
+        const size_t tile = (size_t)WG * tab_items(ids, c->scan_build), tiles = ((size_t)ids + tile - 1) / tile;
         t.ids = (int)ids;
         t.ent_cap = (int)std::min<long long>(ids, q->max_particles);
         A.need(&t.cnt, (size_t)ids);

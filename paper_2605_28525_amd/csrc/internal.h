@@ -489,6 +489,17 @@ constexpr int radix_passes(int key_bits) { return key_bits <= 8 ? 1 : (key_bits 
 // Largest domain: 32 MB of counts and positions; 4.1 million blocks add 10 us.
 constexpr int TAB_MAX_IDS = 1 << 22;
 constexpr int TAB_MAX_ONCE = 1 << 20;
+// Entries per thread of the scan over the table.  Its tiles are all the
+// parallelism it has (12 tiles of 2048 in the domain of 262,144 particles, a
+// dense grid's block tables written by each thread in turn: 9 us; of 512: 5),
+// and every tile reads the sums of all.  Builds of 262,144 particles with 2 / 8
+// entries: 17,576 blocks hashed 33.8 / 34.5 us, dense 29.7 / 35.4; 250,047 34.7 /
+// 34.8 and 59.4 / 63.6; 438,976 hashed 35.6 / 34.8; 1,061,208 40.1 / 36.6.
+constexpr int TAB_SMALL_IDS = 1 << 18;
+constexpr int TAB_SMALL_ITEMS = 2;
+constexpr int tab_items(long long ids, bool scan_build) {
+    return !scan_build && ids <= TAB_SMALL_IDS ? TAB_SMALL_ITEMS : SCAN_ITEMS;
+}
 struct TabSort {
     unsigned* cnt;    // particles per owner block (instance and linear block); zero between sorts
     unsigned* start;  // first position of each occupied block

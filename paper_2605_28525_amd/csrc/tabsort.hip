@@ -17,7 +17,7 @@
 //            the hash table (hash-built grids): its occupied cells are known.
 //
 // On a dense grid the scan also writes the block tables and work items, as the
-// block index is Phi there (six launches, 22 us of a step of 262,144 particles
+// block index is Phi there (it took six launches, 22 us of a step of 262,144 particles
 // in 23,465 blocks, less), and P2G walks the entries instead of the domain (30
 // us against 40).  For a scan-built context the order leaves each block's
 // occupied cells and the counts stay for the build (scanbuild.hip).
@@ -40,18 +40,18 @@ namespace mpmx {
 
 namespace {
 
-// Per tile of SCAN_TILE table entries: particles and occupied blocks; DENSE: work
+// Per tile of WG ITEMS table entries: particles and occupied blocks; DENSE: work
 // items; SCAN: bounding box of the occupied blocks.
-template <int DIM, TabMode MODE>
+template <int DIM, TabMode MODE, int ITEMS>
 __global__ __launch_bounds__(WG) void k_tab_reduce(DevParams P, TabSort T) {
     __shared__ unsigned lds[WG / 64];
     __shared__ int red[WG / 64][6];
-    const int base = blockIdx.x * SCAN_TILE + threadIdx.x;
-    unsigned c = 0, z = 0, w = 0, v[SCAN_ITEMS];
+    const int base = blockIdx.x * (WG * ITEMS) + threadIdx.x;
+    unsigned c = 0, z = 0, w = 0, v[ITEMS];
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j * WG < T.ids ? T.cnt[base + j * WG] : 0u;
+    for (int j = 0; j < ITEMS; ++j) v[j] = base + j * WG < T.ids ? T.cnt[base + j * WG] : 0u;
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         c += v[j];
         z += v[j] != 0u ? 1u : 0u;
         if (MODE == TAB_DENSE) w += block_chunks(P, (int)v[j]);
@@ -69,7 +69,7 @@ __global__ __launch_bounds__(WG) void k_tab_reduce(DevParams P, TabSort T) {
         int lo[3] = {INT_MAX, INT_MAX, INT_MAX}, hi[3] = {-1, -1, -1};
         if (tz != 0u) {
 #pragma unroll 1
-            for (int j = 0; j < SCAN_ITEMS; ++j) {
+            for (int j = 0; j < ITEMS; ++j) {
                 if (base + j * WG >= T.ids || T.cnt[base + j * WG] == 0u) continue;
                 int bc[3];
                 linear_to_block<DIM>(P, (uint32_t)(base + j * WG), bc);
@@ -90,14 +90,14 @@ __global__ __launch_bounds__(WG) void k_tab_reduce(DevParams P, TabSort T) {
     }
 }
 
-template <TabMode MODE>
+template <TabMode MODE, int ITEMS>
 __global__ __launch_bounds__(WG) void k_tab_down(DevParams P, TabSort T, int tiles) {
     __shared__ unsigned lds[WG / 64], red[WG / 64][5];
     const int lane = __lane_id(), w = threadIdx.x >> 6;
-    const int base = blockIdx.x * SCAN_TILE + threadIdx.x * SCAN_ITEMS;
-    unsigned v[SCAN_ITEMS], s[5] = {0u, 0u, 0u, 0u, 0u}, c = 0u, z = 0u, it = 0u;
+    const int base = blockIdx.x * (WG * ITEMS) + threadIdx.x * ITEMS;
+    unsigned v[ITEMS], s[5] = {0u, 0u, 0u, 0u, 0u}, c = 0u, z = 0u, it = 0u;
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) v[j] = base + j < T.ids ? T.cnt[base + j] : 0u;
+    for (int j = 0; j < ITEMS; ++j) v[j] = base + j < T.ids ? T.cnt[base + j] : 0u;
     // sums of the tiles before this one, and the occupied blocks (DENSE: and
     // the work items) of all
     for (int i = threadIdx.x; i < tiles; i += WG) {
@@ -120,7 +120,7 @@ __global__ __launch_bounds__(WG) void k_tab_down(DevParams P, TabSort T, int til
 #pragma unroll
         for (int q = 0; q < NS; ++q) red[w][q] = s[q];
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         c += v[j];
         z += v[j] != 0u ? 1u : 0u;
         if (MODE == TAB_DENSE) it += block_chunks(P, (int)v[j]);
@@ -150,7 +150,7 @@ __global__ __launch_bounds__(WG) void k_tab_down(DevParams P, TabSort T, int til
     }
     bool over = false;
 #pragma unroll
-    for (int j = 0; j < SCAN_ITEMS; ++j) {
+    for (int j = 0; j < ITEMS; ++j) {
         const int b = base + j;
         if (MODE == TAB_DENSE && b < T.ids) {
             const unsigned k = block_chunks(P, (int)v[j]);
@@ -387,14 +387,20 @@ template <int DIM, TabMode MODE>
 hipError_t tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, uint32_t* rank, uint32_t* tmp,
                     uint32_t* order, uint32_t* skeys, int n, unsigned H, hipStream_t s) {
     constexpr bool HASH = MODE == TAB_HASH;
-    const int g = (n + WG - 1) / WG, tiles = (T.ids + SCAN_TILE - 1) / SCAN_TILE;
+    const int items = tab_items(T.ids, MODE == TAB_SCAN);
+    const int g = (n + WG - 1) / WG, tiles = (T.ids + WG * items - 1) / (WG * items);
     const int go = std::max(1, std::min(T.ent_cap, 2048));  // what the chip holds
     int bits = 1;
     while (bits < 30 && (1 << bits) < n) ++bits;
     // (hash: at least 64 workgroups for the clearing)
     if (n > 0) k_tab_count<DIM, HASH><<<HASH ? std::max(g, 64) : g, WG, 0, s>>>(P, T, keys, rank, n, H);
-    k_tab_reduce<DIM, MODE><<<tiles, WG, 0, s>>>(P, T);
-    k_tab_down<MODE><<<tiles, WG, 0, s>>>(P, T, tiles);
+    if (MODE != TAB_SCAN && items == TAB_SMALL_ITEMS) {
+        k_tab_reduce<DIM, MODE, TAB_SMALL_ITEMS><<<tiles, WG, 0, s>>>(P, T);
+        k_tab_down<MODE, TAB_SMALL_ITEMS><<<tiles, WG, 0, s>>>(P, T, tiles);
+    } else {
+        k_tab_reduce<DIM, MODE, SCAN_ITEMS><<<tiles, WG, 0, s>>>(P, T);
+        k_tab_down<MODE, SCAN_ITEMS><<<tiles, WG, 0, s>>>(P, T, tiles);
+    }
     if (n > 0) {
         k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
         k_tab_order<DIM, MODE><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);

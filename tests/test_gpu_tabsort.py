@@ -130,6 +130,39 @@ def test_order_around_table_tiles(cells):
         sim.close()
 
 
+@pytest.mark.parametrize("grid", ["sparse", "dense"])
+@pytest.mark.parametrize("cells", [(31, 31, 31), (32, 31, 31), (2047, 2047), (2048, 2047)])
+def test_order_around_the_scan_s_sizes(cells, grid):
+    """Domains of 512 and 576 blocks (one tile of the short scan, and two) and
+    of 2^18 and 262,656 (the last with short tiles, and past it); particles in
+    random order everywhere, in the first and in the last block."""
+    import torch
+    from paper_2605_28525_amd import mpm as M
+    dim = len(cells)
+    w = wl.tiny_3d(n=48, ties=False) if dim == 3 else wl.collapse_2d()
+    w.dim, w.dx, w.cells = dim, 0.25, cells
+    rng = np.random.default_rng(12)
+    top = np.asarray(cells, np.float64)[:, None] - 0.6
+    x = np.concatenate([rng.uniform(0.6, top, (dim, 3000)), rng.uniform(0.6, 2.0, (dim, 70)),
+                        rng.uniform(top - 1.0, top, (dim, 70))], axis=1)
+    x = x[:, rng.permutation(x.shape[1])] * w.dx
+    for k, a in _state(x, 4).items():
+        setattr(w, k, a)
+    _announce("table sort, scan size", cells, grid)
+    sim = M.Simulation(w, flags=M.MPM_FLAG_FULL_SORT, block_capacity=1 << 14,  # up to 4 blocks a particle
+                       grid_mode=M.MPM_GRID_DENSE if grid == "dense" else M.MPM_GRID_SPARSE)
+    try:
+        M.mpm_sparse_build(sim.ctx, sim.a.view())
+        M.mpm_p2g(sim.ctx, sim.a.view())
+        order = torch.empty(w.n, dtype=torch.int32, device="cuda")
+        M.mpm_get_order(sim.ctx, order, w.n)
+        rc, f = sim.status()
+        assert rc == 0, f
+        assert np.array_equal(order.cpu().numpy(), expected_order(w.x, w.dx, cells, dim))
+    finally:
+        sim.close()
+
+
 def test_order_of_an_ensemble():
     """Instances first, then blocks: the particles shuffled across instances."""
     import torch
