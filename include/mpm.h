@@ -346,7 +346,8 @@ int mpm_step_adj(mpm_ctx* ctx, const mpm_particles* in, const mpm_particles* out
  *   one size, consecutive ones distinct; runs n_steps steps, step j from
  *   states[j] to states[j+1] (as mpm_step on that pair), keeping slot j.
  *   n_steps <= n_slots.  Afterwards no build is current (mpm_p2g etc. need a
- *   new mpm_sparse_build).
+ *   new mpm_sparse_build).  A slot keeps the work item size it was recorded
+ *   with: mpm_set_tuning and mpm_autotune do not change what is on the tape.
  * mpm_tape_adjoint: the reverse sweep over the same steps and the same sets,
  *   unchanged since mpm_tape_forward: on entry `bar` holds dL/d(states[n_steps])
  *   (in that set's order), on return dL/d(states[0]) (in states[0]'s order);

@@ -142,10 +142,11 @@ struct mpm_ctx {
         float4 *grid = nullptr, *grid_u = nullptr;
         int* b_lo = nullptr;
         uint32_t *osrc = nullptr, *skeys = nullptr;
+        int chunk = 0;  // particles per work item when it was recorded
     };
     Arena own, sized, taped;  // per context; by the capacities; the tape's slots
     std::vector<TapeSlot> tape;
-    long long tape_serial = 0;  // changes with the slots' contents, or with what reads them (the chunk size)
+    long long tape_serial = 0;  // changes with the slots' contents
     DevCounters* tape_ctr = nullptr;  // one per slot
 };
 
@@ -535,6 +536,7 @@ void bind_slot(mpm_ctx* c, int j) {
     c->P.w_end = t.w_end;
     c->P.grid = t.grid;
     c->P.grid_u = t.grid_u;
+    c->P.chunk = t.chunk;
     c->P.ctr = c->tape_ctr + j;
 }
 
@@ -998,6 +1000,7 @@ int mpm_tape_forward(mpm_ctx* c, const mpm_particles* states, int n_steps, void*
     const DevParams saved = c->P;
     const bool any = states[0].n > 0;
     for (int j = 0; j < n_steps && st == MPM_OK; ++j) {
+        c->tape[(size_t)j].chunk = c->chunk;
         bind_slot(c, j);
         // the sort and P2G write the slot's arrays; the grid update and the
         // next step's binning run where mpm_step runs them
@@ -1205,7 +1208,6 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
     if (chunk) c->asked_chunk = chunk;
     if (new_chunk != c->chunk) {
         c->chunk = c->P.chunk = new_chunk;
-        ++c->tape_serial;
         c->built = false;  // work items of the last build used the old size
     }
     c->g2p_block = new_block;
@@ -1217,7 +1219,6 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
 int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int* chosen, void* stream) {
     if (!c || !particles_ok(c, a, true) || !b || b->n != a->n) return MPM_ERR_ARG;
     hipStream_t s = (hipStream_t)stream;
-    ++c->tape_serial;
     // (G2P workgroup size, particles per work item) pairs, persistent workgroup counts
     static const int shapes[][2] = {{64, 64},   {64, 128},  {128, 128}, {128, 256},
                                     {256, 256}, {256, 512}, {256, 768}};
