@@ -56,7 +56,8 @@ struct mpm_ctx {
     mpm_params prm;
     int dim = 3;
     int nblk[3] = {1, 1, 1};
-    long long n_blocks_total = 0;
+    long long n_blocks_total = 0;  // of one instance's domain
+    long long block_max = 0;       // of all instances: what can be active at most
     int key_bits = 0;
     int block_cap = 0;
     int H_log2 = 0;
@@ -574,7 +575,7 @@ int sparse_build(mpm_ctx* c, const mpm_particles* p, hipStream_t s, bool keys_re
             if (st != MPM_OK) return st;
             if (!(h.flags & MPM_FLAG_OVERFLOW)) break;
             const long long want = std::max<long long>(2ll * c->block_cap, (long long)h.n_touched);
-            c->block_cap = (int)std::min<long long>(want, c->n_blocks_total);
+            c->block_cap = (int)std::min<long long>(want, c->block_max);
             if (c->H_log2 < 30) ++c->H_log2;
             while ((1ll << c->H_log2) < 2ll * c->block_cap && c->H_log2 < 30) ++c->H_log2;
             st = alloc_capacity_buffers(c);
@@ -679,6 +680,7 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
         total *= c->nblk[a];
     }
     c->n_blocks_total = total;
+    c->block_max = total * n_inst;
     c->n_inst = n_inst;
     c->blk_bits = bits_for(total - 1);
     // sort key: instance | linear block | local cell, all in 32 bits
@@ -695,7 +697,7 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     } else {
         long long def = std::max(4096ll, 2ll * q->max_particles / (1 << (2 * c->dim)) + 4096ll);
         long long cap = q->block_capacity > 0 ? q->block_capacity : def;
-        c->block_cap = (int)std::min(cap, total + 0ll);
+        c->block_cap = (int)std::min(cap, c->block_max);
     }
     {
         int hl = q->hash_capacity_log2;
