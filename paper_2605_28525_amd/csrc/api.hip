@@ -1207,11 +1207,12 @@ int mpm_set_tuning(mpm_ctx* c, int chunk, int g2p_block, int p2g_workgroups, int
     const int new_chunk = chunk ? chunk : c->chunk;
     const int new_block = g2p_block ? g2p_block : c->g2p_block;
     if (std::max(new_chunk, chunk ? 0 : c->asked_chunk) > g2p_max_items(new_block)) return MPM_ERR_ARG;
+    // Another size than the one in force needs a new build.  The one in force
+    // counts as asked_chunk, also where the items are smaller (small contexts'
+    // default): the transfers take smaller items than c->chunk as they are.
+    if (chunk && chunk != c->asked_chunk) c->built = false;
     if (chunk) c->asked_chunk = chunk;
-    if (new_chunk != c->chunk) {
-        c->chunk = c->P.chunk = new_chunk;
-        c->built = false;  // work items of the last build used the old size
-    }
+    c->chunk = c->P.chunk = new_chunk;
     c->g2p_block = new_block;
     if (p2g_workgroups) c->p2g_wgs = p2g_workgroups;
     if (g2p_workgroups) c->g2p_wgs = g2p_workgroups;
