@@ -754,8 +754,9 @@ __global__ __launch_bounds__(64 * NW) void k_scatter_adj(DevParams P, int n, con
             sa += __shfl_xor(sa, o);
         }
         if (threadIdx.x == 0) {
-            P.param_bar[0] += (float)se;
-            P.param_bar[1] += (float)(sa * (double)P.dalpha_dphi);
+            // (the accumulator is the caller's: several contexts may add to one)
+            atomicAdd(&P.param_bar[0], (float)se);
+            atomicAdd(&P.param_bar[1], (float)(sa * (double)P.dalpha_dphi));
         }
     }
     for (int b = blockIdx.x; b < nb; b += gridDim.x) {
