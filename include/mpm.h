@@ -390,8 +390,11 @@ int mpm_set_tuning(mpm_ctx* ctx, int chunk, int g2p_block, int p2g_workgroups, i
  * 64), (64, 128), (128, 128), (128, 256), (256, 256), (256, 512), (256, 768)}
  * x persistent workgroups in {1024, 2048, 4096, 8192}) runs one warm-up and 5 timed steps
  * that read a and write b (a is left unchanged; b ends one step ahead of a;
- * G2P as inside mpm_step, binning and counting for a next build),
- * keeps the fastest P2G workgroup count and the fastest G2P shape, and
+ * P2G, grid update and G2P as in a step of mpm_step before a call's last: G2P
+ * bins and counts for a next build, and forms the nodes it reads where
+ * mpm_step has it do so), keeps the fastest P2G workgroup count and the fastest
+ * G2P shape (its time with P2G's where the shapes share that work out
+ * differently), and
  * reports them in chosen[4] = {chunk, g2p_block, p2g_workgroups,
  * g2p_workgroups} (host ints, may be NULL).  Synchronises the stream. */
 int mpm_autotune(mpm_ctx* ctx, const mpm_particles* a, const mpm_particles* b, int* chosen, void* stream);

@@ -871,6 +871,20 @@ int mpm_g2p(mpm_ctx* c, const mpm_particles* in, const mpm_particles* out, void*
     return g2p_impl(c, in, out, (hipStream_t)stream, nullptr, nullptr);
 }
 
+namespace {
+// How mpm_step runs P2G's second pass and the grid update.  On a sparse grid the
+// update runs inside the second pass (the grid between the two is not visible
+// to the caller there; the reverse mode's copy of it is written either way);
+// with zero particles it still runs on its own.  Between two steps nothing else
+// reads the grid either, and small steps leave both to G2P (`last`: the grid
+// stays readable).
+P2GSecond step_second(const mpm_ctx* c, int n, bool last) {
+    if (c->dense || n == 0) return P2G_SUM;
+    const bool gather = !last && !c->adjoint && n <= G2P_GATHER_MAX_N && c->g2p_block == 256 && c->chunk <= 512;
+    return gather ? P2G_LEFT_TO_G2P : P2G_UPDATE;
+}
+}  // namespace
+
 int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_steps, void* stream) {
     if (!c || !a || !b || n_steps < 0 || a->n != b->n) return MPM_ERR_ARG;
     if (!particles_ok(c, a, true) || !particles_ok(c, b, true)) return MPM_ERR_ARG;
@@ -880,16 +894,9 @@ int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_s
     bool keys_ready = false;  // the previous step's G2P binned the positions it wrote
     for (int k = 0; k < n_steps; ++k) {
         int st = sparse_build(c, cur, s, keys_ready);
-        // on a sparse grid the grid update runs inside P2G's second pass (the
-        // grid between the two is not visible to the caller here; the reverse
-        // mode's copy of it is written either way); with zero particles the
-        // grid update still runs on its own
-        const bool fuse_update = !c->dense && cur->n > 0;
-        // between two steps nothing else reads the grid either
-        const bool gather = fuse_update && k + 1 < n_steps && !c->adjoint && cur->n <= G2P_GATHER_MAX_N &&
-                            c->g2p_block == 256 && c->chunk <= 512;
-        if (st == MPM_OK) st = p2g_impl(c, cur, s, gather ? P2G_LEFT_TO_G2P : fuse_update ? P2G_UPDATE : P2G_SUM);
-        if (st == MPM_OK && !fuse_update) st = mpm_grid_update(c, stream);
+        const P2GSecond second = step_second(c, cur->n, k + 1 == n_steps);
+        if (st == MPM_OK) st = p2g_impl(c, cur, s, second);
+        if (st == MPM_OK && second == P2G_SUM) st = mpm_grid_update(c, stream);
         // Between two steps of this call nothing else touches the positions,
         // so G2P bins them as it writes them.
         keys_ready = k + 1 < n_steps && cur->n > 0;
@@ -897,7 +904,7 @@ int mpm_step(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int n_s
         uint32_t* keys_out = keys_ready ? next_bin_buffer(c, next_reuse) : nullptr;
         // with an incremental re-sort next, G2P also does its counting
         uint32_t* movers_out = keys_ready && next_reuse ? c->movers : nullptr;
-        if (st == MPM_OK) st = g2p_impl(c, cur, nxt, s, keys_out, movers_out, gather);
+        if (st == MPM_OK) st = g2p_impl(c, cur, nxt, s, keys_out, movers_out, second == P2G_LEFT_TO_G2P);
         if (st != MPM_OK) return st;
         std::swap(cur, nxt);
     }
@@ -1231,10 +1238,12 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
     int st = MPM_OK;
     for (int i = 0; i < 4 && st == MPM_OK; ++i)
         if (hipEventCreate(&ev[i]) != hipSuccess) st = MPM_ERR_HIP;
-    double p2g_ms[NW] = {0}, g2p_ms[NS][NW] = {{0}};
-    // Every trial reads a and writes b, so a is left as it was.  P2G does not
-    // depend on the G2P shape: its time per workgroup count is summed over
-    // the shapes.
+    double p2g_ms[NW] = {0}, g2p_ms[NS][NW] = {{0}}, second_ms[NS] = {0};
+    bool any_gather = false;  // whether the shapes differ in who runs P2G's second pass
+    // Every trial reads a and writes b, so a is left as it was, and runs the
+    // transfers as a step of mpm_step that is not a call's last.  P2G's first
+    // pass does not depend on the G2P shape: its time per workgroup count is
+    // summed over the shapes.
     for (int si = 0; si < NS && st == MPM_OK; ++si) {
         for (int wi = 0; wi < NW && st == MPM_OK; ++wi) {
             c->g2p_block = shapes[si][0];
@@ -1243,17 +1252,20 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
             for (int r = 0; r <= REPS && st == MPM_OK; ++r) {
                 st = mpm_sparse_build(c, a, s);
                 if (st == MPM_OK && hipEventRecord(ev[0], s) != hipSuccess) st = MPM_ERR_HIP;
-                if (st == MPM_OK) st = mpm_p2g(c, a, s);
+                const P2GSecond second = step_second(c, a->n, false);
+                const bool gather = second == P2G_LEFT_TO_G2P;
+                any_gather = any_gather || gather;
+                if (st == MPM_OK) st = p2g_impl(c, a, s, second);
                 if (st == MPM_OK && hipEventRecord(ev[1], s) != hipSuccess) st = MPM_ERR_HIP;
-                if (st == MPM_OK) st = mpm_grid_update(c, s);
+                if (st == MPM_OK && second == P2G_SUM) st = mpm_grid_update(c, s);
                 if (st == MPM_OK && hipEventRecord(ev[2], s) != hipSuccess) st = MPM_ERR_HIP;
                 if (st == MPM_OK) {
-                    // G2P as inside mpm_step: it also bins and counts for the
-                    // next build (which the next trial's build ignores)
+                    // (G2P also bins and counts for the next build, which the
+                    // next trial's build ignores)
                     const bool next_reuse = would_reuse(c, b->n);
                     uint32_t* keys_out = a->n > 0 ? next_bin_buffer(c, next_reuse) : nullptr;
                     uint32_t* movers_out = keys_out && next_reuse ? c->movers : nullptr;
-                    st = g2p_impl(c, a, b, s, keys_out, movers_out);
+                    st = g2p_impl(c, a, b, s, keys_out, movers_out, gather);
                 }
                 if (st == MPM_OK && hipEventRecord(ev[3], s) != hipSuccess) st = MPM_ERR_HIP;
                 if (st == MPM_OK && hipEventSynchronize(ev[3]) != hipSuccess) st = MPM_ERR_HIP;
@@ -1263,6 +1275,7 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
                     hipEventElapsedTime(&t_g2p, ev[2], ev[3]) != hipSuccess)
                     st = MPM_ERR_HIP;
                 p2g_ms[wi] += t_p2g;
+                second_ms[si] += t_p2g / NW;
                 g2p_ms[si][wi] += t_g2p;
             }
         }
@@ -1270,6 +1283,11 @@ int mpm_autotune(mpm_ctx* c, const mpm_particles* a, const mpm_particles* b, int
     for (int i = 0; i < 4; ++i)
         if (ev[i]) (void)hipEventDestroy(ev[i]);
     if (st != MPM_OK) return st;
+    // where G2P takes over the second pass for some shapes, the others' cost
+    // includes their P2G's (of its mean over the workgroup counts)
+    if (any_gather)
+        for (int si = 0; si < NS; ++si)
+            for (int wi = 0; wi < NW; ++wi) g2p_ms[si][wi] += second_ms[si];
     int best_p2g = 0, best_s = 0, best_w = 0;
     for (int wi = 1; wi < NW; ++wi)
         if (p2g_ms[wi] < p2g_ms[best_p2g]) best_p2g = wi;
