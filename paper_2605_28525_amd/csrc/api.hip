@@ -735,9 +735,15 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     if (hn) A.need(&c->heightmap, hn);
     const long long ids = n_inst > 1 ? (long long)n_inst << c->blk_bits : c->n_blocks_total;
     const bool each_step = c->dense || c->adjoint || c->scan_build || c->det_order || (q->flags & MPM_FLAG_FULL_SORT);
-    const bool table = ids <= TAB_MAX_IDS && (each_step || q->max_particles <= TAB_MAX_ONCE);
+    // particles of a full cell at rest (what the host knows of the blocks' occupancy)
+    double vol = n_inst > 1 ? q->instances[0].p_vol0 : q->p_vol0;
+    for (int i = 1; i < n_inst; ++i) vol = std::min<double>(vol, q->instances[i].p_vol0);
+    const double per_cell = pow(q->dx, q->dim) / vol, per_block = per_cell * (1 << (2 * q->dim));
+    const bool table = ids <= TAB_MAX_IDS && per_cell <= TAB_MAX_PER_CELL && per_block <= TAB_MAX_PER_BLOCK &&
+                       (each_step || q->max_particles <= TAB_MAX_ONCE);
     if (table) {
         TabSort& t = c->tab;
+        t.stage = 1.5 * per_block <= TAB_STAGE ? TAB_STAGE : TAB_STAGE_MAX;
         const size_t tile = (size_t)WG * tab_items(ids, c->scan_build), tiles = ((size_t)ids + tile - 1) / tile;
         t.ids = (int)ids;
         t.ent_cap = (int)std::min<long long>(ids, q->max_particles);

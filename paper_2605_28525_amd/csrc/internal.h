@@ -484,7 +484,7 @@ constexpr int radix_passes(int key_bits) { return key_bits <= 8 ? 1 : (key_bits 
 // domain) that were in order, as every step after the first finds them: 29 / 32 /
 // 68 / 109 us, by radix passes 96 / 122 / 165 / 221; in random order 30 / 71 /
 // 228 / 397, by radix passes 96 / 123 / 165 / 222 (the two lines cross at 1.2
-// million).  So a context that sorts in every step takes the table, one that
+// million; all with 8 particles per cell).  So a context that sorts in every step takes the table, one that
 // sorts only for its first build takes it up to TAB_MAX_ONCE particles.
 // Largest domain: 32 MB of counts and positions; 4.1 million blocks add 10 us.
 constexpr int TAB_MAX_IDS = 1 << 22;
@@ -500,6 +500,22 @@ constexpr int TAB_SMALL_ITEMS = 2;
 constexpr int tab_items(long long ids, bool scan_build) {
     return !scan_build && ids <= TAB_SMALL_IDS ? TAB_SMALL_ITEMS : SCAN_ITEMS;
 }
+// Particles of a block that a workgroup puts in order in LDS (5 bytes each): up to
+// TAB_BATCH they are held in registers meanwhile; up to TAB_STAGE as many
+// workgroups stay resident as the wave slots take; contexts whose full cells hold
+// more (half as many again as at rest still fit) stage up to TAB_STAGE_MAX.  What
+// does not fit is ordered by one wave in passes over global memory.
+// Above TAB_MAX_PER_CELL particles in a cell at rest the order within a cell, which
+// each particle finds by counting the smaller indices of its cell, costs more
+// than the radix passes, above TAB_MAX_PER_BLOCK in a block the two readings do, and
+// those contexts keep the radix sort.  Full steps of 262,144 particles with 8 / 27 / 64 / 125 per cell by the table 75 / 107 / 198 / 467
+// us, by radix passes 162 / 164 / 200 / 318 (with blocks of more than 1024
+// particles left to one wave 75 / 193 / 335 / 632); 2D with 16 / 64 / 100 / 144 per
+// cell 75 / 126 / 145 / 206, radix 118 / 147 / 149 / 175, on a dense grid 55 / 111 /
+// 137 / 199 and 95 / 132 / 163 / 169; 2.1 million with 27 per cell 290 (308 staging
+// 8192), radix 360.
+constexpr int TAB_BATCH = 1024, TAB_STAGE = 3072, TAB_STAGE_MAX = 8192;
+constexpr double TAB_MAX_PER_CELL = 110.0, TAB_MAX_PER_BLOCK = 4608.0;
 struct TabSort {
     unsigned* cnt;    // particles per owner block (instance and linear block); zero between sorts
     unsigned* start;  // first position of each occupied block
@@ -508,6 +524,7 @@ struct TabSort {
                       // 8 for a scan-built context, whose build keeps its own there afterwards)
     int* n_ent;
     int ids, ent_cap;
+    int stage;  // particles of a block that fit LDS: TAB_STAGE or TAB_STAGE_MAX
     // scan-built contexts: occupied base cells and entry of each block (occ zero
     // between builds), bounding box of each tile's occupied blocks
     uint64_t* occ;

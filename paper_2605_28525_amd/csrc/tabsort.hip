@@ -1,7 +1,7 @@
 // Full sort of the particles by (owner block, base cell), stable, by counting in
 // a table of every owner block of the potential domain.  Gives exactly the order
 // of the radix sort (sort.hip), which serves domains too large for a table
-// (TAB_MAX_IDS).
+// (TAB_MAX_IDS) and cells too full (TAB_MAX_PER_CELL).
 //
 //   count    one thread per particle: lanes of a wave that share a block are
 //            merged, one add per block and wave claims their places in the
@@ -214,8 +214,6 @@ __global__ __launch_bounds__(WG) void k_tab_place(TabSort T, const uint32_t* __r
 
 namespace {
 
-constexpr int TAB_STAGE = 1024;  // particles of a block that a workgroup orders in LDS
-
 // A block too full for LDS: LSD radix passes by the wave over its c indices
 // (8-bit digits of the index, then the cell), a -> b -> a ..., ending in b.
 // cnt64: particles per cell on return (lane = cell).
@@ -282,9 +280,9 @@ __device__ void wave_radix(uint32_t* a, uint32_t* b, int c, int idx_bits, const 
 template <int DIM, TabMode MODE>
 __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const uint32_t* __restrict__ keys,
                                                   uint32_t* tmp, uint32_t* order, uint32_t* skeys, int n, int idx_bits) {
-    constexpr int CB = 2 * DIM, NC = 1 << CB, NB = 1 << DIM, R = TAB_STAGE / WG;
-    __shared__ uint32_t sidx[TAB_STAGE];
-    __shared__ unsigned char scell[TAB_STAGE];
+    constexpr int CB = 2 * DIM, NC = 1 << CB, NB = 1 << DIM, R = TAB_BATCH / WG;
+    extern __shared__ uint32_t sidx[];                              // T.stage indices
+    unsigned char* const scell = (unsigned char*)(sidx + T.stage);  // and their cells
     __shared__ unsigned cnt[NC], first[NC], hist[256];
     const int lane = __lane_id(), t = threadIdx.x;
     const int ne = min(*T.n_ent, T.ent_cap);
@@ -292,10 +290,37 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
         const uint4 en = T.ent[e];
         const uint32_t id = en.x;
         const int st = (int)en.y, c = min((int)en.z, n - st);
-        const bool staged = c <= TAB_STAGE;
+        const bool staged = c <= T.stage;
         if (t < NC) cnt[t] = 0u;
         __syncthreads();
-        if (staged) {
+        if (staged && c > TAB_BATCH) {
+            // more particles than the registers hold: counted, then read again
+            auto batch = [&](auto&& f) {
+                for (int r0 = 0; r0 < c; r0 += R * WG) {
+                    uint32_t ix[R];
+                    unsigned cl[R];
+#pragma unroll
+                    for (int r = 0; r < R; ++r) ix[r] = r0 + r * WG + t < c ? tmp[st + r0 + r * WG + t] : 0u;
+#pragma unroll
+                    for (int r = 0; r < R; ++r) cl[r] = r0 + r * WG + t < c ? keys[ix[r]] & (NC - 1) : 0u;
+#pragma unroll
+                    for (int r = 0; r < R; ++r)
+                        if (r0 + r * WG + t < c) f(ix[r], cl[r]);
+                }
+            };
+            batch([&](uint32_t, unsigned cl) { atomicAdd(&cnt[cl], 1u); });
+            __syncthreads();
+            if (t < 64) {
+                const unsigned m = t < NC ? cnt[t] : 0u, f = wave_incl_scan(m) - m;
+                if (t < NC) first[t] = hist[t] = f;
+            }
+            __syncthreads();
+            batch([&](uint32_t ix, unsigned cl) {
+                const unsigned p = atomicAdd(&hist[cl], 1u);
+                sidx[p] = ix;
+                scell[p] = (unsigned char)cl;
+            });
+        } else if (staged) {
             uint32_t ix[R];
             unsigned cl[R], at[R];
 #pragma unroll
@@ -403,7 +428,7 @@ hipError_t tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, 
     }
     if (n > 0) {
         k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
-        k_tab_order<DIM, MODE><<<go, WG, 0, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+        k_tab_order<DIM, MODE><<<go, WG, (size_t)T.stage * 5, s>>>(P, T, keys, tmp, order, skeys, n, bits);
     }
     return hipGetLastError();
 }
