@@ -183,6 +183,38 @@ __global__ __launch_bounds__(WG) void k_count_items(DevParams P, int H) {
     if (threadIdx.x == 0) P.t_cnt[blockIdx.x * LINE + 1] = tot;
 }
 
+// Running sums of the tiles' counts, for tables of many tiles (one workgroup).
+__global__ __launch_bounds__(WG) void k_tile_sums(DevParams P, int tiles) {
+    __shared__ unsigned lds[WG / 64];
+    constexpr int R = 8;  // tiles per thread and round, their loads issued together
+    unsigned c0 = 0u, w0 = 0u;
+    for (int b = 0; b < tiles; b += R * WG) {
+        const int t0 = b + (int)threadIdx.x * R;
+        unsigned c[R], w[R], cs = 0u, ws = 0u, ct, wt;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = t0 + r < tiles;
+            c[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE] : 0u;
+            w[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE + 1] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            cs += c[r];
+            ws += w[r];
+        }
+        unsigned ca = c0 + wg_excl_scan(cs, lds, &ct), wa = w0 + wg_excl_scan(ws, lds, &wt);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (t0 + r < tiles) *(uint2*)&P.t_pre[2 * (size_t)(t0 + r)] = make_uint2(ca, wa);
+            ca += c[r];
+            wa += w[r];
+        }
+        c0 += ct;
+        w0 += wt;
+    }
+    if (threadIdx.x == 0) *(uint2*)&P.t_pre[2 * (size_t)tiles] = make_uint2(c0, w0);
+}
+
 // Compaction: Phi in slot order and the block tables, one workgroup per tile of
 // SCAN_TILE slots, whose occupied slots and work items the insertion counted
 // (t_cnt), so that each tile adds up the counts before it and no pass over the
@@ -211,7 +243,7 @@ __global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int ti
     }
     // sums over the tiles: occupied slots and items before this one, and all
     unsigned sum[4] = {0u, 0u, 0u, 0u};
-    for (int i = threadIdx.x; i < tiles; i += WG) {
+    for (int i = threadIdx.x; i < (P.t_pre ? 0 : tiles); i += WG) {
         const unsigned c = P.t_cnt[i * LINE], it = P.t_cnt[i * LINE + 1];
         sum[0] += i < (int)blockIdx.x ? c : 0u;
         sum[1] += i < (int)blockIdx.x ? it : 0u;
@@ -250,6 +282,12 @@ __global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int ti
         it0 += red[q][1];
         total += red[q][2];
         wtotal += red[q][3];
+    }
+    if (P.t_pre) {
+        phi0 = P.t_pre[2 * (size_t)blockIdx.x];
+        it0 = P.t_pre[2 * (size_t)blockIdx.x + 1];
+        total = P.t_pre[2 * (size_t)tiles];
+        wtotal = P.t_pre[2 * (size_t)tiles + 1];
     }
     bool over = false;
 #pragma unroll 1
@@ -502,6 +540,7 @@ hipError_t build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsign
             if (!det) k_count_items<<<tiles, WG, 0, s>>>(P, (int)H);
         }
     }
+    if (P.t_pre) k_tile_sums<<<1, WG, 0, s>>>(P, tiles);
     // without the key order, Phi is slot order and the compaction also writes
     // the work items
     if (!det) {

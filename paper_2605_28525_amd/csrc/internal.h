@@ -62,6 +62,12 @@ constexpr int LINE = 32;
 // against 14.0 + 9.5 for the scan, P2G +3 us against a 7 us pass; 20 M: 82
 // against 68 + 9, P2G +30 us against 10).
 constexpr int FOLD_MAX_N = 1 << 22;
+// Tiles of the hash table up to which each tile of the compaction adds up the
+// counts of the tiles before it, a line each; above, one workgroup makes their
+// running sums first.  Steps of 262,144 particles with a table of 2^21 / 2^22 / 2^23 /
+// 2^24 / 2^25 slots (2048 in a tile) in 76 / 84 / 93 / 113 / 190 us, without the extra
+// launch 73 / 90 / 136 / 321 / 1120.
+constexpr int FOLD_MAX_TILES = 1024;
 
 // Up to this many particles mpm_step leaves P2G's second pass to G2P, except in
 // its last step, whose grid stays readable: a launch less, against nodes formed
@@ -108,6 +114,8 @@ struct DevParams {
     int* h_nslot;           // hash-built tables: per slot of an owner block, the slots of the 2^d
                             // blocks its stencils reach (d = 0: itself; -1: not reached)
     unsigned* t_cnt;        // per SCAN_TILE slots, LINE words apart: occupied ones, work items
+    unsigned* t_pre;        // large tables: sums of t_cnt over the tiles before each, and over all (2 words
+                            // each); null: every tile of the compaction adds them up itself
     unsigned h_mask_bits;   // H - 1
     int n_probe;
     // compact blocks
