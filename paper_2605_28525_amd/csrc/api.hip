@@ -747,6 +747,7 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
                        (each_step || q->max_particles <= TAB_MAX_ONCE);
     if (table) {
         TabSort& t = c->tab;
+        t.waves = per_block <= TAB_WAVE_MEAN;
         t.stage = 1.5 * per_block <= TAB_STAGE ? TAB_STAGE : TAB_STAGE_MAX;
         const size_t tile = (size_t)WG * tab_items(ids, c->scan_build), tiles = ((size_t)ids + tile - 1) / tile;
         t.ids = (int)ids;

@@ -522,6 +522,11 @@ constexpr int tab_items(long long ids, bool scan_build) {
 // cell 75 / 126 / 145 / 206, radix 118 / 147 / 149 / 175, on a dense grid 55 / 111 /
 // 137 / 199 and 95 / 132 / 163 / 169; 2.1 million with 27 per cell 290 (308 staging
 // 8192), radix 360.
+// Blocks of up to TAB_WAVE particles are ordered by a wave each where a block at rest
+// holds TAB_WAVE_MEAN or fewer: full steps of 4 million particles in 2D with 4 per cell
+// (64 in a block) 516 us, a workgroup each 644, the radix sort 597; 16,641 with 9 per
+// cell (144) 47.6 by waves and 45.9 by workgroups.
+constexpr int TAB_WAVE = 128, TAB_WAVE_MEAN = 96;
 constexpr int TAB_BATCH = 1024, TAB_STAGE = 3072, TAB_STAGE_MAX = 8192;
 constexpr double TAB_MAX_PER_CELL = 110.0, TAB_MAX_PER_BLOCK = 4608.0;
 struct TabSort {
@@ -533,6 +538,7 @@ struct TabSort {
     int* n_ent;
     int ids, ent_cap;
     int stage;  // particles of a block that fit LDS: TAB_STAGE or TAB_STAGE_MAX
+    bool waves;  // small blocks: a wave each
     // scan-built contexts: occupied base cells and entry of each block (occ zero
     // between builds), bounding box of each tile's occupied blocks
     uint64_t* occ;

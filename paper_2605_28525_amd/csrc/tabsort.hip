@@ -10,7 +10,7 @@
 //   scan     two launches over the table: first position and entry number of
 //            each occupied block, entries in ascending block order;
 //   place    one thread per particle: its index goes to its place;
-//   order    one workgroup per entry: the block's indices are counted into its
+//   order    one workgroup per entry (one wave where blocks are small): the block's indices are counted into its
 //            cells and each cell's few indices put in ascending order, which
 //            makes the sort stable whatever the claims' order was; permutation
 //            and keys are written.  One wave meanwhile inserts the block into
@@ -273,20 +273,128 @@ __device__ void wave_radix(uint32_t* a, uint32_t* b, int c, int idx_bits, const 
 
 }  // namespace
 
+namespace {
+
+// What the rest of the build reads of entry e, by one wave (m, f: particles and
+// first place of cell `lane`, for lanes below 4^d): cell ranges, the emptied
+// table, the block's cells, and its insertion into the hash.
+template <int DIM, TabMode MODE>
+__device__ __forceinline__ void tab_entry_out(const DevParams& P, const TabSort& T, int e, uint32_t id, int st, int c,
+                                              unsigned m, unsigned f, int lane) {
+    constexpr int NC = 1 << (2 * DIM), NB = 1 << DIM;
+    if (e < P.row_cap && lane < NC) P.rs_off[(size_t)e * NC + lane] = (unsigned)st + f;
+    if (MODE != TAB_SCAN && lane == 0) T.cnt[id] = 0u;  // the table is left empty (a scan build empties it itself)
+    if (MODE == TAB_DENSE) return;
+    const uint64_t occ = (uint64_t)__ballot(lane < NC && m != 0u);
+    if (MODE == TAB_SCAN && lane == 0) T.occ[id] = occ;
+    if (MODE != TAB_HASH) return;
+    const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
+    const int own = readlane32(slot, 0);
+    if (own < 0) return;
+    const bool row = e < P.row_cap;  // with the cell ranges, for P2G
+    if (lane < NB) {
+        if (row)
+            P.rs_nslot[(size_t)e * NB + lane] = slot;
+        else
+            P.h_nslot[(size_t)own * NB + lane] = slot;
+    }
+    if (lane == 0) {
+        P.h_start[own] = st;
+        P.h_end[own] = st + c;
+        if (row) P.h_entry[own] = e;
+        atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
+    }
+}
+
+// The order of a block of at most TAB_WAVE particles, by one wave (sidx, scell, cnt,
+// first: its own).
+template <int DIM, TabMode MODE>
+__device__ __forceinline__ void tab_order_wave(const DevParams& P, const TabSort& T, int e, uint4 en, int n,
+                                               const uint32_t* __restrict__ keys, const uint32_t* tmp, uint32_t* order,
+                                               uint32_t* skeys, uint32_t* sidx, unsigned char* scell, unsigned* cnt,
+                                               unsigned* first, int lane) {
+    constexpr int CB = 2 * DIM, NC = 1 << CB, R = TAB_WAVE / 64;
+    const uint32_t id = en.x;
+    const int st = (int)en.y, c = min((int)en.z, n - st);
+    auto fence = [] {  // a wave's LDS accesses are served in order
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+    };
+    uint32_t ix[R];
+    unsigned cl[R], at[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) ix[r] = r * 64 + lane < c ? tmp[st + r * 64 + lane] : 0u;
+    if (lane < NC) cnt[lane] = 0u;
+    fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) cl[r] = r * 64 + lane < c ? keys[ix[r]] & (NC - 1) : 0u;
+#pragma unroll
+    for (int r = 0; r < R; ++r) at[r] = r * 64 + lane < c ? atomicAdd(&cnt[cl[r]], 1u) : 0u;
+    fence();
+    const unsigned m = lane < NC ? cnt[lane] : 0u, f = wave_incl_scan(m) - m;
+    if (lane < NC) first[lane] = f;
+    fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r)
+        if (r * 64 + lane < c) {
+            const unsigned p = first[cl[r]] + at[r];
+            sidx[p] = ix[r];
+            scell[p] = (unsigned char)cl[r];
+        }
+    fence();
+#pragma unroll
+    for (int r = 0; r < R; ++r) {
+        const int j = r * 64 + lane;
+        if (j >= c) continue;
+        const uint32_t v = sidx[j];
+        const unsigned k = scell[j], f0 = first[k], mk = cnt[k];
+        unsigned to = f0;
+        for (unsigned q = 0; q < mk; ++q) to += sidx[f0 + q] < v ? 1u : 0u;
+        order[st + to] = v;
+        skeys[st + to] = (id << CB) | k;
+    }
+    tab_entry_out<DIM, MODE>(P, T, e, id, st, c, m, f, lane);
+    fence();  // (the next entry writes the same LDS)
+}
+
+}  // namespace
+
 // tmp and skeys may be one buffer: a block's range is read before it is written.
-// One workgroup per occupied block.  Its particles are listed cell by cell in
+// One workgroup per occupied block, or (WAVES, where cells at rest put TAB_WAVE_MEAN
+// particles or fewer in a block) one wave per block that fits it (a block's chain of
+// dependent accesses is as long for 16 particles as for 500, so what counts is how
+// many blocks are in flight: 63,504 2D blocks of 63 in 93 us, by a workgroup each in
+// 208; 251,990 of 16 in 368 and 885).
+// A workgroup's block: its particles are listed cell by cell in
 // LDS, then each counts the smaller indices of its cell: no step depends on the
 // one before it, where ordering a cell by insertion is a chain of LDS accesses.
-template <int DIM, TabMode MODE>
+template <int DIM, TabMode MODE, bool WAVES>
 __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const uint32_t* __restrict__ keys,
                                                   uint32_t* tmp, uint32_t* order, uint32_t* skeys, int n, int idx_bits) {
-    constexpr int CB = 2 * DIM, NC = 1 << CB, NB = 1 << DIM, R = TAB_BATCH / WG;
+    constexpr int CB = 2 * DIM, NC = 1 << CB, R = TAB_BATCH / WG;
     extern __shared__ uint32_t sidx[];                              // T.stage indices
     unsigned char* const scell = (unsigned char*)(sidx + T.stage);  // and their cells
     __shared__ unsigned cnt[NC], first[NC], hist[256];
     const int lane = __lane_id(), t = threadIdx.x;
     const int ne = min(*T.n_ent, T.ent_cap);
-    for (int e = blockIdx.x; e < ne; e += gridDim.x) {
+    // entries of a workgroup at a time: GS in a row, then GS past the other workgroups'
+    constexpr int GS = WAVES ? WG / 64 : 1;
+    for (int e = blockIdx.x * GS; e < ne; e += e % GS == GS - 1 ? (gridDim.x - 1) * GS + 1 : 1) {
+        if (WAVES) {
+            if (e % GS == 0) {  // every wave its own
+                const int w = t >> 6, ew = e + w;
+                constexpr int WAVE_LDS = TAB_WAVE * 4 + 2 * NC * 4 + TAB_WAVE;
+                static_assert(WG / 64 * WAVE_LDS <= TAB_STAGE * 5, "the waves share the staging");
+                uint32_t* const wi = (uint32_t*)((char*)sidx + w * WAVE_LDS);
+                const uint4 we = ew < ne ? T.ent[ew] : make_uint4(0u, 0u, ~0u, 0u);
+                if (we.z <= (unsigned)TAB_WAVE)
+                    tab_order_wave<DIM, MODE>(P, T, ew, we, n, keys, tmp, order, skeys, wi,
+                                              (unsigned char*)(wi + TAB_WAVE + 2 * NC), wi + TAB_WAVE,
+                                              wi + TAB_WAVE + NC, lane);
+            }
+            if (T.ent[e].z <= (unsigned)TAB_WAVE) continue;
+            __syncthreads();  // the waves have finished with the staging
+        }
         const uint4 en = T.ent[e];
         const uint32_t id = en.x;
         const int st = (int)en.y, c = min((int)en.z, n - st);
@@ -346,36 +454,15 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
         } else if (t < 64) {
             unsigned m = 0u;
             wave_radix<CB>(tmp + st, order + st, c, idx_bits, keys, hist, lane, &m);
-            if (t < NC) cnt[t] = m;
-        }
-        __syncthreads();
-        if (!staged && t < 64) {
-            const unsigned m = t < NC ? cnt[t] : 0u, f = wave_incl_scan(m) - m;
-            if (t < NC) first[t] = f;
-        }
-        if (e < P.row_cap && t < NC) P.rs_off[(size_t)e * NC + t] = (unsigned)st + first[t];
-        if (MODE != TAB_SCAN && t == 0) T.cnt[id] = 0u;  // the table is left empty (a scan build empties it itself)
-        if (MODE != TAB_DENSE && t >= WG - 64) {
-            const uint64_t occ = (uint64_t)__ballot(lane < NC && cnt[lane & (NC - 1)] != 0u);
-            if (MODE == TAB_SCAN && lane == 0) T.occ[id] = occ;
-            if (MODE == TAB_HASH) {
-                const int slot = lane < NB ? insert_block<DIM>(P, id, occ, lane) : -1;
-                const int own = readlane32(slot, 0);
-                const bool row = e < P.row_cap;  // with the cell ranges below, for P2G
-                if (own >= 0 && lane < NB) {
-                    if (row)
-                        P.rs_nslot[(size_t)e * NB + lane] = slot;
-                    else
-                        P.h_nslot[(size_t)own * NB + lane] = slot;
-                }
-                if (own >= 0 && lane == 0) {
-                    P.h_start[own] = st;
-                    P.h_end[own] = st + c;
-                    if (row) P.h_entry[own] = e;
-                    atomicAdd(&P.t_cnt[own / SCAN_TILE * LINE + 1], block_chunks(P, c));
-                }
+            const unsigned f = wave_incl_scan(m) - m;
+            if (t < NC) {
+                cnt[t] = m;
+                first[t] = f;
             }
         }
+        __syncthreads();
+        if (t >= WG - 64)  // (the wave with the fewest particles)
+            tab_entry_out<DIM, MODE>(P, T, e, id, st, c, lane < NC ? cnt[lane] : 0u, lane < NC ? first[lane] : 0u, lane);
         if (staged) {
             for (int j = t; j < c; j += WG) {
                 const uint32_t v = sidx[j];
@@ -428,7 +515,8 @@ hipError_t tab_sort(const DevParams& P, const TabSort& T, const uint32_t* keys, 
     }
     if (n > 0) {
         k_tab_place<2 * DIM><<<g, WG, 0, s>>>(T, keys, rank, tmp, n);
-        k_tab_order<DIM, MODE><<<go, WG, (size_t)T.stage * 5, s>>>(P, T, keys, tmp, order, skeys, n, bits);
+        const auto k = T.waves ? k_tab_order<DIM, MODE, true> : k_tab_order<DIM, MODE, false>;
+        k<<<go, WG, (size_t)T.stage * 5, s>>>(P, T, keys, tmp, order, skeys, n, bits);
     }
     return hipGetLastError();
 }

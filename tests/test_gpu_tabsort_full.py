@@ -1,4 +1,6 @@
-"""GPU: the counting sort where blocks are full.  Blocks of up to 1024 particles
+"""GPU: the counting sort where blocks are full, and where they are small.  Contexts
+with up to 96 particles in a block at rest order blocks of up to 128 by a wave each.
+Otherwise (and above 128) a workgroup orders a block.  Blocks of up to 1024 particles
 pass through registers, larger ones are read twice, up to 3072 or (contexts
 whose cells at rest hold more than 32 particles in 3D) 8192 of them in LDS, the rest
 by one wave; contexts with more than 110 particles in a cell at rest, or 4608 in a
@@ -18,6 +20,9 @@ pytestmark = pytest.mark.gpu
 
 # cells of a row (four to a block): particles per cell
 ROWS = {
+    64: [64, 0, 0, 0, 1, 2, 3, 58, 20, 21, 22],
+    127: [100, 27, 0, 0, 128, 0, 0, 0, 1],
+    129: [32, 32, 32, 33, 64, 0, 64, 0, 700],
     1023: [300, 300, 300, 123, 5],
     1024: [1, 1000, 23, 0, 5],
     1025: [256, 257, 256, 256, 0, 9],
@@ -40,7 +45,7 @@ def _workload(dim, per_cell, x, seed):
 
 
 @pytest.mark.parametrize("flags", ["full", "scan", "dense", "adjoint"])
-@pytest.mark.parametrize("per_cell", [8, 64, 72, 73, 110, 111])
+@pytest.mark.parametrize("per_cell", [1, 4, 8, 64, 72, 73, 110, 111])
 @pytest.mark.parametrize("dim", [2, 3])
 def test_order_of_full_blocks(dim, per_cell, flags):
     import torch
