@@ -82,7 +82,7 @@ struct mpm_ctx {
     // hash
     uint64_t *h_keys = nullptr, *h_mask = nullptr;
     int *h_vals = nullptr, *h_start = nullptr, *h_end = nullptr, *h_nslot = nullptr;
-    unsigned *t_cnt = nullptr, *t_pre = nullptr;
+    unsigned* t_cnt = nullptr;
     // blocks
     uint64_t *b_keys = nullptr, *b_mask = nullptr;
     int *b_nbr = nullptr, *b_start = nullptr, *b_count = nullptr, *b_hs = nullptr;
@@ -246,7 +246,6 @@ void fill_params(mpm_ctx* c) {
     P.h_end = c->h_end;
     P.h_nslot = c->h_nslot;
     P.t_cnt = c->t_cnt;
-    P.t_pre = c->t_pre;
     P.h_mask_bits = (unsigned)((1u << c->H_log2) - 1u);
     P.n_probe = 1 << c->H_log2;
     P.b_keys = c->b_keys;
@@ -320,10 +319,7 @@ int alloc_capacity_buffers(mpm_ctx* c) {
         A.need(&c->h_start, H);
         A.need(&c->h_end, H);
         A.need(&c->h_nslot, H * NB);
-        const size_t tiles = (H + SCAN_TILE - 1) / SCAN_TILE;
-        A.need(&c->t_cnt, LINE * tiles);
-        c->t_pre = nullptr;
-        if (tiles > (size_t)FOLD_MAX_TILES) A.need(&c->t_pre, 2 * (tiles + 1));
+        A.need(&c->t_cnt, LINE * ((H + SCAN_TILE - 1) / SCAN_TILE + 1));
         A.need(&c->b_hs, cap);
     }
     if (!c->dense) {

@@ -183,38 +183,6 @@ __global__ __launch_bounds__(WG) void k_count_items(DevParams P, int H) {
     if (threadIdx.x == 0) P.t_cnt[blockIdx.x * LINE + 1] = tot;
 }
 
-// Running sums of the tiles' counts, for tables of many tiles (one workgroup).
-__global__ __launch_bounds__(WG) void k_tile_sums(DevParams P, int tiles) {
-    __shared__ unsigned lds[WG / 64];
-    constexpr int R = 8;  // tiles per thread and round, their loads issued together
-    unsigned c0 = 0u, w0 = 0u;
-    for (int b = 0; b < tiles; b += R * WG) {
-        const int t0 = b + (int)threadIdx.x * R;
-        unsigned c[R], w[R], cs = 0u, ws = 0u, ct, wt;
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            const bool in = t0 + r < tiles;
-            c[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE] : 0u;
-            w[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE + 1] : 0u;
-        }
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            cs += c[r];
-            ws += w[r];
-        }
-        unsigned ca = c0 + wg_excl_scan(cs, lds, &ct), wa = w0 + wg_excl_scan(ws, lds, &wt);
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            if (t0 + r < tiles) *(uint2*)&P.t_pre[2 * (size_t)(t0 + r)] = make_uint2(ca, wa);
-            ca += c[r];
-            wa += w[r];
-        }
-        c0 += ct;
-        w0 += wt;
-    }
-    if (threadIdx.x == 0) *(uint2*)&P.t_pre[2 * (size_t)tiles] = make_uint2(c0, w0);
-}
-
 // Compaction: Phi in slot order and the block tables, one workgroup per tile of
 // SCAN_TILE slots, whose occupied slots and work items the insertion counted
 // (t_cnt), so that each tile adds up the counts before it and no pass over the
@@ -226,7 +194,8 @@ __global__ __launch_bounds__(WG) void k_tile_sums(DevParams P, int tiles) {
 // 4.8 + 10.2 us at 32,768 slots and 8.8 + 17.6 us at 2,097,152.)
 // ITEMS: also the work items and the state that the counting of the next
 // incremental re-sort starts from.
-template <int DIM, bool ITEMS>
+// PRE: the sums over the tiles have been made (launch_tile_sums).
+template <int DIM, bool ITEMS, bool PRE>
 __global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int tiles) {
     constexpr int NB = 1 << DIM, NC = 1 << (2 * DIM);
     constexpr int NW = WG / 64, ROUNDS = SCAN_TILE / WG;
@@ -243,7 +212,7 @@ __global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int ti
     }
     // sums over the tiles: occupied slots and items before this one, and all
     unsigned sum[4] = {0u, 0u, 0u, 0u};
-    for (int i = threadIdx.x; i < (P.t_pre ? 0 : tiles); i += WG) {
+    for (int i = threadIdx.x; !PRE && i < tiles; i += WG) {
         const unsigned c = P.t_cnt[i * LINE], it = P.t_cnt[i * LINE + 1];
         sum[0] += i < (int)blockIdx.x ? c : 0u;
         sum[1] += i < (int)blockIdx.x ? it : 0u;
@@ -283,11 +252,11 @@ __global__ __launch_bounds__(WG) void k_compact_write(DevParams P, int H, int ti
         total += red[q][2];
         wtotal += red[q][3];
     }
-    if (P.t_pre) {
-        phi0 = P.t_pre[2 * (size_t)blockIdx.x];
-        it0 = P.t_pre[2 * (size_t)blockIdx.x + 1];
-        total = P.t_pre[2 * (size_t)tiles];
-        wtotal = P.t_pre[2 * (size_t)tiles + 1];
+    if (PRE) {
+        phi0 = P.t_cnt[(size_t)blockIdx.x * LINE + 2];
+        it0 = P.t_cnt[(size_t)blockIdx.x * LINE + 3];
+        total = P.t_cnt[(size_t)tiles * LINE + 2];
+        wtotal = P.t_cnt[(size_t)tiles * LINE + 3];
     }
     bool over = false;
 #pragma unroll 1
@@ -540,11 +509,16 @@ hipError_t build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsign
             if (!det) k_count_items<<<tiles, WG, 0, s>>>(P, (int)H);
         }
     }
-    if (P.t_pre) k_tile_sums<<<1, WG, 0, s>>>(P, tiles);
+    const bool pre = tiles > FOLD_MAX_TILES;
+    if (pre) {
+        hipError_t e = launch_tile_sums(P, tiles, s);
+        if (e != hipSuccess) return e;
+    }
     // without the key order, Phi is slot order and the compaction also writes
     // the work items
     if (!det) {
-        k_compact_write<DIM, true><<<tiles, WG, 0, s>>>(P, (int)H, tiles);
+        const auto k = !pre ? k_compact_write<DIM, true, false> : k_compact_write<DIM, true, true>;
+        k<<<tiles, WG, 0, s>>>(P, (int)H, tiles);
         // no grid clear: the second P2G pass writes every node of every active block
         return hipGetLastError();
     }
@@ -557,7 +531,8 @@ hipError_t build_sparse(const DevParams& P, const uint32_t* skeys, int n, unsign
     Pa.b_start = det->start;
     Pa.b_count = det->count;
     Pa.b_hs = det->slot;
-    k_compact_write<DIM, false><<<tiles, WG, 0, s>>>(Pa, (int)H, tiles);
+    const auto k = !pre ? k_compact_write<DIM, false, false> : k_compact_write<DIM, false, true>;
+    k<<<tiles, WG, 0, s>>>(Pa, (int)H, tiles);
     const int kb = P.blk_bits + (P.n_inst > 1 ? 6 : 0);
     const uint32_t sentinel = kb >= 32 ? 0xFFFFFFFFu : ((1u << kb) - 1u);
     k_det_keys<DIM><<<gb, WG, 0, s>>>(P, det->keys, det->k[1], sentinel);

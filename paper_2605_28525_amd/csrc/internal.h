@@ -113,9 +113,8 @@ struct DevParams {
     int* h_end;
     int* h_nslot;           // hash-built tables: per slot of an owner block, the slots of the 2^d
                             // blocks its stencils reach (d = 0: itself; -1: not reached)
-    unsigned* t_cnt;        // per SCAN_TILE slots, LINE words apart: occupied ones, work items
-    unsigned* t_pre;        // large tables: sums of t_cnt over the tiles before each, and over all (2 words
-                            // each); null: every tile of the compaction adds them up itself
+    unsigned* t_cnt;        // per SCAN_TILE slots, LINE words apart: occupied ones, work items; in large
+                            // tables also their sums over the tiles before (a line past the last: over all)
     unsigned h_mask_bits;   // H - 1
     int n_probe;
     // compact blocks
@@ -469,6 +468,7 @@ __device__ __forceinline__ void box_reduce(int* lo, int* hi, int (*red)[6]) {
 hipError_t scan_exclusive(const unsigned* in, unsigned* out, int n, const int* n_dev, unsigned* partials,
                           unsigned* total_out, hipStream_t s);
 int scan_partials_size(int n);
+hipError_t launch_tile_sums(const DevParams& P, int tiles, hipStream_t s);
 size_t sb_scratch_bytes(long long max_m);
 SbScratch sb_carve(void* base, long long max_m, int* seg_lo, int* seg_hi);
 hipError_t launch_scan_active(const DevParams& P, const float* x, int n, const SbScratch& S, uint64_t* keys_out,

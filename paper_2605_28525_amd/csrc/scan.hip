@@ -80,4 +80,42 @@ hipError_t scan_exclusive(const unsigned* in, unsigned* out, int n, const int* n
     return hipGetLastError();
 }
 
+// Running sums of the hash table's per-tile counts (t_cnt), for tables of many tiles
+// (one workgroup).
+__global__ __launch_bounds__(WG) void k_tile_sums(DevParams P, int tiles) {
+    __shared__ unsigned lds[WG / 64];
+    constexpr int R = 8;  // tiles per thread and round, their loads issued together
+    unsigned c0 = 0u, w0 = 0u;
+    for (int b = 0; b < tiles; b += R * WG) {
+        const int t0 = b + (int)threadIdx.x * R;
+        unsigned c[R], w[R], cs = 0u, ws = 0u, ct, wt;
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            const bool in = t0 + r < tiles;
+            c[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE] : 0u;
+            w[r] = in ? P.t_cnt[(size_t)(t0 + r) * LINE + 1] : 0u;
+        }
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            cs += c[r];
+            ws += w[r];
+        }
+        unsigned ca = c0 + wg_excl_scan(cs, lds, &ct), wa = w0 + wg_excl_scan(ws, lds, &wt);
+#pragma unroll
+        for (int r = 0; r < R; ++r) {
+            if (t0 + r < tiles) *(uint2*)&P.t_cnt[(size_t)(t0 + r) * LINE + 2] = make_uint2(ca, wa);
+            ca += c[r];
+            wa += w[r];
+        }
+        c0 += ct;
+        w0 += wt;
+    }
+    if (threadIdx.x == 0) *(uint2*)&P.t_cnt[(size_t)tiles * LINE + 2] = make_uint2(c0, w0);
+}
+
+hipError_t launch_tile_sums(const DevParams& P, int tiles, hipStream_t s) {
+    k_tile_sums<<<1, WG, 0, s>>>(P, tiles);
+    return hipGetLastError();
+}
+
 }  // namespace mpmx
