@@ -438,7 +438,7 @@ uint32_t* next_bin_buffer(const mpm_ctx* c, bool next_reuse) {
 // The device parameters of a launch over n particles.
 DevParams params_for(const mpm_ctx* c, int n) {
     DevParams P = c->P;
-    if (n > FOLD_MAX_N) P.rs_tile = nullptr;
+    if (n > FOLD_MAX_N || c->block_cap > FOLD_MAX_BLOCKS) P.rs_tile = nullptr;
     return P;
 }
 
@@ -887,7 +887,8 @@ namespace {
 // stays readable).
 P2GSecond step_second(const mpm_ctx* c, int n, bool last) {
     if (c->dense || n == 0) return P2G_SUM;
-    const bool gather = !last && !c->adjoint && n <= G2P_GATHER_MAX_N && c->g2p_block == 256 && c->chunk <= 512;
+    const bool gather = !last && !c->adjoint && n <= G2P_GATHER_MAX_N && c->block_cap <= G2P_GATHER_MAX_BLOCKS &&
+                        c->g2p_block == 256 && c->chunk <= 512;
     return gather ? P2G_LEFT_TO_G2P : P2G_UPDATE;
 }
 }  // namespace

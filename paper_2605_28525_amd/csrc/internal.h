@@ -62,6 +62,12 @@ constexpr int LINE = 32;
 // against 14.0 + 9.5 for the scan, P2G +3 us against a 7 us pass; 20 M: 82
 // against 68 + 9, P2G +30 us against 10).
 constexpr int FOLD_MAX_N = 1 << 22;
+// And blocks (what the host knows of their number is the capacity): the folded
+// scan's loads grow with the square of the blocks, of which scattered particles
+// have several each.  Steps of 65,536 / 131,072 / 262,144 particles scattered over
+// 208,556 / 418,253 / 774,874 blocks in 1021 / 1961 / 4175 us folded, 970 / 1733 /
+// 3273 not; 262,144 particles in 1000 blocks with room for 524,288 in 79 and 84.
+constexpr int FOLD_MAX_BLOCKS = 1 << 18;
 // Tiles of the hash table up to which each tile of the compaction adds up the
 // counts of the tiles before it, a line each; above, one workgroup makes their
 // running sums first.  Steps of 262,144 particles with a table of 2^21 / 2^22 / 2^23 /
@@ -76,6 +82,10 @@ constexpr int FOLD_MAX_TILES = 1024;
 // 61 / 62 / 73 / 79 / 267; in a graph of 25,600 53 against 56, of 4,096 in 2D
 // 38 against 40.
 constexpr int G2P_GATHER_MAX_N = 1 << 16;
+// And where contexts have room for at most as many blocks: 65,536 particles
+// scattered over 129,339 blocks (2D) in 464 us, with the pass 382; over 208,556 (3D)
+// 972 and 909.
+constexpr int G2P_GATHER_MAX_BLOCKS = 1 << 16;
 
 // Per-instance material and step constants (one entry for a single simulation).
 struct InstMat {
