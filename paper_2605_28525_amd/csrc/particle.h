@@ -250,11 +250,4 @@ __device__ __forceinline__ int interleave_pos_cj(const Interleave<DIM>& L, int c
     return L.st + L.R[IL_ROUNDS] + L.op[c] + (j - IL_ROUNDS);
 }
 
-// Output position of the particle at sorted position i (sort key `key`).
-template <int DIM>
-__device__ __forceinline__ int interleave_pos(const Interleave<DIM>& L, int i, uint32_t key) {
-    const int c = (int)(key & (Interleave<DIM>::NC - 1));
-    return interleave_pos_cj<DIM>(L, c, i - L.cs[c]);
-}
-
 }  // namespace mpmx
