@@ -90,6 +90,7 @@ class Rollout:
         self._bufs = [a, b]
         return a
 
+    @torch.no_grad()   # create_graph runs this with gradients enabled; x_bar may then require one
     def backward(self, checkpoints, final_ids: torch.Tensor, x_bar: torch.Tensor, E: float, phi: float, recorded=None):
         """x_bar: dL/dx of the final state of the forward pass that kept
         `checkpoints` (same order as `final_ids`).  The material of that pass is
