@@ -75,7 +75,10 @@ class Rollout:
         for s0 in range(0, self.steps, self.K):
             k = min(self.K, self.steps - s0)
             if record and keep_checkpoints and s0 + k == self.steps:
-                # the state itself is the checkpoint: no step overwrites it
+                # the state itself is the checkpoint: no step overwrites it (and,
+                # as it may be from another stream, it is freed behind this one)
+                for key in ("x", "v", "C", "F", "tau", "id"):
+                    getattr(a, key).record_stream(torch.cuda.current_stream())
                 self.checkpoints.append(a)
                 self._bufs = [M.ParticleSet(self.dim, self.n, self.device, zero=False), b]
                 states = self._segment(k, a)
