@@ -337,7 +337,7 @@ int mpm_step_adj(mpm_ctx* ctx, const mpm_particles* in, const mpm_particles* out
  * order).  mpm_step_adj recomputes them; a tape keeps them instead, one slot
  * per step of a segment, so that the reverse sweep runs only the three
  * adjoint transfers per step.  A slot holds 2 x 4^d x 16 B of grid plus about
- * 80 B of tables per block of capacity and 8 B per particle of capacity
+ * 90 B of tables per block of capacity and 8 B per particle of capacity
  * (about 28 MB for 262,144 particles at the default block capacity).
  *
  * mpm_tape_reserve: allocates n_slots slots (0 frees them; synchronises the

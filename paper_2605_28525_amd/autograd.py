@@ -12,10 +12,10 @@ the tape in between.
 Gradients: dL/dE, dL/dphi (per degree) and dL/dv0 (in the initial particle
 order).
 
-The library reorders particles every step, and a recomputed segment need not
-repeat the first pass's order: the compact block order follows the hash slots
-that concurrent insertions claim, and the particles are stored block by block.
-Adjoints are carried across segment boundaries by particle id.
+The library reorders particles every step.  A recomputed segment repeats the
+first pass's order (adjoint contexts sort from scratch in every step, stably),
+but nothing here relies on it: adjoints are carried across segment boundaries
+by particle id.
 """
 from __future__ import annotations
 

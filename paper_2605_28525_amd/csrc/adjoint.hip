@@ -78,10 +78,17 @@ __device__ __forceinline__ float log1p_small(float m) {
 // is settled by one fixed evaluation of F_trial (trial_by_nodes) and of the
 // strains (NODES), not by the faster ones used elsewhere: the gradients jump
 // there, so a particle that fell on the other side would move dL/dphi by its
-// whole share (3e-4 of it, in one of 262,144 particles over 20 steps).
+// whole share (3e-4 of it, in one of 262,144 particles over 20 steps).  (It is
+// not the forward pass's evaluation, which takes the branch from the matrix
+// series: within rounding of a kink the two can differ.)
 // The two evaluations of tr differ by 3e-8 rms (1 + M rounds in each strain).
-// Deciding takes 7 us of 50 at 262,144 particles: 4 us for the registers of
-// the second copy of the code, 3 us to run it.
+// Deciding takes 7 us of 48 at 262,144 particles of loaded material: 4 us for the
+// registers of the second copy of the code, 3 us to run it.  Undeformed
+// particles are all in doubt (F = I is the kink): a rollout from rest, 61 us.
+//
+// Error of the gradients against 64 bits over 80 calibration passes of 1,000 to
+// 60,000 particles (the same with expf, sqrtf and divisions in these maps, in
+// brackets): dL/dE median 1.6e-7 (1.7e-7), dL/dphi 2.4e-6 (2.4e-6).
 constexpr float KINK_TOL = 2.5e-7f;
 struct Principal {
     float U[3][3];                 // eigenvectors of F_trial F_trial^T
@@ -645,8 +652,9 @@ __device__ __forceinline__ bool g2p_adj_particle(const DevParams& P, const float
 // particles are listed, so the item's part is walked in output order: the
 // output adjoints and the scratch are read and written contiguously.
 // Bound by its arithmetic and registers (about 3000 instructions a particle at
-// three waves per SIMD; its bytes take 16 us): 262,144 particles in 50 us, 109
-// before (27 nodes times all Hessian factors, 283 registers, one wave per SIMD).
+// three waves per SIMD, for which it spills 24 bytes a lane; its bytes take 16
+// us): 262,144 particles of loaded material in 48 us, 109 before (27 nodes times
+// all Hessian factors, 283 registers, one wave per SIMD).
 template <int DIM>
 __global__ __launch_bounds__(ADJ_WG, 3) void k_g2p_adj(DevParams P, const float* __restrict__ x,
                                                     const float* __restrict__ F, OutBar ob, float* __restrict__ x_bar,
@@ -997,7 +1005,7 @@ struct PBar {
 };
 
 // Input adjoints of P2G, a particle per lane in output order.  Bound like
-// k_g2p_adj: 262,144 particles in 31 us, 44 before (node by node).
+// k_g2p_adj: 262,144 particles in 27 us, 44 before (node by node).
 template <int DIM>
 __global__ __launch_bounds__(ADJ_WG, 3) void k_p2g_adj(DevParams P, PIn in, PBar bar, int n,
                                                     const uint32_t* __restrict__ osrc, int parts) {

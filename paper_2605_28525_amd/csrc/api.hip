@@ -710,7 +710,9 @@ int mpm_create(const mpm_params* q, mpm_ctx** out) {
     // Work items of 256 particles instead of 512, one per thread of G2P, where
     // there are few: steps of 25,600 particles 572 -> 557 us, gradients of 4,096
     // 3.11 -> 3.02 ms, of 262,144 5.27 -> 5.10; steps of 262,144 858 and 860 us;
-    // of 2,097,152 3.08 -> 3.14 ms.
+    // of 2,097,152 3.08 -> 3.14 ms (8 per cell in blocks cut at random; a step of about
+    // 262,144 in whole blocks with 1 / 8 / 27 / 64 per cell 129 / 73 / 94 / 138 -> 126 / 75 /
+    // 99 / 144 us, of 131,072 91 / 65 / 88 / 131 -> 89 / 67 / 89 / 132).
     if (q->max_particles <= 1 << 18) c->chunk = 256;
     if (const char* ch = getenv("MPMX_CHUNK")) {
         int v = atoi(ch);

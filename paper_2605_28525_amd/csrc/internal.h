@@ -80,7 +80,8 @@ constexpr int FOLD_MAX_TILES = 1024;
 // by each block that reads them.  Whole steps of 4,096 / 32,768 / 65,536 / 131,072 /
 // 262,144 / 2,097,152 particles in 56 / 59 / 61 / 74 / 80 / 290 us, with the pass 57 /
 // 61 / 62 / 73 / 79 / 267; in a graph of 25,600 53 against 56, of 4,096 in 2D
-// 38 against 40.
+// 38 against 40 (all with 2^d particles per cell; of 64,000 with 1 / 27 per cell 71 / 78
+// against 67 / 81, of 65,536 in 2D with 1 81 against 72).
 constexpr int G2P_GATHER_MAX_N = 1 << 16;
 // And where contexts have room for at most as many blocks: 65,536 particles
 // scattered over 129,339 blocks (2D) in 464 us, with the pass 382; over 208,556 (3D)

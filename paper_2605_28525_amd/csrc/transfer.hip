@@ -1289,7 +1289,9 @@ __global__ __launch_bounds__(GS) void k_g2p(DevParams P, G2PIn in, G2POut out, i
 // Two waves per block share its components where one per block leaves SIMDs
 // idle: P2G (with the gather, 8 particles per cell) of 4,096 / 65,536 /
 // 262,144 / 393,216 / 524,288 / 2,097,152 particles in 26 / 25 / 29 / 35 / 39 / 85
-// us, with one wave 31 / 32 / 34 / 38 / 39 / 82.  (A wave per component: 26 / 29 /
+// us, with one wave 31 / 32 / 34 / 38 / 39 / 82.  Whole steps of about 262,144 with 1 /
+// 8 / 27 / 64 per cell 126 / 74 / 99 / 144, with one wave 123 / 78 / 106 / 148; of 2.1
+// million 633 / 259 / 274 / 589 and 617 / 257 / 265 / 600.  (A wave per component: 26 / 29 /
 // 45 / 53 / 58 / 122; loads two particles ahead instead of one: 24 / 25 / 35 / 43 /
 // 48 / 105, and no gain inside a step.)
 constexpr int P2G_SPLIT_MAX_N = 3 << 17;
