@@ -363,7 +363,7 @@ int alloc_capacity_buffers(mpm_ctx* c) {
         A.need(&c->rs_oldblk, 2 * cap);
         A.need(&c->rs_cnt, 2 * cap);
         A.need(&c->rs_start, 2 * cap);
-        A.need(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
+        if (c->block_cap <= FOLD_MAX_BLOCKS) A.need(&c->rs_tile, LINE * ((cap + RS_TILE - 1) / RS_TILE));
         A.need(&c->it_mov, (size_t)c->work_cap);
         A.need(&c->rs_occ, 2 * cap);
         A.need(&c->nh_keys, H);
@@ -438,7 +438,7 @@ uint32_t* next_bin_buffer(const mpm_ctx* c, bool next_reuse) {
 // The device parameters of a launch over n particles.
 DevParams params_for(const mpm_ctx* c, int n) {
     DevParams P = c->P;
-    if (n > FOLD_MAX_N || c->block_cap > FOLD_MAX_BLOCKS) P.rs_tile = nullptr;
+    if (n > FOLD_MAX_N) P.rs_tile = nullptr;
     return P;
 }
 

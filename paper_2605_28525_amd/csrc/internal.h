@@ -173,7 +173,7 @@ struct DevParams {
     uint32_t* nh_owner;   //   and the owner-block part of their sort key
     uint32_t* rs_new;     // second-table slots in the order of their claims (block_cap entries)
     unsigned* rs_tile;    // particles per RS_TILE previous blocks (sums of rs_cnt), LINE words apart; null
-                          // above FOLD_MAX_N particles
+                          // above FOLD_MAX_N particles or FOLD_MAX_BLOCKS blocks
     unsigned* it_mov;     // movers of each work item, listed from the item's first position on
     int* h_entry;         // the sort's entry of each hash slot's owner block (-1: none)
     int* b_entry;         // the sort's entry of each compact block (-1: none): its cell
