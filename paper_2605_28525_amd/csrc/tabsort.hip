@@ -275,15 +275,21 @@ __device__ void wave_radix(uint32_t* a, uint32_t* b, int c, int idx_bits, const 
 
 namespace {
 
-// What the rest of the build reads of entry e, by one wave (m, f: particles and
-// first place of cell `lane`, for lanes below 4^d): cell ranges, the emptied
-// table, the block's cells, and its insertion into the hash.
+// What the rest of the build reads of entry e, each by one wave (m, f: particles and
+// first place of cell `lane`, for lanes below 4^d): the cell ranges, beside the
+// emptied table ...
 template <int DIM, TabMode MODE>
-__device__ __forceinline__ void tab_entry_out(const DevParams& P, const TabSort& T, int e, uint32_t id, int st, int c,
-                                              unsigned m, unsigned f, int lane) {
-    constexpr int NC = 1 << (2 * DIM), NB = 1 << DIM;
+__device__ __forceinline__ void tab_entry_row(const DevParams& P, const TabSort& T, int e, uint32_t id, int st,
+                                              unsigned f, int lane) {
+    constexpr int NC = 1 << (2 * DIM);
     if (e < P.row_cap && lane < NC) P.rs_off[(size_t)e * NC + lane] = (unsigned)st + f;
     if (MODE != TAB_SCAN && lane == 0) T.cnt[id] = 0u;  // the table is left empty (a scan build empties it itself)
+}
+// ... the block's cells and its insertion into the hash.
+template <int DIM, TabMode MODE>
+__device__ __forceinline__ void tab_entry_insert(const DevParams& P, const TabSort& T, int e, uint32_t id, int st,
+                                                 int c, unsigned m, int lane) {
+    constexpr int NC = 1 << (2 * DIM), NB = 1 << DIM;
     if (MODE == TAB_DENSE) return;
     const uint64_t occ = (uint64_t)__ballot(lane < NC && m != 0u);
     if (MODE == TAB_SCAN && lane == 0) T.occ[id] = occ;
@@ -353,7 +359,8 @@ __device__ __forceinline__ void tab_order_wave(const DevParams& P, const TabSort
         order[st + to] = v;
         skeys[st + to] = (id << CB) | k;
     }
-    tab_entry_out<DIM, MODE>(P, T, e, id, st, c, m, f, lane);
+    tab_entry_row<DIM, MODE>(P, T, e, id, st, f, lane);
+    tab_entry_insert<DIM, MODE>(P, T, e, id, st, c, m, lane);
     fence();  // (the next entry writes the same LDS)
 }
 
@@ -461,8 +468,9 @@ __global__ __launch_bounds__(WG) void k_tab_order(DevParams P, TabSort T, const 
             }
         }
         __syncthreads();
+        if (t < 64) tab_entry_row<DIM, MODE>(P, T, e, id, st, t < NC ? first[t] : 0u, t);
         if (t >= WG - 64)  // (the wave with the fewest particles)
-            tab_entry_out<DIM, MODE>(P, T, e, id, st, c, lane < NC ? cnt[lane] : 0u, lane < NC ? first[lane] : 0u, lane);
+            tab_entry_insert<DIM, MODE>(P, T, e, id, st, c, lane < NC ? cnt[lane] : 0u, lane);
         if (staged) {
             for (int j = t; j < c; j += WG) {
                 const uint32_t v = sidx[j];
