@@ -382,8 +382,9 @@ int mpm_graph_release(mpm_ctx* ctx);
  * (64..768, used by G2P and the reverse kernels), G2P workgroup size
  * `g2p_block` (64, 128 or 256; chunk <= 2 g2p_block, or 3 g2p_block at 256)
  * and the persistent workgroup counts of the P2G and G2P launches.  0 keeps a
- * value.  Takes effect on the next build; a captured graph keeps the shape it
- * was recorded with.  MPM_ERR_ARG for values out of range. */
+ * value.  Takes effect on the next build, which a chunk other than the one asked
+ * for last (512 where none was) makes necessary; a captured graph keeps the
+ * shape it was recorded with.  MPM_ERR_ARG for values out of range. */
 int mpm_set_tuning(mpm_ctx* ctx, int chunk, int g2p_block, int p2g_workgroups, int g2p_workgroups);
 
 /* Autotuner: for every candidate launch shape ((g2p_block, chunk) in {(64,
