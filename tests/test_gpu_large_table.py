@@ -4,13 +4,12 @@ sums are made by a launch of their own.  The size changes only where blocks lie
 in the table: the active set and (with a stable sort) every particle are the
 same, and a step may not grow with the square of the table.
 """
-import time
-
 import numpy as np
 import pytest
 
 from paper_2605_28525_amd import workloads as wl
 from test_gpu_tabsort import _announce, _far_cloud, _state
+from test_gpu_tabsort_full import step_times
 
 pytestmark = pytest.mark.gpu
 
@@ -68,24 +67,14 @@ def test_step_does_not_grow_with_the_square_of_the_table():
     """262,144 particles with 2^17 and 2^24 slots: the larger table is read once more
     (16.8 million keys), 71 and 113 us; with every tile adding up all tiles' counts it
     was 321 us."""
-    import torch
     from paper_2605_28525_amd import mpm as M
     w = wl.collapse_3d(seed=2, scale=2)
     _announce("large table, time", w.n)
-    t = []
-    for log2 in (17, 24):
-        sim = M.Simulation(w, hash_capacity_log2=log2)
-        try:
-            laps = []
-            for _ in range(7):
-                torch.cuda.synchronize()
-                t0 = time.perf_counter()
-                sim.step(20)
-                torch.cuda.synchronize()
-                laps.append(time.perf_counter() - t0)
-            assert sim.status()[0] == 0
-            t.append(sorted(laps)[2])
-        finally:
+    sims = [M.Simulation(w, hash_capacity_log2=log2) for log2 in (17, 24)]
+    try:
+        t = step_times(sims, 20)
+    finally:
+        for sim in sims:
             sim.close()
-    print("us per step", [round(1e6 * v / 20, 1) for v in t])
+    print("us per step", [round(1e6 * v, 1) for v in t])
     assert t[1] < 2.5 * t[0]

@@ -7,13 +7,13 @@ particles, which have several blocks each, must not pay for the re-sort more
 than a sort from scratch does.
 """
 import re
-import time
 
 import numpy as np
 import pytest
 
 from paper_2605_28525_amd import workloads as wl
 from test_gpu_tabsort import _announce, _far_cloud, _state
+from test_gpu_tabsort_full import step_times
 
 pytestmark = pytest.mark.gpu
 
@@ -69,25 +69,15 @@ def test_forms_by_the_room_for_blocks(capacity, gathers, folded):
 def test_scattered_particles_re_sort_as_fast_as_they_sort():
     """262,144 particles over about 518,000 blocks: 1323 us a step re-sorted, 1339
     sorted from scratch; with the folded scan 1684."""
-    import torch
     from paper_2605_28525_amd import mpm as M
     rng = np.random.default_rng(3)
     w = _workload((0.25 * rng.uniform(4, 5996, (2, 262144))).astype(np.float32), (6000, 6000))
     _announce("scattered particles", w.n)
-    t = []
-    for flags in (0, M.MPM_FLAG_FULL_SORT):
-        sim = M.Simulation(w, flags=flags, block_capacity=4 * w.n)
-        try:
-            laps = []
-            for _ in range(7):
-                torch.cuda.synchronize()
-                t0 = time.perf_counter()
-                sim.step(10)
-                torch.cuda.synchronize()
-                laps.append(time.perf_counter() - t0)
-            assert sim.status()[0] == 0
-            t.append(sorted(laps)[2])
-        finally:
+    sims = [M.Simulation(w, flags=flags, block_capacity=4 * w.n) for flags in (0, M.MPM_FLAG_FULL_SORT)]
+    try:
+        t = step_times(sims, 10)
+    finally:
+        for sim in sims:
             sim.close()
-    print("us per step", [round(1e5 * v, 1) for v in t])
+    print("us per step", [round(1e6 * v, 1) for v in t])
     assert t[0] < 1.12 * t[1]

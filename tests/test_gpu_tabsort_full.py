@@ -73,6 +73,21 @@ def test_order_of_full_blocks(dim, per_cell, flags):
             sim.close()
 
 
+def step_times(sims, steps):
+    """Median seconds per step of each simulation, lap by lap in turn."""
+    import torch
+    laps = [[] for _ in sims]
+    for _ in range(7):
+        for lap, sim in zip(laps, sims):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            sim.step(steps)
+            torch.cuda.synchronize()
+            lap.append((time.perf_counter() - t0) / steps)
+    assert all(sim.status()[0] == 0 for sim in sims)
+    return [sorted(lap)[2] for lap in laps]
+
+
 def _column(dim, side, per_axis):
     rng = np.random.default_rng(3)
     dx, E, rho = 0.01, 1e6, 2000.0
@@ -91,25 +106,14 @@ def test_a_full_sort_is_not_a_multiple_of_a_step(dim, side, per_axis):
     """About 260,000 particles at 27, 125 and (2D) 100 per cell: a step that sorts
     from scratch takes 1.1 to 1.3 times one that re-sorts; with one wave per full
     block it took 1.7 to 2.4 times."""
-    import torch
     from paper_2605_28525_amd import mpm as M
     w = _column(dim, side, per_axis)
     _announce("cost of a full sort", dim, per_axis, w.n)
-    t = {}
-    for flags in (0, M.MPM_FLAG_FULL_SORT):
-        sim = M.Simulation(w, flags=flags)
-        try:
-            laps = []
-            for _ in range(7):
-                torch.cuda.synchronize()
-                t0 = time.perf_counter()
-                sim.step(20)
-                torch.cuda.synchronize()
-                laps.append(time.perf_counter() - t0)
-            assert sim.status()[0] == 0
-            t[flags] = sorted(laps)[2]
-        finally:
+    sims = [M.Simulation(w, flags=flags) for flags in (0, M.MPM_FLAG_FULL_SORT)]
+    try:
+        t = step_times(sims, 20)
+    finally:
+        for sim in sims:
             sim.close()
-    ratio = t[M.MPM_FLAG_FULL_SORT] / t[0]
-    print("ratio", round(ratio, 2), "us per step", {k: round(1e6 * v / 20, 1) for k, v in t.items()})
-    assert ratio < 1.5
+    print("ratio", round(t[1] / t[0], 2), "us per step", [round(1e6 * v, 1) for v in t])
+    assert t[1] < 1.5 * t[0]
